@@ -6,43 +6,55 @@
 // ctx goes to per-workgroup slots, or, with a stored scale (Eq. 4), the int8 codes of ctx are
 // written directly (Eq. 1) and ctx itself need not be stored at all.
 //
-// MFMA kernel (head width 64): a workgroup of four waves owns 128 queries of one (sequence,
-// head); each wave keeps its 32 query rows in registers (pre-multiplied by scale * log2 e) and
-// walks the keys in stages of 64, K and V tiles staged in LDS and shared by the four waves.
-// Scores are formed transposed, S^T = K Q^T, with v_mfma_f32_32x32x2_f32: a lane then holds 16
-// keys of ONE query per 32-key block, so the softmax statistics are per-lane loops plus a single
-// exchange between the two half-waves, and the probabilities sit exactly where the B operand of
-// O^T += V^T P^T wants them -- no data movement between the two products.  Softmax is the
-// running-maximum form (scores never exist in memory), evaluated with exp2.
-// The key loop is skewed by one stage (the scores of stage i+1 are formed while the softmax of
-// stage i runs) and its instruction streams are interleaved by hand, because a wave issues in
-// order: see attention_trip.
-// Work per (sequence, head): 4 S^2 64 flops; bound by the fp32 matrix pipes (157 TFLOP/s) plus
-// the vector arithmetic of the softmax, which on this part is paid on top of the MFMA time
-// rather than beside it; the traffic (qkv read once per query block from L2, ctx written once)
-// is small beside both.
+// FP32 products on the bf16 matrix pipes.  A binary32 number is the exact sum of three bf16 numbers (8 + 8 + 8
+// significant bits, each part the rounded remainder of the ones before it), so a product is nine bf16 products; the
+// three smallest (m l, l m, l l: together below 2^-26 of the product, a quarter of the last place of binary32) are left
+// out and six run on v_mfma_f32_32x32x16_bf16, accumulated in binary32 like before.  The bf16 pipes are 16 times as
+// fast as the fp32 ones, so six products take 3/8 of the time of one fp32 MFMA pass, and -- unlike the fp32 MFMAs,
+// which share their lanes with the vector ALU -- they run beside the softmax arithmetic.  Error against binary64 is no
+// larger than that of the fp32 pipes (fewer roundings: one accumulation per 16 products instead of per 2).
+//
+// Kernel (head widths up to 128): a workgroup of four waves owns 128 queries of one (sequence, head); each wave keeps
+// its 32 query rows, split, in registers (pre-multiplied by scale * log2 e) and walks the keys in stages of 32.  The K
+// and V rows of a stage are split once per workgroup on their way into LDS, V transposed.  Scores are formed
+// transposed, S^T = K Q^T: a lane then holds 16 keys of ONE query, so the softmax statistics are per-lane loops plus
+// a single exchange between the two half-waves, and the probabilities sit exactly where the B operand of
+// O^T += V^T P^T wants them (the keys of a V row are stored in that order) -- no data movement between the two
+// products.  Softmax is the running-maximum form (scores never exist in memory), evaluated with exp2.
+// The key loop is skewed by one stage: the scores of stage i+1 are formed while the softmax of stage i runs, and the
+// split of the stages ahead runs under P V; a wave issues in order, so the pieces are interleaved by hand.
 #include "q8_device.h"
 #include "q8_launch.h"
+
+#include <type_traits>
 
 namespace q8 {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
-constexpr int kAtD = 64;                   // head width of the MFMA kernel
 constexpr int kAtWaves = 4;                // waves per workgroup
 constexpr int kAtThreads = kAtWaves * 64;
 constexpr int kAtQW = 32;                  // queries per wave
 constexpr int kAtQB = kAtQW * kAtWaves;    // queries per workgroup
-constexpr int kAtKB = 64;                  // keys per stage
-// LDS row strides in floats.  K rows are read 16 bytes per lane, 16 lanes (keys) per cycle: 68 = 4 (mod 64)
-// spreads them over all 64 banks.  V rows are read 4 bytes per lane, the two half-waves four keys apart:
-// 4 * 72 = 32 (mod 64) puts the halves on disjoint banks.
-constexpr int kAtKStride = 68;
-constexpr int kAtVStride = 72;
-constexpr int kAtKTile = kAtKB * kAtKStride + kAtKB;     // floats of a K tile in LDS, the stage's mask row behind it
-constexpr int kAtVTile = kAtKB * kAtVStride;
-constexpr int kAtStageFloats = kAtKTile + kAtVTile;
+constexpr int kAtKB = 32;                  // keys per stage
+constexpr int kAtMaxD = 128;               // head widths of the MFMA kernel: multiples of 4 up to here
 constexpr int kAtSlots = 2048;             // abs-max slots (= Q8_AMAX_SLOTS)
+
+// LDS of one stage, for heads padded to 32 * kDB columns: three parts of the K tile (a row per key), three parts of the
+// V tile (a row per column, its 32 keys in the order the P V operands take them), the stage's mask row.  Rows carry 16
+// bytes of padding: strides of 16 kDB + 4 and 20 dwords put the 16 rows a 16-byte read serves per cycle on all 64 banks.
+template <int kDB>
+struct AttnTile {
+    static constexpr int kKStride = 64 * kDB + 16, kVStride = 2 * kAtKB + 16;   // bytes
+    static constexpr int kKPart = kAtKB * kKStride, kVPart = 32 * kDB * kVStride;
+    static constexpr int kMask = 3 * kKPart;                                    // the mask row sits behind the K parts
+    static constexpr int kKTile = 3 * kKPart + 4 * kAtKB, kVTile = 3 * kVPart;
+    static constexpr int kBytes = 2 * (kKTile + kVTile);
+};
 
 struct AttnArgs {
     const float* qkv;     // [B*S, 3*heads*d]
@@ -53,243 +65,322 @@ struct AttnArgs {
     unsigned* q_out;      // int8 codes of ctx, packed four to a dword, or null
     int64_t S;
     int heads;
+    int d;
     int n_qblocks;        // ceil(S / 128)
     int slots_atomic;     // more workgroups than slots: fold with atomics into cleared slots
     float c;              // scale * log2(e)
 };
 
-// The score accumulators of a stage start at its mask row (log2 units, -inf beyond the sequence; it sits behind
-// the K tile), so the mask costs no addition: s[sub][e] of lane (lq, hi) belongs to key 32 sub + 8 (e/4) + 4 hi + e%4.
-__device__ __forceinline__ void attention_load_mask(const float* Ks, int hi, v16f (&s)[2])
+template <int I, int E, class F>
+__device__ __forceinline__ void at_static_for(F&& f)
 {
-    const float* mrow = Ks + kAtKB * kAtKStride + 4 * hi;
-#pragma unroll
-    for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const float4 mk = *reinterpret_cast<const float4*>(mrow + sub * 32 + 8 * g);
-            s[sub][4 * g + 0] = mk.x;
-            s[sub][4 * g + 1] = mk.y;
-            s[sub][4 * g + 2] = mk.z;
-            s[sub][4 * g + 3] = mk.w;
-        }
+    if constexpr (I < E) {
+        f(std::integral_constant<int, I>{});
+        at_static_for<I + 1, E>(f);
+    }
 }
 
-// S^T block of one stage (the prologue's; the trips form theirs chunk by chunk): s[sub][e] of lane (lq, hi) =
-// mask + <K[32 sub + 8 (e/4) + 4 hi + e%4], c Q[lq]>.  MFMA number 4t + i pairs column 8t + i (lower half-wave)
-// with column 8t + 4 + i (upper half-wave) of both operands.
-__device__ __forceinline__ void attention_scores(const float* Ks, const float (&q)[32], int lq, int hi, v16f (&s)[2])
+// Two binary32 numbers as three packed pairs of bf16 numbers whose sums they are, exactly: each part is the
+// nearest bf16 of what the parts before it leave, and the differences are exact.
+struct Bf16x3 {
+    unsigned h, m, l;
+};
+__device__ __forceinline__ unsigned pack_bf16(float a, float b)
 {
-    attention_load_mask(Ks, hi, s);
-#pragma unroll
-    for (int t = 0; t < 8; ++t)
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-            const float4 kf = *reinterpret_cast<const float4*>(Ks + (sub * 32 + lq) * kAtKStride + 4 * hi + 8 * t);
-            s[sub] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.x, q[4 * t + 0], s[sub], 0, 0, 0);
-            s[sub] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.y, q[4 * t + 1], s[sub], 0, 0, 0);
-            s[sub] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.z, q[4 * t + 2], s[sub], 0, 0, 0);
-            s[sub] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf.w, q[4 * t + 3], s[sub], 0, 0, 0);
-        }
+    v2f v;
+    v.x = a;
+    v.y = b;
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, v2bf));
+}
+__device__ __forceinline__ Bf16x3 split_bf16x3(float a, float b)
+{
+    Bf16x3 s;
+    s.h = pack_bf16(a, b);
+    const float ra = a - __uint_as_float(s.h << 16), rb = b - __uint_as_float(s.h & 0xffff0000u);
+    s.m = pack_bf16(ra, rb);
+    s.l = pack_bf16(ra - __uint_as_float(s.m << 16), rb - __uint_as_float(s.m & 0xffff0000u));
+    return s;
 }
 
-// Global -> registers -> LDS staging of the K and V tiles (and the mask row) of a stage.  Thread t carries chunks
-// t, t + 256, ... of the 64 x 16 float4 chunks of a tile: chunk i is key st_key + 16 i, 16-byte column st_ch.
-// Offsets within the sequence fit 32 bits (checked by the launcher); rows beyond the sequence repeat the last one.
+// Three-part operand of an MFMA: eight numbers of one lane, two to a dword.
+struct Frag3 {
+    v4u part[3];
+};
+__device__ __forceinline__ v8bf as_bf(v4u v) { return __builtin_bit_cast(v8bf, v); }
+
+// One of the six partial products of a . b, the small ones first.
+template <int I>
+__device__ __forceinline__ v16f mfma_part(const Frag3& a, const Frag3& b, v16f acc)
+{
+    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf(a.part[pa[I]]), as_bf(b.part[pb[I]]), acc, 0, 0, 0);
+}
+
+__device__ __forceinline__ float4 buf_f4(__amdgpu_buffer_rsrc_t r, unsigned off)
+{
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    const u4 v = __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
+}
+
+// Global -> registers -> (split) -> LDS staging of a stage.  An item is eight numbers: of the K tile eight columns of one
+// key, of the V tile the eight keys one half-wave takes to a 16-key step, of one column.  Descriptors span one stage
+// of one sequence, so offsets are 32 bits whatever the size of qkv, and rows beyond the sequence read as zeros.
+template <int kDB>
 struct AttnStager {
+    using T = AttnTile<kDB>;
+    static constexpr int kItems = (kAtKB * 4 * kDB + kAtThreads - 1) / kAtThreads;   // items of each tile per thread
+    static constexpr int kAll = kAtKB * 4 * kDB;
     const float *kbase, *vbase;   // K and V of token 0 of this sequence and head (wave-uniform)
     const float* mrow;            // mask row of the sequence, or null
-    float *k_tiles, *v_tiles;     // two (K tile + mask row); two V tiles
-    unsigned off_st0, off_16, off_stage, off_last;
-    int S32, tid, st_key, st_ch;
-    float4 k0, k1, k2, k3, v0, v1, v2, v3;
+    char *k_tiles, *v_tiles;      // two (K tile + mask row); two V tiles
+    int64_t ld;
+    int S32, d, tid;
+    unsigned k_off[kItems][2];    // byte offsets of an item's two float4 inside a stage
+    unsigned v_off[kItems];
+    int k_dst[kItems], v_dst[kItems];
+    float4 k[kItems][2];
+    float v[kItems][8];
     float m;
 
-    __device__ __forceinline__ unsigned off(int stage, int i) const
+    __device__ __forceinline__ void init(int t)
     {
-        return min(off_st0 + (unsigned)stage * off_stage + (unsigned)i * off_16, off_last);
-    }
-    __device__ __forceinline__ static float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
-    __device__ __forceinline__ void fetch_k01(int stage) { k0 = ld4(kbase + off(stage, 0)); k1 = ld4(kbase + off(stage, 1)); }
-    __device__ __forceinline__ void fetch_k23(int stage)
-    {
-        k2 = ld4(kbase + off(stage, 2));
-        k3 = ld4(kbase + off(stage, 3));
-        if (mrow) m = mrow[min(stage * kAtKB + (tid & 63), S32 - 1)];
-    }
-    __device__ __forceinline__ void fetch_v01(int stage) { v0 = ld4(vbase + off(stage, 0)); v1 = ld4(vbase + off(stage, 1)); }
-    __device__ __forceinline__ void fetch_v23(int stage) { v2 = ld4(vbase + off(stage, 2)); v3 = ld4(vbase + off(stage, 3)); }
-    // the mask row goes in with the K tile, in log2 units; beyond the sequence -inf: weight 0 whatever the
-    // (repeated) row holds
-    __device__ __forceinline__ float mask_value(int stage) const
-    {
-        return (stage * kAtKB + tid < S32) ? m * 1.44269504088896341f : -__builtin_inff();
-    }
-    __device__ __forceinline__ void stash_k(int buf, int stage) const
-    {
-        float* w = k_tiles + buf * kAtKTile + st_key * kAtKStride + 4 * st_ch;
-        *reinterpret_cast<float4*>(w) = k0;
-        *reinterpret_cast<float4*>(w + 16 * kAtKStride) = k1;
-        *reinterpret_cast<float4*>(w + 32 * kAtKStride) = k2;
-        *reinterpret_cast<float4*>(w + 48 * kAtKStride) = k3;
-        if (tid < kAtKB) k_tiles[buf * kAtKTile + kAtKB * kAtKStride + tid] = mask_value(stage);
-    }
-    // One LDS store of the stash that follows trip st: pieces 0-3 the V tile of stage st + 1, 4-7 the K tile
-    // of stage nk fetched during that trip, 8 its mask row.
-    __device__ __forceinline__ void stash_piece(int j, int st, int nk) const
-    {
-        if (j < 4) {
-            const float4 v = j == 0 ? v0 : j == 1 ? v1 : j == 2 ? v2 : v3;
-            *reinterpret_cast<float4*>(v_tiles + ((st + 1) & 1) * kAtVTile + (st_key + 16 * j) * kAtVStride + 4 * st_ch) = v;
-        } else if (j < 8) {
-            const float4 k = j == 4 ? k0 : j == 5 ? k1 : j == 6 ? k2 : k3;
-            *reinterpret_cast<float4*>(k_tiles + (st & 1) * kAtKTile + (st_key + 16 * (j - 4)) * kAtKStride + 4 * st_ch) = k;
-        } else if (tid < kAtKB) {
-            k_tiles[(st & 1) * kAtKTile + kAtKB * kAtKStride + tid] = mask_value(nk);
+        tid = t;
+        m = 0.0f;
+        const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) {
+            const int it = min(i * kAtThreads + t, kAll - 1), key = it / (4 * kDB), c = it % (4 * kDB);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) k_off[i][u] = 4u * ((unsigned)key * (unsigned)ld + (unsigned)min(8 * c + 4 * u, d - 4));
+            k_dst[i] = key * T::kKStride + 16 * c;
+            const int col = min(64 * i + lane, 32 * kDB - 1);
+            v_off[i] = 4u * (unsigned)min(col, d - 1);
+            v_dst[i] = col * T::kVStride + 16 * wave;   // wave = 2 * (16-key step) + half-wave
         }
     }
-    __device__ __forceinline__ void stash_v(int buf) const
+    // rows of a stage that exist, as a descriptor
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const float* base, int stage) const
     {
-        float* w = v_tiles + buf * kAtVTile + st_key * kAtVStride + 4 * st_ch;
-        *reinterpret_cast<float4*>(w) = v0;
-        *reinterpret_cast<float4*>(w + 16 * kAtVStride) = v1;
-        *reinterpret_cast<float4*>(w + 32 * kAtVStride) = v2;
-        *reinterpret_cast<float4*>(w + 48 * kAtVStride) = v3;
+        const int rows = min(S32 - stage * kAtKB, kAtKB);
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base) + (int64_t)stage * kAtKB * ld, 0,
+                                                 rows > 0 ? 4 * ((rows - 1) * (int)ld + d) : 0, 0x00020000);
+    }
+    __device__ __forceinline__ void fetch_k(int stage)
+    {
+        const auto r = rsrc(kbase, stage);
+#pragma unroll
+        for (int i = 0; i < kItems; ++i)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) k[i][u] = buf_f4(r, k_off[i][u]);
+        if (mrow) m = mrow[min(stage * kAtKB + (tid & (kAtKB - 1)), S32 - 1)];
+    }
+    __device__ __forceinline__ void fetch_v(int stage)
+    {
+        const auto r = rsrc(vbase, stage);
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int row0 = 16 * (wave >> 1) + 4 * (wave & 1);
+#pragma unroll
+        for (int i = 0; i < kItems; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                v[i][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)v_off[i], 4 * (row0 + (e & 3) + 8 * (e >> 2)) * (int)ld, 0));
+    }
+    // Pieces of the stash: per tile and item four splits of two numbers, then the three stores; the last piece is the
+    // mask row of the K stage (log2 units; -inf beyond the sequence: weight 0 whatever the row holds).
+    static constexpr int kPieces = 10 * kItems + 1;
+    Frag3 f;
+    template <int P>
+    __device__ __forceinline__ void piece(int k_buf, int v_buf, int k_stage)
+    {
+        if constexpr (P == kPieces - 1) {
+            if (tid < kAtKB)
+                *reinterpret_cast<float*>(k_tiles + k_buf * T::kKTile + T::kMask + 4 * tid) =
+                    (k_stage * kAtKB + tid < S32) ? m * 1.44269504088896341f : -__builtin_inff();
+        } else {
+            constexpr int i = P / 10, q = P % 10, u = q % 5;
+            constexpr bool is_v = q >= 5;
+            if constexpr (u < 4) {
+                float a, b;
+                if constexpr (is_v)
+                    a = v[i][2 * u], b = v[i][2 * u + 1];
+                else if constexpr ((u & 1) == 0)
+                    a = k[i][u >> 1].x, b = k[i][u >> 1].y;
+                else
+                    a = k[i][u >> 1].z, b = k[i][u >> 1].w;
+                const Bf16x3 s = split_bf16x3(a, b);
+                f.part[0][u] = s.h;
+                f.part[1][u] = s.m;
+                f.part[2][u] = s.l;
+            } else {
+                // threads past the last item (their loads repeated one) store nothing
+                const bool live = is_v ? 64 * i + (tid & 63) < 32 * kDB : i * kAtThreads + tid < kAll;
+                if (live) {
+                    char* w = is_v ? v_tiles + v_buf * T::kVTile + v_dst[i] : k_tiles + k_buf * T::kKTile + k_dst[i];
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) *reinterpret_cast<v4u*>(w + p * (is_v ? T::kVPart : T::kKPart)) = f.part[p];
+                }
+            }
+        }
+    }
+    // the same, all at once (prologue)
+    __device__ __forceinline__ void stash_k(int buf, int stage)
+    {
+        at_static_for<0, kPieces>([&](auto pc) {
+            constexpr int P = decltype(pc)::value;
+            if constexpr (P == kPieces - 1 || P % 10 < 5) piece<P>(buf, 0, stage);
+        });
+    }
+    __device__ __forceinline__ void stash_v(int buf)
+    {
+        at_static_for<0, kPieces - 1>([&](auto pc) {
+            constexpr int P = decltype(pc)::value;
+            if constexpr (P % 10 >= 5) piece<P>(0, buf, 0);
+        });
     }
 };
 
-// One trip of the key loop, skewed by a stage: the vector ALU runs the running-maximum softmax of the
-// current stage's scores `sc` (log2 units, mask included) while -- kMore -- the matrix pipe forms the next stage's
-// scores `sn` from the K tile Kn, its accumulators starting at that stage's mask row; then O^T += V^T P^T of the current stage.  A wave issues in order, so anything
-// that waits (an LDS read used at once, a block of address arithmetic and loads, arithmetic behind a run of
-// MFMAs) stops its MFMAs as well.  The streams are therefore cut into eight chunks issued in a fixed pattern
-// (scheduling groups): every chunk first requests what the NEXT chunk needs from LDS, then alternates one
-// MFMA with a few vector instructions.
-//   chunks 1-3: row maximum of this lane's 32 scores; exchange between the half-waves
-//   chunk  3  : reference maximum m; if it has to move, everything accumulated so far shrinks by 2^(m_old - m)
-//   chunks 4-7: p = 2^(s - m) and their sum
-//   chunks 0-3: the tile fetches of the stages ahead (V of stage st + 1, K of stage nk), two loads per chunk:
-//               issued between MFMAs they cost the matrix pipe nothing, issued in a block they stop it
-template <bool kMore>
-__device__ __forceinline__ void attention_trip(const float* Kn, const float* Vs, const float (&q)[32], int lq, int hi,
-                                               v16f (&sc)[2], v16f (&sn)[2], v16f (&o)[2], float& m_run, float& l_run,
-                                               AttnStager& sg, int st, int nk)
+// The score accumulators of a stage start at its mask row, so the mask costs no addition: s[e] of lane (lq, hi) belongs
+// to key 8 (e/4) + 4 hi + e%4.
+__device__ __forceinline__ v16f attention_mask_row(const char* row, int hi)
 {
-    float mx = -__builtin_inff(), m_new = 0.0f, psum = 0.0f;
-    const float* krow = Kn + lq * kAtKStride + 4 * hi;     // sub-block 1 is 32 rows further on
-    float4 kf[2], kf_next[2];
-    if (kMore) {
-        attention_load_mask(Kn, hi, sn);
+    v16f s;
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) kf[sub] = *reinterpret_cast<const float4*>(krow + sub * 32 * kAtKStride);
+    for (int g = 0; g < 4; ++g) {
+        const float4 mk = *reinterpret_cast<const float4*>(row + 16 * hi + 32 * g);
+        s[4 * g + 0] = mk.x;
+        s[4 * g + 1] = mk.y;
+        s[4 * g + 2] = mk.z;
+        s[4 * g + 3] = mk.w;
     }
+    return s;
+}
+
+// Running state of a wave's 32 queries (lane (lq, hi) and lane (lq, 1 - hi) belong to the same query).
+template <int kDB>
+struct AttnWave {
+    Frag3 q[2 * kDB];   // the queries, times scale * log2 e, split: step j holds columns 16 j + 8 hi .. + 7
+    v16f o[kDB];        // O^T: o[blk][e] = ctx[query lq][column 32 blk + 8 (e/4) + 4 hi + e%4], not yet normalised
+    float m_run;        // running reference maximum (log2 units)
+    float l_run;        // this lane's share of the running denominator
+};
+
+// Row maximum of a stage and the reference it is taken against.  The reference moves only when some row of the wave
+// outgrows it by more than 2^8: below that the probabilities are merely up to 256 times larger (harmless in binary32,
+// and the final division takes it out again), and the multiplications that shrink O are saved.  The first stage
+// always moves it (the reference starts at -inf; key 0 of the wave's first stage is inside the sequence).
+template <int kDB>
+__device__ __forceinline__ void attention_move_reference(AttnWave<kDB>& w, float mx)
+{
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    const float row_max = __builtin_fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    if (__builtin_amdgcn_ballot_w64(row_max > w.m_run + 8.0f) != 0) {
+        const float m_up = __builtin_fmaxf(w.m_run, row_max);
+        const float alpha = __builtin_amdgcn_exp2f(w.m_run - m_up);
+        w.m_run = m_up;
+        w.l_run *= alpha;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        // LDS requests for the next chunk: its K fragments
-        if (kMore && t < 7) {
+        for (int b = 0; b < kDB; ++b)
 #pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
-                kf_next[sub] = *reinterpret_cast<const float4*>(krow + sub * 32 * kAtKStride + 8 * (t + 1));
-        }
-        if (kMore) {
-            if (t == 0) sg.fetch_v01(st + 1);
-            if (t == 1) sg.fetch_v23(st + 1);
-            if (t == 2) sg.fetch_k01(nk);
-            if (t == 3) sg.fetch_k23(nk);
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub) {
-                sn[sub] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[sub].x, q[4 * t + 0], sn[sub], 0, 0, 0);
-                sn[sub] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[sub].y, q[4 * t + 1], sn[sub], 0, 0, 0);
-                sn[sub] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[sub].z, q[4 * t + 2], sn[sub], 0, 0, 0);
-                sn[sub] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[sub].w, q[4 * t + 3], sn[sub], 0, 0, 0);
-            }
-        }
-        if (t >= 1 && t <= 3) {
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                const int grp = 3 * (t - 1) + j;
-                if (grp < 8) {
-                    const int sub = grp >> 2, g = grp & 3;   // group = 4 consecutive keys
-                    mx = __builtin_fmaxf(mx, __builtin_fmaxf(__builtin_fmaxf(sc[sub][4 * g], sc[sub][4 * g + 1]),
-                                                             __builtin_fmaxf(sc[sub][4 * g + 2], sc[sub][4 * g + 3])));
-                }
-            }
-            if (t == 3) {
-                // both half-waves hold keys of the same query: swap the halves of two copies and take the maximum.
-                // Key 0 of stage 0 is always inside the sequence, so the maximum is finite from the first stage on.
-                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-                const float row_max = __builtin_fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-                // The reference maximum moves only when some row of the wave outgrows it by more than 2^8: below
-                // that the probabilities are merely up to 256 times larger (harmless in binary32, and the final
-                // division takes it out again), and the 32 multiplications that shrink O are saved.  The first
-                // stage always moves it (the reference starts at -inf).
-                if (__builtin_amdgcn_ballot_w64(row_max > m_run + 8.0f) != 0) {
-                    const float m_up = __builtin_fmaxf(m_run, row_max);
-                    const float alpha = __builtin_amdgcn_exp2f(m_run - m_up);
-                    m_run = m_up;
-                    l_run *= alpha;
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        o[0][e] *= alpha;
-                        o[1][e] *= alpha;
-                    }
-                }
-                m_new = m_run;
-            }
-        } else if (t >= 4) {
-#pragma unroll
-            for (int i = 8 * (t - 4); i < 8 * (t - 4) + 8; ++i) {
-                sc[i >> 4][i & 15] = __builtin_amdgcn_exp2f(sc[i >> 4][i & 15] - m_new);
-                psum += sc[i >> 4][i & 15];
-            }
-        }
-        if (kMore) {   // issue order within the chunk: the LDS reads, then one MFMA, four vector instructions, one MFMA, ...
-            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x402, 4, 0);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        kf[0] = kf_next[0];
-        kf[1] = kf_next[1];
-    }
-    l_run += psum;
-    // O^T += V^T P^T: MFMA pair i = (sub, e) joins key 32 sub + 8 (e/4) + e%4 (lower half-wave) with the key four
-    // further on (upper half-wave) -- the keys whose probabilities the two halves hold in register e.  The V
-    // operands of a pair are read kAhead pairs before their MFMAs (explicit ring, fenced so that it stays that
-    // way), and -- kMore -- the tiles fetched above go to LDS one store at a time under the last pairs (their
-    // buffers were last read in the previous trip).
-    constexpr int kAhead = 4;
-    float va[kAhead + 1][2];
-    const float* vcol = Vs + 4 * hi * kAtVStride + lq;
-    auto vkey = [](int i) { return (i >> 4) * 32 + 8 * ((i & 15) >> 2) + (i & 3); };
-#pragma unroll
-    for (int i = 0; i < kAhead; ++i) {
-        va[i][0] = vcol[vkey(i) * kAtVStride];
-        va[i][1] = vcol[vkey(i) * kAtVStride + 32];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < 32; ++i) {
-        if (i + kAhead < 32) {
-            va[(i + kAhead) % (kAhead + 1)][0] = vcol[vkey(i + kAhead) * kAtVStride];
-            va[(i + kAhead) % (kAhead + 1)][1] = vcol[vkey(i + kAhead) * kAtVStride + 32];
-        }
-        o[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i % (kAhead + 1)][0], sc[i >> 4][i & 15], o[0], 0, 0, 0);
-        o[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i % (kAhead + 1)][1], sc[i >> 4][i & 15], o[1], 0, 0, 0);
-        if (kMore && i >= 20 && i < 29) sg.stash_piece(i - 20, st, nk);
-        __builtin_amdgcn_sched_barrier(0);
+            for (int e = 0; e < 16; ++e) w.o[b][e] *= alpha;
     }
 }
 
-__global__ __launch_bounds__(kAtThreads, 2) void attention_mfma_kernel(AttnArgs a)
+// One trip of the key loop, skewed by a stage: the softmax of the current stage's scores `sc` (log2 units, mask
+// included) while -- kMore -- the matrix pipes form the next stage's scores from the K tile; then O^T += V^T P^T of the
+// current stage while the rows fetched a trip ago (K of stage st + 2, V of stage st + 1) are split and stored.
+template <int kDB, bool kMore>
+__device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, int lq, int hi, v16f& sc, AttnWave<kDB>& w,
+                                               AttnStager<kDB>& sg, int st)
 {
-    extern __shared__ __align__(16) float lds[];   // K tiles (+ mask rows) of two stages, then V tiles of two stages
+    using T = AttnTile<kDB>;
+    const char* krow = Kn + lq * T::kKStride + 16 * hi;
+    const char* vrow = Vs + lq * T::kVStride + 16 * hi;
+    constexpr int kSteps = 2 * kDB, kNqk = 6 * kSteps;
+    auto read_k = [&](int j) {
+        Frag3 f;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) f.part[p] = *reinterpret_cast<const v4u*>(krow + p * T::kKPart + 32 * j);
+        return f;
+    };
+    v16f sn;
+    Frag3 kf[2];
+    if constexpr (kMore) {
+        sn = attention_mask_row(Kn + T::kMask, hi);
+        kf[0] = read_k(0);
+    }
+    float mx = -__builtin_inff(), psum = 0.0f;
+    Frag3 pf[2];        // the probabilities, split: step j holds s[8 j .. 8 j + 7]
+    // softmax pieces: 0, 1 maximum; 2 reference; 3 + 2 i probabilities 2 i and 2 i + 1, 4 + 2 i their split
+    constexpr int kSoft = 19;
+    auto soft = [&](auto pc) {
+        constexpr int P = decltype(pc)::value;
+        if constexpr (P < 2) {
+#pragma unroll
+            for (int g = 2 * P; g < 2 * P + 2; ++g)
+                mx = __builtin_fmaxf(mx, __builtin_fmaxf(__builtin_fmaxf(sc[4 * g], sc[4 * g + 1]), __builtin_fmaxf(sc[4 * g + 2], sc[4 * g + 3])));
+        } else if constexpr (P == 2) {
+            attention_move_reference(w, mx);
+        } else {
+            constexpr int i = (P - 3) / 2;
+            if constexpr ((P & 1) == 1) {
+                sc[2 * i] = __builtin_amdgcn_exp2f(sc[2 * i] - w.m_run);
+                sc[2 * i + 1] = __builtin_amdgcn_exp2f(sc[2 * i + 1] - w.m_run);
+                psum += sc[2 * i];
+                psum += sc[2 * i + 1];
+            } else {
+                const Bf16x3 s = split_bf16x3(sc[2 * i], sc[2 * i + 1]);
+                pf[i >> 2].part[0][i & 3] = s.h;
+                pf[i >> 2].part[1][i & 3] = s.m;
+                pf[i >> 2].part[2][i & 3] = s.l;
+            }
+        }
+    };
+    if constexpr (kMore) {
+        at_static_for<0, kNqk>([&](auto nc) {
+            constexpr int n = decltype(nc)::value, j = n / 6;
+            if constexpr (n % 6 == 0 && j + 1 < kSteps) kf[(j + 1) & 1] = read_k(j + 1);
+            sn = mfma_part<n % 6>(kf[j & 1], w.q[j], sn);
+            at_static_for<kSoft * n / kNqk, kSoft*(n + 1) / kNqk>(soft);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    } else {
+        at_static_for<0, kSoft>(soft);
+    }
+    w.l_run += psum;
+    // P V: step j joins the keys of s[8 j .. 8 j + 7] of both half-waves
+    constexpr int kNpv = 12 * kDB;
+    auto read_v = [&](int n) {   // fragment n / 6: step (n / 6) / kDB, column block (n / 6) % kDB
+        const int j = n / kDB, b = n % kDB;
+        Frag3 f;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) f.part[p] = *reinterpret_cast<const v4u*>(vrow + p * T::kVPart + b * 32 * T::kVStride + 32 * j);
+        return f;
+    };
+    Frag3 vf[2];
+    vf[0] = read_v(0);
+    at_static_for<0, kNpv>([&](auto nc) {
+        constexpr int n = decltype(nc)::value, g = n / 6, j = g / kDB, b = g % kDB;
+        if constexpr (n % 6 == 0 && g + 1 < 2 * kDB) vf[(g + 1) & 1] = read_v(g + 1);
+        w.o[b] = mfma_part<n % 6>(vf[g & 1], pf[j], w.o[b]);
+        if constexpr (kMore) {
+            constexpr int kP = AttnStager<kDB>::kPieces;
+            at_static_for<kP * n / kNpv, kP*(n + 1) / kNpv>([&](auto pc) { sg.template piece<decltype(pc)::value>(st & 1, (st + 1) & 1, st + 2); });
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    if constexpr (kMore) sc = sn;
+}
+
+template <int kDB>
+__global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_kernel(AttnArgs a)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    using T = AttnTile<kDB>;
+    extern __shared__ __align__(16) char lds[];   // K tiles (+ mask rows) of two stages, then V tiles of two stages
     __shared__ unsigned wave_amax[kAtWaves];
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lq = lane & 31, hi = lane >> 5;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, lq = lane & 31, hi = lane >> 5;
     // Workgroups of one (sequence, head) are neighbours in the logical order; each XCD takes a contiguous
     // run of it so that they find the K and V rows in the same L2.
     int wid = blockIdx.x;
@@ -299,99 +390,103 @@ __global__ __launch_bounds__(kAtThreads, 2) void attention_mfma_kernel(AttnArgs 
     const int bh = wid / a.n_qblocks;
     const int h = bh % a.heads;
     const int64_t b = bh / a.heads;
-    const int64_t S = a.S, HD = (int64_t)a.heads * kAtD, ld = 3 * HD;
-    const float* base = a.qkv + b * S * ld + (int64_t)h * kAtD;   // Q of token 0 of this sequence and head
+    const int64_t S = a.S, HD = (int64_t)a.heads * a.d, ld = 3 * HD;
+    const float* base = a.qkv + b * S * ld + (int64_t)h * a.d;   // Q of token 0 of this sequence and head
     const int64_t q0 = (int64_t)qb * kAtQB + wave * kAtQW;
+    const bool wave_live = q0 < S;      // a wave whose queries all lie beyond the sequence only helps with the staging
 
-    AttnStager sg;
-    const int S32 = (int)S, ld32 = (int)ld;
-    const int n_stages = (S32 + kAtKB - 1) / kAtKB;
-    sg.S32 = S32;
-    sg.tid = tid;
-    sg.st_key = tid >> 4;
-    sg.st_ch = tid & 15;
+    AttnStager<kDB> sg;
     sg.kbase = base + HD;
     sg.vbase = base + 2 * HD;
     sg.mrow = a.mask ? a.mask + b * S : nullptr;
     sg.k_tiles = lds;
-    sg.v_tiles = lds + 2 * kAtKTile;
-    // offset (in floats, from kbase / vbase) of this thread's chunk 0 of stage 0, the steps to the next chunk and
-    // the next stage, and the offset of the same column in the last row of the sequence
-    sg.off_st0 = (unsigned)sg.st_key * (unsigned)ld32 + 4u * sg.st_ch;
-    sg.off_16 = 16u * (unsigned)ld32;
-    sg.off_stage = (unsigned)kAtKB * (unsigned)ld32;
-    sg.off_last = (unsigned)(S32 - 1) * (unsigned)ld32 + 4u * sg.st_ch;
-    sg.m = 0.0f;
-    float* const k_tiles = sg.k_tiles;
-    float* const v_tiles = sg.v_tiles;
+    sg.v_tiles = lds + 2 * T::kKTile;
+    sg.ld = ld;
+    sg.S32 = (int)S;
+    sg.d = a.d;
+    sg.init(tid);
+    const int n_stages = (sg.S32 + kAtKB - 1) / kAtKB, last = n_stages - 1;
 
-    v16f o[2];           // O^T: o[blk][e] = ctx[query lq][column 32 blk + 8 (e/4) + 4 hi + e%4], not yet normalised
-#pragma unroll
-    for (int e = 0; e < 16; ++e) o[0][e] = o[1][e] = 0.0f;
-    float m_run = -__builtin_inff();   // running maximum of this lane's query (log2 units), same in both half-waves
-    float l_run = 0.0f;                // this lane's share of the running denominator
-
-    // The loop is skewed by one stage: trip st forms the scores of stage st + 1 on the matrix pipe while the
-    // vector ALU runs the softmax of stage st, then accumulates P V of stage st.  So K runs one stage ahead
-    // of V in LDS, and two ahead in the staging registers.
-    v16f s_cur[2], s_nxt[2];
-    const int last = n_stages - 1;
-    sg.fetch_k01(0);
-    sg.fetch_k23(0);
-    // The wave's queries, requested behind the first K tile so that the two latencies overlap: lane (lq, hi)
-    // holds, for t = 0..7, columns 8t + 4hi .. 8t + 4hi + 3 of query lq, times scale * log2 e.  A row beyond
-    // the sequence repeats the last one (computed, never stored).
-    float q[32];
-    float4 qraw[8];
+    // the first K and V tiles, the second K tile and the wave's queries in one latency; columns beyond d are zeros in
+    // the queries (whatever K holds there)
+    sg.fetch_k(0);
+    AttnWave<kDB> w;
+    float4 qraw[2 * kDB][2];
     {
         const int64_t qrow = (q0 + lq < S) ? q0 + lq : S - 1;
-        const float4* qp = reinterpret_cast<const float4*>(base + qrow * ld) + hi;
+        const float* qp = base + qrow * ld;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) qraw[t] = qp[2 * t];
+        for (int j = 0; j < 2 * kDB; ++j)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) qraw[j][u] = *reinterpret_cast<const float4*>(qp + min(16 * j + 8 * hi + 4 * u, a.d - 4));
     }
+    sg.fetch_v(0);
     sg.stash_k(0, 0);
-    sg.fetch_v01(0);
-    sg.fetch_v23(0);
-    sg.fetch_k01(min(1, last));
-    sg.fetch_k23(min(1, last));
+    sg.fetch_k(1);
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        q[4 * t + 0] = qraw[t].x * a.c;
-        q[4 * t + 1] = qraw[t].y * a.c;
-        q[4 * t + 2] = qraw[t].z * a.c;
-        q[4 * t + 3] = qraw[t].w * a.c;
-    }
+    for (int j = 0; j < 2 * kDB; ++j)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const float c = (16 * j + 8 * hi + 4 * u < a.d) ? a.c : 0.0f;
+            const Bf16x3 s0 = split_bf16x3(qraw[j][u].x * c, qraw[j][u].y * c), s1 = split_bf16x3(qraw[j][u].z * c, qraw[j][u].w * c);
+            w.q[j].part[0][2 * u] = s0.h, w.q[j].part[1][2 * u] = s0.m, w.q[j].part[2][2 * u] = s0.l;
+            w.q[j].part[0][2 * u + 1] = s1.h, w.q[j].part[1][2 * u + 1] = s1.m, w.q[j].part[2][2 * u + 1] = s1.l;
+        }
+#pragma unroll
+    for (int blk = 0; blk < kDB; ++blk)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) w.o[blk][e] = 0.0f;
+    w.m_run = -__builtin_inff();
+    w.l_run = 0.0f;
     __syncthreads();
-    attention_scores(k_tiles, q, lq, hi, s_cur);
+    v16f sc;
+    {
+        const char* krow = sg.k_tiles + lq * T::kKStride + 16 * hi;
+        sc = attention_mask_row(sg.k_tiles + T::kMask, hi);
+        at_static_for<0, 2 * kDB>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            Frag3 f;
+#pragma unroll
+            for (int p = 0; p < 3; ++p) f.part[p] = *reinterpret_cast<const v4u*>(krow + p * T::kKPart + 32 * j);
+            at_static_for<0, 6>([&](auto ic) { sc = mfma_part<decltype(ic)::value>(f, w.q[j], sc); });
+        });
+    }
     sg.stash_v(0);
-    sg.stash_k(1, min(1, last));
+    sg.stash_k(1, 1);
+    sg.fetch_v(1);
+    sg.fetch_k(2);
     __syncthreads();
 
     for (int st = 0; st < last; ++st) {
-        attention_trip<true>(k_tiles + ((st + 1) & 1) * kAtKTile, v_tiles + (st & 1) * kAtVTile, q, lq, hi, s_cur, s_nxt, o, m_run,
-                             l_run, sg, st, min(st + 2, last));
+        if (wave_live) {
+            attention_trip<kDB, true>(sg.k_tiles + ((st + 1) & 1) * T::kKTile, sg.v_tiles + (st & 1) * T::kVTile, lq, hi, sc, w, sg, st);
+        } else {
+            sg.stash_k(st & 1, st + 2);
+            sg.stash_v((st + 1) & 1);
+        }
+        sg.fetch_v(st + 2);   // past the last stage: empty descriptors, nothing is read
+        sg.fetch_k(st + 3);
         __syncthreads();
-        s_cur[0] = s_nxt[0];
-        s_cur[1] = s_nxt[1];
     }
-    attention_trip<false>(k_tiles, v_tiles + (last & 1) * kAtVTile, q, lq, hi, s_cur, s_nxt, o, m_run, l_run, sg, last, last);
+    if (wave_live)
+        attention_trip<kDB, false>(sg.k_tiles, sg.v_tiles + (last & 1) * T::kVTile, lq, hi, sc, w, sg, last);
 
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    const float l_tot = w.l_run + __shfl_xor(w.l_run, 32, 64);
     const float inv = 1.0f / l_tot;
     const bool live = q0 + lq < S;
     const float qs = a.q_out ? a.q_scale[0] : 0.0f;
     float amax = 0.0f;
-    const int64_t out_off = (b * S + q0 + lq) * HD + (int64_t)h * kAtD + 4 * hi;
+    const int64_t out_off = (b * S + q0 + lq) * HD + (int64_t)h * a.d + 4 * hi;
 #pragma unroll
-    for (int blk = 0; blk < 2; ++blk)
+    for (int blk = 0; blk < kDB; ++blk)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             float4 v;
-            v.x = o[blk][4 * g + 0] * inv;
-            v.y = o[blk][4 * g + 1] * inv;
-            v.z = o[blk][4 * g + 2] * inv;
-            v.w = o[blk][4 * g + 3] * inv;
-            if (live) {
+            v.x = w.o[blk][4 * g + 0] * inv;
+            v.y = w.o[blk][4 * g + 1] * inv;
+            v.z = w.o[blk][4 * g + 2] * inv;
+            v.w = w.o[blk][4 * g + 3] * inv;
+            if (live && 32 * blk + 8 * g + 4 * hi < a.d) {
                 const int64_t off = out_off + 32 * blk + 8 * g;
                 if (a.ctx) *reinterpret_cast<float4*>(a.ctx + off) = v;
                 if (a.q_out)  // Eq. 1 with the stored scale of the next FC layer, four codes per lane
@@ -407,7 +502,7 @@ __global__ __launch_bounds__(kAtThreads, 2) void attention_mfma_kernel(AttnArgs 
         __syncthreads();
         if (tid == 0) {
 #pragma unroll
-            for (int w = 1; w < kAtWaves; ++w) m = max(m, wave_amax[w]);
+            for (int w2 = 1; w2 < kAtWaves; ++w2) m = max(m, wave_amax[w2]);
             if (a.slots_atomic) {
                 if (m) atomicMax(a.slots + (blockIdx.x % kAtSlots), m);
             } else {
@@ -417,6 +512,7 @@ __global__ __launch_bounds__(kAtThreads, 2) void attention_mfma_kernel(AttnArgs 
         if (!a.slots_atomic && blockIdx.x == 0)  // slots no workgroup owns
             for (int i = gridDim.x + tid; i < kAtSlots; i += kAtThreads) a.slots[i] = 0u;
     }
+#endif
 }
 
 // Any head width and alignment: one wave per (sequence, head, query).  Scores go to LDS, the softmax is the
@@ -485,9 +581,22 @@ int attention_generic_max_s() { return 16384; }   // scores of one query in 64 K
 bool attention_mfma_eligible(const float* qkv, int64_t B, int64_t S, int heads, int d, const float* ctx, const int8_t* q_out)
 {
     const int64_t wgs = B * heads * ((S + kAtQB - 1) / kAtQB);
-    // 32-bit arithmetic inside: the workgroup count, and offsets within one sequence of qkv
-    return d == kAtD && at_aligned(qkv, 16) && (!ctx || at_aligned(ctx, 16)) && at_aligned(q_out, 4) &&
-           wgs < ((int64_t)1 << 31) && S * 3 * heads * kAtD < ((int64_t)1 << 31);
+    // 32-bit arithmetic inside: the workgroup count, the row index, and byte offsets within 32 rows of qkv
+    return d % 4 == 0 && d <= kAtMaxD && at_aligned(qkv, 16) && (!ctx || at_aligned(ctx, 16)) && at_aligned(q_out, 4) &&
+           wgs < ((int64_t)1 << 31) && S < ((int64_t)1 << 30) && (int64_t)kAtKB * 3 * heads * d < ((int64_t)1 << 29);
+}
+
+template <int kDB>
+static int launch_attention_width(const AttnArgs& a, int64_t wgs, hipStream_t st)
+{
+    constexpr int lds_bytes = AttnTile<kDB>::kBytes;
+    if constexpr (lds_bytes > 64 * 1024) {   // more than 64 KiB of dynamic LDS has to be asked for
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(attention_mfma_kernel<kDB>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                lds_bytes) != hipSuccess)
+            return 1;
+    }
+    hipLaunchKernelGGL(attention_mfma_kernel<kDB>, dim3((unsigned)wgs), dim3(kAtThreads), lds_bytes, st, a);
+    return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
 int launch_attention(const float* qkv, int64_t B, int64_t S, int heads, int d, const float* mask, float scale, float* ctx,
@@ -511,19 +620,17 @@ int launch_attention(const float* qkv, int64_t B, int64_t S, int heads, int d, c
         a.q_out = reinterpret_cast<unsigned*>(q_out);
         a.S = S;
         a.heads = heads;
+        a.d = d;
         a.n_qblocks = (int)n_qblocks;
         a.slots_atomic = wgs > kAtSlots;
         a.c = c;
         if (slots && a.slots_atomic) hipLaunchKernelGGL(attention_slots_clear_kernel, dim3(1), dim3(256), 0, st, slots);
-        static bool attr_set = false;   // more than 64 KiB of dynamic LDS has to be asked for once
-        const size_t lds_bytes = 2 * kAtStageFloats * sizeof(float);
-        if (!attr_set) {
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(attention_mfma_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess)
-                return 1;
-            attr_set = true;
+        switch ((d + 31) / 32) {
+            case 1: return launch_attention_width<1>(a, wgs, st);
+            case 2: return launch_attention_width<2>(a, wgs, st);
+            case 3: return launch_attention_width<3>(a, wgs, st);
+            default: return launch_attention_width<4>(a, wgs, st);
         }
-        hipLaunchKernelGGL(attention_mfma_kernel, dim3((unsigned)wgs), dim3(kAtThreads), lds_bytes, st, a);
     } else {
         const int64_t blocks = B * heads * S;
         if (blocks >= ((int64_t)1 << 31)) return 1;
