@@ -81,10 +81,10 @@ __device__ __forceinline__ void at_static_for(F&& f)
 }
 
 // Two binary32 numbers as three packed pairs of bf16 numbers whose sums they are, exactly: each part is the
-// nearest bf16 of what the parts before it leave, and the differences are exact.
-struct Bf16x3 {
-    unsigned h, m, l;
-};
+// nearest bf16 of what the parts before it leave, and the differences are exact.  In two halves, so that the pieces that
+// go between two MFMAs stay small.  (v_dot2_f32_bf16 would unpack and subtract in one instruction, 7 for the pair
+// instead of 11, but it waits for the MFMA in flight: measured 62 cycles per MFMA with four of them between, 33 with
+// four ordinary instructions.)
 __device__ __forceinline__ unsigned pack_bf16(float a, float b)
 {
     v2f v;
@@ -92,19 +92,31 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b)
     v.y = b;
     return __builtin_bit_cast(unsigned, __builtin_convertvector(v, v2bf));
 }
-__device__ __forceinline__ Bf16x3 split_bf16x3(float a, float b)
-{
-    Bf16x3 s;
-    s.h = pack_bf16(a, b);
-    const float ra = a - __uint_as_float(s.h << 16), rb = b - __uint_as_float(s.h & 0xffff0000u);
-    s.m = pack_bf16(ra, rb);
-    s.l = pack_bf16(ra - __uint_as_float(s.m << 16), rb - __uint_as_float(s.m & 0xffff0000u));
-    return s;
-}
+struct Bf16x3 {
+    unsigned h, m, l;
+    float ra, rb;   // what h leaves
+    __device__ __forceinline__ void first(float a, float b)
+    {
+        h = pack_bf16(a, b);
+        ra = a - __uint_as_float(h << 16);
+        rb = b - __uint_as_float(h & 0xffff0000u);
+    }
+    __device__ __forceinline__ void second()
+    {
+        m = pack_bf16(ra, rb);
+        l = pack_bf16(ra - __uint_as_float(m << 16), rb - __uint_as_float(m & 0xffff0000u));
+    }
+};
 
 // Three-part operand of an MFMA: eight numbers of one lane, two to a dword.
 struct Frag3 {
     v4u part[3];
+    __device__ __forceinline__ void set(int i, const Bf16x3& s)
+    {
+        part[0][i] = s.h;
+        part[1][i] = s.m;
+        part[2][i] = s.l;
+    }
 };
 __device__ __forceinline__ v8bf as_bf(v4u v) { return __builtin_bit_cast(v8bf, v); }
 
@@ -139,14 +151,17 @@ struct AttnStager {
     unsigned k_off[kItems][2];    // byte offsets of an item's two float4 inside a stage
     unsigned v_off[kItems];
     int k_dst[kItems], v_dst[kItems];
-    float4 k[kItems][2];
-    float v[kItems][8];
-    float m;
+    // Rows in flight.  Set st & 1 holds what trip st stores: K of stage st + 2 and V of stage st + 1, requested two trips
+    // earlier; sets 2 and 3 are the prologue's.
+    float4 k[4][kItems][2];
+    float v[3][kItems][8];
+    float m[4];
+    bool masked;                  // the mask row of the K stage stashed last is not all zeros (wave-uniform)
 
     __device__ __forceinline__ void init(int t)
     {
         tid = t;
-        m = 0.0f;
+        m[0] = m[1] = m[2] = m[3] = 0.0f;
         const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
 #pragma unroll
         for (int i = 0; i < kItems; ++i) {
@@ -166,15 +181,17 @@ struct AttnStager {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base) + (int64_t)stage * kAtKB * ld, 0,
                                                  rows > 0 ? 4 * ((rows - 1) * (int)ld + d) : 0, 0x00020000);
     }
+    template <int kSet>
     __device__ __forceinline__ void fetch_k(int stage)
     {
         const auto r = rsrc(kbase, stage);
 #pragma unroll
         for (int i = 0; i < kItems; ++i)
 #pragma unroll
-            for (int u = 0; u < 2; ++u) k[i][u] = buf_f4(r, k_off[i][u]);
-        if (mrow) m = mrow[min(stage * kAtKB + (tid & (kAtKB - 1)), S32 - 1)];
+            for (int u = 0; u < 2; ++u) k[kSet][i][u] = buf_f4(r, k_off[i][u]);
+        if (mrow) m[kSet] = mrow[min(stage * kAtKB + (tid & (kAtKB - 1)), S32 - 1)];
     }
+    template <int kSet>
     __device__ __forceinline__ void fetch_v(int stage)
     {
         const auto r = rsrc(vbase, stage);
@@ -184,99 +201,137 @@ struct AttnStager {
         for (int i = 0; i < kItems; ++i)
 #pragma unroll
             for (int e = 0; e < 8; ++e)
-                v[i][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)v_off[i], 4 * (row0 + (e & 3) + 8 * (e >> 2)) * (int)ld, 0));
+                v[kSet][i][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)v_off[i], 4 * (row0 + (e & 3) + 8 * (e >> 2)) * (int)ld, 0));
     }
-    // Pieces of the stash: per tile and item four splits of two numbers, then the three stores; the last piece is the
-    // mask row of the K stage (log2 units; -inf beyond the sequence: weight 0 whatever the row holds).
-    static constexpr int kPieces = 10 * kItems + 1;
-    Frag3 f;
-    template <int P>
-    __device__ __forceinline__ void piece(int k_buf, int v_buf, int k_stage)
+    template <int kSet>
+    __device__ __forceinline__ void stash_mask(int buf, int stage)
     {
-        if constexpr (P == kPieces - 1) {
-            if (tid < kAtKB)
-                *reinterpret_cast<float*>(k_tiles + k_buf * T::kKTile + T::kMask + 4 * tid) =
-                    (k_stage * kAtKB + tid < S32) ? m * 1.44269504088896341f : -__builtin_inff();
-        } else {
-            constexpr int i = P / 10, q = P % 10, u = q % 5;
-            constexpr bool is_v = q >= 5;
-            if constexpr (u < 4) {
-                float a, b;
-                if constexpr (is_v)
-                    a = v[i][2 * u], b = v[i][2 * u + 1];
+        const int key = tid & (kAtKB - 1);   // eight threads write each value: no branch
+        const float v = (stage * kAtKB + key < S32) ? m[kSet] * 1.44269504088896341f : -__builtin_inff();   // beyond the sequence: weight 0 whatever the row holds
+        *reinterpret_cast<float*>(k_tiles + buf * T::kKTile + T::kMask + 4 * key) = v;
+        masked = __builtin_amdgcn_ballot_w64(v != 0.0f) != 0;
+    }
+    // What a trip does for the stages ahead, in pieces: per item the two halves of four splits of its K numbers, then their
+    // three stores; the mask row; the request of the K rows after those; the same for V.
+    static constexpr int kPieces = 18 * kItems + 4;
+    Frag3 f;
+    Bf16x3 part;
+    template <int kSet, bool kIsV, int kItem, int Q>
+    __device__ __forceinline__ void stash_piece(int buf)
+    {
+        constexpr int u = Q / 2;
+        if constexpr (u < 4) {
+            if constexpr (Q % 2 == 0) {
+                if constexpr (kIsV)
+                    part.first(v[kSet][kItem][2 * u], v[kSet][kItem][2 * u + 1]);
                 else if constexpr ((u & 1) == 0)
-                    a = k[i][u >> 1].x, b = k[i][u >> 1].y;
+                    part.first(k[kSet][kItem][u >> 1].x, k[kSet][kItem][u >> 1].y);
                 else
-                    a = k[i][u >> 1].z, b = k[i][u >> 1].w;
-                const Bf16x3 s = split_bf16x3(a, b);
-                f.part[0][u] = s.h;
-                f.part[1][u] = s.m;
-                f.part[2][u] = s.l;
+                    part.first(k[kSet][kItem][u >> 1].z, k[kSet][kItem][u >> 1].w);
             } else {
-                // threads past the last item (their loads repeated one) store nothing
-                const bool live = is_v ? 64 * i + (tid & 63) < 32 * kDB : i * kAtThreads + tid < kAll;
-                if (live) {
-                    char* w = is_v ? v_tiles + v_buf * T::kVTile + v_dst[i] : k_tiles + k_buf * T::kKTile + k_dst[i];
+                part.second();
+                f.set(u, part);
+            }
+        } else {
+            // threads past the last item (their loads repeated one) store nothing
+            constexpr bool all_live = kIsV ? 64 * (kItem + 1) <= 32 * kDB : (kItem + 1) * kAtThreads <= kAll;
+            if (all_live || (kIsV ? 64 * kItem + (tid & 63) < 32 * kDB : kItem * kAtThreads + tid < kAll)) {
+                char* w = kIsV ? v_tiles + buf * T::kVTile + v_dst[kItem] : k_tiles + buf * T::kKTile + k_dst[kItem];
 #pragma unroll
-                    for (int p = 0; p < 3; ++p) *reinterpret_cast<v4u*>(w + p * (is_v ? T::kVPart : T::kKPart)) = f.part[p];
-                }
+                for (int p = 0; p < 3; ++p) *reinterpret_cast<v4u*>(w + p * (kIsV ? T::kVPart : T::kKPart)) = f.part[p];
             }
         }
     }
-    // the same, all at once (prologue)
+    // kSet: parity of the current stage; k_stage: the K stage to store (two ahead; the V stage is the one before it)
+    template <int kSet, int P>
+    __device__ __forceinline__ void piece(int k_stage)
+    {
+        constexpr int kHalf = 9 * kItems + 2;
+        if constexpr (P < 9 * kItems)
+            stash_piece<kSet, false, P / 9, P % 9>(kSet);
+        else if constexpr (P == 9 * kItems)
+            stash_mask<kSet>(kSet, k_stage);
+        else if constexpr (P == kHalf - 1)
+            fetch_k<kSet>(k_stage + 2);
+        else if constexpr (P < kHalf + 9 * kItems)
+            stash_piece<kSet, true, (P - kHalf) / 9, (P - kHalf) % 9>(kSet ^ 1);
+        else if constexpr (P == kPieces - 1)
+            fetch_v<kSet>(k_stage + 1);   // past the last stage: empty descriptors, nothing is read
+    }
+    // the same, all at once
+    template <int kSet>
     __device__ __forceinline__ void stash_k(int buf, int stage)
     {
-        at_static_for<0, kPieces>([&](auto pc) {
-            constexpr int P = decltype(pc)::value;
-            if constexpr (P == kPieces - 1 || P % 10 < 5) piece<P>(buf, 0, stage);
-        });
+        at_static_for<0, 9 * kItems>([&](auto pc) { stash_piece<kSet, false, decltype(pc)::value / 9, decltype(pc)::value % 9>(buf); });
+        stash_mask<kSet>(buf, stage);
     }
+    template <int kSet>
     __device__ __forceinline__ void stash_v(int buf)
     {
-        at_static_for<0, kPieces - 1>([&](auto pc) {
-            constexpr int P = decltype(pc)::value;
-            if constexpr (P % 10 >= 5) piece<P>(0, buf, 0);
-        });
+        at_static_for<0, 9 * kItems>([&](auto pc) { stash_piece<kSet, true, decltype(pc)::value / 9, decltype(pc)::value % 9>(buf); });
+    }
+    template <int kSet>
+    __device__ __forceinline__ void all_pieces(int k_stage)
+    {
+        at_static_for<0, kPieces>([&](auto pc) { piece<kSet, decltype(pc)::value>(k_stage); });
     }
 };
 
-// The score accumulators of a stage start at its mask row, so the mask costs no addition: s[e] of lane (lq, hi) belongs
-// to key 8 (e/4) + 4 hi + e%4.
-__device__ __forceinline__ v16f attention_mask_row(const char* row, int hi)
-{
-    v16f s;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const float4 mk = *reinterpret_cast<const float4*>(row + 16 * hi + 32 * g);
-        s[4 * g + 0] = mk.x;
-        s[4 * g + 1] = mk.y;
-        s[4 * g + 2] = mk.z;
-        s[4 * g + 3] = mk.w;
-    }
-    return s;
-}
+// The maximum that the three-operand instruction takes directly (the other one first quiets each operand).
+__device__ __forceinline__ float at_max(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 
 // Running state of a wave's 32 queries (lane (lq, hi) and lane (lq, 1 - hi) belong to the same query).
 template <int kDB>
 struct AttnWave {
     Frag3 q[2 * kDB];   // the queries, times scale * log2 e, split: step j holds columns 16 j + 8 hi .. + 7
     v16f o[kDB];        // O^T: o[blk][e] = ctx[query lq][column 32 blk + 8 (e/4) + 4 hi + e%4], not yet normalised
-    float m_run;        // running reference maximum (log2 units)
+    float m_run;        // reference maximum (log2 units)
     float l_run;        // this lane's share of the running denominator
 };
 
-// Row maximum of a stage and the reference it is taken against.  The reference moves only when some row of the wave
-// outgrows it by more than 2^8: below that the probabilities are merely up to 256 times larger (harmless in binary32,
-// and the final division takes it out again), and the multiplications that shrink O are saved.  The first stage
-// always moves it (the reference starts at -inf; key 0 of the wave's first stage is inside the sequence).
+// First of the 6 * 2 kDB MFMAs of a stage's scores: the accumulators start at the stage's mask row, or at zero where that
+// is all zeros.  s[e] of lane (lq, hi) belongs to key 8 (e/4) + 4 hi + e%4.
+template <int kDB>
+__device__ __forceinline__ v16f attention_first_mfma(const char* mask_row, int hi, const AttnWave<kDB>& w, const Frag3& kf, bool masked)
+{
+    v16f s;
+    if (!masked) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[e] = 0.0f;
+        return mfma_part<0>(kf, w.q[0], s);
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const float4 mk = *reinterpret_cast<const float4*>(mask_row + 16 * hi + 32 * g);
+        s[4 * g + 0] = mk.x;
+        s[4 * g + 1] = mk.y;
+        s[4 * g + 2] = mk.z;
+        s[4 * g + 3] = mk.w;
+    }
+    return mfma_part<0>(kf, w.q[0], s);
+}
+
+// Part kP of 2 of the maximum of a lane's sixteen scores.
+template <int kP>
+__device__ __forceinline__ void attention_max_piece(const v16f& s, float& mx)
+{
+    if constexpr (kP == 0) mx = s[0];
+#pragma unroll
+    for (int e = 8 * kP; e < 8 * kP + 8; e += 2) mx = at_max(mx, at_max(s[e], s[e + 1]));
+    asm volatile("" : "+v"(mx));   // here, and not where it is used
+}
+
+// The reference against which a stage's probabilities are taken, from the maximum of the lane's scores.  It moves only
+// when some query of the wave outgrows it by more than 2^8: below that the probabilities are merely up to 256 times larger
+// (harmless in binary32, and the final division takes it out again), and the operations that shrink O are saved.  The
+// first stage always moves it (it starts at -inf; key 0 is inside the sequence).
 template <int kDB>
 __device__ __forceinline__ void attention_move_reference(AttnWave<kDB>& w, float mx)
 {
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-    const float row_max = __builtin_fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    const float row_max = at_max(__uint_as_float(sw[0]), __uint_as_float(sw[1]));   // both half-waves hold keys of the query
     if (__builtin_amdgcn_ballot_w64(row_max > w.m_run + 8.0f) != 0) {
-        const float m_up = __builtin_fmaxf(w.m_run, row_max);
-        const float alpha = __builtin_amdgcn_exp2f(w.m_run - m_up);
+        const float m_up = at_max(w.m_run, row_max), alpha = __builtin_amdgcn_exp2f(w.m_run - m_up);
         w.m_run = m_up;
         w.l_run *= alpha;
 #pragma unroll
@@ -286,90 +341,87 @@ __device__ __forceinline__ void attention_move_reference(AttnWave<kDB>& w, float
     }
 }
 
-// One trip of the key loop, skewed by a stage: the softmax of the current stage's scores `sc` (log2 units, mask
-// included) while -- kMore -- the matrix pipes form the next stage's scores from the K tile; then O^T += V^T P^T of the
-// current stage while the rows fetched a trip ago (K of stage st + 2, V of stage st + 1) are split and stored.
-template <int kDB, bool kMore>
-__device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, int lq, int hi, v16f& sc, AttnWave<kDB>& w,
-                                               AttnStager<kDB>& sg, int st)
+// One trip of the key loop, skewed by a stage: the softmax of the current stage's scores `sc` while -- kMore -- the
+// matrix pipes form the next stage's, `sn`, from the K tile; then O^T += V^T P^T of the current stage while the rows
+// requested two trips ago (K of `k_stage`, two ahead, and V of the stage before it) are split and stored and the next ones
+// requested.  A wave issues in order, so the vector work goes between the MFMAs in pieces of a few instructions: an
+// MFMA takes 32 cycles, and up to six vector instructions behind it are free; and the operands of six MFMAs are read
+// from LDS two groups of six ahead (one group ahead, a group waited 50 to 100 cycles for them).  kSet: parity of the
+// current stage.
+template <int kDB, bool kMore, int kSet>
+__device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, int lq, int hi, v16f& sc, v16f& sn, AttnWave<kDB>& w,
+                                               AttnStager<kDB>& sg, int k_stage)
 {
     using T = AttnTile<kDB>;
     const char* krow = Kn + lq * T::kKStride + 16 * hi;
     const char* vrow = Vs + lq * T::kVStride + 16 * hi;
-    constexpr int kSteps = 2 * kDB, kNqk = 6 * kSteps;
-    auto read_k = [&](int j) {
-        Frag3 f;
+    constexpr int kKG = kMore ? 2 * kDB : 0, kGroups = kKG + 2 * kDB;   // groups of six MFMAs: K steps, then V steps x column blocks
+    Frag3 frag[3];
+    auto read_group = [&](auto gc) {
+        constexpr int g = decltype(gc)::value;
+        if constexpr (g < kKG) {
 #pragma unroll
-        for (int p = 0; p < 3; ++p) f.part[p] = *reinterpret_cast<const v4u*>(krow + p * T::kKPart + 32 * j);
-        return f;
-    };
-    v16f sn;
-    Frag3 kf[2];
-    if constexpr (kMore) {
-        sn = attention_mask_row(Kn + T::kMask, hi);
-        kf[0] = read_k(0);
-    }
-    float mx = -__builtin_inff(), psum = 0.0f;
-    Frag3 pf[2];        // the probabilities, split: step j holds s[8 j .. 8 j + 7]
-    // softmax pieces: 0, 1 maximum; 2 reference; 3 + 2 i probabilities 2 i and 2 i + 1, 4 + 2 i their split
-    constexpr int kSoft = 19;
-    auto soft = [&](auto pc) {
-        constexpr int P = decltype(pc)::value;
-        if constexpr (P < 2) {
+            for (int p = 0; p < 3; ++p) frag[g % 3].part[p] = *reinterpret_cast<const v4u*>(krow + p * T::kKPart + 32 * g);
+        } else if constexpr (g < kGroups) {
+            constexpr int n = g - kKG;
 #pragma unroll
-            for (int g = 2 * P; g < 2 * P + 2; ++g)
-                mx = __builtin_fmaxf(mx, __builtin_fmaxf(__builtin_fmaxf(sc[4 * g], sc[4 * g + 1]), __builtin_fmaxf(sc[4 * g + 2], sc[4 * g + 3])));
-        } else if constexpr (P == 2) {
-            attention_move_reference(w, mx);
-        } else {
-            constexpr int i = (P - 3) / 2;
-            if constexpr ((P & 1) == 1) {
-                sc[2 * i] = __builtin_amdgcn_exp2f(sc[2 * i] - w.m_run);
-                sc[2 * i + 1] = __builtin_amdgcn_exp2f(sc[2 * i + 1] - w.m_run);
-                psum += sc[2 * i];
-                psum += sc[2 * i + 1];
-            } else {
-                const Bf16x3 s = split_bf16x3(sc[2 * i], sc[2 * i + 1]);
-                pf[i >> 2].part[0][i & 3] = s.h;
-                pf[i >> 2].part[1][i & 3] = s.m;
-                pf[i >> 2].part[2][i & 3] = s.l;
-            }
+            for (int p = 0; p < 3; ++p)
+                frag[g % 3].part[p] = *reinterpret_cast<const v4u*>(vrow + p * T::kVPart + (n % kDB) * 32 * T::kVStride + 32 * (n / kDB));
         }
     };
+    read_group(std::integral_constant<int, 0>{});
+    read_group(std::integral_constant<int, 1>{});
+
+    Frag3 pf[2];        // the probabilities, split: step j holds s[8 j .. 8 j + 7]
+    Bf16x3 part;
+    constexpr int kSoft = 24, kSoftFirst = kMore ? 6 : kSoft;   // the first ones go under the latency of the first operands
+    auto soft = [&](auto pc) {   // per pair of keys: their probabilities, then the halves of their split
+        constexpr int P = decltype(pc)::value, i = P / 3, q = P % 3;
+        if constexpr (q == 0) {
+            sc[2 * i] = __builtin_amdgcn_exp2f(sc[2 * i] - w.m_run);
+            sc[2 * i + 1] = __builtin_amdgcn_exp2f(sc[2 * i + 1] - w.m_run);
+            w.l_run += sc[2 * i] + sc[2 * i + 1];
+            asm volatile("" : "+v"(w.l_run));   // here, and not gathered into one chain behind the trip
+        } else if constexpr (q == 1) {
+            part.first(sc[2 * i], sc[2 * i + 1]);
+        } else {
+            part.second();
+            pf[i >> 2].set(i & 3, part);
+        }
+    };
+    at_static_for<0, kSoftFirst>(soft);
+    __builtin_amdgcn_sched_barrier(0);
     if constexpr (kMore) {
+        constexpr int kNqk = 6 * kKG;
         at_static_for<0, kNqk>([&](auto nc) {
-            constexpr int n = decltype(nc)::value, j = n / 6;
-            if constexpr (n % 6 == 0 && j + 1 < kSteps) kf[(j + 1) & 1] = read_k(j + 1);
-            sn = mfma_part<n % 6>(kf[j & 1], w.q[j], sn);
-            at_static_for<kSoft * n / kNqk, kSoft*(n + 1) / kNqk>(soft);
+            constexpr int n = decltype(nc)::value, g = n / 6;
+            if constexpr (n % 6 == 0) read_group(std::integral_constant<int, g + 2>{});
+            if constexpr (n == 0)
+                sn = attention_first_mfma(Kn + T::kMask, hi, w, frag[0], sg.masked);
+            else
+                sn = mfma_part<n % 6>(frag[g % 3], w.q[g], sn);
+            at_static_for<kSoftFirst + (kSoft - kSoftFirst) * n / kNqk, kSoftFirst + (kSoft - kSoftFirst) * (n + 1) / kNqk>(soft);
             __builtin_amdgcn_sched_barrier(0);
         });
-    } else {
-        at_static_for<0, kSoft>(soft);
     }
-    w.l_run += psum;
     // P V: step j joins the keys of s[8 j .. 8 j + 7] of both half-waves
     constexpr int kNpv = 12 * kDB;
-    auto read_v = [&](int n) {   // fragment n / 6: step (n / 6) / kDB, column block (n / 6) % kDB
-        const int j = n / kDB, b = n % kDB;
-        Frag3 f;
-#pragma unroll
-        for (int p = 0; p < 3; ++p) f.part[p] = *reinterpret_cast<const v4u*>(vrow + p * T::kVPart + b * 32 * T::kVStride + 32 * j);
-        return f;
-    };
-    Frag3 vf[2];
-    vf[0] = read_v(0);
+    float mx = 0.0f;
     at_static_for<0, kNpv>([&](auto nc) {
-        constexpr int n = decltype(nc)::value, g = n / 6, j = g / kDB, b = g % kDB;
-        if constexpr (n % 6 == 0 && g + 1 < 2 * kDB) vf[(g + 1) & 1] = read_v(g + 1);
-        w.o[b] = mfma_part<n % 6>(vf[g & 1], pf[j], w.o[b]);
+        constexpr int n = decltype(nc)::value, g = kKG + n / 6, j = (n / 6) / kDB, b = (n / 6) % kDB;
+        if constexpr (n % 6 == 0) read_group(std::integral_constant<int, g + 2>{});
+        w.o[b] = mfma_part<n % 6>(frag[g % 3], pf[j], w.o[b]);
         if constexpr (kMore) {
-            constexpr int kP = AttnStager<kDB>::kPieces;
-            at_static_for<kP * n / kNpv, kP*(n + 1) / kNpv>([&](auto pc) { sg.template piece<decltype(pc)::value>(st & 1, (st + 1) & 1, st + 2); });
+            if constexpr (n == 3) attention_max_piece<0>(sn, mx);
+            if constexpr (n == 4) attention_max_piece<1>(sn, mx);
+            constexpr int kP = AttnStager<kDB>::kPieces, kFrom = 5;
+            if constexpr (n >= kFrom)
+                at_static_for<kP*(n - kFrom) / (kNpv - kFrom), kP*(n + 1 - kFrom) / (kNpv - kFrom)>(
+                    [&](auto pc) { sg.template piece<kSet, decltype(pc)::value>(k_stage); });
         }
         __builtin_amdgcn_sched_barrier(0);
     });
-    if constexpr (kMore) sc = sn;
+    if constexpr (kMore) attention_move_reference(w, mx);
 }
 
 template <int kDB>
@@ -407,9 +459,9 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
     sg.init(tid);
     const int n_stages = (sg.S32 + kAtKB - 1) / kAtKB, last = n_stages - 1;
 
-    // the first K and V tiles, the second K tile and the wave's queries in one latency; columns beyond d are zeros in
-    // the queries (whatever K holds there)
-    sg.fetch_k(0);
+    // Everything the first trips need is requested at once -- a 128-token sequence in full -- so that its way from memory
+    // is waited for once; columns beyond d are zeros in the queries (whatever K holds there).
+    sg.template fetch_k<2>(0);
     AttnWave<kDB> w;
     float4 qraw[2 * kDB][2];
     {
@@ -420,17 +472,26 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
 #pragma unroll
             for (int u = 0; u < 2; ++u) qraw[j][u] = *reinterpret_cast<const float4*>(qp + min(16 * j + 8 * hi + 4 * u, a.d - 4));
     }
-    sg.fetch_v(0);
-    sg.stash_k(0, 0);
-    sg.fetch_k(1);
+    sg.template fetch_v<2>(0);
+    sg.template fetch_k<3>(1);
+    sg.template fetch_k<0>(2);
+    sg.template fetch_v<0>(1);
+    sg.template fetch_k<1>(3);
+    sg.template fetch_v<1>(2);
+    __builtin_amdgcn_sched_barrier(0);
+    sg.template stash_k<2>(0, 0);
 #pragma unroll
     for (int j = 0; j < 2 * kDB; ++j)
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const float c = (16 * j + 8 * hi + 4 * u < a.d) ? a.c : 0.0f;
-            const Bf16x3 s0 = split_bf16x3(qraw[j][u].x * c, qraw[j][u].y * c), s1 = split_bf16x3(qraw[j][u].z * c, qraw[j][u].w * c);
-            w.q[j].part[0][2 * u] = s0.h, w.q[j].part[1][2 * u] = s0.m, w.q[j].part[2][2 * u] = s0.l;
-            w.q[j].part[0][2 * u + 1] = s1.h, w.q[j].part[1][2 * u + 1] = s1.m, w.q[j].part[2][2 * u + 1] = s1.l;
+            Bf16x3 part;
+            part.first(qraw[j][u].x * c, qraw[j][u].y * c);
+            part.second();
+            w.q[j].set(2 * u, part);
+            part.first(qraw[j][u].z * c, qraw[j][u].w * c);
+            part.second();
+            w.q[j].set(2 * u + 1, part);
         }
 #pragma unroll
     for (int blk = 0; blk < kDB; ++blk)
@@ -439,40 +500,60 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
     w.m_run = -__builtin_inff();
     w.l_run = 0.0f;
     __syncthreads();
-    v16f sc;
+    v16f s0, s1;
     {
         const char* krow = sg.k_tiles + lq * T::kKStride + 16 * hi;
-        sc = attention_mask_row(sg.k_tiles + T::kMask, hi);
         at_static_for<0, 2 * kDB>([&](auto jc) {
             constexpr int j = decltype(jc)::value;
             Frag3 f;
 #pragma unroll
             for (int p = 0; p < 3; ++p) f.part[p] = *reinterpret_cast<const v4u*>(krow + p * T::kKPart + 32 * j);
-            at_static_for<0, 6>([&](auto ic) { sc = mfma_part<decltype(ic)::value>(f, w.q[j], sc); });
+            if constexpr (j == 0) s0 = attention_first_mfma(sg.k_tiles + T::kMask, hi, w, f, sg.masked);
+            at_static_for<(j == 0 ? 1 : 0), 6>([&](auto ic) { s0 = mfma_part<decltype(ic)::value>(f, w.q[j], s0); });
         });
     }
-    sg.stash_v(0);
-    sg.stash_k(1, 1);
-    sg.fetch_v(1);
-    sg.fetch_k(2);
+    sg.template stash_v<2>(0);
+    sg.template stash_k<3>(1, 1);
+    {
+        float mx;
+        attention_max_piece<0>(s0, mx);
+        attention_max_piece<1>(s0, mx);
+        attention_move_reference(w, mx);
+    }
     __syncthreads();
 
-    for (int st = 0; st < last; ++st) {
-        if (wave_live) {
-            attention_trip<kDB, true>(sg.k_tiles + ((st + 1) & 1) * T::kKTile, sg.v_tiles + (st & 1) * T::kVTile, lq, hi, sc, w, sg, st);
-        } else {
-            sg.stash_k(st & 1, st + 2);
-            sg.stash_v((st + 1) & 1);
+    // Two trips per turn, so that the scores of the next stage become those of the current one without a copy.  A wave
+    // without queries passes the same barriers.
+    char *const k0 = sg.k_tiles, *const k1 = k0 + T::kKTile, *const v0 = sg.v_tiles, *const v1 = v0 + T::kVTile;
+    int st = 0;
+    if (wave_live) {
+        for (; st + 2 <= last; st += 2) {
+            attention_trip<kDB, true, 0>(k1, v0, lq, hi, s0, s1, w, sg, st + 2);
+            __syncthreads();
+            attention_trip<kDB, true, 1>(k0, v1, lq, hi, s1, s0, w, sg, st + 3);
+            __syncthreads();
         }
-        sg.fetch_v(st + 2);   // past the last stage: empty descriptors, nothing is read
-        sg.fetch_k(st + 3);
-        __syncthreads();
+        if (st < last) {
+            attention_trip<kDB, true, 0>(k1, v0, lq, hi, s0, s1, w, sg, st + 2);
+            __syncthreads();
+            s0 = s1;
+        }
+        attention_trip<kDB, false, 0>(k0, (last & 1) ? v1 : v0, lq, hi, s0, s1, w, sg, 0);
+    } else {
+        for (; st + 2 <= last; st += 2) {
+            sg.template all_pieces<0>(st + 2);
+            __syncthreads();
+            sg.template all_pieces<1>(st + 3);
+            __syncthreads();
+        }
+        if (st < last) {
+            sg.template all_pieces<0>(st + 2);
+            __syncthreads();
+        }
     }
-    if (wave_live)
-        attention_trip<kDB, false>(sg.k_tiles, sg.v_tiles + (last & 1) * T::kVTile, lq, hi, sc, w, sg, last);
 
-    const float l_tot = w.l_run + __shfl_xor(w.l_run, 32, 64);
-    const float inv = 1.0f / l_tot;
+    const auto l2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(w.l_run), __float_as_uint(w.l_run), false, false);
+    const float inv = 1.0f / (__uint_as_float(l2[0]) + __uint_as_float(l2[1]));
     const bool live = q0 + lq < S;
     const float qs = a.q_out ? a.q_scale[0] : 0.0f;
     float amax = 0.0f;
