@@ -78,14 +78,25 @@ __device__ __forceinline__ float gelu_erf(float v)
     return __builtin_fmaf(-a, __builtin_amdgcn_exp2f(p), __builtin_fmaxf(v, 0.0f));  // one rounding, one operation less
 }
 
+// Maximum over the 64 lanes, the same value in every lane: a scan inside each row of 16 lanes with DPP row shifts (lanes
+// shifted in from outside contribute zero), the row totals carried across with the two row broadcasts, lane 63's total
+// read back as a scalar.  Every step stays in the vector ALU; six exchanges through LDS (ds_bpermute) take ten times as
+// long, and the small kernels here end in one to three of these reductions with nothing else to do.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ unsigned dpp_max_u32(unsigned v)
+{
+    const unsigned o = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, kRowMask, 0xf, true);
+    return v > o ? v : o;
+}
 __device__ __forceinline__ unsigned wave_max_u32(unsigned v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        unsigned o = (unsigned)__shfl_xor((int)v, off, 64);
-        v = v > o ? v : o;
-    }
-    return v;
+    v = dpp_max_u32<0x111, 0xf>(v);  // row_shr:1
+    v = dpp_max_u32<0x112, 0xf>(v);  // row_shr:2
+    v = dpp_max_u32<0x114, 0xf>(v);  // row_shr:4
+    v = dpp_max_u32<0x118, 0xf>(v);  // row_shr:8   -> lane 15 of each row holds its row's maximum
+    v = dpp_max_u32<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+    v = dpp_max_u32<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3 -> lane 63 holds the total
+    return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
 }
 
 }  // namespace q8
