@@ -120,8 +120,9 @@ q8_status q8_quantize_amax(const float* x, int64_t n, const float* amax, int n_a
  *   (one atomic max per workgroup lands in it).
  *   Epilogue order: dequantize, GELU, abs-max, requantize.
  * M, N >= 0 (either 0: nothing is written); 0 <= K <= Q8_MAX_K; sizes are otherwise
- * free -- shapes with K % 128 == 0 and 16-byte aligned xq/wq take the MFMA kernel,
- * anything else a slower generic kernel with identical results.
+ * free -- shapes with K % 128 == 0 and 16-byte aligned xq/wq take the MFMA kernels with
+ * operands staged straight into LDS, anything else one that loads them through registers,
+ * with identical results (large launches: at about a quarter of the rate).
  * bq + sum must fit int32 (it wraps otherwise; unreachable for BERT-sized biases).
  */
 q8_status q8_linear(const int8_t* xq, const int8_t* wq, const float* bias,
@@ -362,8 +363,9 @@ q8_status q8_attention(const float* qkv, int64_t B, int64_t S, int heads, int d,
  * ---- tuning / debugging (not part of the method) ----
  *
  * Forces the tile shape of the MFMA GEMM behind q8_linear for every later call of this process:
- * 0 = automatic choice from the shape (the default), 1..6 = one fixed tile variant (tests and
- * tile sweeps use it to run every variant on every shape).  Process-global and unsynchronised: set it
+ * 0 = automatic choice from the shape (the default), 1..7 = one fixed tile variant of the staged
+ * kernel (shapes it cannot take go to the direct kernel), 8 = the direct kernel (tests and tile
+ * sweeps use it to run every variant on every shape).  Process-global and unsynchronised: set it
  * while no other thread is inside q8_linear.  An unknown variant makes q8_linear return Q8_ERR_LAUNCH.
  */
 void q8_debug_set_gemm_variant(int variant);

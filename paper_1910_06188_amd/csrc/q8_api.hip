@@ -77,7 +77,7 @@ q8::Epilogue make_epilogue(const float* bias, const float* sx, const float* sw, 
     return ep;
 }
 
-// Checks, fills the epilogue and picks the MFMA kernel or the generic one.
+// Checks, fills the epilogue and launches the GEMM.
 q8_status linear_launch(const int8_t* xq, const int8_t* wq, const float* bias, const float* sx, const float* sw,
                         int n_groups, int64_t M, int64_t N, int64_t K, void* y, int32_t* acc_out, float* out_amax,
                         const float* next_scale, const float* residual, uint32_t flags, void* stream)
@@ -85,10 +85,7 @@ q8_status linear_launch(const int8_t* xq, const int8_t* wq, const float* bias, c
     q8_status s = check_linear(xq, wq, bias, sx, sw, n_groups, M, N, K, y, acc_out, out_amax, next_scale, flags);
     if (s != Q8_OK || M == 0 || N == 0) return s;
     const q8::Epilogue ep = make_epilogue(bias, sx, sw, n_groups, N, y, acc_out, out_amax, next_scale, residual, flags);
-    int rc = q8::gemm_mfma_eligible(xq, wq, M, N, K)
-                 ? q8::launch_gemm_mfma(xq, wq, M, N, K, ep, as_stream(stream))
-                 : q8::launch_gemm_generic(xq, wq, M, N, K, ep, as_stream(stream));
-    return rc ? Q8_ERR_LAUNCH : Q8_OK;
+    return q8::launch_gemm(xq, wq, M, N, K, ep, as_stream(stream)) ? Q8_ERR_LAUNCH : Q8_OK;
 }
 
 }  // namespace

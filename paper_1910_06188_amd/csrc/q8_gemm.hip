@@ -12,25 +12,32 @@
 // v_mfma_i32_32x32x32_i8.  LDS rows are swizzled so fragment reads are free of bank
 // conflicts; the swizzle costs nothing on the way in because each lane of a
 // direct-to-LDS load picks its own global address while the LDS side stays linear.
+//
+// Any other K or alignment, and launches of at most 256 tiles of 32x32, go to the kernel of q8_gemm_direct.hip; a handful
+// of products to the one-thread-per-output kernel below.
 #include "q8_device.h"
 #include "q8_epilogue.h"
 #include "q8_launch.h"
 
 namespace q8 {
 
-constexpr int kBK = 128;  // the MFMA kernel's K granularity (see q8_gemm_kernel.h)
+constexpr int kBK = 128;  // the staged kernel's K granularity (see q8_gemm_kernel.h)
 
 // One translation unit per tile shape.
 int launch_tile_256x256_w4(const int8_t*, const int8_t*, int, int, int, int, const Epilogue&, hipStream_t);
 int launch_tile_256x256_w8(const int8_t*, const int8_t*, int, int, int, int, const Epilogue&, hipStream_t);
 int launch_tile_128x128_w4(const int8_t*, const int8_t*, int, int, int, int, const Epilogue&, hipStream_t);
+int launch_tile_64x64_w4(const int8_t*, const int8_t*, int, int, int, int, const Epilogue&, hipStream_t);
 int launch_tile_192x256_w4(const int8_t*, const int8_t*, int, int, int, int, const Epilogue&, hipStream_t);
 int launch_tile_192x256_w8(const int8_t*, const int8_t*, int, int, int, int, const Epilogue&, hipStream_t);
 int launch_tile_192x128_w4(const int8_t*, const int8_t*, int, int, int, int, const Epilogue&, hipStream_t);
 
-// Any shape and alignment: one thread per output element.  Slow; same results.
-__global__ __launch_bounds__(256) void gemm_generic_kernel(const int8_t* __restrict__ X, const int8_t* __restrict__ W,
-                                                            int64_t M, int64_t N, int64_t K, Epilogue ep)
+// One thread per output element: reductions so short that the loads of a direct-kernel tile take longer than the whole sum
+// (5 x 33 x 9: 2.6 us against 4.7; 64 x 4096 x 9: 3.8 against 5.1; 1 x 2 x 17: 2.9 against 4.4).  The chain of K byte loads costs 45 ns
+// an element, and many outputs queue up: 16384 x 64 x 9 takes 8.5 us against 6.7.
+constexpr int64_t kScalarMaxK = 32, kScalarMaxProducts = (int64_t)1 << 22;
+__global__ __launch_bounds__(256) void gemm_scalar_kernel(const int8_t* __restrict__ X, const int8_t* __restrict__ W,
+                                                           int64_t M, int64_t N, int64_t K, Epilogue ep)
 {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const bool valid = idx < M * N;
@@ -55,9 +62,12 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const int8_t* __restr
 
 static int g_variant = 0;
 void set_gemm_variant(int v) { g_variant = v; }
-int get_gemm_variant() { return g_variant; }
 
-bool gemm_mfma_eligible(const int8_t* xq, const int8_t* wq, int64_t M, int64_t N, int64_t K)
+// Variants 1 to 6 are the staged tile shapes of full launches, 7 the small one with deep rings, 8 the direct kernel.
+constexpr int kVariant64 = 7, kVariantDirect = 8;
+
+// What the staged kernels can take.
+static bool gemm_staged_eligible(const int8_t* xq, const int8_t* wq, int64_t M, int64_t N, int64_t K)
 {
     if (K < kBK || K % kBK != 0) return false;
     if ((reinterpret_cast<uintptr_t>(xq) & 15) || (reinterpret_cast<uintptr_t>(wq) & 15)) return false;
@@ -66,11 +76,27 @@ bool gemm_mfma_eligible(const int8_t* xq, const int8_t* wq, int64_t M, int64_t N
     return M > 0 && N > 0;
 }
 
-int launch_gemm_mfma(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, int64_t K64, const Epilogue& ep,
-                     hipStream_t st)
+int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, int64_t K64, const Epilogue& ep, hipStream_t st)
 {
-    const int M = (int)M64, N = (int)N64, K = (int)K64;
     int v = g_variant;
+    if (v == 0 && K64 <= kScalarMaxK && M64 * N64 <= kScalarMaxProducts / (K64 > 0 ? K64 : 1)) {
+        hipLaunchKernelGGL(gemm_scalar_kernel, dim3((unsigned)((M64 * N64 + 255) / 256)), dim3(256), 0, st, xq, wq, M64, N64, K64, ep);
+        return hipGetLastError() == hipSuccess ? 0 : 1;
+    }
+    if (v == kVariantDirect || !gemm_staged_eligible(xq, wq, M64, N64, K64)) return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);
+    const int M = (int)M64, N = (int)N64, K = (int)K64;
+    if (v == 0) {
+        // Launches that leave compute units idle are bound by the chain of stages each workgroup walks, so they get the
+        // smallest tile that still fits the chip in one round.  One 32x32 tile per unit, the reduction split over eight
+        // waves: 256 x 768 x 3072 6.5 us against 8.4 with 64x64 tiles and 14.7 with 128x128, 128 x 768 x 768 4.1 against
+        // 4.4 and 6.1; at 288 such tiles (384 x 768 x 768) the 64x64 ones are ahead, 4.4 against 4.8.  Two 64x64 tiles
+        // per unit: 651 x 768 x 3072 8.7 us against 15.1 with 128x128, 651 x 2304 x 768 (396 tiles) 6.8 against 8.0,
+        // 2048 x 1024 x 1024 (512) 8.0 against 8.8; at 576 (1024 x 2304 x 768) the large tiles win, 8.2 against 9.5.
+        const int64_t tiles32 = (((int64_t)M + 31) / 32) * (((int64_t)N + 31) / 32);
+        const int64_t tiles64 = (((int64_t)M + 63) / 64) * (((int64_t)N + 63) / 64);
+        if (tiles32 <= 256) return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);
+        if (tiles64 <= 512) v = kVariant64;
+    }
     if (v == 0) {
         // Pick the tile shape with the best expected use of the chip: the fraction of the launch's
         // workgroup slots that hold work (256 compute units; tiles whose rings take half of the
@@ -124,16 +150,9 @@ int launch_gemm_mfma(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N6
         case 4: return launch_tile_192x256_w4(xq, wq, M, N, K, group_m, ep, st);
         case 5: return launch_tile_192x256_w8(xq, wq, M, N, K, group_m, ep, st);
         case 6: return launch_tile_192x128_w4(xq, wq, M, N, K, group_m, ep, st);
+        case kVariant64: return launch_tile_64x64_w4(xq, wq, M, N, K, group_m, ep, st);
         default: return 1;
     }
-}
-
-int launch_gemm_generic(const int8_t* xq, const int8_t* wq, int64_t M, int64_t N, int64_t K, const Epilogue& ep,
-                        hipStream_t st)
-{
-    const int64_t blocks = (M * N + 255) / 256;
-    hipLaunchKernelGGL(gemm_generic_kernel, dim3((unsigned)blocks), dim3(256), 0, st, xq, wq, M, N, K, ep);
-    return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
 }  // namespace q8

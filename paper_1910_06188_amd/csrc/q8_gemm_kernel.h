@@ -92,7 +92,7 @@ __device__ __forceinline__ void static_for(F&& f)
 // which only happens if each wave also stays within half of the register file.
 constexpr int mfma_waves_per_simd(int BM, int BN, int SB, int NW)
 {
-    return ((2 * BM + SB * BN) * kBK <= 80 * 1024 ? 2 : 1) * (NW / 4);
+    return (((SB > 3 ? SB : 2) * BM + SB * BN) * kBK <= 80 * 1024 ? 2 : 1) * (NW / 4);
 }
 
 // Software-pipelined MFMA kernel.
@@ -115,6 +115,11 @@ constexpr int mfma_waves_per_simd(int BM, int BN, int SB, int NW)
 // the first three k-steps, leaving only the A loads for the last one; where LDS cannot hold
 // it (SB = 2) all loads fall in the last k-step.
 //
+// Deep rings (SB > 3; SA = SB then): a launch with fewer tiles than the chip has places waits for memory, not for the
+// matrix pipe, so both operands run SB - 1 stages ahead, all loads spread over the first three k-steps.  Used for the
+// 64x64 tile (five stages of 16 KiB, two workgroups per compute unit: 651 x 768 x 3072 15.1 -> 8.7 us); the same ring
+// under a 128x128 tile gains nothing (17.1 us either way at 4096 x 768 x 3072: bound by its LDS traffic).
+//
 // Every memory operation of a k-step is placed by hand behind a given MFMA (LDS reads early,
 // global loads at least two MFMAs apart).  Loads past the end of K go through an empty
 // buffer descriptor (num_records = 0): the hardware drops them and returns zeros, so the
@@ -130,7 +135,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, mfma_waves_per_simd(BM, BN, SB, WGM*
                                                                    int tiles_n, int group_m, Epilogue ep)
 {
 #if defined(__HIP_DEVICE_COMPILE__)  // the host pass only needs the launch stub
-    constexpr int SA = 2;
+    constexpr bool kDeep = SB > 3;
+    constexpr int SA = kDeep ? SB : 2;
     constexpr bool kGen = kEpi < 0, kPlain = kEpi == 0;
     const bool do_gelu = kGen ? (ep.flags & 1u) != 0 : (kEpi & 1) != 0;
     const bool do_amax = kGen ? (ep.flags & 2u) != 0 : (kEpi & 2) != 0;
@@ -146,9 +152,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, mfma_waves_per_simd(BM, BN, SB, WGM*
     constexpr int A_LOADS = BM / 8 / NW, B_LOADS = BN / 8 / NW;  // 1 KiB wave loads per stage
     static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile rows must split over the waves");
     static_assert(TM % 32 == 0 && TN % 32 == 0, "wave tile must be made of 32x32 blocks");
-    static_assert(SB == 2 || SB == 3, "B ring depth");
+    static_assert(SB >= 2, "ring depth");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS is 160 KiB per compute unit");
-    static_assert(A_LOADS + B_LOADS <= 63, "vmcnt is a 6-bit counter");
+    static_assert((kDeep ? SB - 1 : 1) * (A_LOADS + B_LOADS) <= 63, "vmcnt is a 6-bit counter");
 
     __shared__ __attribute__((aligned(1024))) char lds[LDS_BYTES];
 
@@ -289,12 +295,14 @@ __global__ __launch_bounds__(WGM* WGN * 64, mfma_waves_per_simd(BM, BN, SB, WGM*
     };
     if constexpr (!kGen) fetch_first_residuals();
 
-    // Prologue: stages 0 and 1 of both operands; wait for stage 0.
-    load_all_a(src_a(0, 0));
-    load_all_b(src_b(0, 0));
-    load_all_a(src_a(1, 1));
-    load_all_b(src_b(1, 1));
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(A_LOADS + B_LOADS));
+    // Prologue: stages 0 and 1 of both operands (deep rings: all but one slot); wait for stage 0.
+    constexpr int kAhead = kDeep ? SB - 1 : 2;
+    static_for<0, kAhead>([&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+        load_all_a(src_a(p, p));
+        load_all_b(src_b(p, p));
+    });
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm((kAhead - 1) * (A_LOADS + B_LOADS)));
     __syncthreads();
 #pragma unroll
     for (int f = 0; f < FM; ++f) fa[0][f] = *reinterpret_cast<const v4i*>(lds + a_frag_off[f][0]);
@@ -304,20 +312,21 @@ __global__ __launch_bounds__(WGM* WGN * 64, mfma_waves_per_simd(BM, BN, SB, WGM*
     constexpr int NM = FM * FN, NR = FM + FN;
     int a_slot = 0, b_slot = 0;  // ring slots of the stage being consumed
     for (int kt = 0; kt < KT; ++kt) {
-        const int a_next = a_slot ^ 1;
+        const int a_next = (a_slot + 1 == SA) ? 0 : a_slot + 1;
         const int b_next = (b_slot + 1 == SB) ? 0 : b_slot + 1;
         const int b_prev = (b_slot == 0) ? SB - 1 : b_slot - 1;
         const char* cur_a = lds + a_slot * A_BYTES;
         const char* cur_b = lds + b_slot * B_BYTES;
         // SB = 3: the B slot of stage kt-1 was left by every wave at the last barrier (at
-        // kt = 0 it has not been used yet); it takes the B tile of stage kt+2
-        const Src qb3 = src_b(kt + 2, b_prev);
+        // kt = 0 it has not been used yet); it takes the B tile of stage kt+2.  Deep rings: both tiles of stage kt+SB-1
+        const Src qb3 = src_b(kt + (kDeep ? SB - 1 : 2), b_prev);
+        const Src qa3 = src_a(kt + SB - 1, b_prev);  // deep rings only
         // k-steps 0..2
         static_for<0, kKS - 1>([&](auto ksc) {
             constexpr int ks = decltype(ksc)::value;
             constexpr int C = ks & 1, Nx = (ks + 1) & 1;
-            constexpr int bl0 = (SB == 3) ? (B_LOADS * ks) / (kKS - 1) : 0;
-            constexpr int bl1 = (SB == 3) ? (B_LOADS * (ks + 1)) / (kKS - 1) : 0;
+            constexpr int kSpread = SB == 2 ? 0 : kDeep ? A_LOADS + B_LOADS : B_LOADS;  // loads of these k-steps, B first
+            constexpr int bl0 = (kSpread * ks) / (kKS - 1), bl1 = (kSpread * (ks + 1)) / (kKS - 1);
             constexpr int ND = bl1 - bl0;
             static_for<0, NM>([&](auto ic) {
                 constexpr int idx = decltype(ic)::value;
@@ -331,17 +340,20 @@ __global__ __launch_bounds__(WGM* WGN * 64, mfma_waves_per_simd(BM, BN, SB, WGM*
                     else
                         fb[Nx][r - FM] = *reinterpret_cast<const v4i*>(cur_b + b_frag_off[r - FM][ks + 1]);
                 });
-                // B loads, spread over the k-step
+                // operand loads, spread over the k-step
                 static_for<(ND * idx) / NM, (ND * (idx + 1)) / NM>([&](auto lc) {
                     constexpr int l = bl0 + decltype(lc)::value;
-                    lds_dma16_run<l>(qb3.rsrc, b_off[l], qb3.koff, qb3.dst);
+                    if constexpr (l < B_LOADS)
+                        lds_dma16_run<l>(qb3.rsrc, b_off[l], qb3.koff, qb3.dst);
+                    else
+                        lds_dma16_run<l - B_LOADS>(qa3.rsrc, a_off[l - B_LOADS], qa3.koff, qa3.dst);
                 });
                 __builtin_amdgcn_sched_barrier(0);
             });
         });
-        // own LDS reads of stage kt are complete and own loads of stage kt+1 have landed;
-        // with SB = 3 the B loads just issued may still be in flight
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(SB == 3 ? B_LOADS : 0));
+        // own LDS reads of stage kt are complete and own loads of stage kt+1 have landed; with SB = 3 the B loads
+        // just issued may still be in flight, with deep rings everything of the stages behind kt+1
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm_lgkm0(kDeep ? (SB - 2) * (A_LOADS + B_LOADS) : SB == 3 ? B_LOADS : 0));
         __syncthreads();
         __builtin_amdgcn_sched_barrier(0);
         // last k-step: every wave has left stage kt's slots
@@ -351,7 +363,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, mfma_waves_per_simd(BM, BN, SB, WGM*
             const char* nxt_a = lds + a_next * A_BYTES;
             const char* nxt_b = lds + b_next * B_BYTES;
             constexpr int C = (kKS - 1) & 1;
-            constexpr int ND = A_LOADS + (SB == 2 ? B_LOADS : 0);
+            constexpr int ND = kDeep ? 0 : A_LOADS + (SB == 2 ? B_LOADS : 0);
             static_for<0, NM>([&](auto ic) {
                 constexpr int idx = decltype(ic)::value;
                 constexpr int i = idx / FN, j = idx % FN;

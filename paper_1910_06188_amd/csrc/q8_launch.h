@@ -49,13 +49,10 @@ int launch_ema_update(const float* amax, int n_amax, float decay, float* state, 
                       hipStream_t st);
 int launch_ste_backward(const float* g, int64_t n, float* gx, hipStream_t st);
 
-// True when the MFMA kernel can take the problem (K % 128 == 0, K >= 128, 16-byte
-// aligned operands; operands and output may be of any size, they are addressed per tile).
-bool gemm_mfma_eligible(const int8_t* xq, const int8_t* wq, int64_t M, int64_t N, int64_t K);
-int launch_gemm_mfma(const int8_t* xq, const int8_t* wq, int64_t M, int64_t N, int64_t K, const Epilogue& ep,
-                     hipStream_t st);
-int launch_gemm_generic(const int8_t* xq, const int8_t* wq, int64_t M, int64_t N, int64_t K, const Epilogue& ep,
-                        hipStream_t st);
+// The Int8 GEMM with its epilogue, any shape and alignment: picks the kernel and its tile (q8_gemm.hip).
+int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M, int64_t N, int64_t K, const Epilogue& ep, hipStream_t st);
+// The kernel for small launches and for any K and alignment (q8_gemm_direct.hip).
+int launch_gemm_direct(const int8_t* xq, const int8_t* wq, int64_t M, int64_t N, int64_t K, const Epilogue& ep, hipStream_t st);
 
 // The dynamic-quantization FC layer of at most 32 tokens in one launch (q8_fc_small.hip): every workgroup runs the
 // quantizer itself and keeps the codes in LDS.  Eligible: M <= 32, M * K <= 16384, K a multiple of 128 up to 1024,
@@ -98,6 +95,5 @@ int launch_loop_probe(int what, const void* opbuf, float* ybuf, int stages, int*
 // Tuning hook used by the benchmark and tests: selects the MFMA tile variant
 // (0 = automatic choice from the shape).
 void set_gemm_variant(int v);
-int get_gemm_variant();
 
 }  // namespace q8

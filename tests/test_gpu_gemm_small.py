@@ -1,0 +1,79 @@
+"""The kernels of small and ragged FC launches: 64x64 tiles with deep rings (variant 7) and the direct kernel (variant 8,
+and variant 0 wherever K is no multiple of 128 or an operand is not 16-byte aligned), and the one-thread-per-output kernel
+of the very shortest reductions.  Every output must carry the bits of
+the staged 128x128 kernel on operands zero-padded to a multiple of 128, which the other tests pin to the oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from oracle import q8_oracle as O
+from paper_1910_06188_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def q8():
+    from paper_1910_06188_amd import q8 as m
+    return m
+
+
+def at_offset(a, off):
+    """A device copy of the int8 array whose first byte lies `off` bytes behind a 16-byte boundary and whose last byte
+    ends the allocation's used part."""
+    buf = torch.zeros(a.size + off, dtype=torch.int8, device="cuda")
+    buf[off:] = torch.from_numpy(a.reshape(-1)).cuda()
+    return buf[off:].view(a.shape)
+
+
+@pytest.mark.parametrize("M,K,N,variant,off", [
+    # the direct kernel: every class of row end (bytes, words, one vector, a unit and what follows it) on ragged tiles
+    (5, 1, 3, 8, 0), (33, 3, 34, 8, 0), (31, 4, 32, 8, 1), (40, 7, 65, 8, 3), (64, 15, 31, 8, 0), (1, 16, 2, 8, 5), (33, 17, 70, 8, 0),
+    (20, 31, 24, 8, 2), (65, 127, 33, 0, 0), (32, 128, 32, 0, 1), (37, 129, 100, 0, 0), (70, 250, 129, 0, 7), (96, 1000, 200, 0, 0),
+    (18, 1151, 40, 0, 0), (8, 2048, 96, 8, 0), (130, 3072, 64, 0, 0), (33, 4095, 31, 0, 15),
+    # one thread per output, and the direct kernel right behind it
+    (5, 1, 3, 0, 0), (33, 31, 70, 0, 1), (64, 32, 2048, 0, 0), (65, 32, 2048, 0, 0), (40, 33, 20, 0, 0),
+    # 512 / 513 tiles and beyond: eight, four, two and one wave a tile
+    (512, 130, 1024, 0, 0), (513, 130, 1000, 0, 0), (1024, 257, 1024, 0, 0), (1025, 40, 1020, 0, 0), (2048, 100, 1024, 0, 0), (2050, 300, 1030, 0, 1),
+    # 64x64 tiles: fewer stages than the ring holds, more of them, ragged edges, interior tiles
+    (64, 128, 64, 7, 0), (65, 256, 63, 7, 0), (128, 512, 192, 7, 0), (130, 640, 200, 7, 0), (192, 768, 256, 7, 0), (651, 1152, 130, 7, 0),
+    # the rule's own choice on both sides of 256 small and 512 medium tiles
+    (256, 256, 1024, 0, 0), (257, 256, 1024, 0, 0), (1024, 256, 2048, 0, 0), (1025, 256, 2048, 0, 0),
+])
+def test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, variant, off):
+    g = synth.rng(9000 + M + K + N)
+    xh, wh = synth.random_int8(g, (M, K)), synth.random_int8(g, (N, K))
+    Kp = (K + 127) // 128 * 128
+    pad = lambda a: torch.from_numpy(np.pad(a, ((0, 0), (0, Kp - K)))).cuda()
+    xp, wp, x, w = pad(xh), pad(wh), at_offset(xh, off), at_offset(wh, off)
+    b = torch.from_numpy(synth.bias(g, N)).cuda()
+    res = torch.from_numpy(g.standard_normal((M, N)).astype(np.float32)).cuda()
+    one = lambda v: torch.tensor([v], dtype=torch.float32, device="cuda")
+    sx, sw, ns = one(24.0), one(900.0), one(9.0)
+    guard = 64
+
+    def run(v, x, w, flags, residual=False, dump=False):
+        dt = torch.int8 if flags & 4 else torch.float32
+        buf = torch.full((M * N + guard,), 77, dtype=dt, device="cuda")
+        y, am = buf[:M * N].view(M, N), one(0.0)
+        acc = torch.empty((M, N), dtype=torch.int32, device="cuda") if dump else None
+        q8.set_gemm_variant(v)
+        try:
+            if residual:
+                q8.q8_linear_residual(x, w, b, sx, sw, res, y, acc_out=acc, out_amax=am if flags & 2 else None, flags=flags)
+            else:
+                q8.q8_linear(x, w, b, sx, sw, y, acc_out=acc, out_amax=am if flags & 2 else None, next_scale=ns if flags & 4 else None, flags=flags)
+        finally:
+            q8.set_gemm_variant(0)
+        torch.cuda.synchronize()
+        assert bool((buf[M * N:] == 77).all()), "wrote behind y"
+        return y, am.item(), acc
+
+    for flags, residual in [(f, False) for f in range(8)] + [(0, True), (3, True)]:
+        y, am, _ = run(variant, x, w, flags, residual)
+        y_ref, am_ref, _ = run(3, xp, wp, flags, residual)
+        assert torch.equal(y, y_ref) and am == am_ref, (flags, residual)
+    _, _, acc = run(variant, x, w, 3, dump=True)
+    bq = O.quantize_bias(b.cpu().numpy(), N, 24.0, [900.0])
+    np.testing.assert_array_equal(acc.cpu().numpy(), O.gemm_i8(xh, wh, bq, threads=8))
