@@ -294,15 +294,10 @@ q8_status q8_fake_quantize_ema(const float* x, int64_t n, float decay, float* st
     if (!state || !scal_work) return Q8_ERR_NULL;
     if (n > 0 && (!x || !xq)) return Q8_ERR_NULL;
     if (misaligned(x, 4) || misaligned(xq, 4) || misaligned(state, 4) || misaligned(scal_work, 4)) return Q8_ERR_ALIGN;
-    int slots = 1;
-    if (n == 0) {
-        if (q8::launch_absmax(x, 0, scal_work + 2, nullptr, as_stream(stream))) return Q8_ERR_LAUNCH;
-    } else if (q8::launch_absmax_partial(x, n, scal_work + 2, &slots, as_stream(stream))) {
-        return Q8_ERR_LAUNCH;
-    }
-    if (q8::launch_ema_update(scal_work + 2, slots, decay, state, scal_work, scal_work + 1, as_stream(stream)))
-        return Q8_ERR_LAUNCH;
-    return q8::launch_fake_quantize(x, n, scal_work + 1, xq, as_stream(stream)) ? Q8_ERR_LAUNCH : Q8_OK;
+    if (n > 0) return q8::launch_fake_quantize_ema(x, n, decay, state, scal_work, xq, as_stream(stream)) ? Q8_ERR_LAUNCH : Q8_OK;
+    // an empty tensor still takes a step of the average
+    if (q8::launch_absmax(x, 0, scal_work + 2, nullptr, as_stream(stream))) return Q8_ERR_LAUNCH;
+    return q8::launch_ema_update(scal_work + 2, 1, decay, state, scal_work, scal_work + 1, as_stream(stream)) ? Q8_ERR_LAUNCH : Q8_OK;
 }
 
 q8_status q8_ste_backward(const float* grad_xq, int64_t n, float* grad_x, void* stream)

@@ -3,6 +3,7 @@
 // Eq. 4 and the straight-through gradient (Eq. 5).  All are single passes over fp32 data and
 // are bound by HBM bandwidth: abs-max reads 4 B per element, quantize reads 4 B and writes
 // 1 B, fake quantization and the gradient copy read 4 B and write 4 B.
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -29,6 +30,16 @@ __device__ __forceinline__ float4 load_f4_nt(const float4* p)
     const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
     return make_float4(v.x, v.y, v.z, v.w);
 }
+
+// The training-side passes write a tensor as large as the one they read.  Stored non-temporally, an output beyond a quarter
+// of the 256 MB Infinity Cache (it could not stay there until its consumer runs) neither evicts what the next pass reads
+// nor leaves dirty lines to drain under it: 12288 x 4096, fake quantization and gradient of one FC 202 -> 174 us.
+// Smaller outputs (37 MB: 45 us either way) are left in the cache for their consumer.
+__device__ __forceinline__ void store_f4_nt(float4* p, float4 v)
+{
+    __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4*>(p));
+}
+static bool stream_out(int64_t n) { return n * (int64_t)sizeof(float) > ((int64_t)64 << 20); }
 
 __global__ void absmax_init_kernel(unsigned* amax_bits) { amax_bits[0] = 0u; }
 
@@ -101,10 +112,13 @@ __global__ __launch_bounds__(kEwThreads) void absmax_atomic_kernel(const float* 
 }
 
 // Fused path: each workgroup leaves its abs-max in its own slot; the quantize kernel that
-// follows folds the slots.  No atomics at all.
+// follows folds the slots.  No atomics at all.  old_state (or null): where the two floats of a moving average are copied
+// to, for the kernel that follows to read in every workgroup while one of them writes the new ones.
 __global__ __launch_bounds__(kEwThreads) void absmax_partial_kernel(const float* __restrict__ x, int64_t n, int head,
-                                                                     unsigned* __restrict__ partials)
+                                                                     unsigned* __restrict__ partials,
+                                                                     const float* __restrict__ state, float* __restrict__ old_state)
 {
+    if (old_state && blockIdx.x == 0 && threadIdx.x < 2) old_state[threadIdx.x] = state[threadIdx.x];
     unsigned m = block_max_u32(absmax_thread(x, n, head));
     if (threadIdx.x == 0) partials[blockIdx.x] = m;
 }
@@ -303,13 +317,53 @@ __device__ __forceinline__ float4 fake_quantize4(float4 v, float s)
                        fake_quantize_value(v.w, s));
 }
 
-// x and xq 16-byte aligned (they may be the same buffer: every element is read before its
-// own store and by no other thread).
-template <bool kVec>
-__global__ __launch_bounds__(kEwThreads) void fake_quantize_kernel(const float* x, int64_t n,
-                                                                    const float* __restrict__ scale, float* xq)
+// One step of the moving average under Eq. 4: the old state and the new abs-max give the next average, four binary32
+// operations in this order; on the first call (state[1] == 0) the abs-max itself.
+__device__ __forceinline__ float ema_step(float old_average, float seen, float decay, float amax)
 {
-    const float s = scale[0];
+    if (seen == 0.0f) return amax;
+    const float keep = __fmul_rn(decay, old_average);
+    const float take = __fmul_rn(__fsub_rn(1.0f, decay), amax);
+    return __fadd_rn(keep, take);
+}
+
+struct EmaArgs {
+    const float* amax;       // n_amax abs-max values of x
+    int n_amax;
+    float decay;
+    const float* old_state;  // copy of the state before this step
+    float* state;
+    float *amax_out, *scale_out;
+};
+
+// Scale of a moving-average quantizer, the same in every workgroup; block 0 also writes the new state and publishes.
+// In a launch of its own (one workgroup between the abs-max pass and this one) the step costs 3 to 4 us.
+__device__ __forceinline__ float ema_scale(const EmaArgs& e)
+{
+    __shared__ unsigned folded;
+    unsigned m = 0u;
+    for (int i = threadIdx.x; i < e.n_amax; i += kEwThreads) m = max(m, abs_bits(e.amax[i]));
+    m = block_max_u32(m);
+    if (threadIdx.x == 0) folded = m;
+    __syncthreads();
+    const float a = __uint_as_float(folded);
+    const float average = ema_step(e.old_state[0], e.old_state[1], e.decay, a);
+    const float s = scale_from_amax(average);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        e.state[0] = average;
+        e.state[1] = 1.0f;
+        e.amax_out[0] = a;
+        e.scale_out[0] = s;
+    }
+    return s;
+}
+
+// x and xq 16-byte aligned for kVec (they may be the same buffer: every element is read before its
+// own store and by no other thread).  kEma: the scale comes from a moving average, else from scale[0].
+template <bool kVec, bool kNt, bool kEma>
+__global__ __launch_bounds__(kEwThreads) void fake_quantize_kernel(const float* x, int64_t n,
+                                                                    const float* __restrict__ scale, float* xq, EmaArgs ema)
+{
     if (kVec) {
         const float4* xv = reinterpret_cast<const float4*>(x);
         float4* yv = reinterpret_cast<float4*>(xq);
@@ -317,12 +371,30 @@ __global__ __launch_bounds__(kEwThreads) void fake_quantize_kernel(const float* 
         // trips over blocks of kEwUnroll neighbouring 4 KiB pieces, block (trip * grid + b) to workgroup b (see absmax_thread)
         const int64_t step = (int64_t)gridDim.x * (kEwUnroll * kEwThreads);
         int64_t i = (int64_t)blockIdx.x * (kEwUnroll * kEwThreads) + threadIdx.x;
-        for (; i + (kEwUnroll - 1) * kEwThreads < nvec; i += step) {
-            float4 v[kEwUnroll];
+        float4 v[kEwUnroll];
+        const bool full_first = i + (kEwUnroll - 1) * kEwThreads < nvec;
+        if (full_first) {  // in flight while the scale is formed
 #pragma unroll
             for (int u = 0; u < kEwUnroll; ++u) v[u] = xv[i + u * kEwThreads];
+        }
+        const float s = kEma ? ema_scale(ema) : scale[0];
+        auto store_trip = [&]() {
 #pragma unroll
-            for (int u = 0; u < kEwUnroll; ++u) yv[i + u * kEwThreads] = fake_quantize4(v[u], s);
+            for (int u = 0; u < kEwUnroll; ++u) {
+                if (kNt)
+                    store_f4_nt(&yv[i + u * kEwThreads], fake_quantize4(v[u], s));
+                else
+                    yv[i + u * kEwThreads] = fake_quantize4(v[u], s);
+            }
+        };
+        if (full_first) {
+            store_trip();
+            i += step;
+        }
+        for (; i + (kEwUnroll - 1) * kEwThreads < nvec; i += step) {
+#pragma unroll
+            for (int u = 0; u < kEwUnroll; ++u) v[u] = xv[i + u * kEwThreads];
+            store_trip();
         }
         for (; i < nvec; i += step)  // the ragged last block
             for (int u = 0; u < kEwUnroll && i + u * kEwThreads < nvec; ++u) yv[i + u * kEwThreads] = fake_quantize4(xv[i + u * kEwThreads], s);
@@ -331,14 +403,13 @@ __global__ __launch_bounds__(kEwThreads) void fake_quantize_kernel(const float* 
             if (t < n) xq[t] = fake_quantize_value(x[t], s);
         }
     } else {
+        const float s = kEma ? ema_scale(ema) : scale[0];
         const int64_t stride = (int64_t)gridDim.x * kEwThreads;
         for (int64_t i = (int64_t)blockIdx.x * kEwThreads + threadIdx.x; i < n; i += stride) xq[i] = fake_quantize_value(x[i], s);
     }
 }
 
-// One step of the moving average under Eq. 4 (one workgroup): a = max of the n_amax values,
-// state[0] <- a on the first call (state[1] == 0), else decay * state[0] + (1 - decay) * a,
-// four binary32 operations in this order; state[1] <- 1; the scale is 127 over the average.
+// The moving average on its own (one workgroup): a = max of the n_amax values, one step, the scale 127 over the average.
 __global__ __launch_bounds__(kEwThreads) void ema_update_kernel(const float* __restrict__ amax, int n_amax,
                                                                  float decay, float* state, float* amax_out,
                                                                  float* scale_out)
@@ -348,12 +419,7 @@ __global__ __launch_bounds__(kEwThreads) void ema_update_kernel(const float* __r
     m = block_max_u32(m);
     if (threadIdx.x == 0) {
         const float a = __uint_as_float(m);
-        float e = a;
-        if (state[1] != 0.0f) {
-            const float keep = __fmul_rn(decay, state[0]);
-            const float take = __fmul_rn(__fsub_rn(1.0f, decay), a);
-            e = __fadd_rn(keep, take);
-        }
+        const float e = ema_step(state[0], state[1], decay, a);
         state[0] = e;
         state[1] = 1.0f;
         if (amax_out) amax_out[0] = a;
@@ -362,7 +428,7 @@ __global__ __launch_bounds__(kEwThreads) void ema_update_kernel(const float* __r
 }
 
 // Eq. 5: the gradient passes unchanged.  A plain streaming copy.
-template <bool kVec>
+template <bool kVec, bool kNt>
 __global__ __launch_bounds__(kEwThreads) void ste_backward_kernel(const float* __restrict__ g, int64_t n,
                                                                    float* __restrict__ gx)
 {
@@ -376,9 +442,14 @@ __global__ __launch_bounds__(kEwThreads) void ste_backward_kernel(const float* _
         for (; i + (kEwUnroll - 1) * kEwThreads < nvec; i += step) {
             float4 v[kEwUnroll];
 #pragma unroll
-            for (int u = 0; u < kEwUnroll; ++u) v[u] = gv[i + u * kEwThreads];
+            for (int u = 0; u < kEwUnroll; ++u) v[u] = kNt ? load_f4_nt(&gv[i + u * kEwThreads]) : gv[i + u * kEwThreads];
 #pragma unroll
-            for (int u = 0; u < kEwUnroll; ++u) ov[i + u * kEwThreads] = v[u];
+            for (int u = 0; u < kEwUnroll; ++u) {
+                if (kNt)
+                    store_f4_nt(&ov[i + u * kEwThreads], v[u]);
+                else
+                    ov[i + u * kEwThreads] = v[u];
+            }
         }
         for (; i < nvec; i += step)  // the ragged last block
             for (int u = 0; u < kEwUnroll && i + u * kEwThreads < nvec; ++u) ov[i + u * kEwThreads] = gv[i + u * kEwThreads];
@@ -437,7 +508,7 @@ int launch_absmax_partial(const float* x, int64_t n, float* partials, int* n_par
     const int g = am_grid((n - head) >> 2);
     *n_partials = g;
     hipLaunchKernelGGL(absmax_partial_kernel, dim3(g), dim3(kEwThreads), 0, st, x, n, head,
-                       reinterpret_cast<unsigned*>(partials));
+                       reinterpret_cast<unsigned*>(partials), nullptr, nullptr);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
@@ -705,15 +776,34 @@ int launch_quantize(const float* x, int64_t n, const float* scale, int8_t* q, hi
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
+template <bool kEma>
+static int launch_fake_quantize_any(const float* x, int64_t n, const float* scale, float* xq, const EmaArgs& ema, hipStream_t st)
+{
+    const bool vec = ((reinterpret_cast<uintptr_t>(x) & 15) == 0) && ((reinterpret_cast<uintptr_t>(xq) & 15) == 0);
+    const dim3 grid(ew_grid(vec ? n >> 2 : n)), block(kEwThreads);
+    if (vec && stream_out(n))
+        hipLaunchKernelGGL((fake_quantize_kernel<true, true, kEma>), grid, block, 0, st, x, n, scale, xq, ema);
+    else if (vec)
+        hipLaunchKernelGGL((fake_quantize_kernel<true, false, kEma>), grid, block, 0, st, x, n, scale, xq, ema);
+    else
+        hipLaunchKernelGGL((fake_quantize_kernel<false, false, kEma>), grid, block, 0, st, x, n, scale, xq, ema);
+    return hipGetLastError() == hipSuccess ? 0 : 1;
+}
+
 int launch_fake_quantize(const float* x, int64_t n, const float* scale, float* xq, hipStream_t st)
 {
-    if (n == 0) return 0;
-    bool vec = ((reinterpret_cast<uintptr_t>(x) & 15) == 0) && ((reinterpret_cast<uintptr_t>(xq) & 15) == 0);
-    if (vec)
-        hipLaunchKernelGGL(fake_quantize_kernel<true>, dim3(ew_grid(n >> 2)), dim3(kEwThreads), 0, st, x, n, scale, xq);
-    else
-        hipLaunchKernelGGL(fake_quantize_kernel<false>, dim3(ew_grid(n)), dim3(kEwThreads), 0, st, x, n, scale, xq);
-    return hipGetLastError() == hipSuccess ? 0 : 1;
+    return n == 0 ? 0 : launch_fake_quantize_any<false>(x, n, scale, xq, EmaArgs{}, st);
+}
+
+// scal_work: [0] abs-max, [1] scale, then the slots of the abs-max pass, its last two words the copy of the state.
+int launch_fake_quantize_ema(const float* x, int64_t n, float decay, float* state, float* scal_work, float* xq, hipStream_t st)
+{
+    const int head = head_of(x, n);
+    const int g = std::min(am_grid((n - head) >> 2), kMaxEwGrid - 2);
+    float *slots = scal_work + 2, *old_state = slots + kMaxEwGrid - 2;
+    hipLaunchKernelGGL(absmax_partial_kernel, dim3(g), dim3(kEwThreads), 0, st, x, n, head, reinterpret_cast<unsigned*>(slots), state, old_state);
+    if (hipGetLastError() != hipSuccess) return 1;
+    return launch_fake_quantize_any<true>(x, n, nullptr, xq, EmaArgs{slots, g, decay, old_state, state, scal_work, scal_work + 1}, st);
 }
 
 int launch_ema_update(const float* amax, int n_amax, float decay, float* state, float* amax_out, float* scale_out,
@@ -728,10 +818,12 @@ int launch_ste_backward(const float* g, int64_t n, float* gx, hipStream_t st)
 {
     if (n == 0 || g == gx) return 0;
     bool vec = ((reinterpret_cast<uintptr_t>(g) & 15) == 0) && ((reinterpret_cast<uintptr_t>(gx) & 15) == 0);
-    if (vec)
-        hipLaunchKernelGGL(ste_backward_kernel<true>, dim3(ew_grid(n >> 2)), dim3(kEwThreads), 0, st, g, n, gx);
+    if (vec && stream_out(n))
+        hipLaunchKernelGGL((ste_backward_kernel<true, true>), dim3(ew_grid(n >> 2)), dim3(kEwThreads), 0, st, g, n, gx);
+    else if (vec)
+        hipLaunchKernelGGL((ste_backward_kernel<true, false>), dim3(ew_grid(n >> 2)), dim3(kEwThreads), 0, st, g, n, gx);
     else
-        hipLaunchKernelGGL(ste_backward_kernel<false>, dim3(ew_grid(n)), dim3(kEwThreads), 0, st, g, n, gx);
+        hipLaunchKernelGGL((ste_backward_kernel<false, false>), dim3(ew_grid(n)), dim3(kEwThreads), 0, st, g, n, gx);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 

@@ -45,6 +45,8 @@ int launch_quantize(const float* x, int64_t n, const float* scale, int8_t* q, hi
 
 // Training side: fake quantization (Section 2.2), moving average of max|x| (Eq. 4), gradient copy (Eq. 5).
 int launch_fake_quantize(const float* x, int64_t n, const float* scale, float* xq, hipStream_t st);
+// The three in two launches (n > 0): abs-max of x, then the moving average's step inside the fake quantization.
+int launch_fake_quantize_ema(const float* x, int64_t n, float decay, float* state, float* scal_work, float* xq, hipStream_t st);
 int launch_ema_update(const float* amax, int n_amax, float decay, float* state, float* amax_out, float* scale_out,
                       hipStream_t st);
 int launch_ste_backward(const float* g, int64_t n, float* gx, hipStream_t st);

@@ -157,3 +157,34 @@ def test_training_argument_checks(q8):
     assert lib.q8_ste_backward(p(x), 8, None, None) == 1
     assert lib.q8_ste_backward(p(x), -2, p(x), None) == 2
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("n,off", [(1, 0), (3, 1), (4096, 0), (4099, 0), (8192 * 6 + 5, 1), (17_000_003, 0), (17_000_000, 1)])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_ema_inside_the_fake_quantization(q8, n, off, in_place):
+    """The two-launch moving-average quantizer over every path of its kernels -- one workgroup, a ragged last block, more
+    blocks than partial maxima, outputs beyond 64 MiB (stored past the cache), 4-byte aligned tensors -- and the gradient
+    copy of the same sizes.  Two steps, so that the second one reads a state the first has written."""
+    g = torch.Generator(device="cuda").manual_seed(n + off)
+    state, work = dev(np.zeros(2, np.float32)), torch.full((q8.SCAL_WORK,), 9e9, device="cuda")
+    average, started = np.float32(0), False
+    for _ in range(2):
+        buf = torch.randn(n + off, generator=g, device="cuda")
+        x = buf[off:]
+        xc = x.clone()
+        y = x if in_place else torch.empty(n + off, device="cuda")[off:]
+        q8.q8_fake_quantize_ema(x, 0.9, state, work, y)
+        a = np.float32(xc.abs().max().item())
+        average = O.ema_update(average, started, a, np.float32(0.9))
+        started = True
+        s = np.float32(127.0) / average
+        assert host(state)[0] == average and host(state)[1] == 1.0
+        assert host(work)[0] == a and host(work)[1] == s
+        ref = torch.empty_like(xc)
+        q8.q8_fake_quantize(xc, dev(np.array([s], np.float32)), ref)    # pinned to the oracle above
+        assert torch.equal(y, ref)
+        part = slice(max(0, n - 5000), n)
+        np.testing.assert_array_equal(host(y[part]), O.fake_quantize(host(xc[part]), s))
+    out = torch.full((n + off + 4,), 7.0, device="cuda")
+    q8.q8_ste_backward(xc, out[off:off + n])
+    assert torch.equal(out[off:off + n], xc) and bool((out[off + n:] == 7.0).all())
