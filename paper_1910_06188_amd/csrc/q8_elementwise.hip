@@ -98,6 +98,23 @@ __device__ __forceinline__ unsigned block_max_u32(unsigned m)
     return m;
 }
 
+// This thread's share of n abs-max values.  All loads of up to 2048 values are requested together (the last trip repeats the
+// final value instead of branching) instead of one after the other, eight round trips to the L2 in front of the work of
+// every quantizer that folds the slots of its producer (BERT-Base forward, 8192 tokens, three layers: 719 -> 710 us).
+constexpr int kFoldUnroll = 8;
+__device__ __forceinline__ unsigned fold_thread(const float* __restrict__ amax, int n)
+{
+    unsigned m = 0u;
+    for (int i = threadIdx.x; i < n; i += kFoldUnroll * kEwThreads) {
+        unsigned v[kFoldUnroll];
+#pragma unroll
+        for (int u = 0; u < kFoldUnroll; ++u) v[u] = abs_bits(amax[min(i + u * kEwThreads, n - 1)]);
+#pragma unroll
+        for (int u = 0; u < kFoldUnroll; ++u) m = max(m, v[u]);
+    }
+    return m;
+}
+
 // Stand-alone abs-max: one atomic max per workgroup into a zeroed word.  No fences and
 // no "last block" ticket: device-scope fences cost an L2 write-back per workgroup on a
 // chip whose eight L2s are not coherent with each other, so the scale is left to a
@@ -168,9 +185,7 @@ __device__ __forceinline__ float scale_from_partials(const float* __restrict__ a
                                                      float* scale_out, float* zero_slot)
 {
     __shared__ unsigned folded;
-    unsigned m = 0u;
-    for (int i = threadIdx.x; i < n_amax; i += kEwThreads) m = max(m, abs_bits(amax[i]));
-    m = block_max_u32(m);
+    unsigned m = block_max_u32(fold_thread(amax, n_amax));
     if (threadIdx.x == 0) folded = m;
     __syncthreads();
     const float a = __uint_as_float(folded);
@@ -341,9 +356,7 @@ struct EmaArgs {
 __device__ __forceinline__ float ema_scale(const EmaArgs& e)
 {
     __shared__ unsigned folded;
-    unsigned m = 0u;
-    for (int i = threadIdx.x; i < e.n_amax; i += kEwThreads) m = max(m, abs_bits(e.amax[i]));
-    m = block_max_u32(m);
+    const unsigned m = block_max_u32(fold_thread(e.amax, e.n_amax));
     if (threadIdx.x == 0) folded = m;
     __syncthreads();
     const float a = __uint_as_float(folded);
@@ -414,9 +427,7 @@ __global__ __launch_bounds__(kEwThreads) void ema_update_kernel(const float* __r
                                                                  float decay, float* state, float* amax_out,
                                                                  float* scale_out)
 {
-    unsigned m = 0u;
-    for (int i = threadIdx.x; i < n_amax; i += kEwThreads) m = max(m, abs_bits(amax[i]));
-    m = block_max_u32(m);
+    unsigned m = block_max_u32(fold_thread(amax, n_amax));
     if (threadIdx.x == 0) {
         const float a = __uint_as_float(m);
         const float e = ema_step(state[0], state[1], decay, a);
@@ -495,7 +506,8 @@ int launch_absmax(const float* x, int64_t n, float* amax_out, float* scale_out, 
     unsigned* bits = reinterpret_cast<unsigned*>(amax_out);
     const int head = head_of(x, n);
     hipLaunchKernelGGL(absmax_init_kernel, dim3(1), dim3(1), 0, st, bits);
-    // every workgroup ends in a read of one address and, while the maximum still grows, a read-modify-write of it
+    // every workgroup ends in a read of one address and, while the maximum still grows, a read-modify-write of it (94 MB:
+    // 512 workgroups 3.6 us slower than 256, 1024 12 us)
     const int g = am_grid((n - head) >> 2);
     hipLaunchKernelGGL(absmax_atomic_kernel, dim3(g < 256 ? g : 256), dim3(kEwThreads), 0, st, x, n, head, bits);
     if (scale_out) hipLaunchKernelGGL(scale_from_amax_kernel, dim3(1), dim3(1), 0, st, amax_out, scale_out);
