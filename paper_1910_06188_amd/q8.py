@@ -1,4 +1,5 @@
-"""Thin ctypes binding over libq8.so (the C ABI declared in include/q8.h).
+"""Thin binding over libq8.so (the C ABI declared in include/q8.h): the method's entry points through the native module
+_binding, the tuning and measurement hooks through ctypes.
 
 Argument marshalling only: every step of the quantized FC layer runs in the HIP
 kernels behind the library.  PyTorch supplies device memory and the stream.
@@ -21,6 +22,11 @@ if not os.path.exists(LIB_PATH):
         "There is no fallback path.")
 
 _lib = C.CDLL(LIB_PATH)
+try:
+    from . import _binding   # csrc/binding.cpp: the entry points below, called without ctypes (links the same libq8.so)
+except ImportError as e:
+    raise ImportError(f"{_HERE}/_binding.so is missing or does not load: build the library first "
+                      "(python -m paper_1910_06188_amd.build).") from e
 
 OK = 0
 EPI_GELU, EPI_ABSMAX, EPI_REQUANT = 1, 2, 4
@@ -94,17 +100,13 @@ def _ptr(t):
     return t.data_ptr()
 
 
-# The current stream's raw handle without building a torch.cuda.Stream object for it (2.7 us per call, about
-# as much as the launch itself); the public accessor is the fallback.
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-
-
 def _stream(stream=None):
-    if stream is not None:
-        return stream.cuda_stream
-    if _raw_stream is not None:
-        return _raw_stream(torch.cuda.current_device())
-    return torch.cuda.current_stream().cuda_stream
+    """What the native entry points take: a raw handle, or None for torch's current stream, which they look up."""
+    return None if stream is None else stream.cuda_stream
+
+
+def _raw_stream(stream=None):
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def version() -> str:
@@ -126,25 +128,25 @@ def set_quantize_one_pass(enabled: bool = True, barrier_polls: int = 64) -> None
 
 def q8_absmax(x, amax_out, scale_out=None, stream=None) -> None:
     """amax_out[0] = max|x|, scale_out[0] = 127/amax (Eq. 3)."""
-    _ck(_lib.q8_absmax(_ptr(x), x.numel(), _ptr(amax_out), _ptr(scale_out), _stream(stream)), "q8_absmax")
+    _ck(_binding.q8_absmax(x, x.numel(), amax_out, scale_out, _stream(stream)), "q8_absmax")
 
 
 def q8_scale_from_amax(amax, scale_out, stream=None) -> None:
-    _ck(_lib.q8_scale_from_amax(_ptr(amax), _ptr(scale_out), _stream(stream)), "q8_scale_from_amax")
+    _ck(_binding.q8_scale_from_amax(amax, scale_out, _stream(stream)), "q8_scale_from_amax")
 
 
 def q8_quantize(x, scale, q, stream=None) -> None:
     """q = Clamp(round(x * scale), -127, 127) (Eq. 1)."""
     if q.numel() != x.numel():
         raise ValueError("q8_quantize: q and x differ in size")
-    _ck(_lib.q8_quantize(_ptr(x), x.numel(), _ptr(scale), _ptr(q), _stream(stream)), "q8_quantize")
+    _ck(_binding.q8_quantize(x, x.numel(), scale, q, _stream(stream)), "q8_quantize")
 
 
 def q8_quantize_amax(x, amax, scale_out, q, amax_out=None, stream=None) -> None:
     """S = 127 / max(amax[:]) (Eq. 3), then q = Quantize(x | S, 127) (Eq. 1), one launch."""
     if q.numel() != x.numel():
         raise ValueError("q8_quantize_amax: q and x differ in size")
-    _ck(_lib.q8_quantize_amax(_ptr(x), x.numel(), _ptr(amax), amax.numel(), _ptr(amax_out), _ptr(scale_out), _ptr(q),
+    _ck(_binding.q8_quantize_amax(x, x.numel(), amax, amax.numel(), amax_out, scale_out, q,
                               _stream(stream)), "q8_quantize_amax")
 
 
@@ -152,7 +154,7 @@ def q8_quantize_dynamic(x, q, scal_work, zero_slot=None, stream=None) -> None:
     """Dynamic quantizer (Section 4.1): scal_work[0] = max|x|, scal_work[1] = S = 127/max, q = Quantize(x | S, 127)."""
     if q.numel() != x.numel() or scal_work.numel() < SCAL_WORK:
         raise ValueError("q8_quantize_dynamic: shape mismatch")
-    _ck(_lib.q8_quantize_dynamic(_ptr(x), x.numel(), _ptr(q), _ptr(scal_work), _ptr(zero_slot), _stream(stream)),
+    _ck(_binding.q8_quantize_dynamic(x, x.numel(), q, scal_work, zero_slot, _stream(stream)),
         "q8_quantize_dynamic")
 
 
@@ -160,21 +162,21 @@ def debug_mfma_rate(operands, iters, workgroups, sink, stream=None) -> float:
     """Launches the register-resident i8 MFMA loop; returns the int8 operations it performs."""
     if operands.numel() < 65536:
         raise ValueError("debug_mfma_rate: operands holds 65536 int8 values")
-    _ck(_lib.q8_debug_mfma_rate(_ptr(operands), int(iters), int(workgroups), _ptr(sink), _stream(stream)), "q8_debug_mfma_rate")
+    _ck(_lib.q8_debug_mfma_rate(_ptr(operands), int(iters), int(workgroups), _ptr(sink), _raw_stream(stream)), "q8_debug_mfma_rate")
     return 2.0 * 32 * 32 * 32 * 8 * iters * 8 * workgroups
 
 
 def debug_stream_copy(src, dst, stream=None) -> None:
     """dst = src with 16-byte accesses (src None: fill)."""
     nbytes = dst.numel() * dst.element_size()
-    _ck(_lib.q8_debug_stream_copy(_ptr(src), _ptr(dst), nbytes, _stream(stream)), "q8_debug_stream_copy")
+    _ck(_lib.q8_debug_stream_copy(_ptr(src), _ptr(dst), nbytes, _raw_stream(stream)), "q8_debug_stream_copy")
 
 
 def debug_loop_probe(what, operand_window, store_window, stages, sink, stream=None) -> None:
     """One stage of a GEMM main loop piece by piece (see include/q8.h); 256 workgroups x `stages` stages."""
     if operand_window.numel() * operand_window.element_size() < (4 << 20) or store_window.numel() * store_window.element_size() < (32 << 20):
         raise ValueError("debug_loop_probe: windows of 4 MiB and 32 MiB")
-    _ck(_lib.q8_debug_loop_probe(int(what), _ptr(operand_window), _ptr(store_window), int(stages), _ptr(sink), _stream(stream)),
+    _ck(_lib.q8_debug_loop_probe(int(what), _ptr(operand_window), _ptr(store_window), int(stages), _ptr(sink), _raw_stream(stream)),
         "q8_debug_loop_probe")
 
 
@@ -187,8 +189,8 @@ def q8_linear(xq, wq, bias, sx, sw, y, n_groups=1, acc_out=None, out_amax=None, 
         raise ValueError("q8_linear: shape mismatch")
     if sw.numel() != n_groups or (bias is not None and bias.numel() != N):
         raise ValueError("q8_linear: scale/bias size mismatch")
-    _ck(_lib.q8_linear(_ptr(xq), _ptr(wq), _ptr(bias), _ptr(sx), _ptr(sw), n_groups, M, N, K, _ptr(y),
-                       _ptr(acc_out), _ptr(out_amax), _ptr(next_scale), flags, _stream(stream)), "q8_linear")
+    _ck(_binding.q8_linear(xq, wq, bias, sx, sw, n_groups, M, N, K, y,
+                       acc_out, out_amax, next_scale, flags, _stream(stream)), "q8_linear")
 
 
 def q8_linear_residual(xq, wq, bias, sx, sw, residual, y, n_groups=1, acc_out=None, out_amax=None, flags=0,
@@ -200,8 +202,8 @@ def q8_linear_residual(xq, wq, bias, sx, sw, residual, y, n_groups=1, acc_out=No
         raise ValueError("q8_linear_residual: shape mismatch")
     if sw.numel() != n_groups or (bias is not None and bias.numel() != N):
         raise ValueError("q8_linear_residual: scale/bias size mismatch")
-    _ck(_lib.q8_linear_residual(_ptr(xq), _ptr(wq), _ptr(bias), _ptr(sx), _ptr(sw), n_groups, M, N, K, _ptr(residual),
-                                _ptr(y), _ptr(acc_out), _ptr(out_amax), flags, _stream(stream)), "q8_linear_residual")
+    _ck(_binding.q8_linear_residual(xq, wq, bias, sx, sw, n_groups, M, N, K, residual,
+                                y, acc_out, out_amax, flags, _stream(stream)), "q8_linear_residual")
 
 
 def q8_linear_f32(x, wq, bias, sw, xq_work, scal_work, y, n_groups=1, acc_out=None, out_amax=None, next_scale=None,
@@ -213,8 +215,8 @@ def q8_linear_f32(x, wq, bias, sw, xq_work, scal_work, y, n_groups=1, acc_out=No
         raise ValueError("q8_linear_f32: shape mismatch")
     if sw.numel() != n_groups or (bias is not None and bias.numel() != N):
         raise ValueError("q8_linear_f32: scale/bias size mismatch")
-    _ck(_lib.q8_linear_f32(_ptr(x), _ptr(wq), _ptr(bias), _ptr(sw), n_groups, M, N, K, _ptr(xq_work),
-                           _ptr(scal_work), _ptr(y), _ptr(acc_out), _ptr(out_amax), _ptr(next_scale), flags,
+    _ck(_binding.q8_linear_f32(x, wq, bias, sw, n_groups, M, N, K, xq_work,
+                           scal_work, y, acc_out, out_amax, next_scale, flags,
                            _stream(stream)), "q8_linear_f32")
 
 
@@ -227,8 +229,8 @@ def q8_linear_f32_static(x, wq, bias, sw, y, n_groups=1, stats_out=None, out_ama
         raise ValueError("q8_linear_f32_static: shape mismatch")
     if sw.numel() != n_groups or (bias is not None and bias.numel() != N):
         raise ValueError("q8_linear_f32_static: scale/bias size mismatch")
-    _ck(_lib.q8_linear_f32_static(_ptr(x), _ptr(wq), _ptr(bias), _ptr(sw), n_groups, M, N, K, _ptr(y), _ptr(stats_out),
-                                  _ptr(out_amax), _ptr(next_scale), flags, _stream(stream)), "q8_linear_f32_static")
+    _ck(_binding.q8_linear_f32_static(x, wq, bias, sw, n_groups, M, N, K, y, stats_out,
+                                  out_amax, next_scale, flags, _stream(stream)), "q8_linear_f32_static")
 
 
 def q8_linear_f32_slots(x, amax_slots, wq, bias, sw, xq_work, scal_work, y, n_groups=1, acc_out=None, out_amax=None,
@@ -240,9 +242,9 @@ def q8_linear_f32_slots(x, amax_slots, wq, bias, sw, xq_work, scal_work, y, n_gr
         raise ValueError("q8_linear_f32_slots: shape mismatch")
     if sw.numel() != n_groups or (bias is not None and bias.numel() != N):
         raise ValueError("q8_linear_f32_slots: scale/bias size mismatch")
-    _ck(_lib.q8_linear_f32_slots(_ptr(x), _ptr(amax_slots), amax_slots.numel(), _ptr(wq), _ptr(bias), _ptr(sw), n_groups,
-                                 M, N, K, _ptr(xq_work), _ptr(scal_work), _ptr(y), _ptr(acc_out), _ptr(out_amax),
-                                 _ptr(next_scale), flags, _stream(stream)), "q8_linear_f32_slots")
+    _ck(_binding.q8_linear_f32_slots(x, amax_slots, amax_slots.numel(), wq, bias, sw, n_groups,
+                                 M, N, K, xq_work, scal_work, y, acc_out, out_amax,
+                                 next_scale, flags, _stream(stream)), "q8_linear_f32_slots")
 
 
 def q8_embedding(table, scale, ids, out, err_flag=None, stream=None) -> None:
@@ -252,7 +254,7 @@ def q8_embedding(table, scale, ids, out, err_flag=None, stream=None) -> None:
     if out.numel() != T * H:
         raise ValueError("q8_embedding: shape mismatch")
     out_is_int8 = 1 if out.dtype == torch.int8 else 0
-    _ck(_lib.q8_embedding(_ptr(table), _ptr(scale), V, H, _ptr(ids), T, _ptr(out), out_is_int8, _ptr(err_flag),
+    _ck(_binding.q8_embedding(table, scale, V, H, ids, T, out, out_is_int8, err_flag,
                           _stream(stream)), "q8_embedding")
 
 
@@ -261,8 +263,8 @@ def q8_embedding_sum3(word, pos, typ, scales, wid, pid, tid, out, err_flag=None,
     T = wid.numel()
     if pos.shape[1] != H or typ.shape[1] != H or out.numel() != T * H or pid.numel() != T or tid.numel() != T:
         raise ValueError("q8_embedding_sum3: shape mismatch")
-    _ck(_lib.q8_embedding_sum3(_ptr(word), word.shape[0], _ptr(pos), pos.shape[0], _ptr(typ), typ.shape[0],
-                               _ptr(scales), H, _ptr(wid), _ptr(pid), _ptr(tid), T, _ptr(out), _ptr(err_flag),
+    _ck(_binding.q8_embedding_sum3(word, word.shape[0], pos, pos.shape[0], typ, typ.shape[0],
+                               scales, H, wid, pid, tid, T, out, err_flag,
                                _stream(stream)), "q8_embedding_sum3")
 
 
@@ -270,14 +272,14 @@ def q8_fake_quantize(x, scale, xq, stream=None) -> None:
     """xq = Quantize(x | S, 127) / S in fp32 (Section 2.2); xq may be x."""
     if xq.numel() != x.numel():
         raise ValueError("q8_fake_quantize: xq and x differ in size")
-    _ck(_lib.q8_fake_quantize(_ptr(x), x.numel(), _ptr(scale), _ptr(xq), _stream(stream)), "q8_fake_quantize")
+    _ck(_binding.q8_fake_quantize(x, x.numel(), scale, xq, _stream(stream)), "q8_fake_quantize")
 
 
 def q8_ema_update(amax, decay, state, amax_out=None, scale_out=None, stream=None) -> None:
     """One step of the moving average of max|x| under Eq. 4; state = [average, started]."""
     if state.numel() < 2:
         raise ValueError("q8_ema_update: state holds two floats")
-    _ck(_lib.q8_ema_update(_ptr(amax), amax.numel(), float(decay), _ptr(state), _ptr(amax_out), _ptr(scale_out),
+    _ck(_binding.q8_ema_update(amax, amax.numel(), float(decay), state, amax_out, scale_out,
                            _stream(stream)), "q8_ema_update")
 
 
@@ -285,7 +287,7 @@ def q8_fake_quantize_ema(x, decay, state, scal_work, xq, stream=None) -> None:
     """abs-max, moving-average step, fake quantization with the updated scale, in one call."""
     if xq.numel() != x.numel() or state.numel() < 2 or scal_work.numel() < SCAL_WORK:
         raise ValueError("q8_fake_quantize_ema: shape mismatch")
-    _ck(_lib.q8_fake_quantize_ema(_ptr(x), x.numel(), float(decay), _ptr(state), _ptr(scal_work), _ptr(xq),
+    _ck(_binding.q8_fake_quantize_ema(x, x.numel(), float(decay), state, scal_work, xq,
                                   _stream(stream)), "q8_fake_quantize_ema")
 
 
@@ -293,7 +295,7 @@ def q8_ste_backward(grad_xq, grad_x, stream=None) -> None:
     """Eq. 5: grad_x = grad_xq."""
     if grad_x.numel() != grad_xq.numel():
         raise ValueError("q8_ste_backward: sizes differ")
-    _ck(_lib.q8_ste_backward(_ptr(grad_xq), grad_xq.numel(), _ptr(grad_x), _stream(stream)), "q8_ste_backward")
+    _ck(_binding.q8_ste_backward(grad_xq, grad_xq.numel(), grad_x, _stream(stream)), "q8_ste_backward")
 
 
 def q8_layernorm_absmax(a, gamma, beta, y, eps=1e-12, residual=None, amax_slots=None, q_scale=None, q_out=None,
@@ -307,8 +309,8 @@ def q8_layernorm_absmax(a, gamma, beta, y, eps=1e-12, residual=None, amax_slots=
         raise ValueError("q8_layernorm_absmax: amax_slots holds AMAX_SLOTS floats")
     if q_out is not None and q_out.numel() != M * H:
         raise ValueError("q8_layernorm_absmax: q_out and y differ in size")
-    _ck(_lib.q8_layernorm_absmax(_ptr(a), _ptr(residual), _ptr(gamma), _ptr(beta), float(eps), M, H, _ptr(y),
-                                 _ptr(amax_slots), _ptr(q_scale), _ptr(q_out), _stream(stream)), "q8_layernorm_absmax")
+    _ck(_binding.q8_layernorm_absmax(a, residual, gamma, beta, float(eps), M, H, y,
+                                 amax_slots, q_scale, q_out, _stream(stream)), "q8_layernorm_absmax")
 
 
 def q8_embedding_sum3_layernorm(word, pos, typ, scales, wid, pid, tid, gamma, beta, y, eps=1e-12, amax_slots=None,
@@ -320,9 +322,9 @@ def q8_embedding_sum3_layernorm(word, pos, typ, scales, wid, pid, tid, gamma, be
         raise ValueError("q8_embedding_sum3_layernorm: shape mismatch")
     if gamma.numel() != H or beta.numel() != H or (amax_slots is not None and amax_slots.numel() < AMAX_SLOTS):
         raise ValueError("q8_embedding_sum3_layernorm: parameter size mismatch")
-    _ck(_lib.q8_embedding_sum3_layernorm(_ptr(word), word.shape[0], _ptr(pos), pos.shape[0], _ptr(typ), typ.shape[0],
-                                         _ptr(scales), H, _ptr(wid), _ptr(pid), _ptr(tid), T, _ptr(gamma), _ptr(beta),
-                                         float(eps), _ptr(y), _ptr(amax_slots), _ptr(q_scale), _ptr(q_out), _ptr(err_flag),
+    _ck(_binding.q8_embedding_sum3_layernorm(word, word.shape[0], pos, pos.shape[0], typ, typ.shape[0],
+                                         scales, H, wid, pid, tid, T, gamma, beta,
+                                         float(eps), y, amax_slots, q_scale, q_out, err_flag,
                                          _stream(stream)),
         "q8_embedding_sum3_layernorm")
 
@@ -343,8 +345,8 @@ def q8_attention(qkv, B, S, heads, d, ctx=None, mask=None, scale=None, amax_slot
         raise ValueError("q8_attention: amax_slots holds AMAX_SLOTS floats")
     if scale is None:
         scale = 1.0 / float(d) ** 0.5
-    _ck(_lib.q8_attention(_ptr(qkv), B, S, heads, d, _ptr(mask), float(scale), _ptr(ctx), _ptr(amax_slots), _ptr(q_scale),
-                          _ptr(q_out), _stream(stream)), "q8_attention")
+    _ck(_binding.q8_attention(qkv, B, S, heads, d, mask, float(scale), ctx, amax_slots, q_scale,
+                          q_out, _stream(stream)), "q8_attention")
 
 
 def raw():
