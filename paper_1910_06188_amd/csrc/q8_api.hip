@@ -354,8 +354,9 @@ q8_status q8_attention(const float* qkv, int64_t B, int64_t S, int heads, int d,
     if (B > 0 && (!qkv || (!ctx && !q_out))) return Q8_ERR_NULL;
     if (misaligned(qkv, 4) || misaligned(mask, 4) || misaligned(ctx, 4) || misaligned(amax_slots, 4) || misaligned(q_scale, 4))
         return Q8_ERR_ALIGN;
-    // sequences beyond the generic kernel's scores in LDS are taken at the paper's head width only, whatever kernel runs
-    if (B > 0 && (d != 64 || !q8::attention_mfma_eligible(qkv, B, S, heads, d, ctx, q_out))) {
+    // sequences beyond the generic kernel's scores in LDS are taken at the paper's head width only, and up to 2^31 floats of
+    // qkv, whatever kernel runs
+    if (B > 0 && (d != 64 || S * 3 * heads * d >= ((int64_t)1 << 31) || !q8::attention_mfma_eligible(qkv, B, S, heads, d, ctx, q_out))) {
         if (S > q8::attention_generic_max_s() || B * heads * S >= ((int64_t)1 << 31)) return Q8_ERR_SHAPE;
     }
     return q8::launch_attention(qkv, B, S, heads, d, mask, scale, ctx, amax_slots, q_scale, q_out, as_stream(stream))
