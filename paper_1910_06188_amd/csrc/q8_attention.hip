@@ -108,6 +108,14 @@ struct Bf16x3 {
     }
 };
 
+__device__ __forceinline__ Bf16x3 split_bf16(float a, float b)
+{
+    Bf16x3 s;
+    s.first(a, b);
+    s.second();
+    return s;
+}
+
 // Three-part operand of an MFMA: eight numbers of one lane, two to a dword.
 struct Frag3 {
     v4u part[3];
@@ -126,6 +134,14 @@ __device__ __forceinline__ v16f mfma_part(const Frag3& a, const Frag3& b, v16f a
 {
     constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf(a.part[pa[I]]), as_bf(b.part[pb[I]]), acc, 0, 0, 0);
+}
+
+// A mask value in log2 units.  The lowest values of the type would overflow to -inf, and a stage of nothing else has no
+// maximum to take its probabilities against: they stay finite, far below any score.  (A NaN stays one.)
+__device__ __forceinline__ float mask_log2(float m)
+{
+    const float v = m * 1.44269504088896341f;
+    return v < -3.0e38f ? -3.0e38f : v;
 }
 
 __device__ __forceinline__ float4 buf_f4(__amdgpu_buffer_rsrc_t r, unsigned off)
@@ -207,7 +223,7 @@ struct AttnStager {
     __device__ __forceinline__ void stash_mask(int buf, int stage)
     {
         const int key = tid & (kAtKB - 1);   // eight threads write each value: no branch
-        const float v = (stage * kAtKB + key < S32) ? m[kSet] * 1.44269504088896341f : -__builtin_inff();   // beyond the sequence: weight 0 whatever the row holds
+        const float v = (stage * kAtKB + key < S32) ? mask_log2(m[kSet]) : -__builtin_inff();   // beyond the sequence: weight 0 whatever the row holds
         *reinterpret_cast<float*>(k_tiles + buf * T::kKTile + T::kMask + 4 * key) = v;
         masked = __builtin_amdgcn_ballot_w64(v != 0.0f) != 0;
     }
@@ -596,6 +612,211 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
 #endif
 }
 
+// The same products for launches that leave most of the chip idle: 32 queries of one (sequence, head) a workgroup, the
+// key stages dealt out over its four waves, each with running statistics of its own that meet in LDS at the end.  A short
+// sequence is a chain of latencies -- rows from memory, then per stage 48 MFMAs (of 32 cycles, at width 64) that the
+// kernel above walks one after the other on an eighth of the compute units.  No wave shares its keys, so K and V go straight
+// from memory into operand registers and nothing is staged: for every 32 queries they are read and split again, which is
+// why full launches keep the kernel above.  One sequence of 128 tokens, 12 heads of 64: 10.1 -> 7.4 us; of 512: 25.1 ->
+// 14.3; 2 x 256 of width 32: 12.4 -> 7.0.  Error against binary64 no larger (2.1e-7 against 2.6e-7 at 128 tokens).
+template <int kDB>
+__global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_kernel(AttnArgs a)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int kRow = 32 * kDB + 4;   // floats of a query's row of partial sums; the padding spreads rows over the banks
+    __shared__ __attribute__((aligned(16))) float part_o[kAtWaves * kAtQW * kRow];
+    __shared__ float part_m[kAtWaves * kAtQW], part_l[kAtWaves * kAtQW];
+    __shared__ unsigned wave_amax[kAtWaves];
+
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, lq = lane & 31, hi = lane >> 5;
+    int wid = blockIdx.x;
+    const int total = gridDim.x;
+    if ((total & 7) == 0) wid = (wid & 7) * (total >> 3) + (wid >> 3);   // as above: an XCD takes whole (sequence, head)s
+    const int qb = wid % a.n_qblocks, bh = wid / a.n_qblocks, h = bh % a.heads;
+    const int64_t b = bh / a.heads;
+    const int S = (int)a.S, d = a.d;
+    const int64_t HD = (int64_t)a.heads * d, ld = 3 * HD;
+    const float* base = a.qkv + b * S * ld + (int64_t)h * d;
+    const float *kbase = base + HD, *vbase = base + 2 * HD;
+    const float* mrow = a.mask ? a.mask + b * S : nullptr;
+    const int q0 = qb * kAtQW, n_stages = (S + kAtKB - 1) / kAtKB;
+
+    unsigned k_off[2 * kDB][2], v_off[kDB];   // byte offsets inside a stage
+#pragma unroll
+    for (int j = 0; j < 2 * kDB; ++j)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) k_off[j][u] = 4u * ((unsigned)lq * (unsigned)ld + (unsigned)min(16 * j + 8 * hi + 4 * u, d - 4));
+#pragma unroll
+    for (int c = 0; c < kDB; ++c) v_off[c] = 4u * ((unsigned)(4 * hi) * (unsigned)ld + (unsigned)min(32 * c + lq, d - 1));
+    // rows of a stage that exist, as a descriptor: the others read as zeros
+    auto rsrc = [&](const float* p, int stage) {
+        const int rows = min(S - stage * kAtKB, kAtKB);
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p) + (int64_t)stage * kAtKB * ld, 0, rows > 0 ? 4 * ((rows - 1) * (int)ld + d) : 0, 0x00020000);
+    };
+    float4 k[2 * kDB][2];
+    float v[2][kDB][8], mk[16];
+    auto fetch_k = [&](int stage) {
+        const auto r = rsrc(kbase, stage);
+#pragma unroll
+        for (int j = 0; j < 2 * kDB; ++j)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) k[j][u] = buf_f4(r, k_off[j][u]);
+        if (mrow) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) mk[e] = mrow[min(stage * kAtKB + 8 * (e >> 2) + 4 * hi + (e & 3), S - 1)];
+        }
+    };
+    auto fetch_v = [&](int stage) {   // step j, column block c: the eight keys this half-wave takes to the step
+        const auto r = rsrc(vbase, stage);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int c = 0; c < kDB; ++c)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    v[j][c][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)v_off[c], 4 * (16 * j + (e & 3) + 8 * (e >> 2)) * (int)ld, 0));
+    };
+
+    AttnWave<kDB> w;
+    w.m_run = -__builtin_inff();
+    w.l_run = 0.0f;
+#pragma unroll
+    for (int c = 0; c < kDB; ++c)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) w.o[c][e] = 0.0f;
+    if (wave < n_stages) {
+        float4 qraw[2 * kDB][2];
+        const float* qp = base + (int64_t)min(q0 + lq, S - 1) * ld;
+#pragma unroll
+        for (int j = 0; j < 2 * kDB; ++j)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) qraw[j][u] = *reinterpret_cast<const float4*>(qp + min(16 * j + 8 * hi + 4 * u, d - 4));
+        fetch_k(wave);
+        fetch_v(wave);
+#pragma unroll
+        for (int j = 0; j < 2 * kDB; ++j)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const float c = (16 * j + 8 * hi + 4 * u < d) ? a.c : 0.0f;   // columns beyond d are zeros here, whatever K holds
+                w.q[j].set(2 * u, split_bf16(qraw[j][u].x * c, qraw[j][u].y * c));
+                w.q[j].set(2 * u + 1, split_bf16(qraw[j][u].z * c, qraw[j][u].w * c));
+            }
+    }
+    for (int st = wave; st < n_stages; st += kAtWaves) {
+        // a stage that is walked has a key inside the sequence, so its maximum is above -inf
+        v16f s;
+        const int keys = S - st * kAtKB;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const float m0 = mrow ? mask_log2(mk[e]) : 0.0f;
+            s[e] = 8 * (e >> 2) + 4 * hi + (e & 3) < keys ? m0 : -__builtin_inff();
+        }
+#pragma unroll
+        for (int j = 0; j < 2 * kDB; ++j) {
+            Frag3 f;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                f.set(2 * u, split_bf16(k[j][u].x, k[j][u].y));
+                f.set(2 * u + 1, split_bf16(k[j][u].z, k[j][u].w));
+            }
+            at_static_for<0, 6>([&](auto ic) { s = mfma_part<decltype(ic)::value>(f, w.q[j], s); });
+        }
+        const bool more = st + kAtWaves < n_stages;
+        if (more) fetch_k(st + kAtWaves);
+        float mx;
+        attention_max_piece<0>(s, mx);
+        attention_max_piece<1>(s, mx);
+        attention_move_reference(w, mx);
+        Frag3 pf[2];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float p0 = __builtin_amdgcn_exp2f(s[2 * i] - w.m_run), p1 = __builtin_amdgcn_exp2f(s[2 * i + 1] - w.m_run);
+            w.l_run += p0 + p1;
+            pf[i >> 2].set(i & 3, split_bf16(p0, p1));
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int c = 0; c < kDB; ++c) {
+                Frag3 f;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) f.set(u, split_bf16(v[j][c][2 * u], v[j][c][2 * u + 1]));
+                at_static_for<0, 6>([&](auto ic) { w.o[c] = mfma_part<decltype(ic)::value>(f, pf[j], w.o[c]); });
+            }
+        if (more) fetch_v(st + kAtWaves);
+    }
+
+    // The waves' shares, each against its own reference; a wave without a stage has reference -inf and weight 0.
+    {
+        const auto l2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(w.l_run), __float_as_uint(w.l_run), false, false);
+        if (hi == 0) {
+            part_m[wave * kAtQW + lq] = w.m_run;
+            part_l[wave * kAtQW + lq] = __uint_as_float(l2[0]) + __uint_as_float(l2[1]);
+        }
+        float* row = part_o + (wave * kAtQW + lq) * kRow + 4 * hi;
+#pragma unroll
+        for (int c = 0; c < kDB; ++c)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                *reinterpret_cast<float4*>(row + 32 * c + 8 * g) = make_float4(w.o[c][4 * g], w.o[c][4 * g + 1], w.o[c][4 * g + 2], w.o[c][4 * g + 3]);
+    }
+    __syncthreads();
+    const int q = tid >> 3;   // eight threads a query, four columns of every 32 each
+    float m_all = part_m[q];
+#pragma unroll
+    for (int i = 1; i < kAtWaves; ++i) m_all = at_max(m_all, part_m[i * kAtQW + q]);
+    float f[kAtWaves], den = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kAtWaves; ++i) {
+        f[i] = __builtin_amdgcn_exp2f(part_m[i * kAtQW + q] - m_all);
+        den += f[i] * part_l[i * kAtQW + q];
+    }
+    const float inv = 1.0f / den;
+    const float qs = a.q_out ? a.q_scale[0] : 0.0f;
+    float amax = 0.0f;
+    if (q0 + q < S) {
+        const int64_t out_off = (b * S + q0 + q) * HD + (int64_t)h * d;
+#pragma unroll
+        for (int c = 0; c < kDB; ++c) {
+            const int col = 32 * c + 4 * (tid & 7);
+            if (col < d) {
+                float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+                for (int i = 0; i < kAtWaves; ++i) {
+                    const float4 p = *reinterpret_cast<const float4*>(part_o + (i * kAtQW + q) * kRow + col);
+                    o.x += f[i] * p.x;
+                    o.y += f[i] * p.y;
+                    o.z += f[i] * p.z;
+                    o.w += f[i] * p.w;
+                }
+                o.x *= inv;
+                o.y *= inv;
+                o.z *= inv;
+                o.w *= inv;
+                if (a.ctx) *reinterpret_cast<float4*>(a.ctx + out_off + col) = o;
+                if (a.q_out)
+                    a.q_out[(out_off + col) >> 2] = ((unsigned)quantize_code(o.x, qs) & 0xffu) | (((unsigned)quantize_code(o.y, qs) & 0xffu) << 8) |
+                                                    (((unsigned)quantize_code(o.z, qs) & 0xffu) << 16) | ((unsigned)quantize_code(o.w, qs) << 24);
+                amax = __builtin_fmaxf(amax, __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(o.x), __builtin_fabsf(o.y)),
+                                                            __builtin_fmaxf(__builtin_fabsf(o.z), __builtin_fabsf(o.w))));
+            }
+        }
+    }
+    if (a.slots) {   // never more workgroups than slots here
+        unsigned m = wave_max_u32(__float_as_uint(amax));
+        if (lane == 0) wave_amax[wave] = m;
+        __syncthreads();
+        if (tid == 0) {
+#pragma unroll
+            for (int i = 1; i < kAtWaves; ++i) m = max(m, wave_amax[i]);
+            a.slots[blockIdx.x] = m;
+        }
+        if (blockIdx.x == 0)
+            for (int i = gridDim.x + tid; i < kAtSlots; i += kAtThreads) a.slots[i] = 0u;
+    }
+#endif
+}
+
 // Any head width and alignment: one wave per (sequence, head, query).  Scores go to LDS, the softmax is the
 // plain three-step form, then each lane sums its columns of V.  Slow; same tolerance.
 __global__ __launch_bounds__(64) void attention_generic_kernel(const float* __restrict__ qkv, const float* __restrict__ mask,
@@ -668,8 +889,19 @@ bool attention_mfma_eligible(const float* qkv, int64_t B, int64_t S, int heads, 
 }
 
 template <int kDB>
-static int launch_attention_width(const AttnArgs& a, int64_t wgs, hipStream_t st)
+static int launch_attention_width(AttnArgs a, int64_t wgs, hipStream_t st)
 {
+    // The split kernel while each of its workgroups has a compute unit of its own (7 x 93 tokens, 252 workgroups: 7.9 us
+    // against 9.1); with two on a unit (widths up to 64) only where there is a chain to shorten or a single stage to
+    // walk: 2 x 512 (384) 22.0 against 26.0, 32 x 32 (384) 7.0 against 8.2, but 16 x 64 (384) 8.8 against 7.4 and
+    // 8 x 128 (384) even; beyond, 6 x 256 (576) 20.9 against 17.2.
+    const int64_t bh = wgs / a.n_qblocks, n_q32 = (a.S + kAtQW - 1) / kAtQW, wgs32 = bh * n_q32;
+    const bool split = wgs32 <= 256 || (kDB <= 2 && wgs32 <= 512 && (n_q32 == 1 || n_q32 >= 8));
+    if (split) {
+        a.n_qblocks = (int)n_q32;
+        hipLaunchKernelGGL(attention_split_kernel<kDB>, dim3((unsigned)wgs32), dim3(kAtThreads), 0, st, a);
+        return hipGetLastError() == hipSuccess ? 0 : 1;
+    }
     constexpr int lds_bytes = AttnTile<kDB>::kBytes;
     if constexpr (lds_bytes > 64 * 1024) {   // more than 64 KiB of dynamic LDS has to be asked for
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(attention_mfma_kernel<kDB>), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -1,0 +1,64 @@
+"""Both attention kernels around the rule that chooses between them: few workgroups (the key stages dealt out over the waves
+of a workgroup) and many (all four waves walk every stage)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def q8():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1910_06188_amd import q8 as mod
+    return mod
+
+
+def reference(qkv, B, S, heads, d, mask):
+    """Plain attention in 64 bits on the CPU."""
+    q, k, v = qkv.cpu().double().view(B, S, 3, heads, d).permute(2, 0, 3, 1, 4).contiguous()
+    s = torch.matmul(q, k.transpose(-1, -2).contiguous()) / d ** 0.5
+    if mask is not None:
+        s = s + mask.cpu().double().view(B, 1, 1, S).clamp(min=-1e30)
+    return torch.matmul(s.softmax(-1), v).permute(0, 2, 1, 3).reshape(B * S, heads * d)
+
+
+@pytest.mark.parametrize("B,S,heads,d,mask", [
+    # one stage; a stage and a key; fewer stages than waves; as many; one more; ragged last stages; several a wave
+    (1, 1, 1, 4, "none"), (2, 31, 2, 8, "some"), (1, 33, 3, 64, "low"), (2, 96, 2, 64, "some"), (3, 128, 2, 32, "low"), (1, 129, 4, 48, "some"),
+    (1, 161, 2, 64, "low"), (2, 255, 2, 40, "some"), (1, 300, 2, 128, "low"), (1, 290, 3, 96, "some"), (1, 1000, 2, 64, "low"),
+    # 256 / 260 workgroups, 512 / 520 of eight stages, 384 of one
+    (16, 128, 4, 64, "some"), (5, 416, 4, 64, "some"), (13, 128, 5, 64, "some"), (16, 256, 4, 64, "low"), (13, 256, 5, 64, "low"), (96, 30, 4, 32, "some"), (65, 128, 1, 80, "low"),
+    # many workgroups: the other kernel on ragged sequences, its first stages masked with the lowest number
+    (40, 93, 12, 64, "some"), (40, 93, 12, 32, "low"), (33, 70, 8, 128, "low"), (24, 130, 8, 96, "some"),
+])
+def test_attention_on_both_sides_of_the_split(q8, B, S, heads, d, mask):
+    g = torch.Generator(device="cuda").manual_seed(B * 7919 + S * 31 + heads + d)
+    qkv = torch.randn((B * S, 3 * heads * d), generator=g, device="cuda")
+    m = None
+    if mask == "some":
+        m = torch.where(torch.rand((B, S), generator=g, device="cuda") < 0.3, -10000.0, 0.0)
+    elif mask == "low":      # left padding with the lowest number of the type: whole stages of it before the first key
+        m = torch.zeros((B, S), device="cuda")
+        m[:, : (2 * S) // 3] = torch.finfo(torch.float32).min
+    if m is not None:
+        m[:, S - 1] = 0.0
+    n, guard = B * S * heads * d, 64
+    buf = torch.full((n + guard,), 7.0, device="cuda")
+    ctx, slots = buf[:n].view(B * S, heads * d), torch.full((q8.AMAX_SLOTS,), 9e9, device="cuda")
+    q8.q8_attention(qkv, B, S, heads, d, ctx=ctx, mask=m, amax_slots=slots)
+    scale = torch.tensor([40.0], device="cuda")
+    codes = torch.full((n + guard,), 5, dtype=torch.int8, device="cuda")
+    q8.q8_attention(qkv, B, S, heads, d, mask=m, q_scale=scale, q_out=codes[:n])
+    torch.cuda.synchronize()
+    ref = reference(qkv, B, S, heads, d, m)
+    got = ctx.cpu().double()
+    # probabilities and outputs carry a few roundings of 2^-24 each, the scores one of their own size (|s| < 8): 2e-6 of the
+    # largest |V| is the bar of the other attention tests
+    assert (got - ref).abs().max().item() <= 2e-6 * qkv[:, 2 * heads * d:].abs().max().item()
+    assert slots.max().item() == ctx.abs().max().item()
+    assert bool((buf[n:] == 7.0).all()) and bool((codes[n:] == 5).all())
+    q_ref = torch.empty((n,), dtype=torch.int8, device="cuda")
+    q8.q8_quantize(ctx.reshape(-1), scale, q_ref)
+    np.testing.assert_array_equal(codes[:n].cpu().numpy(), q_ref.cpu().numpy())
