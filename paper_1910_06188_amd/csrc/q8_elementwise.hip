@@ -577,7 +577,7 @@ int launch_quantize_onepass(const float* x, int64_t n, float* amax_out, float* s
 // thread), leaves its maximum in a slot, waits at a grid-wide barrier, folds the slots, and quantizes from
 // registers -- 5 bytes per element, x read once.
 //
-// The barrier needs every workgroup of the launch to be resident at once: the grid is one workgroup of 1024
+// The barrier needs every workgroup of the launch to be resident at once: the grid is at most one workgroup of 1024
 // threads per compute unit, so it is whenever the chip is not held by something else; and no wait is unbounded --
 // a workgroup that has polled `spin_limit` times stops waiting and reads the shares of the workgroups that have
 // not published yet itself (same result, slower; what two such launches from different streams that each hold
@@ -595,6 +595,7 @@ constexpr int kRqThreads = 1024;
 constexpr int kRqVec = 12;  // float4 per thread
 constexpr int kRqMaxGroups = 256;
 constexpr int kRqRing = 64;
+constexpr int64_t kRqSmall = 524288;  // elements up to which a grid smaller than the chip pays
 static __device__ unsigned long long g_rq_slots[kRqRing][kRqMaxGroups];
 
 __global__ __launch_bounds__(kRqThreads) void quantize_resident_kernel(const float4* __restrict__ x4, int n4,
@@ -735,7 +736,12 @@ int launch_quantize_resident(const float* x, int64_t n, float* amax_out, float* 
         groups = g_rq_groups[dev];
     }
     const int64_t n4 = n >> 2;
-    if (n4 < (int64_t)groups * kRqThreads || n4 > (int64_t)groups * kRqThreads * kRqVec) return 2;
+    if (n4 > (int64_t)groups * kRqThreads * kRqVec) return 2;
+    // A small tensor takes as many workgroups as it fills: one launch and a short barrier (us in one pass / in two: 20 000 elements
+    // 4.2 / 6.3, 98 304 5.3 / 6.6, 400 000 6.0 / 6.5, but 777 000 6.6 / 6.5 and 1 000 000 7.0 / 6.3: the barrier grows with the
+    // workgroups while the second launch stays the same).  A tensor that fills the grid is read from memory once.
+    if (n4 > kRqSmall / 4 && n4 < (int64_t)groups * kRqThreads) return 2;
+    groups = (int)std::min<int64_t>(groups, (n4 + kRqThreads - 1) / kRqThreads);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
         (void)hipGetLastError();

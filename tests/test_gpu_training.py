@@ -188,3 +188,25 @@ def test_ema_inside_the_fake_quantization(q8, n, off, in_place):
     out = torch.full((n + off + 4,), 7.0, device="cuda")
     q8.q8_ste_backward(xc, out[off:off + n])
     assert torch.equal(out[off:off + n], xc) and bool((out[off + n:] == 7.0).all())
+
+
+@pytest.mark.parametrize("n", [16388, 20_000, 4096 * 5, 4096 * 5 + 4, 131_076, 524_288, 524_292, 16389])
+@pytest.mark.parametrize("polls", [64, 0])
+def test_dynamic_quantizer_of_small_tensors(q8, n, polls):
+    """One launch with a grid of its own size (up to half a million elements), waiting at the barrier and giving up at once
+    (every workgroup reads the shares of the others); one element more or a ragged count takes two launches."""
+    x = torch.randn(n, generator=torch.Generator(device="cuda").manual_seed(n), device="cuda")
+    x[n - 1] = -9.5                                     # the maximum sits in the last workgroup
+    q, work, zero = torch.full((n + 64,), 77, dtype=torch.int8, device="cuda"), torch.zeros(q8.SCAL_WORK, device="cuda"), torch.ones(1, device="cuda")
+    q8.set_quantize_one_pass(True, polls)
+    try:
+        for _ in range(3):
+            q8.q8_quantize_dynamic(x, q[:n], work, zero_slot=zero)
+        torch.cuda.synchronize()
+    finally:
+        q8.set_quantize_one_pass(True, 64)
+    xh = host(x)
+    s = O.scale(O.absmax(xh))
+    assert host(work)[0] == O.absmax(xh) and host(work)[1] == s and host(zero)[0] == 0.0
+    np.testing.assert_array_equal(host(q[:n]), O.quantize(xh, s))
+    assert bool((q[n:] == 77).all())
