@@ -372,12 +372,13 @@ void q8_debug_set_gemm_variant(int variant);
 
 /*
  * The dynamic quantizer (q8_quantize_dynamic, q8_linear_f32, q8_linear_f32_static) takes a one-pass kernel for
- * tensors that fit the register files of the chip: 4-element multiples of n between 4096 and 49152 floats per
- * compute unit, x 16-byte aligned, stream not under graph capture.  Its workgroups meet at a barrier; one that has
+ * tensors that fit the register files of the chip: 4-element multiples of n up to 524288 floats, or between 4096 and
+ * 49152 floats per compute unit, x 16-byte aligned, stream not under graph capture.  Its workgroups meet at a barrier; one that has
  * polled `barrier_polls` times (default 64, about 80 us) stops waiting and reads the shares of the absent
  * workgroups itself, so the result never depends on the wait.  enabled = 0 turns the kernel off (two passes over
  * x, same results); barrier_polls = 0 makes a workgroup scan for every other one that is not there at its first
- * look (tests).  Process-global, unsynchronised.
+ * look (tests).  q8_absmax follows the same switch: one launch whose first workgroup waits for the others, or three.
+ * Process-global, unsynchronised.
  */
 void q8_debug_set_quantize_one_pass(int enabled, uint32_t barrier_polls);
 

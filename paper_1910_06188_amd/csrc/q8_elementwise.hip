@@ -55,7 +55,7 @@ __global__ void absmax_empty_kernel(float* amax, float* scale)
 // A maximum does not mind seeing an element twice, so the last trip clamps its indices to
 // the final vector instead of branching: every trip has kAmUnroll loads in flight.
 constexpr int kAmUnroll = 8;
-__device__ __forceinline__ unsigned absmax_thread(const float* __restrict__ x, int64_t n, int head)
+__device__ __forceinline__ unsigned absmax_thread(const float* __restrict__ x, int64_t n, int head, int block)
 {
     unsigned m = 0u;
     const float4* xv = reinterpret_cast<const float4*>(x + head);
@@ -65,7 +65,7 @@ __device__ __forceinline__ unsigned absmax_thread(const float* __restrict__ x, i
     // time the whole grid reads one contiguous window of x.  With the loads of a trip a grid-stride apart instead
     // (every workgroup touching kAmUnroll distant pages at once) the same pass reads 5.0 TB/s instead of 6.2.
     const int64_t step = (int64_t)gridDim.x * (kAmUnroll * kEwThreads);
-    for (int64_t i = (int64_t)blockIdx.x * (kAmUnroll * kEwThreads) + threadIdx.x; i < nvec; i += step) {
+    for (int64_t i = (int64_t)block * (kAmUnroll * kEwThreads) + threadIdx.x; i < nvec; i += step) {
         float4 v[kAmUnroll];
 #pragma unroll
         for (int u = 0; u < kAmUnroll; ++u) v[u] = xv[min(i + u * kEwThreads, nvec - 1)];
@@ -76,7 +76,7 @@ __device__ __forceinline__ unsigned absmax_thread(const float* __restrict__ x, i
             m = max(m, max(a, b));
         }
     }
-    if (blockIdx.x == 0) {
+    if (block == 0) {
         if ((int)threadIdx.x < head) m = max(m, abs_bits(x[threadIdx.x]));
         int64_t t = tail0 + threadIdx.x;
         if (t < n) m = max(m, abs_bits(x[t]));
@@ -122,7 +122,7 @@ __device__ __forceinline__ unsigned fold_thread(const float* __restrict__ amax, 
 __global__ __launch_bounds__(kEwThreads) void absmax_atomic_kernel(const float* __restrict__ x, int64_t n, int head,
                                                                     unsigned* amax_bits)
 {
-    unsigned m = block_max_u32(absmax_thread(x, n, head));
+    unsigned m = block_max_u32(absmax_thread(x, n, head, (int)blockIdx.x));
     // the maximum only grows: skip the serialising read-modify-write when there is nothing to add
     if (threadIdx.x == 0 && m > __hip_atomic_load(amax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
         atomicMax(amax_bits, m);
@@ -136,8 +136,61 @@ __global__ __launch_bounds__(kEwThreads) void absmax_partial_kernel(const float*
                                                                      const float* __restrict__ state, float* __restrict__ old_state)
 {
     if (old_state && blockIdx.x == 0 && threadIdx.x < 2) old_state[threadIdx.x] = state[threadIdx.x];
-    unsigned m = block_max_u32(absmax_thread(x, n, head));
+    unsigned m = block_max_u32(absmax_thread(x, n, head, (int)blockIdx.x));
     if (threadIdx.x == 0) partials[blockIdx.x] = m;
+}
+
+// Stand-alone abs-max and scale in one launch: every workgroup publishes (ticket, maximum) in a slot of its own, the first
+// one waits for the others' and writes the results.  Nobody waits for the first, so the others always arrive, whatever
+// holds the chip; and the wait is bounded -- shares of workgroups that have not arrived by then, or whose slot a later
+// launch has taken over, are scanned here (same result, slower).  Slots and tickets as in quantize_resident_kernel.
+// Clearing the word, the atomics and the scale took three launches, and the atomics held the grid at 256 workgroups.
+// 30522 x 768, abs-max, quantization and a lookup: 42.4 -> 40.4 us.
+constexpr int kAmSlots = 1024, kAmRing = 256;
+static __device__ unsigned long long g_am_slots[kAmRing][kAmSlots];
+
+__global__ __launch_bounds__(kEwThreads) void absmax_scale_kernel(const float* __restrict__ x, int64_t n, int head,
+                                                                   unsigned long long* slots, unsigned ticket, unsigned spin_limit,
+                                                                   float* amax_out, float* scale_out)
+{
+    __shared__ unsigned long long missing[kAmSlots / 64];
+    unsigned m = block_max_u32(absmax_thread(x, n, head, (int)blockIdx.x));
+    if (threadIdx.x == 0) __hip_atomic_store(&slots[blockIdx.x], ((unsigned long long)ticket << 32) | m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (blockIdx.x != 0) return;
+    m = 0u;
+    for (int i = threadIdx.x; i < kAmSlots; i += kEwThreads) {
+        bool here = i >= (int)gridDim.x;  // slots past the grid count as arrived
+        for (unsigned polls = 0; !here; ++polls) {
+            const unsigned long long sv = __hip_atomic_load(&slots[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned seen = (unsigned)(sv >> 32);
+            if (seen == ticket) {
+                here = true;
+                m = max(m, (unsigned)sv);
+            } else if (polls >= spin_limit || (int)(seen - ticket) > 0) {
+                break;
+            } else {
+                __builtin_amdgcn_s_sleep(4);
+            }
+        }
+        const unsigned long long absent = __ballot(!here);
+        if ((threadIdx.x & 63) == 0) missing[i >> 6] = absent;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int r = 0; r < kAmSlots / 64; ++r) {
+        unsigned long long absent = missing[r];
+        while (absent) {
+            const int g = r * 64 + __builtin_ctzll(absent);
+            absent &= absent - 1ull;
+            m = max(m, absmax_thread(x, n, head, g));
+        }
+    }
+    m = block_max_u32(m);
+    if (threadIdx.x == 0) {
+        const float a = __uint_as_float(m);
+        amax_out[0] = a;
+        if (scale_out) scale_out[0] = scale_from_amax(a);
+    }
 }
 
 __global__ void scale_from_amax_kernel(const float* amax, float* scale) { scale[0] = scale_from_amax(amax[0]); }
@@ -497,23 +550,6 @@ static int head_of(const float* x, int64_t n)
     return head > n ? (int)n : head;
 }
 
-int launch_absmax(const float* x, int64_t n, float* amax_out, float* scale_out, hipStream_t st)
-{
-    if (n == 0) {
-        hipLaunchKernelGGL(absmax_empty_kernel, dim3(1), dim3(1), 0, st, amax_out, scale_out);
-        return hipGetLastError() == hipSuccess ? 0 : 1;
-    }
-    unsigned* bits = reinterpret_cast<unsigned*>(amax_out);
-    const int head = head_of(x, n);
-    hipLaunchKernelGGL(absmax_init_kernel, dim3(1), dim3(1), 0, st, bits);
-    // every workgroup ends in a read of one address and, while the maximum still grows, a read-modify-write of it (94 MB:
-    // 512 workgroups 3.6 us slower than 256, 1024 12 us)
-    const int g = am_grid((n - head) >> 2);
-    hipLaunchKernelGGL(absmax_atomic_kernel, dim3(g < 256 ? g : 256), dim3(kEwThreads), 0, st, x, n, head, bits);
-    if (scale_out) hipLaunchKernelGGL(scale_from_amax_kernel, dim3(1), dim3(1), 0, st, amax_out, scale_out);
-    return hipGetLastError() == hipSuccess ? 0 : 1;
-}
-
 int launch_absmax_partial(const float* x, int64_t n, float* partials, int* n_partials, hipStream_t st)
 {
     const int head = head_of(x, n);
@@ -694,12 +730,84 @@ __global__ __launch_bounds__(kRqThreads) void quantize_resident_kernel(const flo
     }
 }
 
-static std::atomic<unsigned> g_rq_next{0};
 static std::atomic<unsigned> g_rq_spin_limit{64u};   // about 80 us of polling
 static std::atomic<bool> g_rq_enabled{true};
-static std::mutex g_rq_lock;
-static unsigned long long* g_rq_slots_ptr[64] = {};
-static int g_rq_groups[64] = {};
+
+// A ring of slot arrays in device memory, handed out round robin, and the ticket of the launch that takes one.
+struct SlotRing {
+    const void* symbol;
+    int entries, slots;
+    std::atomic<unsigned> next{0};
+    std::mutex lock;
+    unsigned long long* ptr[64] = {};
+    int units[64] = {};
+};
+static SlotRing g_rq_ring{HIP_SYMBOL(g_rq_slots), kRqRing, kRqMaxGroups};
+static SlotRing g_am_ring{HIP_SYMBOL(g_am_slots), kAmRing, kAmSlots};
+
+struct RingEntry {
+    unsigned long long* slots = nullptr;   // null: switched off, a stream under graph capture (a replay would carry the ticket
+                                           // of the capture), or a device the ring cannot be looked up on
+    unsigned ticket = 0;
+    int units = 0;                         // compute units of the device
+};
+static RingEntry ring_entry(SlotRing& ring, hipStream_t st, bool (*fits)(int64_t, int) = nullptr, int64_t n = 0)
+{
+    RingEntry e;
+    int dev = -1;
+    if (!g_rq_enabled.load() || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return e;
+    {
+        std::lock_guard<std::mutex> hold(ring.lock);
+        if (!ring.ptr[dev]) {
+            void* p = nullptr;
+            int cus = 0;
+            if (hipGetSymbolAddress(&p, ring.symbol) != hipSuccess ||
+                hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
+                (void)hipGetLastError();
+                return e;
+            }
+            ring.ptr[dev] = static_cast<unsigned long long*>(p);
+            ring.units[dev] = cus;
+        }
+        e.units = ring.units[dev];
+    }
+    if (fits && !fits(n, e.units)) return e;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return e;
+    }
+    if (cap != hipStreamCaptureStatusNone) return e;
+    const unsigned seq = ring.next.fetch_add(1u);
+    e.ticket = seq + 1u == 0u ? ring.next.fetch_add(1u) + 1u : seq + 1u;   // never 0: the slots start as zeros
+    e.slots = ring.ptr[dev] + (size_t)(seq % (unsigned)ring.entries) * ring.slots;
+    return e;
+}
+
+int launch_absmax(const float* x, int64_t n, float* amax_out, float* scale_out, hipStream_t st)
+{
+    if (n == 0) {
+        hipLaunchKernelGGL(absmax_empty_kernel, dim3(1), dim3(1), 0, st, amax_out, scale_out);
+        return hipGetLastError() == hipSuccess ? 0 : 1;
+    }
+    unsigned* bits = reinterpret_cast<unsigned*>(amax_out);
+    const int head = head_of(x, n);
+    // slots and a ticket for the one-launch form; without them (switched off, a stream under graph capture) the atomics
+    const RingEntry ring = ring_entry(g_am_ring, st);
+    if (ring.slots) {
+        const unsigned polls = g_rq_spin_limit.load() == 0u ? 0u : 1u << 20;   // the others arrive whatever this one does
+        const int grid = std::min(am_grid((n - head) >> 2), kAmSlots);
+        hipLaunchKernelGGL(absmax_scale_kernel, dim3(grid), dim3(kEwThreads), 0, st, x, n, head, ring.slots, ring.ticket, polls, amax_out, scale_out);
+        return hipGetLastError() == hipSuccess ? 0 : 1;
+    }
+    hipLaunchKernelGGL(absmax_init_kernel, dim3(1), dim3(1), 0, st, bits);
+    // every workgroup ends in a read of one address and, while the maximum still grows, a read-modify-write of it (94 MB:
+    // 512 workgroups 3.6 us slower than 256, 1024 12 us)
+    const int g = am_grid((n - head) >> 2);
+    hipLaunchKernelGGL(absmax_atomic_kernel, dim3(g < 256 ? g : 256), dim3(kEwThreads), 0, st, x, n, head, bits);
+    if (scale_out) hipLaunchKernelGGL(scale_from_amax_kernel, dim3(1), dim3(1), 0, st, amax_out, scale_out);
+    return hipGetLastError() == hipSuccess ? 0 : 1;
+}
 
 void set_quantize_resident(bool enabled, unsigned polls)
 {
@@ -707,52 +815,28 @@ void set_quantize_resident(bool enabled, unsigned polls)
     g_rq_spin_limit.store(polls);
 }
 
+// What the registers of the grid hold, and is worth the barrier: a tensor that fills the grid is read from memory once; a
+// small one takes as many workgroups as it fills, one launch and a short barrier (us in one pass / in two: 20 000 elements
+// 4.2 / 6.3, 98 304 5.3 / 6.6, 400 000 6.0 / 6.5, but 777 000 6.6 / 6.5 and 1 000 000 7.0 / 6.3: the barrier grows with the
+// workgroups while the second launch stays the same).
+static bool resident_fits(int64_t n, int units)
+{
+    const int64_t n4 = n >> 2, groups = std::min(units, kRqMaxGroups);
+    return n4 <= groups * kRqThreads * kRqVec && (n <= kRqSmall || n4 >= groups * kRqThreads);
+}
+
 // 0: launched.  1: the runtime refused the launch.  2: not a case for this kernel (the caller takes the two-pass path):
-// shape or alignment, a tensor larger than the registers of the grid, a stream under graph capture (a replay would
-// carry the ticket of the capture), or a device the slot ring cannot be looked up on.
+// shape or alignment, a tensor larger than the registers of the grid, or no ring entry.
 int launch_quantize_resident(const float* x, int64_t n, float* amax_out, float* scale_out, int8_t* q, float* zero_slot,
                              hipStream_t st)
 {
-    if (!g_rq_enabled.load()) return 2;
     if (n % 4 != 0 || (reinterpret_cast<uintptr_t>(x) & 15) || (reinterpret_cast<uintptr_t>(q) & 3)) return 2;
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 2;
-    unsigned long long* ring = nullptr;
-    int groups = 0;
-    {
-        std::lock_guard<std::mutex> hold(g_rq_lock);
-        if (!g_rq_slots_ptr[dev]) {
-            void* p = nullptr;
-            int cus = 0;
-            if (hipGetSymbolAddress(&p, HIP_SYMBOL(g_rq_slots)) != hipSuccess ||
-                hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
-                (void)hipGetLastError();
-                return 2;
-            }
-            g_rq_slots_ptr[dev] = static_cast<unsigned long long*>(p);
-            g_rq_groups[dev] = cus < kRqMaxGroups ? cus : kRqMaxGroups;
-        }
-        ring = g_rq_slots_ptr[dev];
-        groups = g_rq_groups[dev];
-    }
+    const RingEntry ring = ring_entry(g_rq_ring, st, resident_fits, n);
+    if (!ring.slots) return 2;
     const int64_t n4 = n >> 2;
-    if (n4 > (int64_t)groups * kRqThreads * kRqVec) return 2;
-    // A small tensor takes as many workgroups as it fills: one launch and a short barrier (us in one pass / in two: 20 000 elements
-    // 4.2 / 6.3, 98 304 5.3 / 6.6, 400 000 6.0 / 6.5, but 777 000 6.6 / 6.5 and 1 000 000 7.0 / 6.3: the barrier grows with the
-    // workgroups while the second launch stays the same).  A tensor that fills the grid is read from memory once.
-    if (n4 > kRqSmall / 4 && n4 < (int64_t)groups * kRqThreads) return 2;
-    groups = (int)std::min<int64_t>(groups, (n4 + kRqThreads - 1) / kRqThreads);
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        return 2;
-    }
-    if (cap != hipStreamCaptureStatusNone) return 2;
-    unsigned seq = g_rq_next.fetch_add(1u);
-    const unsigned ticket = seq + 1u == 0u ? g_rq_next.fetch_add(1u) + 1u : seq + 1u;   // never 0: the slots start as zeros
-    unsigned long long* slots = ring + (size_t)(seq % kRqRing) * kRqMaxGroups;
+    const int groups = (int)std::min<int64_t>(std::min(ring.units, kRqMaxGroups), (n4 + kRqThreads - 1) / kRqThreads);
     hipLaunchKernelGGL(quantize_resident_kernel, dim3(groups), dim3(kRqThreads), 0, st, reinterpret_cast<const float4*>(x),
-                       (int)n4, slots, ticket, g_rq_spin_limit.load(), amax_out, scale_out,
+                       (int)n4, ring.slots, ring.ticket, g_rq_spin_limit.load(), amax_out, scale_out,
                        reinterpret_cast<unsigned*>(q), zero_slot);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }

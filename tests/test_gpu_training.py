@@ -210,3 +210,47 @@ def test_dynamic_quantizer_of_small_tensors(q8, n, polls):
     assert host(work)[0] == O.absmax(xh) and host(work)[1] == s and host(zero)[0] == 0.0
     np.testing.assert_array_equal(host(q[:n]), O.quantize(xh, s))
     assert bool((q[n:] == 77).all())
+
+
+@pytest.mark.parametrize("n,off", [(1, 0), (2, 1), (7, 3), (1536, 0), (1537, 1), (100_003, 2), (1_572_864, 0), (1_572_869, 1), (6_000_001, 0)])
+@pytest.mark.parametrize("enabled,polls", [(True, 64), (True, 0), (False, 64)])
+def test_absmax_in_one_launch(q8, n, off, enabled, polls):
+    """The abs-max and its scale in one launch (one workgroup, a few, as many as there are slots and several trips each; the
+    first workgroup waiting, and scanning every share that is not there at its first look) and in three."""
+    buf = torch.randn(n + off, generator=torch.Generator(device="cuda").manual_seed(n), device="cuda")
+    x = buf[off:]
+    a, s = torch.full((3,), 5.0, device="cuda"), torch.full((3,), 6.0, device="cuda")
+    q8.set_quantize_one_pass(enabled, polls)
+    try:
+        for pos, value in ((n - 1, -9.5), (0, 11.25), (n // 2, 12.0)):
+            x[pos] = value
+            for _ in range(2):
+                q8.q8_absmax(x, a[1:2], s[1:2])
+            torch.cuda.synchronize()
+            xh = host(x)
+            assert host(a)[1] == O.absmax(xh) and host(s)[1] == O.scale(O.absmax(xh))
+        q8.q8_absmax(x, a[1:2])                                   # no scale asked for
+        assert host(a)[1] == O.absmax(xh)
+        x.zero_()
+        q8.q8_absmax(x, a[1:2], s[1:2])
+        assert host(a).tolist() == [5.0, 0.0, 5.0] and host(s).tolist() == [6.0, 1.0, 6.0]
+    finally:
+        q8.set_quantize_one_pass(True, 64)
+
+
+def test_absmax_many_launches_on_two_streams(q8):
+    """More launches in flight than the ring of slots has entries, sizes mixed over two streams."""
+    sizes = [5, 70_000, 1_000_003, 3_000_000]
+    xs = [torch.randn(n, device="cuda") for n in sizes]
+    peak = [float(x.abs().max()) for x in xs]
+    out = torch.zeros((2, 400), device="cuda")
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for i in range(400):
+        for j, st in enumerate(streams):
+            q8.q8_absmax(xs[(i + j) % 4], out[j, i:i + 1], stream=st)
+    torch.cuda.synchronize()
+    got = host(out)
+    for j in range(2):
+        for i in range(400):
+            assert got[j, i] == np.float32(peak[(i + j) % 4])
