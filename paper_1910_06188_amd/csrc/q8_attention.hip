@@ -144,6 +144,12 @@ __device__ __forceinline__ float mask_log2(float m)
     return v < -3.0e38f ? -3.0e38f : v;
 }
 
+// Loads through a descriptor.  The whole offset is in the vector operand: that is what the bounds check is documented to
+// compare with the descriptor's size (the scalar operand is left out of it), and rows beyond the sequence rely on the check.
+__device__ __forceinline__ float buf_f1(__amdgpu_buffer_rsrc_t r, unsigned off)
+{
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
 __device__ __forceinline__ float4 buf_f4(__amdgpu_buffer_rsrc_t r, unsigned off)
 {
     typedef unsigned u4 __attribute__((ext_vector_type(4)));
@@ -217,7 +223,7 @@ struct AttnStager {
         for (int i = 0; i < kItems; ++i)
 #pragma unroll
             for (int e = 0; e < 8; ++e)
-                v[kSet][i][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)v_off[i], 4 * (row0 + (e & 3) + 8 * (e >> 2)) * (int)ld, 0));
+                v[kSet][i][e] = buf_f1(r, v_off[i] + 4u * (unsigned)(row0 + (e & 3) + 8 * (e >> 2)) * (unsigned)ld);
     }
     template <int kSet>
     __device__ __forceinline__ void stash_mask(int buf, int stage)
@@ -671,10 +677,13 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int c = 0; c < kDB; ++c)
+            for (int c = 0; c < kDB; ++c) {
+                unsigned col = v_off[c];
+                asm volatile("" : "+v"(col));   // added up here: kept across the loop, the sixteen row offsets cost registers that spill
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
-                    v[j][c][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)v_off[c], 4 * (16 * j + (e & 3) + 8 * (e >> 2)) * (int)ld, 0));
+                    v[j][c][e] = buf_f1(r, col + 4u * (unsigned)(16 * j + (e & 3) + 8 * (e >> 2)) * (unsigned)ld);
+            }
     };
 
     AttnWave<kDB> w;

@@ -62,3 +62,27 @@ def test_attention_on_both_sides_of_the_split(q8, B, S, heads, d, mask):
     q_ref = torch.empty((n,), dtype=torch.int8, device="cuda")
     q8.q8_quantize(ctx.reshape(-1), scale, q_ref)
     np.testing.assert_array_equal(codes[:n].cpu().numpy(), q_ref.cpu().numpy())
+
+
+@pytest.mark.parametrize("B,S,heads,d", [
+    (1, 33, 2, 64), (2, 93, 3, 64), (1, 130, 2, 64), (1, 70, 2, 32), (2, 45, 1, 128),          # the stages dealt out
+    (2, 33, 140, 64), (2, 93, 44, 64), (2, 130, 30, 64), (2, 70, 50, 32), (2, 45, 70, 128),    # four waves on every stage
+])
+def test_attention_reads_no_row_behind_its_sequence(q8, B, S, heads, d):
+    """Ragged last stages: the rows behind the last sequence are NaN, and so is every sequence but the first one in a second
+    call; a key row that does not exist would come in as 0 x NaN."""
+    g = torch.Generator(device="cuda").manual_seed(S * 31 + heads + d)
+    n, HD = B * S, heads * d
+    buf = torch.full((n + 64, 3 * HD), float("nan"), device="cuda")
+    buf[:n] = torch.randn((n, 3 * HD), generator=g, device="cuda")
+    clean = buf[:n].clone()
+    vmax = clean[:, 2 * HD:].abs().max().item()
+    ref = reference(clean, B, S, heads, d, None)
+    ctx = torch.empty((n, HD), device="cuda")
+    q8.q8_attention(buf[:n], B, S, heads, d, ctx=ctx)
+    assert (ctx.cpu().double() - ref).abs().max().item() <= 2e-6 * vmax
+    if B > 1:
+        buf[S:] = float("nan")
+        q8.q8_attention(buf[:n], B, S, heads, d, ctx=ctx)
+        assert (ctx[:S].cpu().double() - ref[:S]).abs().max().item() <= 2e-6 * vmax
+        assert bool(ctx[S:].isnan().all())
