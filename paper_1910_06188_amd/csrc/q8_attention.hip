@@ -6,13 +6,18 @@
 // ctx goes to per-workgroup slots, or, with a stored scale (Eq. 4), the int8 codes of ctx are
 // written directly (Eq. 1) and ctx itself need not be stored at all.
 //
-// FP32 products on the bf16 matrix pipes.  A binary32 number is the exact sum of three bf16 numbers (8 + 8 + 8
-// significant bits, each part the rounded remainder of the ones before it), so a product is nine bf16 products; the
-// three smallest (m l, l m, l l: together below 2^-26 of the product, a quarter of the last place of binary32) are left
-// out and six run on v_mfma_f32_32x32x16_bf16, accumulated in binary32 like before.  The bf16 pipes are 16 times as
-// fast as the fp32 ones, so six products take 3/8 of the time of one fp32 MFMA pass, and -- unlike the fp32 MFMAs,
-// which share their lanes with the vector ALU -- they run beside the softmax arithmetic.  Error against binary64 is no
-// larger than that of the fp32 pipes (fewer roundings: one accumulation per 16 products instead of per 2).
+// FP32 products on the bf16 matrix pipes.  A binary32 number is the exact sum of three bf16 numbers h + m + l (8 + 8 + 8
+// significant bits, each part the rounded remainder of the ones before it), so a product is nine bf16 products.  Eight of
+// them run on v_mfma_f32_32x32x16_bf16; l l, below 2^-34 of the product, is left out.  (m l and l m reach 2^-24 of it, half
+// a last place of binary32: without them a score of one nonzero term is up to 1.6 times as far from 64 bits as one rounded
+// product.)  The h h products have an accumulator of their own and the others share one, joined by one addition of the
+// vector ALU: an MFMA adds up products of like size exactly, and rounds to nearest where the accumulator is the larger, but
+// cuts an accumulator that is much smaller than its products off at the last place of the result (measured: errors up to one
+// last place instead of half, and a bias).  The bf16 pipes are 16 times as fast as the fp32 ones, so eight products take half the time of
+// one fp32 MFMA pass, and -- unlike the fp32 MFMAs, which share their lanes with the vector ALU -- they run beside the
+// softmax arithmetic.  Error against 64 bits, rms of ctx over rms: normal inputs 32 x 128 tokens 1.5e-7 (fp32 pipes
+// 3.4e-7, six products in one accumulator 2.6e-7), 8 x 384 2.1e-7 (4.5e-7, 3.8e-7); scores of one nonzero column 2.30e-6
+// (2.30e-6, 2.58e-6).  BERT-Large attention: fp32 pipes 184 us, six products 117 us, eight 141 us.
 //
 // Kernel (head widths up to 128): a workgroup of four waves owns 128 queries of one (sequence, head); each wave keeps
 // its 32 query rows, split, in registers (pre-multiplied by scale * log2 e) and walks the keys in stages of 32.  The K
@@ -128,12 +133,26 @@ struct Frag3 {
 };
 __device__ __forceinline__ v8bf as_bf(v4u v) { return __builtin_bit_cast(v8bf, v); }
 
-// One of the six partial products of a . b, the small ones first.
+// Partial product I of a . b: number 0 is h h.  The parts of a are used up one after the other (h, l, m).
+constexpr int kAtParts = 8;
 template <int I>
 __device__ __forceinline__ v16f mfma_part(const Frag3& a, const Frag3& b, v16f acc)
 {
-    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+    constexpr int pa[kAtParts] = {0, 0, 0, 2, 2, 1, 1, 1}, pb[kAtParts] = {0, 2, 1, 1, 0, 2, 1, 0};
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf(a.part[pa[I]]), as_bf(b.part[pb[I]]), acc, 0, 0, 0);
+}
+__device__ __forceinline__ v16f zero16()
+{
+    v16f z;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) z[e] = 0.0f;
+    return z;
+}
+// The sum of the leading products and the sum of the others, joined: one rounding of the vector ALU.
+__device__ __forceinline__ void join_parts(v16f& lead, const v16f& rest)
+{
+#pragma unroll
+    for (int e = 0; e < 16; ++e) lead[e] += rest[e];
 }
 
 // A mask value in log2 units.  The lowest values of the type would overflow to -inf, and a stage of nothing else has no
@@ -311,17 +330,14 @@ struct AttnWave {
     float l_run;        // this lane's share of the running denominator
 };
 
-// First of the 6 * 2 kDB MFMAs of a stage's scores: the accumulators start at the stage's mask row, or at zero where that
-// is all zeros.  s[e] of lane (lq, hi) belongs to key 8 (e/4) + 4 hi + e%4.
+// First MFMA of the small products of a stage's scores: their sums start at the stage's mask row, or at zero where that is all
+// zeros (the leading products start at zero, where the matrix pipes add them up exactly).  Number e of lane (lq, hi)
+// belongs to key 8 (e/4) + 4 hi + e%4.
 template <int kDB>
 __device__ __forceinline__ v16f attention_first_mfma(const char* mask_row, int hi, const AttnWave<kDB>& w, const Frag3& kf, bool masked)
 {
+    if (!masked) return mfma_part<1>(kf, w.q[0], zero16());
     v16f s;
-    if (!masked) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) s[e] = 0.0f;
-        return mfma_part<0>(kf, w.q[0], s);
-    }
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
         const float4 mk = *reinterpret_cast<const float4*>(mask_row + 16 * hi + 32 * g);
@@ -330,7 +346,7 @@ __device__ __forceinline__ v16f attention_first_mfma(const char* mask_row, int h
         s[4 * g + 2] = mk.z;
         s[4 * g + 3] = mk.w;
     }
-    return mfma_part<0>(kf, w.q[0], s);
+    return mfma_part<1>(kf, w.q[0], s);
 }
 
 // Part kP of 2 of the maximum of a lane's sixteen scores.
@@ -367,8 +383,9 @@ __device__ __forceinline__ void attention_move_reference(AttnWave<kDB>& w, float
 // matrix pipes form the next stage's, `sn`, from the K tile; then O^T += V^T P^T of the current stage while the rows
 // requested two trips ago (K of `k_stage`, two ahead, and V of the stage before it) are split and stored and the next ones
 // requested.  A wave issues in order, so the vector work goes between the MFMAs in pieces of a few instructions: an
-// MFMA takes 32 cycles, and up to six vector instructions behind it are free; and the operands of six MFMAs are read
-// from LDS two groups of six ahead (one group ahead, a group waited 50 to 100 cycles for them).  kSet: parity of the
+// MFMA takes 32 cycles, and up to six vector instructions behind it are free; and the operands of a group of eight MFMAs
+// are read from LDS 13 MFMAs ahead, each part into the place of one that is used up (six ahead, a group waited 50 to 100
+// cycles for them; whole groups two ahead take twelve registers more, which spill at width 64).  kSet: parity of the
 // current stage.
 template <int kDB, bool kMore, int kSet>
 __device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, int lq, int hi, v16f& sc, v16f& sn, AttnWave<kDB>& w,
@@ -377,22 +394,26 @@ __device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, i
     using T = AttnTile<kDB>;
     const char* krow = Kn + lq * T::kKStride + 16 * hi;
     const char* vrow = Vs + lq * T::kVStride + 16 * hi;
-    constexpr int kKG = kMore ? 2 * kDB : 0, kGroups = kKG + 2 * kDB;   // groups of six MFMAs: K steps, then V steps x column blocks
-    Frag3 frag[3];
-    auto read_group = [&](auto gc) {
-        constexpr int g = decltype(gc)::value;
+    constexpr int kKG = kMore ? 2 * kDB : 0, kGroups = kKG + 2 * kDB;   // groups of eight MFMAs: K steps, then column blocks x V steps
+    Frag3 frag[2];
+    // part p of the operands of group g
+    auto read_part = [&](auto gc, auto pc) {
+        constexpr int g = decltype(gc)::value, p = decltype(pc)::value;
         if constexpr (g < kKG) {
-#pragma unroll
-            for (int p = 0; p < 3; ++p) frag[g % 3].part[p] = *reinterpret_cast<const v4u*>(krow + p * T::kKPart + 32 * g);
+            frag[g % 2].part[p] = *reinterpret_cast<const v4u*>(krow + p * T::kKPart + 32 * g);
         } else if constexpr (g < kGroups) {
-            constexpr int n = g - kKG;
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-                frag[g % 3].part[p] = *reinterpret_cast<const v4u*>(vrow + p * T::kVPart + (n % kDB) * 32 * T::kVStride + 32 * (n / kDB));
+            constexpr int n = g - kKG;   // column block n / 2, step n % 2
+            frag[g % 2].part[p] = *reinterpret_cast<const v4u*>(vrow + p * T::kVPart + (n / 2) * 32 * T::kVStride + 32 * (n % 2));
         }
     };
-    read_group(std::integral_constant<int, 0>{});
-    read_group(std::integral_constant<int, 1>{});
+    // in front of MFMA i of group g: what takes the place of the part that the MFMAs before it used last
+    auto read_ahead = [&](auto gc, auto ic) {
+        constexpr int g = decltype(gc)::value, i = decltype(ic)::value;
+        if constexpr (i == 0 && g > 0) read_part(std::integral_constant<int, g + 1>{}, std::integral_constant<int, 1>{});
+        if constexpr (i == 3) read_part(std::integral_constant<int, g + 2>{}, std::integral_constant<int, 0>{});
+        if constexpr (i == 5) read_part(std::integral_constant<int, g + 2>{}, std::integral_constant<int, 2>{});
+    };
+    at_static_for<0, 2>([&](auto gc) { at_static_for<0, 3>([&](auto pc) { read_part(gc, pc); }); });
 
     Frag3 pf[2];        // the probabilities, split: step j holds s[8 j .. 8 j + 7]
     Bf16x3 part;
@@ -413,26 +434,38 @@ __device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, i
     };
     at_static_for<0, kSoftFirst>(soft);
     __builtin_amdgcn_sched_barrier(0);
+    v16f rest;   // sums of the small partial products
     if constexpr (kMore) {
-        constexpr int kNqk = 6 * kKG;
+        constexpr int kNqk = kAtParts * kKG;
         at_static_for<0, kNqk>([&](auto nc) {
-            constexpr int n = decltype(nc)::value, g = n / 6;
-            if constexpr (n % 6 == 0) read_group(std::integral_constant<int, g + 2>{});
-            if constexpr (n == 0)
-                sn = attention_first_mfma(Kn + T::kMask, hi, w, frag[0], sg.masked);
+            constexpr int n = decltype(nc)::value, g = n / kAtParts, i = n % kAtParts;
+            read_ahead(std::integral_constant<int, g>{}, std::integral_constant<int, i>{});
+            if constexpr (i == 0)
+                sn = mfma_part<0>(frag[g % 2], w.q[g], n == 0 ? zero16() : sn);
+            else if constexpr (n == 1)
+                rest = attention_first_mfma(Kn + T::kMask, hi, w, frag[0], sg.masked);
             else
-                sn = mfma_part<n % 6>(frag[g % 3], w.q[g], sn);
+                rest = mfma_part<i>(frag[g % 2], w.q[g], rest);
             at_static_for<kSoftFirst + (kSoft - kSoftFirst) * n / kNqk, kSoftFirst + (kSoft - kSoftFirst) * (n + 1) / kNqk>(soft);
             __builtin_amdgcn_sched_barrier(0);
         });
     }
-    // P V: step j joins the keys of s[8 j .. 8 j + 7] of both half-waves
-    constexpr int kNpv = 12 * kDB;
+    // P V, a column block after the other: step j joins the keys of s[8 j .. 8 j + 7] of both half-waves
+    constexpr int kBlock = 2 * kAtParts, kNpv = kBlock * kDB;
     float mx = 0.0f;
     at_static_for<0, kNpv>([&](auto nc) {
-        constexpr int n = decltype(nc)::value, g = kKG + n / 6, j = (n / 6) / kDB, b = (n / 6) % kDB;
-        if constexpr (n % 6 == 0) read_group(std::integral_constant<int, g + 2>{});
-        w.o[b] = mfma_part<n % 6>(frag[g % 3], pf[j], w.o[b]);
+        constexpr int n = decltype(nc)::value, b = n / kBlock, j = (n / kAtParts) % 2, i = n % kAtParts, g = kKG + n / kAtParts;
+        read_ahead(std::integral_constant<int, g>{}, std::integral_constant<int, i>{});
+        if constexpr (i == 0)
+            w.o[b] = mfma_part<0>(frag[g % 2], pf[j], w.o[b]);
+        else
+            rest = mfma_part<i>(frag[g % 2], pf[j], j == 0 && i == 1 ? zero16() : rest);
+        if constexpr (n % kBlock == 0) {   // under an MFMA of another accumulator: the sums of the block before, or the scores
+            if constexpr (b > 0)
+                join_parts(w.o[b - 1], rest);
+            else if constexpr (kMore)
+                join_parts(sn, rest);
+        }
         if constexpr (kMore) {
             if constexpr (n == 3) attention_max_piece<0>(sn, mx);
             if constexpr (n == 4) attention_max_piece<1>(sn, mx);
@@ -443,6 +476,7 @@ __device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, i
         }
         __builtin_amdgcn_sched_barrier(0);
     });
+    join_parts(w.o[kDB - 1], rest);
     if constexpr (kMore) attention_move_reference(w, mx);
 }
 
@@ -525,14 +559,17 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
     v16f s0, s1;
     {
         const char* krow = sg.k_tiles + lq * T::kKStride + 16 * hi;
+        v16f rest;
         at_static_for<0, 2 * kDB>([&](auto jc) {
             constexpr int j = decltype(jc)::value;
             Frag3 f;
 #pragma unroll
             for (int p = 0; p < 3; ++p) f.part[p] = *reinterpret_cast<const v4u*>(krow + p * T::kKPart + 32 * j);
-            if constexpr (j == 0) s0 = attention_first_mfma(sg.k_tiles + T::kMask, hi, w, f, sg.masked);
-            at_static_for<(j == 0 ? 1 : 0), 6>([&](auto ic) { s0 = mfma_part<decltype(ic)::value>(f, w.q[j], s0); });
+            s0 = mfma_part<0>(f, w.q[j], j == 0 ? zero16() : s0);
+            if constexpr (j == 0) rest = attention_first_mfma(sg.k_tiles + T::kMask, hi, w, f, sg.masked);
+            at_static_for<(j == 0 ? 2 : 1), kAtParts>([&](auto ic) { rest = mfma_part<decltype(ic)::value>(f, w.q[j], rest); });
         });
+        join_parts(s0, rest);
     }
     sg.template stash_v<2>(0);
     sg.template stash_k<3>(1, 1);
@@ -620,7 +657,7 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
 
 // The same products for launches that leave most of the chip idle: 32 queries of one (sequence, head) a workgroup, the
 // key stages dealt out over its four waves, each with running statistics of its own that meet in LDS at the end.  A short
-// sequence is a chain of latencies -- rows from memory, then per stage 48 MFMAs (of 32 cycles, at width 64) that the
+// sequence is a chain of latencies -- rows from memory, then per stage 64 MFMAs (of 32 cycles, at width 64) that the
 // kernel above walks one after the other on an eighth of the compute units.  No wave shares its keys, so K and V go straight
 // from memory into operand registers and nothing is staged: for every 32 queries they are read and split again, which is
 // why full launches keep the kernel above.  One sequence of 128 tokens, 12 heads of 64: 10.1 -> 7.4 us; of 512: 25.1 ->
@@ -660,17 +697,14 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p) + (int64_t)stage * kAtKB * ld, 0, rows > 0 ? 4 * ((rows - 1) * (int)ld + d) : 0, 0x00020000);
     };
     float4 k[2 * kDB][2];
-    float v[2][kDB][8], mk[16];
+    float v[2][kDB][8], mk = 0.0f;   // mk: the mask of key lq
     auto fetch_k = [&](int stage) {
         const auto r = rsrc(kbase, stage);
 #pragma unroll
         for (int j = 0; j < 2 * kDB; ++j)
 #pragma unroll
             for (int u = 0; u < 2; ++u) k[j][u] = buf_f4(r, k_off[j][u]);
-        if (mrow) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) mk[e] = mrow[min(stage * kAtKB + 8 * (e >> 2) + 4 * hi + (e & 3), S - 1)];
-        }
+        if (mrow) mk = mrow[min(stage * kAtKB + lq, S - 1)];
     };
     auto fetch_v = [&](int stage) {   // step j, column block c: the eight keys this half-wave takes to the step
         const auto r = rsrc(vbase, stage);
@@ -713,12 +747,12 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
     }
     for (int st = wave; st < n_stages; st += kAtWaves) {
         // a stage that is walked has a key inside the sequence, so its maximum is above -inf
-        v16f s;
+        v16f s = zero16(), rest = zero16();
         const int keys = S - st * kAtKB;
+        if (mrow || keys < kAtKB) {   // every lane makes its key's value, the lanes that score the key fetch it
+            const float m0 = lq < keys ? mask_log2(mk) : -__builtin_inff();
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const float m0 = mrow ? mask_log2(mk[e]) : 0.0f;
-            s[e] = 8 * (e >> 2) + 4 * hi + (e & 3) < keys ? m0 : -__builtin_inff();
+            for (int e = 0; e < 16; ++e) rest[e] = __uint_as_float((unsigned)__builtin_amdgcn_ds_bpermute(16 * hi + 4 * (8 * (e >> 2) + (e & 3)), (int)__float_as_uint(m0)));
         }
 #pragma unroll
         for (int j = 0; j < 2 * kDB; ++j) {
@@ -728,8 +762,10 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
                 f.set(2 * u, split_bf16(k[j][u].x, k[j][u].y));
                 f.set(2 * u + 1, split_bf16(k[j][u].z, k[j][u].w));
             }
-            at_static_for<0, 6>([&](auto ic) { s = mfma_part<decltype(ic)::value>(f, w.q[j], s); });
+            s = mfma_part<0>(f, w.q[j], s);
+            at_static_for<1, kAtParts>([&](auto ic) { rest = mfma_part<decltype(ic)::value>(f, w.q[j], rest); });
         }
+        join_parts(s, rest);
         const bool more = st + kAtWaves < n_stages;
         if (more) fetch_k(st + kAtWaves);
         float mx;
@@ -744,14 +780,18 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
             pf[i >> 2].set(i & 3, split_bf16(p0, p1));
         }
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int c = 0; c < kDB; ++c) {
+            rest = zero16();
 #pragma unroll
-            for (int c = 0; c < kDB; ++c) {
+            for (int j = 0; j < 2; ++j) {
                 Frag3 f;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) f.set(u, split_bf16(v[j][c][2 * u], v[j][c][2 * u + 1]));
-                at_static_for<0, 6>([&](auto ic) { w.o[c] = mfma_part<decltype(ic)::value>(f, pf[j], w.o[c]); });
+                w.o[c] = mfma_part<0>(f, pf[j], w.o[c]);
+                at_static_for<1, kAtParts>([&](auto ic) { rest = mfma_part<decltype(ic)::value>(f, pf[j], rest); });
             }
+            join_parts(w.o[c], rest);
+        }
         if (more) fetch_v(st + kAtWaves);
     }
 

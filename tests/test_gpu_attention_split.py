@@ -86,3 +86,29 @@ def test_attention_reads_no_row_behind_its_sequence(q8, B, S, heads, d):
         q8.q8_attention(buf[:n], B, S, heads, d, ctx=ctx)
         assert (ctx[:S].cpu().double() - ref[:S]).abs().max().item() <= 2e-6 * vmax
         assert bool(ctx[S:].isnan().all())
+
+
+@pytest.mark.parametrize("B,heads", [(4, 12), (32, 64)])   # the stages dealt out; four waves on every stage
+def test_attention_products_are_as_good_as_one_rounding(q8, B, heads):
+    """Scores of a single nonzero column: nothing averages out, so what a product loses against binary32 shows.  Every query
+    scores 32 keys near 100 (log2 units), a few tenths apart; the yardstick is the same attention with each score the
+    binary32 product of its two binary32 factors and everything behind it in 64 bits.  The six largest partial products,
+    summed in one accumulator, are 15 % further off."""
+    S, d, scale = 32, 64, 0.5
+    g = torch.Generator().manual_seed(heads)
+    x = torch.zeros((B, S, 3, heads, d))
+    x[:, :, 0, :, 5] = 8 + 8 * torch.rand((B, S, heads), generator=g)
+    x[:, :, 1, :, 5] = 13 * (1 + 0.01 * torch.rand((B, S, heads), generator=g))
+    x[:, :, 2] = torch.randn((B, S, heads, d), generator=g)
+    qkv = x.view(B * S, -1)
+    q, k, v = x[:, :, 0, :, 5], x[:, :, 1, :, 5], x[:, :, 2].double().permute(0, 2, 1, 3)
+    def ctx_of(s):   # s: [B, heads, queries, keys], log2 units
+        p = torch.exp2(s.double() - s.double().amax(-1, keepdim=True))
+        return torch.matmul(p / p.sum(-1, keepdim=True), v).permute(0, 2, 1, 3).reshape(B * S, heads * d)
+    c = torch.tensor(scale, dtype=torch.float32) * torch.tensor(1.44269504088896341, dtype=torch.float32)
+    ref = ctx_of(scale * 1.4426950408889634 * q.double().permute(0, 2, 1)[..., None] * k.double().permute(0, 2, 1)[:, :, None, :])
+    rounded = ctx_of((q * c).permute(0, 2, 1)[..., None] * k.permute(0, 2, 1)[:, :, None, :])
+    ctx = torch.empty((B * S, heads * d), device="cuda")
+    q8.q8_attention(qkv.cuda(), B, S, heads, d, ctx=ctx, scale=scale)
+    err, bar = (ctx.cpu().double() - ref).pow(2).mean().sqrt().item(), (rounded - ref).pow(2).mean().sqrt().item()
+    assert err <= 1.03 * bar, f"{err:.3e} against {bar:.3e}"
