@@ -19,6 +19,12 @@
 // 3.4e-7, six products in one accumulator 2.6e-7), 8 x 384 2.1e-7 (4.5e-7, 3.8e-7); scores of one nonzero column 2.30e-6
 // (2.30e-6, 2.58e-6).  BERT-Large attention: fp32 pipes 184 us, six products 117 us, eight 141 us.
 //
+// Range.  The sum is exact, and the products lose nothing, while no number is near the ends of the type: from 3.3953e38 on
+// h rounds to infinity, and the lower parts of numbers below 2^-110 fall under the smallest bf16.  The kernels keep the largest
+// magnitude of the rows they split (a vector instruction for every two numbers) and look at their results: rows that saw a
+// number above 2^96, an infinity or a NaN, or whose results are not finite or so small that lost parts could matter in them,
+// are formed again in plain binary32 (attention_rows_plain).  Slow, but values that occur in earnest never lead there.
+//
 // Kernel (head widths up to 128): a workgroup of four waves owns 128 queries of one (sequence, head); each wave keeps
 // its 32 query rows, split, in registers (pre-multiplied by scale * log2 e) and walks the keys in stages of 32.  The K
 // and V rows of a stage are split once per workgroup on their way into LDS, V transposed.  Scores are formed
@@ -85,6 +91,9 @@ __device__ __forceinline__ void at_static_for(F&& f)
     }
 }
 
+// The maximum that the three-operand instruction takes directly (the other one first quiets each operand).  A NaN stays one.
+__device__ __forceinline__ float at_max(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+
 // Two binary32 numbers as three packed pairs of bf16 numbers whose sums they are, exactly: each part is the
 // nearest bf16 of what the parts before it leave, and the differences are exact.  In two halves, so that the pieces that
 // go between two MFMAs stay small.  (v_dot2_f32_bf16 would unpack and subtract in one instruction, 7 for the pair
@@ -106,6 +115,12 @@ struct Bf16x3 {
         ra = a - __uint_as_float(h << 16);
         rb = b - __uint_as_float(h & 0xffff0000u);
     }
+    __device__ __forceinline__ void first(float a, float b, float& largest)
+    {
+        largest = at_max(largest, at_max(__builtin_fabsf(a), __builtin_fabsf(b)));
+        asm volatile("" : "+v"(largest));   // here, and not gathered behind the trip
+        first(a, b);
+    }
     __device__ __forceinline__ void second()
     {
         m = pack_bf16(ra, rb);
@@ -117,6 +132,13 @@ __device__ __forceinline__ Bf16x3 split_bf16(float a, float b)
 {
     Bf16x3 s;
     s.first(a, b);
+    s.second();
+    return s;
+}
+__device__ __forceinline__ Bf16x3 split_bf16(float a, float b, float& largest)
+{
+    Bf16x3 s;
+    s.first(a, b, largest);
     s.second();
     return s;
 }
@@ -197,12 +219,14 @@ struct AttnStager {
     float4 k[4][kItems][2];
     float v[3][kItems][8];
     float m[4];
+    float largest;                // magnitude of the numbers split so far
     bool masked;                  // the mask row of the K stage stashed last is not all zeros (wave-uniform)
 
     __device__ __forceinline__ void init(int t)
     {
         tid = t;
         m[0] = m[1] = m[2] = m[3] = 0.0f;
+        largest = 0.0f;
         const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
 #pragma unroll
         for (int i = 0; i < kItems; ++i) {
@@ -264,11 +288,11 @@ struct AttnStager {
         if constexpr (u < 4) {
             if constexpr (Q % 2 == 0) {
                 if constexpr (kIsV)
-                    part.first(v[kSet][kItem][2 * u], v[kSet][kItem][2 * u + 1]);
+                    part.first(v[kSet][kItem][2 * u], v[kSet][kItem][2 * u + 1], largest);
                 else if constexpr ((u & 1) == 0)
-                    part.first(k[kSet][kItem][u >> 1].x, k[kSet][kItem][u >> 1].y);
+                    part.first(k[kSet][kItem][u >> 1].x, k[kSet][kItem][u >> 1].y, largest);
                 else
-                    part.first(k[kSet][kItem][u >> 1].z, k[kSet][kItem][u >> 1].w);
+                    part.first(k[kSet][kItem][u >> 1].z, k[kSet][kItem][u >> 1].w, largest);
             } else {
                 part.second();
                 f.set(u, part);
@@ -317,9 +341,6 @@ struct AttnStager {
         at_static_for<0, kPieces>([&](auto pc) { piece<kSet, decltype(pc)::value>(k_stage); });
     }
 };
-
-// The maximum that the three-operand instruction takes directly (the other one first quiets each operand).
-__device__ __forceinline__ float at_max(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 
 // Running state of a wave's 32 queries (lane (lq, hi) and lane (lq, 1 - hi) belong to the same query).
 template <int kDB>
@@ -480,13 +501,96 @@ __device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, i
     if constexpr (kMore) attention_move_reference(w, mx);
 }
 
+// Magnitudes as bit patterns, which order like the numbers (a NaN above all).
+__device__ __forceinline__ unsigned magnitude_bits(float x) { return __float_as_uint(x) & 0x7fffffffu; }
+// The same minus one, doubled, for the smallest magnitude of numbers that are not zero: zero becomes the largest of all.
+__device__ __forceinline__ unsigned nonzero_bits(float x) { return (__float_as_uint(x) << 1) - 1u; }
+
+__device__ __forceinline__ void attention_ends(float4 v, unsigned& smallest, unsigned& amax)
+{
+    smallest = min(smallest, min(min(nonzero_bits(v.x), nonzero_bits(v.y)), min(nonzero_bits(v.z), nonzero_bits(v.w))));
+    amax = max(amax, max(max(magnitude_bits(v.x), magnitude_bits(v.y)), max(magnitude_bits(v.z), magnitude_bits(v.w))));
+}
+
+// Four neighbouring results: ctx, or its codes under the stored scale of the next FC layer (Eq. 1), or both.
+__device__ __forceinline__ void attention_store(const AttnArgs& a, int64_t off, float4 v, float qs)
+{
+    if (a.ctx) *reinterpret_cast<float4*>(a.ctx + off) = v;
+    if (a.q_out)
+        a.q_out[off >> 2] = ((unsigned)quantize_code(v.x, qs) & 0xffu) | (((unsigned)quantize_code(v.y, qs) & 0xffu) << 8) |
+                            (((unsigned)quantize_code(v.z, qs) & 0xffu) << 16) | ((unsigned)quantize_code(v.w, qs) << 24);
+}
+
+// Whether results come out of the split products as they would of binary32 ones.  `largest`: bits of the largest magnitude
+// that went into them; `smallest` and `amax`: of the smallest (nonzero_bits) and the largest result.  What lower parts under the smallest bf16 can do to
+// a result is 2^-134 by a V row of weight 1 and, by the parts of the weights, 2^-134 of `largest` for each of up to 2^20 keys;
+// both stay below 2^-24 of a result above this bound.
+__device__ __forceinline__ bool attention_in_range(unsigned largest, unsigned smallest, unsigned amax)
+{
+    const float f = __uint_as_float(largest);
+    return f <= 0x1p96f && amax < 0x7f800000u && smallest >= nonzero_bits(__builtin_fmaxf(0x1p-100f, f * 0x1p-90f));
+}
+
+// Rows q0 .. q0 + n - 1 of the context by one wave in plain binary32: 64 keys at a time, one per lane, then the columns of V
+// (lane, lane + 64).  Returns this lane's abs-max.
+__device__ __forceinline__ float attention_rows_plain(const AttnArgs& a, int64_t b, int h, int64_t q0, int n)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t HD = (int64_t)a.heads * a.d, ld = 3 * HD;
+    const float* base = a.qkv + b * a.S * ld + (int64_t)h * a.d;
+    const float qs = a.q_out ? a.q_scale[0] : 0.0f;
+    float amax = 0.0f;
+    for (int64_t q = q0; q < q0 + n && q < a.S; ++q) {
+        float m = -__builtin_inff(), l = 0.0f, acc[2] = {0.0f, 0.0f};
+        for (int64_t j0 = 0; j0 < a.S; j0 += 64) {
+            const int64_t j = j0 + lane;
+            float s = -__builtin_inff();
+            if (j < a.S) {
+                const float *qp = base + q * ld, *kp = base + j * ld + HD;
+                s = a.mask ? mask_log2(a.mask[b * a.S + j]) : 0.0f;
+                for (int k = 0; k < a.d; ++k) s = __builtin_fmaf(qp[k] * a.c, kp[k], s);
+            }
+            float m_up = s;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) m_up = __builtin_fmaxf(m_up, __shfl_xor(m_up, off, 64));
+            m_up = __builtin_fmaxf(m, m_up);
+            const float alpha = __builtin_amdgcn_exp2f(m - m_up), p = j < a.S ? __builtin_amdgcn_exp2f(s - m_up) : 0.0f;
+            m = m_up;
+            l = l * alpha + p;
+            acc[0] *= alpha;
+            acc[1] *= alpha;
+            const int keys = (int)min((int64_t)64, a.S - j0);
+            for (int t = 0; t < keys; ++t) {
+                const float pt = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(p), t));
+                const float* vp = base + (j0 + t) * ld + 2 * HD;
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    if (lane + 64 * i < a.d) acc[i] = __builtin_fmaf(pt, vp[lane + 64 * i], acc[i]);
+            }
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
+        const float inv = 1.0f / l;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (lane + 64 * i < a.d) {
+                const float v = acc[i] * inv;
+                const int64_t off = (b * a.S + q) * HD + (int64_t)h * a.d + lane + 64 * i;
+                if (a.ctx) a.ctx[off] = v;
+                if (a.q_out) reinterpret_cast<int8_t*>(a.q_out)[off] = (int8_t)quantize_code(v, qs);
+                amax = __builtin_fmaxf(amax, __builtin_fabsf(v));
+            }
+    }
+    return amax;
+}
+
 template <int kDB>
 __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_kernel(AttnArgs a)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using T = AttnTile<kDB>;
     extern __shared__ __align__(16) char lds[];   // K tiles (+ mask rows) of two stages, then V tiles of two stages
-    __shared__ unsigned wave_amax[kAtWaves];
+    __shared__ uint4 wave_ends[kAtWaves];   // bits of the largest input, the smallest and the largest result of each wave
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, lq = lane & 31, hi = lane >> 5;
     // Workgroups of one (sequence, head) are neighbours in the logical order; each XCD takes a contiguous
@@ -542,10 +646,10 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
         for (int u = 0; u < 2; ++u) {
             const float c = (16 * j + 8 * hi + 4 * u < a.d) ? a.c : 0.0f;
             Bf16x3 part;
-            part.first(qraw[j][u].x * c, qraw[j][u].y * c);
+            part.first(qraw[j][u].x * c, qraw[j][u].y * c, sg.largest);
             part.second();
             w.q[j].set(2 * u, part);
-            part.first(qraw[j][u].z * c, qraw[j][u].w * c);
+            part.first(qraw[j][u].z * c, qraw[j][u].w * c, sg.largest);
             part.second();
             w.q[j].set(2 * u + 1, part);
         }
@@ -615,38 +719,47 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
     const float inv = 1.0f / (__uint_as_float(l2[0]) + __uint_as_float(l2[1]));
     const bool live = q0 + lq < S;
     const float qs = a.q_out ? a.q_scale[0] : 0.0f;
-    float amax = 0.0f;
     const int64_t out_off = (b * S + q0 + lq) * HD + (int64_t)h * a.d + 4 * hi;
+    // Lanes beyond the sequence or the width repeat results of the last query or column: they change neither end.
+    unsigned smallest = ~0u, amax = 0u;
 #pragma unroll
     for (int blk = 0; blk < kDB; ++blk)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            float4 v;
-            v.x = w.o[blk][4 * g + 0] * inv;
-            v.y = w.o[blk][4 * g + 1] * inv;
-            v.z = w.o[blk][4 * g + 2] * inv;
-            v.w = w.o[blk][4 * g + 3] * inv;
-            if (live && 32 * blk + 8 * g + 4 * hi < a.d) {
-                const int64_t off = out_off + 32 * blk + 8 * g;
-                if (a.ctx) *reinterpret_cast<float4*>(a.ctx + off) = v;
-                if (a.q_out)  // Eq. 1 with the stored scale of the next FC layer, four codes per lane
-                    a.q_out[off >> 2] = ((unsigned)quantize_code(v.x, qs) & 0xffu) | (((unsigned)quantize_code(v.y, qs) & 0xffu) << 8) |
-                                        (((unsigned)quantize_code(v.z, qs) & 0xffu) << 16) | ((unsigned)quantize_code(v.w, qs) << 24);
-                amax = __builtin_fmaxf(amax, __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(v.x), __builtin_fabsf(v.y)),
-                                                            __builtin_fmaxf(__builtin_fabsf(v.z), __builtin_fabsf(v.w))));
-            }
+            const float4 v = make_float4(w.o[blk][4 * g + 0] * inv, w.o[blk][4 * g + 1] * inv, w.o[blk][4 * g + 2] * inv, w.o[blk][4 * g + 3] * inv);
+            if (live && 32 * blk + 8 * g + 4 * hi < a.d) attention_store(a, out_off + 32 * blk + 8 * g, v, qs);
+            attention_ends(v, smallest, amax);
         }
-    if (a.slots) {
-        unsigned m = wave_max_u32(__float_as_uint(amax));  // non-negative floats order like their bit patterns
-        if (lane == 0) wave_amax[wave] = m;
-        __syncthreads();
-        if (tid == 0) {
+    if (!wave_live) {   // 0 / 0
+        smallest = ~0u;
+        amax = 0u;
+    }
+    unsigned largest = wave_max_u32(__float_as_uint(sg.largest));
+    smallest = ~wave_max_u32(~smallest);
+    amax = wave_max_u32(amax);
+    if (lane == 0) wave_ends[wave] = make_uint4(largest, smallest, amax, 0u);
+    __syncthreads();
 #pragma unroll
-            for (int w2 = 1; w2 < kAtWaves; ++w2) m = max(m, wave_amax[w2]);
+    for (int i = 0; i < kAtWaves; ++i) {
+        largest = max(largest, wave_ends[i].x);
+        smallest = min(smallest, wave_ends[i].y);
+        amax = max(amax, wave_ends[i].z);
+    }
+    if (__builtin_expect(!attention_in_range(largest, smallest, amax), 0)) {
+        __threadfence();   // behind the stores above
+        amax = wave_max_u32(magnitude_bits(attention_rows_plain(a, b, h, q0, kAtQW)));
+        __syncthreads();   // wave_ends has been read
+        if (lane == 0) wave_ends[wave].z = amax;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kAtWaves; ++i) amax = max(amax, wave_ends[i].z);
+    }
+    if (a.slots) {
+        if (tid == 0) {
             if (a.slots_atomic) {
-                if (m) atomicMax(a.slots + (blockIdx.x % kAtSlots), m);
+                if (amax) atomicMax(a.slots + (blockIdx.x % kAtSlots), amax);
             } else {
-                a.slots[blockIdx.x] = m;
+                a.slots[blockIdx.x] = amax;
             }
         }
         if (!a.slots_atomic && blockIdx.x == 0)  // slots no workgroup owns
@@ -669,7 +782,7 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
     constexpr int kRow = 32 * kDB + 4;   // floats of a query's row of partial sums; the padding spreads rows over the banks
     __shared__ __attribute__((aligned(16))) float part_o[kAtWaves * kAtQW * kRow];
     __shared__ float part_m[kAtWaves * kAtQW], part_l[kAtWaves * kAtQW];
-    __shared__ unsigned wave_amax[kAtWaves];
+    __shared__ uint4 wave_ends[kAtWaves];   // bits of the largest input, the smallest and the largest result of each wave
 
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, lq = lane & 31, hi = lane >> 5;
     int wid = blockIdx.x;
@@ -727,6 +840,7 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
     for (int c = 0; c < kDB; ++c)
 #pragma unroll
         for (int e = 0; e < 16; ++e) w.o[c][e] = 0.0f;
+    float largest = 0.0f;   // magnitude of the numbers split so far
     if (wave < n_stages) {
         float4 qraw[2 * kDB][2];
         const float* qp = base + (int64_t)min(q0 + lq, S - 1) * ld;
@@ -741,8 +855,8 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 const float c = (16 * j + 8 * hi + 4 * u < d) ? a.c : 0.0f;   // columns beyond d are zeros here, whatever K holds
-                w.q[j].set(2 * u, split_bf16(qraw[j][u].x * c, qraw[j][u].y * c));
-                w.q[j].set(2 * u + 1, split_bf16(qraw[j][u].z * c, qraw[j][u].w * c));
+                w.q[j].set(2 * u, split_bf16(qraw[j][u].x * c, qraw[j][u].y * c, largest));
+                w.q[j].set(2 * u + 1, split_bf16(qraw[j][u].z * c, qraw[j][u].w * c, largest));
             }
     }
     for (int st = wave; st < n_stages; st += kAtWaves) {
@@ -759,8 +873,8 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
             Frag3 f;
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                f.set(2 * u, split_bf16(k[j][u].x, k[j][u].y));
-                f.set(2 * u + 1, split_bf16(k[j][u].z, k[j][u].w));
+                f.set(2 * u, split_bf16(k[j][u].x, k[j][u].y, largest));
+                f.set(2 * u + 1, split_bf16(k[j][u].z, k[j][u].w, largest));
             }
             s = mfma_part<0>(f, w.q[j], s);
             at_static_for<1, kAtParts>([&](auto ic) { rest = mfma_part<decltype(ic)::value>(f, w.q[j], rest); });
@@ -786,7 +900,7 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
             for (int j = 0; j < 2; ++j) {
                 Frag3 f;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) f.set(u, split_bf16(v[j][c][2 * u], v[j][c][2 * u + 1]));
+                for (int u = 0; u < 4; ++u) f.set(u, split_bf16(v[j][c][2 * u], v[j][c][2 * u + 1], largest));
                 w.o[c] = mfma_part<0>(f, pf[j], w.o[c]);
                 at_static_for<1, kAtParts>([&](auto ic) { rest = mfma_part<decltype(ic)::value>(f, pf[j], rest); });
             }
@@ -809,56 +923,56 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
             for (int g = 0; g < 4; ++g)
                 *reinterpret_cast<float4*>(row + 32 * c + 8 * g) = make_float4(w.o[c][4 * g], w.o[c][4 * g + 1], w.o[c][4 * g + 2], w.o[c][4 * g + 3]);
     }
+    const unsigned large_bits = wave_max_u32(__float_as_uint(largest));
+    if (lane == 0) wave_ends[wave].x = large_bits;
     __syncthreads();
     const int q = tid >> 3;   // eight threads a query, four columns of every 32 each
     float m_all = part_m[q];
 #pragma unroll
     for (int i = 1; i < kAtWaves; ++i) m_all = at_max(m_all, part_m[i * kAtQW + q]);
     float f[kAtWaves], den = 0.0f;
+    unsigned all_large = 0u;
 #pragma unroll
     for (int i = 0; i < kAtWaves; ++i) {
         f[i] = __builtin_amdgcn_exp2f(part_m[i * kAtQW + q] - m_all);
         den += f[i] * part_l[i * kAtQW + q];
+        all_large = max(all_large, wave_ends[i].x);
     }
     const float inv = 1.0f / den;
     const float qs = a.q_out ? a.q_scale[0] : 0.0f;
-    float amax = 0.0f;
-    if (q0 + q < S) {
-        const int64_t out_off = (b * S + q0 + q) * HD + (int64_t)h * d;
+    const int64_t out_off = (b * S + q0 + q) * HD + (int64_t)h * d;
+    unsigned smallest = ~0u, amax = 0u;   // lanes beyond the sequence or the width repeat other results, as above
 #pragma unroll
-        for (int c = 0; c < kDB; ++c) {
-            const int col = 32 * c + 4 * (tid & 7);
-            if (col < d) {
-                float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int c = 0; c < kDB; ++c) {
+        const int col = 32 * c + 4 * (tid & 7);
+        float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
-                for (int i = 0; i < kAtWaves; ++i) {
-                    const float4 p = *reinterpret_cast<const float4*>(part_o + (i * kAtQW + q) * kRow + col);
-                    o.x += f[i] * p.x;
-                    o.y += f[i] * p.y;
-                    o.z += f[i] * p.z;
-                    o.w += f[i] * p.w;
-                }
-                o.x *= inv;
-                o.y *= inv;
-                o.z *= inv;
-                o.w *= inv;
-                if (a.ctx) *reinterpret_cast<float4*>(a.ctx + out_off + col) = o;
-                if (a.q_out)
-                    a.q_out[(out_off + col) >> 2] = ((unsigned)quantize_code(o.x, qs) & 0xffu) | (((unsigned)quantize_code(o.y, qs) & 0xffu) << 8) |
-                                                    (((unsigned)quantize_code(o.z, qs) & 0xffu) << 16) | ((unsigned)quantize_code(o.w, qs) << 24);
-                amax = __builtin_fmaxf(amax, __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(o.x), __builtin_fabsf(o.y)),
-                                                            __builtin_fmaxf(__builtin_fabsf(o.z), __builtin_fabsf(o.w))));
-            }
+        for (int i = 0; i < kAtWaves; ++i) {
+            const float4 p = *reinterpret_cast<const float4*>(part_o + (i * kAtQW + q) * kRow + col);
+            o.x += f[i] * p.x;
+            o.y += f[i] * p.y;
+            o.z += f[i] * p.z;
+            o.w += f[i] * p.w;
         }
+        o.x *= inv;
+        o.y *= inv;
+        o.z *= inv;
+        o.w *= inv;
+        if (q0 + q < S && col < d) attention_store(a, out_off + col, o, qs);
+        attention_ends(o, smallest, amax);
+    }
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!attention_in_range(all_large, smallest, amax)) != 0, 0)) {
+        __threadfence();   // behind the stores above
+        amax = magnitude_bits(attention_rows_plain(a, b, h, q0 + 8 * wave, 8));   // a wave ends up with eight queries
     }
     if (a.slots) {   // never more workgroups than slots here
-        unsigned m = wave_max_u32(__float_as_uint(amax));
-        if (lane == 0) wave_amax[wave] = m;
+        amax = wave_max_u32(amax);
+        if (lane == 0) wave_ends[wave].z = amax;
         __syncthreads();
         if (tid == 0) {
 #pragma unroll
-            for (int i = 1; i < kAtWaves; ++i) m = max(m, wave_amax[i]);
-            a.slots[blockIdx.x] = m;
+            for (int i = 1; i < kAtWaves; ++i) amax = max(amax, wave_ends[i].z);
+            a.slots[blockIdx.x] = amax;
         }
         if (blockIdx.x == 0)
             for (int i = gridDim.x + tid; i < kAtSlots; i += kAtThreads) a.slots[i] = 0u;

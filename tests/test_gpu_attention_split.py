@@ -112,3 +112,81 @@ def test_attention_products_are_as_good_as_one_rounding(q8, B, heads):
     q8.q8_attention(qkv.cuda(), B, S, heads, d, ctx=ctx, scale=scale)
     err, bar = (ctx.cpu().double() - ref).pow(2).mean().sqrt().item(), (rounded - ref).pow(2).mean().sqrt().item()
     assert err <= 1.03 * bar, f"{err:.3e} against {bar:.3e}"
+
+
+# few heads: the stages dealt out; many: four waves on every stage
+RANGE_SHAPES = [(2, 70, 2, 64), (1, 45, 2, 128), (2, 70, 50, 64), (3, 45, 60, 32), (1, 130, 40, 128)]
+
+
+@pytest.mark.parametrize("B,S,heads,d", RANGE_SHAPES)
+def test_attention_over_the_whole_finite_range(q8, B, S, heads, d):
+    """Numbers at both ends of the type, where a sum of three bf16 numbers does not hold 24 bits: V columns of 1e-36 and below,
+    a V row and a K row next to the largest float, tiny K against huge Q.  Bar: 2e-6 of the column's largest |V|, as
+    everywhere, and one unit of the subnormal numbers for every key."""
+    g = torch.Generator().manual_seed(S + heads)
+    HD = heads * d
+    x = torch.randn((B, S, 3, heads, d), generator=g)
+    mask = torch.zeros((B, S))
+
+    def check(name, x, mask):
+        qkv = x.reshape(B * S, 3 * HD).cuda()
+        ctx, slots = torch.empty((B * S, HD), device="cuda"), torch.full((q8.AMAX_SLOTS,), 9e9, device="cuda")
+        q8.q8_attention(qkv, B, S, heads, d, ctx=ctx, mask=mask.cuda(), amax_slots=slots)
+        ref = reference(qkv, B, S, heads, d, mask).view(B, S, heads, d)
+        vmax = x[:, :, 2].double().abs()
+        if mask.min() < 0:
+            vmax = vmax * (mask.view(B, S, 1, 1) == 0)
+        err = (ctx.cpu().double().view(B, S, heads, d) - ref).abs()
+        worst = (err - S * 2.0 ** -149) / vmax.amax(1, keepdim=True)
+        assert worst.max().item() <= 2e-6, (name, worst.max().item())
+        assert slots.max().item() == ctx.abs().max().item(), name
+        # stored scale: the codes of the same results
+        scale = torch.tensor([40.0], device="cuda")
+        codes, want = torch.empty(B * S * HD, dtype=torch.int8, device="cuda"), torch.empty(B * S * HD, dtype=torch.int8, device="cuda")
+        q8.q8_attention(qkv, B, S, heads, d, mask=mask.cuda(), q_scale=scale, q_out=codes)
+        q8.q8_quantize(ctx.reshape(-1), scale, want)
+        assert torch.equal(codes, want), name
+
+    y = x.clone()
+    y[:, :, 2, :, 1::3] *= 1e-36
+    y[:, :, 2, :, 2::3] *= 1e-30
+    check("small V columns", y, mask)
+    y = x.clone()
+    y[:, :, 2] *= 3e-37
+    check("small V", y, mask)
+    y, m = x.clone(), torch.full((B, S), -10000.0)
+    m[:, S // 2] = 0.0
+    y[:, S // 2, 2] = 3.4e38 * torch.sign(y[:, S // 2, 2])
+    check("one key, V next to the largest float", y, m)
+    y = x.clone()
+    y[:, :, 0, :, 0], y[:, :, 1, :, 0] = 1e-38 * y[:, :, 0, :, 0], 3.4e38 * torch.sign(y[:, :, 1, :, 0])
+    check("K next to the largest float, Q small", y, mask)
+    y = x.clone()
+    y[:, :, 0, :, 0] *= 1e36
+    y[:, :, 1, :, 0] *= 1e-36
+    check("Q huge, K small", y, mask)
+
+
+@pytest.mark.parametrize("B,S,heads,d", RANGE_SHAPES)
+def test_attention_of_infinities(q8, B, S, heads, d):
+    """An infinity in V makes its column infinite and no other; a key whose score is -inf has no weight."""
+    g = torch.Generator().manual_seed(S + heads)
+    HD = heads * d
+    x = torch.randn((B, S, 3, heads, d), generator=g)
+    x[:, :, 0, :, 0] = x[:, :, 0, :, 0].abs() + 0.1
+    y = x.clone()
+    y[0, 3, 2, :, 2] = float("inf")
+    ctx = torch.empty((B * S, HD), device="cuda")
+    q8.q8_attention(y.reshape(B * S, -1).cuda(), B, S, heads, d, ctx=ctx)
+    got = ctx.cpu().double().view(B, S, heads, d)
+    ref = reference(x.reshape(B * S, -1), B, S, heads, d, None).view(B, S, heads, d)
+    assert bool((got[0, :, :, 2] == float("inf")).all())
+    got[0, :, :, 2] = ref[0, :, :, 2]
+    assert (got - ref).abs().max().item() <= 2e-6 * x[:, :, 2].abs().max().item()
+    y = x.clone()
+    y[:, 5, 1, :, 0] = float("-inf")
+    mask = torch.zeros((B, S))
+    mask[:, 5] = -1e30
+    q8.q8_attention(y.reshape(B * S, -1).cuda(), B, S, heads, d, ctx=ctx)
+    ref = reference(x.reshape(B * S, -1), B, S, heads, d, mask)
+    assert (ctx.cpu().double() - ref).abs().max().item() <= 2e-6 * x[:, :, 2].abs().max().item()
