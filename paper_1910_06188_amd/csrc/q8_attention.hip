@@ -1000,7 +1000,7 @@ __global__ __launch_bounds__(64) void attention_generic_kernel(const float* __re
         const float* krow = qkv + (b * S + j) * ld + HD + (int64_t)h * d;
         float dot = 0.0f;
         for (int k = 0; k < d; ++k) dot = __builtin_fmaf(qrow[k] * c, krow[k], dot);
-        if (mask) dot += mask[b * S + j] * 1.44269504088896341f;
+        if (mask) dot += mask_log2(mask[b * S + j]);
         p[j] = dot;
         mx = __builtin_fmaxf(mx, dot);
     }

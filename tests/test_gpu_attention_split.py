@@ -190,3 +190,22 @@ def test_attention_of_infinities(q8, B, S, heads, d):
     q8.q8_attention(y.reshape(B * S, -1).cuda(), B, S, heads, d, ctx=ctx)
     ref = reference(x.reshape(B * S, -1), B, S, heads, d, mask)
     assert (ctx.cpu().double() - ref).abs().max().item() <= 2e-6 * x[:, :, 2].abs().max().item()
+
+
+@pytest.mark.parametrize("B,S,heads,d,offset", [(2, 70, 2, 64, 0), (2, 70, 50, 64, 0), (2, 70, 2, 64, 1), (2, 70, 2, 5, 0), (1, 9, 1, 130, 0)])
+def test_attention_of_a_sequence_that_is_masked_out(q8, B, S, heads, d, offset):
+    """Every key of the first sequence carries the lowest number: the mean of V, whichever kernel runs (both MFMA kernels; a
+    view four bytes into its buffer and other widths: the generic one)."""
+    g = torch.Generator().manual_seed(d)
+    HD = heads * d
+    x = torch.randn((B, S, 3, heads, d), generator=g)
+    mask = torch.zeros((B, S))
+    mask[0] = torch.finfo(torch.float32).min
+    buf = torch.empty(x.numel() + offset, device="cuda")
+    buf[offset:] = x.reshape(-1).cuda()
+    ctx = torch.empty((B * S, HD), device="cuda")
+    q8.q8_attention(buf[offset:], B, S, heads, d, ctx=ctx, mask=mask.cuda())
+    got = ctx.cpu().double().view(B, S, HD)
+    ref = reference(x.reshape(B * S, -1), B, S, heads, d, None).view(B, S, HD)
+    ref[0] = x[0, :, 2].double().reshape(S, HD).mean(0)
+    assert (got - ref).abs().max().item() <= 2e-6 * x[:, :, 2].abs().max().item()
