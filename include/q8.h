@@ -378,6 +378,8 @@ void q8_debug_set_gemm_variant(int variant);
  * workgroups itself, so the result never depends on the wait.  enabled = 0 turns the kernel off (two passes over
  * x, same results); barrier_polls = 0 makes a workgroup scan for every other one that is not there at its first
  * look (tests).  q8_absmax follows the same switch: one launch whose first workgroup waits for the others, or three.
+ * Nobody waits for that workgroup, so the others only have to get their turn; it waits 2^20 polls (about a second) before
+ * it reads their shares itself, with barrier_polls = 0 not at all.
  * Process-global, unsynchronised.
  */
 void q8_debug_set_quantize_one_pass(int enabled, uint32_t barrier_polls);

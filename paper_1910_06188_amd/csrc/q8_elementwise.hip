@@ -140,33 +140,35 @@ __global__ __launch_bounds__(kEwThreads) void absmax_partial_kernel(const float*
     if (threadIdx.x == 0) partials[blockIdx.x] = m;
 }
 
-// Stand-alone abs-max and scale in one launch: every workgroup publishes (ticket, maximum) in a slot of its own, the first
-// one waits for the others' and writes the results.  Nobody waits for the first, so the others always arrive, whatever
-// holds the chip; and the wait is bounded -- shares of workgroups that have not arrived by then, or whose slot a later
-// launch has taken over, are scanned here (same result, slower).  Slots and tickets as in quantize_resident_kernel.
+// Stand-alone abs-max and scale in one launch: every workgroup publishes (generation, maximum) in a slot of its own, the
+// first one waits for the others' and writes the results.  Nobody waits for the first, so the others arrive whatever holds
+// the chip.  Slots come from a ring; should two launches in flight ever share an entry, the maximum keeps the newer one's
+// values whichever of them comes last, and the older launch, whose values they replace, scans those shares here instead
+// (same result, slower; its wait is bounded too).  The generation counts how often the entry has been handed out: 33 bits
+// above the 31 of a magnitude, never 0 (the slots start as zeros).
 // Clearing the word, the atomics and the scale took three launches, and the atomics held the grid at 256 workgroups.
 // 30522 x 768, abs-max, quantization and a lookup: 42.4 -> 40.4 us.
 constexpr int kAmSlots = 1024, kAmRing = 256;
 static __device__ unsigned long long g_am_slots[kAmRing][kAmSlots];
 
 __global__ __launch_bounds__(kEwThreads) void absmax_scale_kernel(const float* __restrict__ x, int64_t n, int head,
-                                                                   unsigned long long* slots, unsigned ticket, unsigned spin_limit,
+                                                                   unsigned long long* slots, unsigned long long generation, unsigned spin_limit,
                                                                    float* amax_out, float* scale_out)
 {
     __shared__ unsigned long long missing[kAmSlots / 64];
     unsigned m = block_max_u32(absmax_thread(x, n, head, (int)blockIdx.x));
-    if (threadIdx.x == 0) __hip_atomic_store(&slots[blockIdx.x], ((unsigned long long)ticket << 32) | m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) __hip_atomic_fetch_max(&slots[blockIdx.x], (generation << 31) | m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (blockIdx.x != 0) return;
     m = 0u;
     for (int i = threadIdx.x; i < kAmSlots; i += kEwThreads) {
         bool here = i >= (int)gridDim.x;  // slots past the grid count as arrived
         for (unsigned polls = 0; !here; ++polls) {
             const unsigned long long sv = __hip_atomic_load(&slots[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const unsigned seen = (unsigned)(sv >> 32);
-            if (seen == ticket) {
+            const unsigned long long seen = sv >> 31;
+            if (seen == generation) {
                 here = true;
-                m = max(m, (unsigned)sv);
-            } else if (polls >= spin_limit || (int)(seen - ticket) > 0) {
+                m = max(m, (unsigned)sv & 0x7fffffffu);
+            } else if (polls >= spin_limit || seen > generation) {
                 break;
             } else {
                 __builtin_amdgcn_s_sleep(4);
@@ -733,11 +735,11 @@ __global__ __launch_bounds__(kRqThreads) void quantize_resident_kernel(const flo
 static std::atomic<unsigned> g_rq_spin_limit{64u};   // about 80 us of polling
 static std::atomic<bool> g_rq_enabled{true};
 
-// A ring of slot arrays in device memory, handed out round robin, and the ticket of the launch that takes one.
+// A ring of slot arrays in device memory, handed out round robin.
 struct SlotRing {
     const void* symbol;
     int entries, slots;
-    std::atomic<unsigned> next{0};
+    std::atomic<unsigned long long> next{0};
     std::mutex lock;
     unsigned long long* ptr[64] = {};
     int units[64] = {};
@@ -748,7 +750,7 @@ static SlotRing g_am_ring{HIP_SYMBOL(g_am_slots), kAmRing, kAmSlots};
 struct RingEntry {
     unsigned long long* slots = nullptr;   // null: switched off, a stream under graph capture (a replay would carry the ticket
                                            // of the capture), or a device the ring cannot be looked up on
-    unsigned ticket = 0;
+    unsigned long long seq = 0;            // launches before this one that took an entry
     int units = 0;                         // compute units of the device
 };
 static RingEntry ring_entry(SlotRing& ring, hipStream_t st, bool (*fits)(int64_t, int) = nullptr, int64_t n = 0)
@@ -778,9 +780,8 @@ static RingEntry ring_entry(SlotRing& ring, hipStream_t st, bool (*fits)(int64_t
         return e;
     }
     if (cap != hipStreamCaptureStatusNone) return e;
-    const unsigned seq = ring.next.fetch_add(1u);
-    e.ticket = seq + 1u == 0u ? ring.next.fetch_add(1u) + 1u : seq + 1u;   // never 0: the slots start as zeros
-    e.slots = ring.ptr[dev] + (size_t)(seq % (unsigned)ring.entries) * ring.slots;
+    e.seq = ring.next.fetch_add(1ull);
+    e.slots = ring.ptr[dev] + (size_t)(e.seq % (unsigned)ring.entries) * ring.slots;
     return e;
 }
 
@@ -792,12 +793,16 @@ int launch_absmax(const float* x, int64_t n, float* amax_out, float* scale_out, 
     }
     unsigned* bits = reinterpret_cast<unsigned*>(amax_out);
     const int head = head_of(x, n);
-    // slots and a ticket for the one-launch form; without them (switched off, a stream under graph capture) the atomics
+    // slots for the one-launch form; without them (switched off, a stream under graph capture), or when the generations are
+    // used up (2^41 launches), the atomics
     const RingEntry ring = ring_entry(g_am_ring, st);
-    if (ring.slots) {
-        const unsigned polls = g_rq_spin_limit.load() == 0u ? 0u : 1u << 20;   // the others arrive whatever this one does
+    const unsigned long long generation = ring.seq / kAmRing + 1;
+    if (ring.slots && generation >> 33 == 0) {
+        // A workgroup that is not there yet only has to wait its turn, and one workgroup scans 50 GB/s: the wait, about a
+        // second at most, is the shorter way out.
+        const unsigned polls = g_rq_spin_limit.load() == 0u ? 0u : 1u << 20;
         const int grid = std::min(am_grid((n - head) >> 2), kAmSlots);
-        hipLaunchKernelGGL(absmax_scale_kernel, dim3(grid), dim3(kEwThreads), 0, st, x, n, head, ring.slots, ring.ticket, polls, amax_out, scale_out);
+        hipLaunchKernelGGL(absmax_scale_kernel, dim3(grid), dim3(kEwThreads), 0, st, x, n, head, ring.slots, generation, polls, amax_out, scale_out);
         return hipGetLastError() == hipSuccess ? 0 : 1;
     }
     hipLaunchKernelGGL(absmax_init_kernel, dim3(1), dim3(1), 0, st, bits);
@@ -831,12 +836,13 @@ int launch_quantize_resident(const float* x, int64_t n, float* amax_out, float* 
                              hipStream_t st)
 {
     if (n % 4 != 0 || (reinterpret_cast<uintptr_t>(x) & 15) || (reinterpret_cast<uintptr_t>(q) & 3)) return 2;
-    const RingEntry ring = ring_entry(g_rq_ring, st, resident_fits, n);
+    RingEntry ring = ring_entry(g_rq_ring, st, resident_fits, n);
+    if (ring.slots && (unsigned)(ring.seq + 1) == 0u) ring = ring_entry(g_rq_ring, st, resident_fits, n);   // ticket 0: the slots start as zeros
     if (!ring.slots) return 2;
     const int64_t n4 = n >> 2;
     const int groups = (int)std::min<int64_t>(std::min(ring.units, kRqMaxGroups), (n4 + kRqThreads - 1) / kRqThreads);
     hipLaunchKernelGGL(quantize_resident_kernel, dim3(groups), dim3(kRqThreads), 0, st, reinterpret_cast<const float4*>(x),
-                       (int)n4, ring.slots, ring.ticket, g_rq_spin_limit.load(), amax_out, scale_out,
+                       (int)n4, ring.slots, (unsigned)(ring.seq + 1), g_rq_spin_limit.load(), amax_out, scale_out,
                        reinterpret_cast<unsigned*>(q), zero_slot);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }

@@ -254,3 +254,39 @@ def test_absmax_many_launches_on_two_streams(q8):
     for j in range(2):
         for i in range(400):
             assert got[j, i] == np.float32(peak[(i + j) % 4])
+
+
+def test_absmax_launches_that_share_a_ring_entry_do_not_stall(q8):
+    """Two launches 256 apart use the same slots.  Both wait for the same event and then run at the same time, the older one
+    up to some tens of microseconds later, so that their writes to a slot come in any order: the older one's values must not
+    stand in for the newer one's, which would then be waited for until the bound of about a second."""
+    import time
+    n, rounds = 24_000_000, 24
+    x = [torch.randn(n, device="cuda") for _ in range(2)]
+    peak = [np.float32(v.abs().max().item()) for v in x]
+    small = torch.randn(8, device="cuda")
+    out, skip, late = torch.zeros((2, rounds), device="cuda"), torch.zeros(1, device="cuda"), torch.zeros(8, device="cuda")
+    first, old, new = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Stream()
+    slowest = 0.0
+    for i in range(rounds):
+        torch.cuda.synchronize()
+        gate = torch.cuda.Event()
+        with torch.cuda.stream(first):
+            torch.cuda._sleep(8_000_000)            # some milliseconds of one thread, in which all but the last launches below come and go
+            gate.record()
+        old.wait_event(gate)
+        with torch.cuda.stream(old):
+            for _ in range(i % 8):
+                late += 1
+        q8.q8_absmax(x[0], out[0, i:i + 1], stream=old)
+        for _ in range(255):
+            q8.q8_absmax(small, skip, stream=new)
+        new.wait_event(gate)
+        q8.q8_absmax(x[1], out[1, i:i + 1], stream=new)
+        start = time.perf_counter()
+        torch.cuda.synchronize()
+        slowest = max(slowest, time.perf_counter() - start)
+    got = host(out)
+    for j in range(2):
+        assert (got[j] == peak[j]).all()
+    assert slowest < 0.2, slowest
