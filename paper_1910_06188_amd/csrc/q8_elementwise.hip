@@ -749,7 +749,8 @@ static SlotRing g_am_ring{HIP_SYMBOL(g_am_slots), kAmRing, kAmSlots};
 
 struct RingEntry {
     unsigned long long* slots = nullptr;   // null: switched off, a stream under graph capture (a replay would carry the ticket
-                                           // of the capture), or a device the ring cannot be looked up on
+                                           // of the capture) or of a device other than the current one (the slots are memory
+                                           // of the current one), or a device the ring cannot be looked up on
     unsigned long long seq = 0;            // launches before this one that took an entry
     int units = 0;                         // compute units of the device
 };
@@ -758,6 +759,19 @@ static RingEntry ring_entry(SlotRing& ring, hipStream_t st, bool (*fits)(int64_t
     RingEntry e;
     int dev = -1;
     if (!g_rq_enabled.load() || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return e;
+    // asked first: the look-up below is none of the calls that a capture allows
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return e;
+    }
+    if (cap != hipStreamCaptureStatusNone) return e;
+    hipDevice_t of_stream = dev;
+    if (st != nullptr && st != hipStreamLegacy && st != hipStreamPerThread && hipStreamGetDevice(st, &of_stream) != hipSuccess) {
+        (void)hipGetLastError();
+        return e;
+    }
+    if (of_stream != dev) return e;
     {
         std::lock_guard<std::mutex> hold(ring.lock);
         if (!ring.ptr[dev]) {
@@ -774,12 +788,6 @@ static RingEntry ring_entry(SlotRing& ring, hipStream_t st, bool (*fits)(int64_t
         e.units = ring.units[dev];
     }
     if (fits && !fits(n, e.units)) return e;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        return e;
-    }
-    if (cap != hipStreamCaptureStatusNone) return e;
     e.seq = ring.next.fetch_add(1ull);
     e.slots = ring.ptr[dev] + (size_t)(e.seq % (unsigned)ring.entries) * ring.slots;
     return e;

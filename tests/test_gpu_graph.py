@@ -155,3 +155,41 @@ def test_attention_block_under_graph_capture(q8):
         for a, b in zip(got, (y, ctx, qkv, slots_b, slots_c)):
             assert torch.equal(a, b), rep
         assert float(y.abs().max()) > 0
+
+
+def test_quantizers_that_take_slots_and_wide_attention_under_graph_capture(q8):
+    """The calls that take another route under capture (abs-max and the dynamic quantizer of small tensors, whose slots carry a
+    number of the host's), the training quantizer with its copied state, and attention of a width whose kernel asks for its
+    LDS at the launch: every replay on new data gives the eager bytes."""
+    n, B, S, heads, d = 100_000, 2, 300, 12, 128
+    x, qkv = torch.randn(n, device="cuda"), torch.randn((B * S, 3 * heads * d), device="cuda")
+    a, s, q, xq = torch.zeros(1, device="cuda"), torch.zeros(1, device="cuda"), torch.empty(n, dtype=torch.int8, device="cuda"), torch.empty(n, device="cuda")
+    scal, work = torch.zeros(q8.SCAL_WORK, device="cuda"), torch.zeros(q8.SCAL_WORK, device="cuda")
+    state, ctx, slots = torch.zeros(2, device="cuda"), torch.empty((B * S, heads * d), device="cuda"), torch.zeros(q8.AMAX_SLOTS, device="cuda")
+
+    def chain():
+        q8.q8_absmax(x, a, s)
+        q8.q8_quantize_dynamic(x, q, scal)
+        q8.q8_fake_quantize_ema(x, 0.9, state, work, xq)
+        q8.q8_attention(qkv, B, S, heads, d, ctx=ctx, amax_slots=slots)
+
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            chain()
+    torch.cuda.synchronize()
+    outs = (a, s, q, scal[:2], state, xq, ctx, slots)
+    for rep in range(4):
+        x.copy_(torch.randn(n, device="cuda") * (0.5 + rep))
+        qkv.copy_(torch.randn((B * S, 3 * heads * d), device="cuda"))
+        before = state.clone()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in outs]
+        state.copy_(before)
+        chain()                                # eager, on the same input
+        torch.cuda.synchronize()
+        for i, (g, t) in enumerate(zip(got, outs)):
+            assert torch.equal(g, t), (rep, i)
+        assert float(ctx.abs().max()) > 0 and int(q.abs().max()) == 127
