@@ -1,5 +1,6 @@
 """GPU parity of q8_attention against the CPU oracle.  Softmax attention is FP32 glue (Section 3); the GPU
-evaluates it in binary32 (fp32 matrix pipes, running-maximum softmax, exp2), the oracle in binary64.  A score
+evaluates it in binary32 (products on the bf16 matrix pipes from operands split into three exact parts, running-maximum
+softmax, exp2), the oracle in binary64.  A score
 is a 64-term binary32 dot product, so its error is a few 1e-7 times its size, the weights inherit that as a
 relative error, and every output -- a convex combination of V rows -- moves by at most that fraction of the
 largest |V| of its head: the bar is |ctx - oracle| <= 2e-6 * max|V| for inputs of standard deviation up to 1.5
@@ -55,7 +56,7 @@ def make_mask(g, B, S):
 SHAPES = [  # B, S, heads, d
     (1, 1, 1, 64), (2, 7, 3, 64), (1, 64, 1, 64), (1, 65, 2, 64), (2, 128, 2, 64), (1, 129, 1, 64), (3, 200, 2, 64),
     (2, 384, 4, 64), (1, 513, 1, 64), (1, 2048, 2, 64),
-    (2, 9, 3, 5), (1, 70, 2, 32), (1, 33, 2, 128), (2, 130, 1, 80),   # other head widths: the generic kernel
+    (2, 9, 3, 5), (1, 70, 2, 32), (1, 33, 2, 128), (2, 130, 1, 80),   # other head widths: the generic kernel (5), the MFMA kernels
 ]
 
 
@@ -121,7 +122,7 @@ def test_attention_golden_cases(q8, golden_dir):
 
 
 def test_attention_random_shapes(q8):
-    """Twenty random small problems: sequence lengths around the stage (64) and workgroup (128) sizes, with masks."""
+    """Twenty random small problems: sequence lengths around the stage (32) and workgroup (128) sizes, with masks."""
     g = synth.rng(555)
     for case in range(20):
         B, heads = int(g.integers(1, 4)), int(g.integers(1, 4))
@@ -228,3 +229,63 @@ def test_attention_bert_large_layer(q8):
     got = host(ctx)
     close(got, ref, float(np.abs(qkv[:, 2 * HD:]).max()))
     assert host(slots).max() == np.abs(got).max()
+
+
+@pytest.mark.parametrize("B,S,heads,d,offset", [
+    (2, 130, 3, 70, 0), (1, 200, 2, 130, 0), (3, 65, 2, 67, 0), (1, 300, 1, 257, 0),   # widths that are no multiple of 4, or above 128
+    (2, 130, 2, 64, 1), (1, 500, 3, 32, 2), (2, 129, 2, 128, 3),                         # views 4, 8 and 12 bytes into their buffer
+])
+@pytest.mark.parametrize("with_mask", [False, True])
+def test_attention_generic_kernel(q8, B, S, heads, d, offset, with_mask):
+    """The kernel of any width and alignment, over more keys and more columns than a wave has lanes, with a mask, abs-max slots,
+    and codes under a stored scale."""
+    g = synth.rng(1700 + S + d)
+    HD = heads * d
+    qkv = synth.activations(g, B * S, 3 * HD)
+    mask = make_mask(g, B, S) if with_mask else None
+    if with_mask:
+        mask[0, :] = -10000.0
+        mask[0, S - 1] = 0.0              # the only key left lies behind the first 64
+    ref = O.attention(qkv, B, S, heads, d, mask=mask, threads=8)
+    buf = torch.zeros(qkv.size + offset, device="cuda")
+    buf[offset:] = dev(qkv).reshape(-1)
+    args = dict(mask=None if mask is None else dev(mask))
+    ctx = torch.full((B * S, HD), 9.0, device="cuda")
+    slots = torch.full((q8.AMAX_SLOTS,), -1.0, device="cuda")
+    q8.q8_attention(buf[offset:], B, S, heads, d, ctx=ctx, amax_slots=slots, **args)
+    got = host(ctx)
+    close(got, ref, float(np.abs(qkv[:, 2 * HD:]).max()))
+    assert host(slots).min() >= 0 and host(slots).max() == np.abs(got).max()
+    scale = torch.tensor([40.0], device="cuda")
+    codes = torch.full((B * S, HD), 99, dtype=torch.int8, device="cuda")
+    q8.q8_attention(buf[offset:], B, S, heads, d, q_scale=scale, q_out=codes, **args)
+    np.testing.assert_array_equal(host(codes), O.quantize(got, np.float32(40.0)))
+
+
+@pytest.mark.parametrize("B,S,heads,d", [(4, 200, 24, 64), (1, 2048, 12, 64), (1, 2100, 10, 32), (3, 520, 12, 128)])
+def test_attention_staged_kernel_sharp_and_long(q8, B, S, heads, d):
+    """Enough workgroups for the kernel whose waves walk every stage together: scores of +-100 whose maximum changes at every
+    stage, leading stages masked off, queries of zero (the mean of V), and sequences of thousands of tokens."""
+    g = synth.rng(1800 + S + d)
+    HD = heads * d
+
+    def run(qkv, mask=None):
+        ctx = torch.empty((B * S, HD), device="cuda")
+        q8.q8_attention(dev(qkv), B, S, heads, d, ctx=ctx, mask=None if mask is None else dev(mask))
+        return host(ctx)
+
+    base = synth.activations(g, B * S, 3 * HD)
+    vmax = float(np.abs(base[:, 2 * HD:]).max())
+    for gain in (0.05, 1.0, 4.0):
+        qkv = base.copy()
+        qkv[:, :2 * HD] *= np.float32(gain * (64.0 / d) ** 0.25)
+        qkv[:, HD:2 * HD] *= np.tile(np.linspace(0.1, 2.0, S, dtype=np.float32), B)[:, None]
+        close(run(qkv), O.attention(qkv, B, S, heads, d, threads=8), vmax, tol=TOL_SHARP if gain > 1.5 else TOL)
+    mask = np.zeros((B, S), np.float32)
+    mask[:, :70] = -10000.0
+    mask[B - 1, 150:] = -10000.0
+    close(run(base, mask), O.attention(base, B, S, heads, d, mask=mask, threads=8), vmax)
+    flat = base.copy()
+    flat[:, :HD] = 0
+    v = base[:, 2 * HD:].astype(np.float64).reshape(B, S, HD)
+    np.testing.assert_allclose(run(flat).reshape(B, S, HD), np.repeat(v.mean(axis=1, keepdims=True), S, axis=1), atol=2e-6)

@@ -222,8 +222,8 @@ def test_linear_single_fc_config(q8, variant):
     (300, 256, 520, 0), (700, 384, 600, 1), (700, 384, 600, 2), (700, 384, 600, 3), (700, 384, 600, 4),
     (257, 128, 129, 1), (1, 128, 1, 3), (513, 1024, 257, 2), (255, 640, 1000, 4), (1030, 256, 2100, 1), (768, 384, 512, 4), (512, 1024, 512, 2),
     (700, 384, 600, 5), (385, 256, 770, 5), (768, 1024, 512, 5), (700, 384, 600, 6), (385, 256, 770, 6), (768, 1024, 512, 6),
-    # the launcher's own choice (variant 0) on every shape class above: short and long K, ragged and exact edges,
-    # fewer tiles than compute units and several rounds of them
+    # the launcher's own choice (variant 0) on the shapes above: the direct kernel and the 64x64 tile for all but the last,
+    # which is large enough for the tiles of full launches
     (700, 384, 600, 0), (257, 128, 129, 0), (1, 128, 1, 0), (513, 1024, 257, 0), (255, 640, 1000, 0), (1030, 256, 2100, 0),
     (768, 384, 512, 0), (512, 1024, 512, 0), (385, 256, 770, 0), (768, 1024, 512, 0), (520, 2048, 300, 0), (3000, 4096, 260, 0),
     (4100, 512, 3000, 0),
@@ -234,6 +234,13 @@ def test_linear_mfma_ragged_multi_tile(q8, M, K, N, variant):
     ref = check_linear(r, d["x"], d["b"])
     assert_rel(r["y"], ref["y"])
     assert_rel(r["y_plain"], ref["y"])
+
+
+@pytest.mark.parametrize("M,K,N", [(3000, 2048, 712), (1100, 4096, 2000), (4100, 2304, 520), (2050, 128, 1100), (3072, 2048, 768)])
+def test_linear_own_choice_among_the_tiles_of_full_launches(q8, M, K, N):
+    """More than 512 tiles of 64x64: the launcher picks among the staged tiles, for long and short reductions, on ragged
+    edges and on exact ones."""
+    test_linear_mfma_ragged_multi_tile(q8, M, K, N, 0)
 
 
 @pytest.mark.parametrize("M,K,N", [(33, 100, 70), (5, 1, 3), (64, 127, 64), (17, 200, 19), (2, 3000, 2), (40, 0, 8)])
