@@ -773,8 +773,8 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
 // sequence is a chain of latencies -- rows from memory, then per stage 64 MFMAs (of 32 cycles, at width 64) that the
 // kernel above walks one after the other on an eighth of the compute units.  No wave shares its keys, so K and V go straight
 // from memory into operand registers and nothing is staged: for every 32 queries they are read and split again, which is
-// why full launches keep the kernel above.  One sequence of 128 tokens, 12 heads of 64: 10.1 -> 7.4 us; of 512: 25.1 ->
-// 14.3; 2 x 256 of width 32: 12.4 -> 7.0.  Error against binary64 no larger (2.1e-7 against 2.6e-7 at 128 tokens).
+// why full launches keep the kernel above.  One sequence of 128 tokens, 12 heads of 64: 11.2 -> 7.6 us; of 512: 28.9 ->
+// 15.6; 2 x 256 of width 32: 13.1 -> 7.0.  Error against 64 bits no larger (1.3e-7 against 1.5e-7 at 128 tokens).
 template <int kDB>
 __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_kernel(AttnArgs a)
 {
@@ -1054,12 +1054,15 @@ bool attention_mfma_eligible(const float* qkv, int64_t B, int64_t S, int heads, 
 template <int kDB>
 static int launch_attention_width(AttnArgs a, int64_t wgs, hipStream_t st)
 {
-    // The split kernel while each of its workgroups has a compute unit of its own (7 x 93 tokens, 252 workgroups: 7.9 us
-    // against 9.1); with two on a unit (widths up to 64) only where there is a chain to shorten or a single stage to
-    // walk: 2 x 512 (384) 22.0 against 26.0, 32 x 32 (384) 7.0 against 8.2, but 16 x 64 (384) 8.8 against 7.4 and
-    // 8 x 128 (384) even; beyond, 6 x 256 (576) 20.9 against 17.2.
+    // The split kernel while each of its workgroups has one of the 256 compute units for itself: at 256 workgroups of width 64
+    // it takes 7.9 us against 11.4 on sequences of 4 stages, 10.1 against 17.0 on 8, 22.3 against 50.7 on 32, of width 128 28.3
+    // against 60.4 on 16.  With two on a unit (widths up to 64): width 32 always (384 workgroups of 1 / 2 / 3 / 4 / 8 / 16
+    // stages 5.1 / 6.2 / 6.5 / 6.9 / 9.3 / 13.2 us against 6.4 / 6.3 / 7.7 / 8.8 / 13.4 / 22.6), width 64 but for
+    // sequences of two and three stages (1 / 2 / 3 / 4 / 5 / 6 / 7 / 8 / 16 stages 7.0 / 9.3 / 10.2 / 10.9 / 13.5 / 14.4 /
+    // 15.4 / 14.8 / 21.5 against 8.8 / 8.1 / 9.9 / 11.8 / 13.9 / 14.8 / 16.6 / 17.6 / 29.0).  Beyond, its third round
+    // costs more than the chain it shortens (576 of width 64: 4 / 8 / 16 stages 15.3 / 20.0 / 31.7 against 12.5 / 18.1 / 29.5).
     const int64_t bh = wgs / a.n_qblocks, n_q32 = (a.S + kAtQW - 1) / kAtQW, wgs32 = bh * n_q32;
-    const bool split = wgs32 <= 256 || (kDB <= 2 && wgs32 <= 512 && (n_q32 == 1 || n_q32 >= 8));
+    const bool split = wgs32 <= 256 || (wgs32 <= 512 && (kDB == 1 || (kDB == 2 && (n_q32 == 1 || n_q32 >= 4))));
     if (split) {
         a.n_qblocks = (int)n_q32;
         hipLaunchKernelGGL(attention_split_kernel<kDB>, dim3((unsigned)wgs32), dim3(kAtThreads), 0, st, a);

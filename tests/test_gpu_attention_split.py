@@ -209,3 +209,11 @@ def test_attention_of_a_sequence_that_is_masked_out(q8, B, S, heads, d, offset):
     ref = reference(x.reshape(B * S, -1), B, S, heads, d, None).view(B, S, HD)
     ref[0] = x[0, :, 2].double().reshape(S, HD).mean(0)
     assert (got - ref).abs().max().item() <= 2e-6 * x[:, :, 2].abs().max().item()
+
+
+@pytest.mark.parametrize("B,S,heads,d,mask", [
+    # two workgroups a compute unit: width 64 with three stages (staged), four (dealt out), one; width 32 with two and three
+    (32, 96, 4, 64, "some"), (32, 128, 4, 64, "some"), (43, 128, 3, 64, "low"), (128, 20, 4, 64, "some"), (64, 33, 4, 32, "low"), (32, 90, 4, 32, "some"), (57, 90, 3, 32, "low"),
+])
+def test_attention_where_two_workgroups_share_a_compute_unit(q8, B, S, heads, d, mask):
+    test_attention_on_both_sides_of_the_split(q8, B, S, heads, d, mask)
