@@ -5,9 +5,9 @@
  *
  * Conventions shared by all entry points
  *   - Every pointer is a DEVICE pointer owned by the caller unless a comment says
- *     "host".  The library never allocates, frees or keeps a pointer.  (Its own state on a GPU is two
- *     static device arrays that come with the code object: the scratch of q8_linear_f32_static and
- *     128 KiB of barrier slots for the one-pass dynamic quantizer.)
+ *     "host".  The library never allocates, frees or keeps a pointer.  (Its own state on a GPU is three
+ *     static device arrays that come with the code object: the scratch of q8_linear_f32_static,
+ *     128 KiB of barrier slots for the one-pass dynamic quantizer and 2 MiB of slots for q8_absmax.)
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Calls
  *     only enqueue work on it: no host synchronisation, no host read of device data.
  *     Data-dependent scalars (abs-max, scales) therefore live in device memory so
@@ -346,10 +346,14 @@ q8_status q8_embedding_sum3_layernorm(const int8_t* word, int64_t Vw, const int8
  *   amax_slots fp32[Q8_AMAX_SLOTS] or NULL: partial maxima of |ctx| for q8_quantize_amax.
  *   q_scale fp32[1] and q_out int8[B*S, heads*d], both or neither: q_out = Quantize(ctx | q_scale[0], 127)
  *   (Eq. 1 on the fp32 value), the whole quantizer of the next FC layer under a stored scale (Eq. 4).
- * Arithmetic is binary32 throughout (fp32 matrix pipes, running-maximum softmax, exp2): ctx agrees
- * with the exact result to about 1e-6 of the largest |V| of its head as long as the scores stay
+ * Arithmetic is that of binary32: each fp32 operand of the two products is taken apart into three
+ * bf16 numbers whose sum it is, eight of the nine partial products run on the bf16 matrix pipes (the
+ * ninth is below 2^-34 of the product) and are summed in fp32; running-maximum softmax, exp2.  ctx
+ * agrees with the exact result to about 1e-6 of the largest |V| of its head as long as the scores stay
  * within a few tens; a sequence whose every key carries a large negative mask loses the low bits of
- * its scores to that offset.  Inputs must be finite.
+ * its scores to that offset.  Any finite input will do: rows that meet numbers above 2^96, or whose
+ * results are below 2^-100 (or 2^-90 of the largest input), are evaluated again in plain fp32, which is slow.  Mask
+ * values below -2.08e38 all count as that; a sequence whose every key carries one gives the mean of V.
  * B >= 0 (B = 0: nothing written, slots cleared); S >= 1; heads, d >= 1.  d = 64 with 16-byte
  * aligned qkv and ctx (4-byte q_out) and one sequence of qkv below 2^31 floats may have any S;
  * other widths, alignments or sizes need S <= 16384 (Q8_ERR_SHAPE beyond).  Widths that are multiples

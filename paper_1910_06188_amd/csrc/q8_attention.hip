@@ -17,7 +17,8 @@
 // one fp32 MFMA pass, and -- unlike the fp32 MFMAs, which share their lanes with the vector ALU -- they run beside the
 // softmax arithmetic.  Error against 64 bits, rms of ctx over rms: normal inputs 32 x 128 tokens 1.5e-7 (fp32 pipes
 // 3.4e-7, six products in one accumulator 2.6e-7), 8 x 384 2.1e-7 (4.5e-7, 3.8e-7); scores of one nonzero column 2.30e-6
-// (2.30e-6, 2.58e-6).  BERT-Large attention: fp32 pipes 184 us, six products 117 us, eight 141 us.
+// (2.30e-6, 2.58e-6).  BERT-Large attention: fp32 pipes 175 us, six products 117 us, eight 140 us
+// (144 with the look at the range).
 //
 // Range.  The sum is exact, and the products lose nothing, while no number is near the ends of the type: from 3.3953e38 on
 // h rounds to infinity, and the lower parts of numbers below 2^-110 fall under the smallest bf16.  The kernels keep the largest
@@ -95,7 +96,7 @@ __device__ __forceinline__ void at_static_for(F&& f)
 __device__ __forceinline__ float at_max(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 
 // Two binary32 numbers as three packed pairs of bf16 numbers whose sums they are, exactly: each part is the
-// nearest bf16 of what the parts before it leave, and the differences are exact.  In two halves, so that the pieces that
+// nearest bf16 of what the parts before it leave, and the differences are exact (inside the range named above).  In two halves, so that the pieces that
 // go between two MFMAs stay small.  (v_dot2_f32_bf16 would unpack and subtract in one instruction, 7 for the pair
 // instead of 11, but it waits for the MFMA in flight: measured 62 cycles per MFMA with four of them between, 33 with
 // four ordinary instructions.)

@@ -118,7 +118,8 @@ constexpr int mfma_waves_per_simd(int BM, int BN, int SB, int NW)
 // Deep rings (SB > 3; SA = SB then): a launch with fewer tiles than the chip has places waits for memory, not for the
 // matrix pipe, so both operands run SB - 1 stages ahead, all loads spread over the first three k-steps.  Used for the
 // 64x64 tile (five stages of 16 KiB, two workgroups per compute unit: 651 x 768 x 3072 15.1 -> 8.7 us); the same ring
-// under a 128x128 tile gains nothing (17.1 us either way at 4096 x 768 x 3072: bound by its LDS traffic).
+// under a 128x128 tile gains nothing (17.1 us either way at 4096 x 768 x 3072, where 192 tiles leave a quarter of the
+// compute units idle: more loads in flight are not what it lacks).
 //
 // Every memory operation of a k-step is placed by hand behind a given MFMA (LDS reads early,
 // global loads at least two MFMAs apart).  Loads past the end of K go through an empty
