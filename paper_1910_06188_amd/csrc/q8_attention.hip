@@ -23,8 +23,9 @@
 // Range.  The sum is exact, and the products lose nothing, while no number is near the ends of the type: from 3.3953e38 on
 // h rounds to infinity, and the lower parts of numbers below 2^-110 fall under the smallest bf16.  The kernels keep the largest
 // magnitude of the rows they split (a vector instruction for every two numbers) and look at their results: rows that saw a
-// number above 2^96, an infinity or a NaN, or whose results are not finite or so small that lost parts could matter in them,
-// are formed again in plain binary32 (attention_rows_plain).  Slow, but values that occur in earnest never lead there.
+// number above 2^96 or an infinity, or whose results are infinite or so small that lost parts could matter in them, are formed
+// again in plain binary32 (attention_rows_plain).  Slow, but values that occur in earnest never lead there.  (Not for a NaN: it
+// makes the same results NaN either way.)
 //
 // Kernel (head widths up to 128): a workgroup of four waves owns 128 queries of one (sequence, head); each wave keeps
 // its 32 query rows, split, in registers (pre-multiplied by scale * log2 e) and walks the keys in stages of 32.  The K
@@ -502,15 +503,15 @@ __device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, i
     if constexpr (kMore) attention_move_reference(w, mx);
 }
 
-// Magnitudes as bit patterns, which order like the numbers (a NaN above all).
-__device__ __forceinline__ unsigned magnitude_bits(float x) { return __float_as_uint(x) & 0x7fffffffu; }
-// The same minus one, doubled, for the smallest magnitude of numbers that are not zero: zero becomes the largest of all.
+// Magnitudes are compared as bit patterns, which order like the numbers (a NaN above all).
+// The bits minus one, doubled, for the smallest magnitude of numbers that are not zero: zero becomes the largest of all.
 __device__ __forceinline__ unsigned nonzero_bits(float x) { return (__float_as_uint(x) << 1) - 1u; }
 
-__device__ __forceinline__ void attention_ends(float4 v, unsigned& smallest, unsigned& amax)
+__device__ __forceinline__ void attention_ends(float4 v, unsigned& smallest, float& amax)
 {
     smallest = min(smallest, min(min(nonzero_bits(v.x), nonzero_bits(v.y)), min(nonzero_bits(v.z), nonzero_bits(v.w))));
-    amax = max(amax, max(max(magnitude_bits(v.x), magnitude_bits(v.y)), max(magnitude_bits(v.z), magnitude_bits(v.w))));
+    // a NaN is passed over, as everywhere in the abs-max of ctx
+    amax = __builtin_fmaxf(amax, __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(v.x), __builtin_fabsf(v.y)), __builtin_fmaxf(__builtin_fabsf(v.z), __builtin_fabsf(v.w))));
 }
 
 // Four neighbouring results: ctx, or its codes under the stored scale of the next FC layer (Eq. 1), or both.
@@ -529,6 +530,7 @@ __device__ __forceinline__ void attention_store(const AttnArgs& a, int64_t off, 
 __device__ __forceinline__ bool attention_in_range(unsigned largest, unsigned smallest, unsigned amax)
 {
     const float f = __uint_as_float(largest);
+    if (largest > 0x7f800000u) return true;   // a NaN among the inputs
     return f <= 0x1p96f && amax < 0x7f800000u && smallest >= nonzero_bits(__builtin_fmaxf(0x1p-100f, f * 0x1p-90f));
 }
 
@@ -548,8 +550,16 @@ __device__ __forceinline__ float attention_rows_plain(const AttnArgs& a, int64_t
             float s = -__builtin_inff();
             if (j < a.S) {
                 const float *qp = base + q * ld, *kp = base + j * ld + HD;
-                s = a.mask ? mask_log2(a.mask[b * a.S + j]) : 0.0f;
-                for (int k = 0; k < a.d; ++k) s = __builtin_fmaf(qp[k] * a.c, kp[k], s);
+                s = 0.0f;
+#pragma unroll 4
+                for (int k = 0; k < a.d; k += 4) {   // the width is a multiple of 4 and rows are 16-byte aligned here
+                    const float4 qv = *reinterpret_cast<const float4*>(qp + k), kv = *reinterpret_cast<const float4*>(kp + k);
+                    s = __builtin_fmaf(qv.x * a.c, kv.x, s);
+                    s = __builtin_fmaf(qv.y * a.c, kv.y, s);
+                    s = __builtin_fmaf(qv.z * a.c, kv.z, s);
+                    s = __builtin_fmaf(qv.w * a.c, kv.w, s);
+                }
+                if (a.mask) s += mask_log2(a.mask[b * a.S + j]);
             }
             float m_up = s;
 #pragma unroll
@@ -561,6 +571,7 @@ __device__ __forceinline__ float attention_rows_plain(const AttnArgs& a, int64_t
             acc[0] *= alpha;
             acc[1] *= alpha;
             const int keys = (int)min((int64_t)64, a.S - j0);
+#pragma unroll 8
             for (int t = 0; t < keys; ++t) {
                 const float pt = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)__float_as_uint(p), t));
                 const float* vp = base + (j0 + t) * ld + 2 * HD;
@@ -722,22 +733,19 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
     const float qs = a.q_out ? a.q_scale[0] : 0.0f;
     const int64_t out_off = (b * S + q0 + lq) * HD + (int64_t)h * a.d + 4 * hi;
     // Lanes beyond the sequence or the width repeat results of the last query or column: they change neither end.
-    unsigned smallest = ~0u, amax = 0u;
+    unsigned smallest = ~0u;
+    float ctx_max = 0.0f;
 #pragma unroll
     for (int blk = 0; blk < kDB; ++blk)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             const float4 v = make_float4(w.o[blk][4 * g + 0] * inv, w.o[blk][4 * g + 1] * inv, w.o[blk][4 * g + 2] * inv, w.o[blk][4 * g + 3] * inv);
             if (live && 32 * blk + 8 * g + 4 * hi < a.d) attention_store(a, out_off + 32 * blk + 8 * g, v, qs);
-            attention_ends(v, smallest, amax);
+            attention_ends(v, smallest, ctx_max);   // 0 / 0 in a wave without queries: neither
         }
-    if (!wave_live) {   // 0 / 0
-        smallest = ~0u;
-        amax = 0u;
-    }
     unsigned largest = wave_max_u32(__float_as_uint(sg.largest));
     smallest = ~wave_max_u32(~smallest);
-    amax = wave_max_u32(amax);
+    unsigned amax = wave_max_u32(__float_as_uint(ctx_max));
     if (lane == 0) wave_ends[wave] = make_uint4(largest, smallest, amax, 0u);
     __syncthreads();
 #pragma unroll
@@ -748,7 +756,7 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
     }
     if (__builtin_expect(!attention_in_range(largest, smallest, amax), 0)) {
         __threadfence();   // behind the stores above
-        amax = wave_max_u32(magnitude_bits(attention_rows_plain(a, b, h, q0, kAtQW)));
+        amax = wave_max_u32(__float_as_uint(attention_rows_plain(a, b, h, q0, kAtQW)));
         __syncthreads();   // wave_ends has been read
         if (lane == 0) wave_ends[wave].z = amax;
         __syncthreads();
@@ -942,7 +950,8 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
     const float inv = 1.0f / den;
     const float qs = a.q_out ? a.q_scale[0] : 0.0f;
     const int64_t out_off = (b * S + q0 + q) * HD + (int64_t)h * d;
-    unsigned smallest = ~0u, amax = 0u;   // lanes beyond the sequence or the width repeat other results, as above
+    unsigned smallest = ~0u;   // lanes beyond the sequence or the width repeat other results, as above
+    float ctx_max = 0.0f;
 #pragma unroll
     for (int c = 0; c < kDB; ++c) {
         const int col = 32 * c + 4 * (tid & 7);
@@ -960,14 +969,14 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
         o.z *= inv;
         o.w *= inv;
         if (q0 + q < S && col < d) attention_store(a, out_off + col, o, qs);
-        attention_ends(o, smallest, amax);
+        attention_ends(o, smallest, ctx_max);
     }
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!attention_in_range(all_large, smallest, amax)) != 0, 0)) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!attention_in_range(all_large, smallest, __float_as_uint(ctx_max))) != 0, 0)) {
         __threadfence();   // behind the stores above
-        amax = magnitude_bits(attention_rows_plain(a, b, h, q0 + 8 * wave, 8));   // a wave ends up with eight queries
+        ctx_max = attention_rows_plain(a, b, h, q0 + 8 * wave, 8);   // a wave ends up with eight queries
     }
     if (a.slots) {   // never more workgroups than slots here
-        amax = wave_max_u32(amax);
+        unsigned amax = wave_max_u32(__float_as_uint(ctx_max));
         if (lane == 0) wave_ends[wave].z = amax;
         __syncthreads();
         if (tid == 0) {

@@ -168,8 +168,9 @@ def test_attention_over_the_whole_finite_range(q8, B, S, heads, d):
 
 
 @pytest.mark.parametrize("B,S,heads,d", RANGE_SHAPES)
-def test_attention_of_infinities(q8, B, S, heads, d):
-    """An infinity in V makes its column infinite and no other; a key whose score is -inf has no weight."""
+def test_attention_of_infinities_and_nans(q8, B, S, heads, d):
+    """An infinity in V makes its column infinite and no other; a key whose score is -inf has no weight; a NaN spreads no
+    further than its column."""
     g = torch.Generator().manual_seed(S + heads)
     HD = heads * d
     x = torch.randn((B, S, 3, heads, d), generator=g)
@@ -181,6 +182,16 @@ def test_attention_of_infinities(q8, B, S, heads, d):
     got = ctx.cpu().double().view(B, S, heads, d)
     ref = reference(x.reshape(B * S, -1), B, S, heads, d, None).view(B, S, heads, d)
     assert bool((got[0, :, :, 2] == float("inf")).all())
+    got[0, :, :, 2] = ref[0, :, :, 2]
+    assert (got - ref).abs().max().item() <= 2e-6 * x[:, :, 2].abs().max().item()
+    # a NaN in V makes its column NaN and no other, and the abs-max passes over it
+    y = x.clone()
+    y[0, 3, 2, :, 2] = float("nan")
+    slots = torch.full((q8.AMAX_SLOTS,), 9e9, device="cuda")
+    q8.q8_attention(y.reshape(B * S, -1).cuda(), B, S, heads, d, ctx=ctx, amax_slots=slots)
+    got = ctx.cpu().double().view(B, S, heads, d)
+    assert bool(got[0, :, :, 2].isnan().all())
+    assert slots.max().item() == got.nan_to_num(nan=0.0).abs().max().item()
     got[0, :, :, 2] = ref[0, :, :, 2]
     assert (got - ref).abs().max().item() <= 2e-6 * x[:, :, 2].abs().max().item()
     y = x.clone()
