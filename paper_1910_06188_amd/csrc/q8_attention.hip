@@ -9,7 +9,7 @@
 // FP32 products on the bf16 matrix pipes.  A binary32 number is the exact sum of three bf16 numbers h + m + l (8 + 8 + 8
 // significant bits, each part the rounded remainder of the ones before it), so a product is nine bf16 products.  Eight of
 // them run on v_mfma_f32_32x32x16_bf16; l l, below 2^-34 of the product, is left out.  (m l and l m reach 2^-24 of it, half
-// a last place of binary32: without them a score of one nonzero term is up to 1.6 times as far from 64 bits as one rounded
+// a last place of binary32: without them a score of one nonzero term is up to 1.7 times as far from 64 bits as one rounded
 // product.)  The h h products have an accumulator of their own and the others share one, joined by one addition of the
 // vector ALU: an MFMA adds up products of like size exactly, and rounds to nearest where the accumulator is the larger, but
 // cuts an accumulator that is much smaller than its products off at the last place of the result (measured: errors up to one
