@@ -115,7 +115,7 @@ def test_attention_products_are_as_good_as_one_rounding(q8, B, heads):
 
 
 # few heads: the stages dealt out; many: four waves on every stage
-RANGE_SHAPES = [(2, 70, 2, 64), (1, 45, 2, 128), (2, 70, 50, 64), (3, 45, 60, 32), (1, 130, 40, 128)]
+RANGE_SHAPES = [(2, 70, 2, 64), (1, 45, 2, 128), (2, 70, 50, 64), (3, 45, 60, 32), (1, 130, 40, 128), (33, 16, 64, 64)]   # the last: more workgroups than slots
 
 
 @pytest.mark.parametrize("B,S,heads,d", RANGE_SHAPES)

@@ -289,4 +289,4 @@ def test_absmax_launches_that_share_a_ring_entry_do_not_stall(q8):
     got = host(out)
     for j in range(2):
         assert (got[j] == peak[j]).all()
-    assert slowest < 0.2, slowest
+    assert slowest < 0.5, slowest
