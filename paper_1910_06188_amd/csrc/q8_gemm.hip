@@ -13,11 +13,14 @@
 // conflicts; the swizzle costs nothing on the way in because each lane of a
 // direct-to-LDS load picks its own global address while the LDS side stays linear.
 //
-// Any other K or alignment, and launches of at most 256 tiles of 32x32, go to the kernel of q8_gemm_direct.hip; a handful
-// of products to the one-thread-per-output kernel below.
+// Short reductions go to the kernel of q8_gemm_ring_kernel.h, the same but for how it overlaps; any other K or alignment, and
+// launches of at most 256 tiles of 32x32, to the kernel of q8_gemm_direct.hip; a handful of products to the one-thread-per-output
+// kernel below.
 #include "q8_device.h"
 #include "q8_epilogue.h"
 #include "q8_launch.h"
+
+#include <math.h>
 
 namespace q8 {
 
@@ -31,6 +34,16 @@ int launch_tile_64x64_w4(const int8_t*, const int8_t*, int, int, int, int, const
 int launch_tile_192x256_w4(const int8_t*, const int8_t*, int, int, int, int, const Epilogue&, hipStream_t);
 int launch_tile_192x256_w8(const int8_t*, const int8_t*, int, int, int, int, const Epilogue&, hipStream_t);
 int launch_tile_192x128_w4(const int8_t*, const int8_t*, int, int, int, int, const Epilogue&, hipStream_t);
+
+// The same for the kernel of q8_gemm_ring_kernel.h (tile, stage buffers); the last integer is whether each XCD takes a contiguous
+// run of tiles.
+#define Q8_RING(NAME) int launch_ring_##NAME(const int8_t*, const int8_t*, int, int, int, int, int, const Epilogue&, hipStream_t)
+Q8_RING(64x64_s3);
+Q8_RING(64x64_s2);
+Q8_RING(128x64_s2);
+Q8_RING(128x128_s1);
+Q8_RING(192x128_s1);
+#undef Q8_RING
 
 // One thread per output element: reductions so short that the loads of a direct-kernel tile take longer than the whole sum
 // (5 x 33 x 9: 2.6 us against 4.7; 64 x 4096 x 9: 3.8 against 5.1; 1 x 2 x 17: 2.9 against 4.4).  The chain of K byte loads costs 45 ns
@@ -63,8 +76,57 @@ __global__ __launch_bounds__(256) void gemm_scalar_kernel(const int8_t* __restri
 static int g_variant = 0;
 void set_gemm_variant(int v) { g_variant = v; }
 
-// Variants 1 to 6 are the staged tile shapes of full launches, 7 the small one with deep rings, 8 the direct kernel.
-constexpr int kVariant64 = 7, kVariantDirect = 8;
+// Variants 1 to 6 are the staged tile shapes of full launches, 7 the small one with deep rings, 8 the direct kernel, 9 and up the rings.
+constexpr int kVariant64 = 7, kVariantDirect = 8, kVariantRing = 9;
+
+// The shapes of q8_gemm_ring_kernel.h and what a launch of each takes (us): `fixed`, the longer of two times per stage of K -- the
+// chain a workgroup walks (`chain`, per round of workgroups) and the work of a compute unit (`work`, per tile) -- and the
+// epilogue of every tile (fp32, fp32 with GELU or abs-max, int8).  The constants are a fit to 143 launches of 300 to 16384
+// rows and N x K from 512 x 512 to 4096 x 1024, outputs rotating through more than the Infinity Cache, off by 5 to 10 % (rms).
+// Choosing by it costs 2.6 % (geometric mean; 14 % at worst) against the best of all shapes measured.  `smooth` says how much
+// of a last, partly filled round counts in full.  Large tiles store better with neighbouring tiles on different XCDs, in panels of four
+// rows (12288 x 3072 x 1024 54.8 -> 48.6 us with 192x128): what is written at the same time then lies together.
+struct Ring {
+    int (*launch)(const int8_t*, const int8_t*, int, int, int, int, int, const Epilogue&, hipStream_t);
+    int bm, bn, wgs;    // tile, workgroups per compute unit
+    int group_m, by_xcd;
+    float fixed, chain, work, out[3], smooth;
+};
+static const Ring kRings[] = {
+    {launch_ring_64x64_s3, 64, 64, 3, 8, 1, 2.84f, 0.222f, 0.182f, {0.51f, 0.70f, 0.71f}, 0.42f},
+    {launch_ring_64x64_s2, 64, 64, 5, 8, 1, 2.42f, 0.411f, 0.176f, {0.48f, 0.64f, 0.65f}, 0.42f},
+    {launch_ring_128x64_s2, 128, 64, 3, 8, 1, 2.58f, 0.481f, 0.284f, {0.83f, 1.11f, 1.17f}, 0.38f},
+    {launch_ring_128x128_s1, 128, 128, 4, 4, 0, 2.17f, 0.863f, 0.437f, {2.17f, 2.49f, 2.61f}, 0.51f},
+    {launch_ring_192x128_s1, 192, 128, 3, 4, 0, 2.65f, 0.949f, 0.604f, {2.66f, 3.80f, 4.59f}, 1.0f},
+};
+constexpr int kNumRings = sizeof(kRings) / sizeof(kRings[0]);
+
+// That kernel has no accumulator dump and no residual, and only the flag combinations that mean something.
+static bool ring_eligible(const Epilogue& ep) { return !ep.acc_out && !ep.residual && ep.flags <= 5u; }
+static int launch_ring(const Ring& r, const int8_t* xq, const int8_t* wq, int M, int N, int K, const Epilogue& ep, hipStream_t st)
+{
+    return r.launch(xq, wq, M, N, K, r.group_m, r.by_xcd, ep, st);
+}
+static const Ring& choose_ring(int M, int N, int K, unsigned flags)
+{
+    const int kind = (flags & 4u) ? 2 : (flags & 3u) ? 1 : 0;
+    const float stages = (float)(K / kBK);
+    int best = 0;
+    float best_us = 0.0f;
+    for (int i = 0; i < kNumRings; ++i) {
+        const Ring& r = kRings[i];
+        const float mean = (float)((((int64_t)M + r.bm - 1) / r.bm) * (((int64_t)N + r.bn - 1) / r.bn)) / 256.0f;   // tiles per compute unit
+        const float most = ceilf(mean), tiles = r.smooth * most + (1.0f - r.smooth) * mean;
+        const float rounds = most > r.wgs ? r.smooth * ceilf(most / r.wgs) + (1.0f - r.smooth) * mean / r.wgs : 1.0f;
+        const float a = rounds * r.chain * stages, b = tiles * r.work * stages;
+        const float us = r.fixed + cbrtf(a * a * a + b * b * b) + tiles * r.out[kind];
+        if (i == 0 || us < best_us) {
+            best = i;
+            best_us = us;
+        }
+    }
+    return kRings[best];
+}
 
 // What the staged kernels can take.
 static bool gemm_staged_eligible(const int8_t* xq, const int8_t* wq, int64_t M, int64_t N, int64_t K)
@@ -76,8 +138,17 @@ static bool gemm_staged_eligible(const int8_t* xq, const int8_t* wq, int64_t M, 
     return M > 0 && N > 0;
 }
 
-int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, int64_t K64, const Epilogue& ep, hipStream_t st)
+int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, int64_t K64, const Epilogue& ep_in, hipStream_t st)
 {
+    Epilogue ep = ep_in;
+    // Which fp32 outputs are stored with the non-temporal hint.  Beyond a quarter of the 256 MB Infinity Cache they could not stay
+    // cached until their reader runs anyway, and kept out they neither evict the next kernels' inputs nor leave dirty lines
+    // to drain under them (whole BERT-Large layer step 5-6 % faster).  Below the 32 MB that the L2s hold they would all be dirty
+    // there at the end of the kernel, which waits for them to be written back (4096 x 768 x 768 8.4 -> 6.8 us, 4096 x 768 x 3072
+    // 18.2 -> 16.5, BERT-Base layer 32 x 128 127 -> 125.5).  In between the hint costs the reader as much as it gains (stored-scale BERT-Large
+    // layer 359.3 -> 356.5 us without it).
+    const double y_mib = (double)M64 * (double)N64 * 4.0 / (1 << 20);
+    ep.stream_out = y_mib > 64.0 || y_mib < 32.0;
     int v = g_variant;
     if (v == 0 && K64 <= kScalarMaxK && M64 * N64 <= kScalarMaxProducts / (K64 > 0 ? K64 : 1)) {
         hipLaunchKernelGGL(gemm_scalar_kernel, dim3((unsigned)((M64 * N64 + 255) / 256)), dim3(256), 0, st, xq, wq, M64, N64, K64, ep);
@@ -85,16 +156,26 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
     }
     if (v == kVariantDirect || !gemm_staged_eligible(xq, wq, M64, N64, K64)) return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);
     const int M = (int)M64, N = (int)N64, K = (int)K64;
+    if (v >= kVariantRing) {
+        if (v < kVariantRing + kNumRings && ring_eligible(ep)) return launch_ring(kRings[v - kVariantRing], xq, wq, M, N, K, ep, st);
+        v = 0;
+    }
     if (v == 0) {
         // Launches that leave compute units idle are bound by the chain of stages each workgroup walks, so they get the
         // smallest tile that still fits the chip in one round.  One 32x32 tile per unit, the reduction split over eight
-        // waves: 256 x 768 x 3072 6.5 us against 8.4 with 64x64 tiles and 14.7 with 128x128, 128 x 768 x 768 4.1 against
-        // 4.4 and 6.1; at 288 such tiles (384 x 768 x 768) the 64x64 ones are ahead, 4.4 against 4.8.  Two 64x64 tiles
-        // per unit: 651 x 768 x 3072 8.7 us against 15.1 with 128x128, 651 x 2304 x 768 (396 tiles) 6.8 against 8.0,
-        // 2048 x 1024 x 1024 (512) 8.0 against 8.8; at 576 (1024 x 2304 x 768) the large tiles win, 8.2 against 9.5.
+        // waves: 256 x 768 x 3072 6.5 us against 8.4 with 64x64 tiles, 128 x 768 x 768 4.1 against 4.4; at 288 such tiles
+        // (384 x 768 x 768) the 64x64 ones are ahead, 4.4 against 4.8.  Long reductions: two 64x64 tiles per unit with five
+        // stages in flight (651 x 768 x 3072 8.2 us against 14.6 with 128x128).  Short ones: many workgroups a unit instead of deep
+        // pipelines (choose_ring); from 16 stages on the large staged tiles come out even or ahead (4096 x 768 x 3072 15.5 us against
+        // 17.0 with the best ring, 12288 x 1024 x 4096 47.5 against 53.8).
         const int64_t tiles32 = (((int64_t)M + 31) / 32) * (((int64_t)N + 31) / 32);
         const int64_t tiles64 = (((int64_t)M + 63) / 64) * (((int64_t)N + 63) / 64);
         if (tiles32 <= 256) return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);
+        // (A plain launch that is one round of 192x256 tiles stays there: BERT-Large attention-output inside the dynamic FC
+        // step 302.6 us against 305.3.)
+        const int64_t tiles192x256 = (((int64_t)M + 191) / 192) * (((int64_t)N + 255) / 256);
+        const bool one_round = ep.flags == 0 && tiles192x256 > 224 && tiles192x256 <= 256;
+        if (K < 2048 && ring_eligible(ep) && !one_round) return launch_ring(choose_ring(M, N, K, ep.flags), xq, wq, M, N, K, ep, st);
         if (tiles64 <= 512) v = kVariant64;
     }
     if (v == 0) {
@@ -105,15 +186,13 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
         // come from timing each FC of a BERT-Large layer inside the whole layer step, where the
         // outputs of the neighbouring kernels keep the HBM busy (timings of a GEMM run alone, its
         // operands and output warm in the caches, rank the shapes differently and do not carry
-        // over): long reductions favour the 192x256 tiles (most MFMAs per byte staged); short ones
-        // the paired tiles -- 128x128 with its three-deep w ring when the output is fp32, 192x128
-        // when the epilogue writes int8.
-        struct Cand { int variant, bm, bn, per_cu; double prior_long, prior_short_f32, prior_short_i8; };
+        // over): long reductions favour the 192x256 tiles (most MFMAs per byte staged); short ones -- here
+        // only with a residual or an accumulator dump -- the paired tiles.
+        struct Cand { int variant, bm, bn, per_cu; double prior_long, prior_short; };
         static const Cand cands[] = {
-            {5, 192, 256, 1, 1.00, 0.97, 0.90}, {4, 192, 256, 1, 0.99, 0.90, 0.85}, {2, 256, 256, 1, 0.96, 0.97, 0.95},
-            {6, 192, 128, 2, 0.95, 0.93, 1.00}, {3, 128, 128, 2, 0.90, 1.00, 0.97},
+            {5, 192, 256, 1, 1.00, 0.97}, {4, 192, 256, 1, 0.99, 0.90}, {2, 256, 256, 1, 0.96, 0.97},
+            {6, 192, 128, 2, 0.95, 0.93}, {3, 128, 128, 2, 0.90, 1.00},
         };
-        const bool int8_out = (ep.flags & 4u) != 0;
         double best = -1.0;
         for (const Cand& c : cands) {
             const int64_t tm = (M + c.bm - 1) / c.bm, tn = (N + c.bn - 1) / c.bn, tiles = tm * tn;
@@ -121,18 +200,9 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
             // rounds of the launch: a last round that fills at most one workgroup per unit of a paired
             // shape runs unshared and ends early
             const int64_t slots = 256 * c.per_cu, full = tiles / slots, rem = tiles % slots;
-            // a short reduction whose fp32 epilogue carries the GELU: inside the BERT-Large layer step the paired
-            // 192x128 tile wins it (314 us for the whole dynamic step against 320 with 256x256 and 321 with 128x128);
-            // at BERT-Base size (4096 x 3072 x 768) one three-quarter-full round of 256x256 tiles beats one and a
-            // half rounds of 128x128 by 7 us of the 147 us layer: the epilogue of the half-empty last round of a
-            // paired shape has nothing to hide under, so it is counted as a whole round here
-            const bool gelu_f32_short = K < 2048 && !int8_out && (ep.flags & 1u);
-            const double rounds =
-                (double)full + (rem == 0 ? 0.0 : (c.per_cu == 2 && rem <= 256 && !gelu_f32_short) ? 0.6 : 1.0);
+            const double rounds = (double)full + (rem == 0 ? 0.0 : (c.per_cu == 2 && rem <= 256) ? 0.6 : 1.0);
             const double slots_used = ((double)tiles / (double)slots) / rounds;
-            double prior = K >= 2048 ? c.prior_long : (int8_out ? c.prior_short_i8 : c.prior_short_f32);
-            if (gelu_f32_short && c.variant == 6) prior = 1.05;
-            if (gelu_f32_short && c.variant == 2) prior = 1.04;
+            const double prior = K >= 2048 ? c.prior_long : c.prior_short;
             const double score = prior * slots_used * inside;
             if (score > best) {
                 best = score;

@@ -31,6 +31,34 @@ __device__ __forceinline__ int xcd_remap(int b, int g)
     return xcd < rem ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
 }
 
+// Tile of the pid-th workgroup: panels of group_m tile rows, column-major inside a panel.
+__device__ __forceinline__ int tile_of_workgroup(int pid, int tiles_m, int tiles_n, int group_m)
+{
+    const int panel = pid / (group_m * tiles_n), first = panel * group_m;
+    const int rows = min(group_m, tiles_m - first), in_panel = pid - panel * group_m * tiles_n;
+    return (first + in_panel % rows) * tiles_n + in_panel / rows;
+}
+
+// Abs-max of a workgroup's outputs into *out: one atomic max, through `scratch` (LDS of kWaves dwords that nothing else uses any more).
+template <int kWaves>
+__device__ __forceinline__ void publish_amax(unsigned amax, unsigned* scratch, float* out)
+{
+    __syncthreads();
+    amax = wave_max_u32(amax);
+    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = amax;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) amax = max(amax, scratch[w]);
+        // The running maximum only grows, so a workgroup whose own maximum does not exceed
+        // what is already there (read past the non-coherent L2) has nothing to add: after
+        // the first few workgroups almost none issues the read-modify-write, which
+        // serialises on one address.
+        unsigned* slot = reinterpret_cast<unsigned*>(out);
+        if (amax > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(slot, amax);
+    }
+}
+
 typedef __attribute__((address_space(3))) char* lds_ptr_t;
 
 // Raw buffer descriptor (gfx9 layout): 48-bit base, stride 0, num_records in bytes.
@@ -163,16 +191,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, mfma_waves_per_simd(BM, BN, SB, WGM*
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned lds_base = (unsigned)(size_t)(lds_ptr_t)lds;
 
-    // tile id -> (tm, tn): panels of group_m tile rows, column-major inside a panel
-    int pid = xcd_remap(blockIdx.x, gridDim.x);
-    const int tiles_m = gridDim.x / tiles_n;
-    {
-        int panel = pid / (group_m * tiles_n);
-        int first = panel * group_m;
-        int rows = min(group_m, tiles_m - first);
-        int in_panel = pid - panel * group_m * tiles_n;
-        pid = (first + in_panel % rows) * tiles_n + in_panel / rows;
-    }
+    const int pid = tile_of_workgroup(xcd_remap(blockIdx.x, gridDim.x), gridDim.x / tiles_n, tiles_n, group_m);
     const int m0 = (pid / tiles_n) * BM;
     const int n0 = (pid % tiles_n) * BN;
 
@@ -412,12 +431,6 @@ __global__ __launch_bounds__(WGM* WGN * 64, mfma_waves_per_simd(BM, BN, SB, WGM*
             reinterpret_cast<char*>(ep.y) + tile_row0 * esize, 0, BM * N * esize, 0x00020000);
         const __amdgpu_buffer_rsrc_t racc = __builtin_amdgcn_make_buffer_rsrc(
             do_dump ? ep.acc_out + tile_row0 : ep.acc_out, 0, do_dump ? BM * N * 4 : 0, 0x00020000);
-        // An fp32 y larger than a quarter of the 256 MB Infinity Cache is stored non-temporally:
-        // it could not stay cached until its consumer runs anyway, and kept out it neither evicts
-        // the next kernels' inputs nor leaves dirty lines to drain under them (whole BERT-Large
-        // layer step 5-6 % faster; a GEMM timed alone with a cache-resident output does not show
-        // it).  Smaller outputs are left for the cache to hand to their consumer.
-        const bool stream_out = (int64_t)M * N * 4 > ((int64_t)64 << 20);
         float famax = 0.0f;
         if constexpr (kGen) fetch_first_residuals();
         auto store_tile = [&](auto ntc) {
@@ -455,7 +468,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, mfma_waves_per_simd(BM, BN, SB, WGM*
             });
         });
         };
-        if (stream_out && !do_req)
+        if (ep.stream_out && !do_req)
             store_tile(std::true_type{});
         else
             store_tile(std::false_type{});
@@ -492,23 +505,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, mfma_waves_per_simd(BM, BN, SB, WGM*
         });
     }
     if constexpr (kGen || (kEpi & 2) != 0) {
-        if (do_amax) {  // one atomic max per workgroup; the stage buffers are dead by now
-            unsigned* wave_amax = reinterpret_cast<unsigned*>(lds);
-            __syncthreads();
-            amax = wave_max_u32(amax);
-            if (lane == 0) wave_amax[wave] = amax;
-            __syncthreads();
-            if (threadIdx.x == 0) {
-#pragma unroll
-                for (int w = 1; w < NW; ++w) amax = max(amax, wave_amax[w]);
-                // The running maximum only grows, so a workgroup whose own maximum does not exceed
-                // what is already there (read past the non-coherent L2) has nothing to add: after
-                // the first few workgroups almost none issues the read-modify-write, which
-                // serialises on one address.
-                unsigned* slot = reinterpret_cast<unsigned*>(ep.out_amax);
-                if (amax > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(slot, amax);
-            }
-        }
+        if (do_amax) publish_amax<NW>(amax, reinterpret_cast<unsigned*>(lds), ep.out_amax);  // the stage buffers are dead by now
     }
 #endif
 }

@@ -21,6 +21,7 @@ struct Epilogue {
     const float* next_scale;  // fp32[1] or null
     const float* residual;    // fp32[M,N] added to the fp32 output (may be y itself), or null
     unsigned flags;
+    int stream_out;           // store an fp32 y with the non-temporal hint (set by launch_gemm)
 };
 
 int launch_absmax(const float* x, int64_t n, float* amax_out, float* scale_out, hipStream_t st);

@@ -77,3 +77,16 @@ def test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, variant, of
     _, _, acc = run(variant, x, w, 3, dump=True)
     bq = O.quantize_bias(b.cpu().numpy(), N, 24.0, [900.0])
     np.testing.assert_array_equal(acc.cpu().numpy(), O.gemm_i8(xh, wh, bq, threads=8))
+
+
+@pytest.mark.parametrize("variant,bm,bn", [(9, 64, 64), (10, 64, 64), (11, 128, 64), (12, 128, 128), (13, 192, 128)])
+@pytest.mark.parametrize("dm,dn,K", [(0, 0, 128), (1, 1, 256), (-1, -1, 384), (0, 7, 512), (33, 0, 1152)])
+def test_ring_gemm_equals_the_staged_kernel(q8, variant, bm, bn, dm, dn, K):
+    """The tiles with few stage buffers: fewer stages than buffers, as many, more; whole tiles, one row or column more or less."""
+    test_small_and_ragged_gemm_equals_the_staged_kernel(q8, 2 * bm + dm, K, 3 * bn + dn, variant, 0)
+
+
+@pytest.mark.parametrize("M,K,N", [(1100, 512, 500), (2050, 384, 1030), (2050, 1920, 520), (2050, 2048, 520), (4100, 256, 1540), (6200, 256, 2050), (2900, 128, 4100)])
+def test_ring_gemm_choice_equals_the_staged_kernel(q8, M, K, N):
+    """What the rule takes for ragged launches of a few to many tiles per compute unit."""
+    test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, 0, 0)
