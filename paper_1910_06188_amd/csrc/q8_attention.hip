@@ -208,6 +208,14 @@ __device__ __forceinline__ float4 buf_f4(__amdgpu_buffer_rsrc_t r, unsigned off)
     return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
 }
 
+// The mask row of a stage; without a mask an empty descriptor, whose loads return zeros.  (Loaded under a branch on the mask, the value was
+// waited for at the branch's end, and with it everything requested before it, in every trip.)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t mask_rsrc(const float* mrow, int stage, int S)
+{
+    const int keys = min(S - stage * kAtKB, kAtKB);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(mrow) + (mrow ? (int64_t)stage * kAtKB : 0), 0, mrow && keys > 0 ? 4 * keys : 0, 0x00020000);
+}
+
 // Global -> registers -> (split) -> LDS staging of a stage.  An item is eight numbers: of the K tile eight columns of one
 // key, of the V tile the eight keys one half-wave takes to a 16-key step, of one column.  Descriptors span one stage
 // of one sequence, so offsets are 32 bits whatever the size of qkv, and rows beyond the sequence read as zeros.
@@ -264,7 +272,7 @@ struct AttnStager {
         for (int i = 0; i < kItems; ++i)
 #pragma unroll
             for (int u = 0; u < 2; ++u) k[kSet][i][u] = buf_f4(r, k_off[i][u]);
-        if (mrow) m[kSet] = mrow[min(stage * kAtKB + (tid & (kAtKB - 1)), S32 - 1)];
+        m[kSet] = buf_f1(mask_rsrc(mrow, stage, S32), 4u * (unsigned)(tid & (kAtKB - 1)));
     }
     template <int kSet>
     __device__ __forceinline__ void fetch_v(int stage)
