@@ -8,7 +8,9 @@
 // squared deviations are accumulated in binary64 and reduced across the wave in a fixed order,
 // and the normalisation itself runs in binary64 with one final rounding, so the result is within
 // an ulp of the exact one and the same bytes come out on every run.  The kernel is bound by
-// memory: the binary64 arithmetic (about ten operations per element) hides under the loads.
+// memory: the binary64 arithmetic (about ten operations per element) hides under the loads where there are other rows to load; what is
+// left in small launches is the chain load - two reductions - store.  8192 x 768 with residual 17.0 -> 15.4 us, 12288 x 1024
+// 28.9 -> 28.4 (5.3 TB/s) and 19.8 -> 18.9 without, from rows behind descriptors, the estimate of 1 / sqrt and the skipped vectors.
 #include "q8_device.h"
 #include "q8_launch.h"
 
@@ -18,6 +20,7 @@ constexpr int kLnThreads = 256;            // four waves = four rows per workgro
 constexpr int kLnMaxVec = 8;               // float4 vectors per lane: rows up to 64 * 4 * 8 = 2048 columns
 constexpr int kLnRowsShort = 2;           // rows a wave carries side by side: plain LayerNorm of rows of at most 1024 columns (with a
                                           // residual or the embedding rows in front the extra registers cost more than they win)
+constexpr int kLnOneTrip = 4096;          // rows that 1024 workgroups take in one trip
 constexpr int kLnSlots = 2048;             // abs-max slots (= Q8_AMAX_SLOTS): one per workgroup, the rest zero
 
 // Sum of a double over the 64 lanes, the same value in every lane, in a fixed order (so the same bytes come out on
@@ -47,11 +50,31 @@ __device__ __forceinline__ double wave_sum_f64(double v)
 // 16-byte load with the non-temporal hint: the inputs of a LayerNorm are read exactly once, and streamed
 // past the Infinity Cache they leave it to the tensors that are read again (layer step with the fused
 // LayerNorms 5 % faster with dynamic scales, 9 % with stored ones).
-typedef float f32x4_ln __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 load_f4_nt_ln(const float4* p)
+// Rows are addressed through a descriptor that ends with the row (and is empty for a row that does not exist): what lies behind
+// it reads as zeros and is not stored, without a branch around every access.
+typedef unsigned u32x4_ln __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* base, int64_t row, int64_t rows, int row_bytes)
 {
-    const f32x4_ln v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_ln*>(p));
-    return make_float4(v.x, v.y, v.z, v.w);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(reinterpret_cast<const char*>(base)) + (row < rows ? row * row_bytes : 0), 0,
+                                             row < rows ? row_bytes : 0, 0x00020000);
+}
+template <int kAux>
+__device__ __forceinline__ float4 load_f4_ln(__amdgpu_buffer_rsrc_t r, int off)
+{
+    const u32x4_ln v = __builtin_bit_cast(u32x4_ln, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kAux));
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
+}
+constexpr int kNt = 2;  // non-temporal
+
+// 1 / sqrt(v), v >= 0: the hardware's estimate (about 2^-23) and two Newton steps, good to the last places of binary64.  The
+// library's square root and division are four times as many dependent operations, and every row waits for them.
+__device__ __forceinline__ double rsqrt_f64(double v)
+{
+    double y = __builtin_amdgcn_rsq(v);
+    const double h = 0.5 * v;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) y = __builtin_fma(y, __builtin_fma(-h * y, y, 0.5), y);
+    return y;
 }
 
 struct EmbedSrc {
@@ -74,19 +97,24 @@ __device__ __forceinline__ float4 dequant4_ln(unsigned packed, float r)
 
 // kSrc: 0 = x is a; 1 = x is a + r (one binary32 addition); 2 = x is the sum of three
 // dequantized embedding rows, (word + position) + type as in the plain lookup.
+// kEarly: launches of one trip, rows of up to 1024 columns.  gamma and beta are requested under the statistics instead of where they are
+// used, no next trip's rows are (128 x 768 with residual 3.7 -> 3.2 us, 1024 x 768 5.3 -> 4.7, 4096 x 768 9.7 -> 9.1).  Longer launches have other rows of the
+// workgroup to wait under, and no registers for it.
 // H % 4 == 0, H <= 256 * kVec (kVec float4 vectors per lane: 4 for rows of up to 1024 columns -- fewer registers, more
 // waves in flight -- 8 up to 2048), every pointer 16-byte aligned (tables 4-byte).
-template <int kSrc, int kVec, int kRows>
-__global__ __launch_bounds__(kLnThreads) void layernorm_rows_kernel(const float* a, const float* r, EmbedSrc es,
+template <int kSrc, int kVec, int kRows, bool kEarly>
+__global__ __launch_bounds__(kLnThreads, kEarly ? 4 : 1) void layernorm_rows_kernel(const float* a, const float* r, EmbedSrc es,
                                                                      const float* __restrict__ gamma,
-                                                                     const float* __restrict__ beta, double eps,
+                                                                     const float* __restrict__ beta, double eps, double inv_h,
                                                                      int64_t M, int H, float* y,
                                                                      unsigned* __restrict__ amax_slots,
                                                                      const float* __restrict__ q_scale,
                                                                      unsigned* __restrict__ q_out)
 {
     __shared__ unsigned wave_amax[kLnThreads / 64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (amax_slots)  // slots no workgroup owns
+        for (int i = gridDim.x + blockIdx.x * kLnThreads + threadIdx.x; i < kLnSlots; i += gridDim.x * kLnThreads) amax_slots[i] = 0u;
     const int nvec = H >> 2;
     const float qs = q_out ? q_scale[0] : 0.0f;
     float amax = 0.0f;
@@ -108,20 +136,17 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_rows_kernel(const float*
     auto request_rows = [&](int64_t r0) {
 #pragma unroll
         for (int q = 0; q < kRows; ++q) {
-            const int64_t row = r0 + q;
-            const float4* av = reinterpret_cast<const float4*>(a) + row * nvec;
-            const float4* rv = kSrc == 1 ? reinterpret_cast<const float4*>(r) + row * nvec : nullptr;
+            const auto av = row_rsrc(a, r0 + q, M, 4 * H), rv = row_rsrc(kSrc == 1 ? r : a, r0 + q, M, 4 * H);
 #pragma unroll
             for (int j = 0; j < kVec; ++j) {
-                const int v = j * 64 + lane;
-                const bool in = row < M && v < nvec;
-                na[q][j] = in ? load_f4_nt_ln(&av[v]) : make_float4(0.f, 0.f, 0.f, 0.f);
-                if (kSrc == 1) nr[q][j] = in ? load_f4_nt_ln(&rv[v]) : make_float4(0.f, 0.f, 0.f, 0.f);
+                na[q][j] = load_f4_ln<kNt>(av, 16 * (j * 64 + lane));
+                if (kSrc == 1) nr[q][j] = load_f4_ln<kNt>(rv, 16 * (j * 64 + lane));
             }
         }
     };
     const int64_t first_row0 = ((int64_t)blockIdx.x * kWaves + wave) * kRows;
     if (kSrc != 2 && first_row0 < M) request_rows(first_row0);
+    const auto rg = row_rsrc(gamma, 0, 1, 4 * H), rb = row_rsrc(beta, 0, 1, 4 * H);
     for (int64_t row0 = first_row0; row0 < M; row0 += row_step) {
         float4 x[kRows][kVec];
         bool live[kRows];
@@ -157,55 +182,66 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_rows_kernel(const float*
                 }
             }
         }
-        if (kSrc != 2 && row0 + row_step < M) request_rows(row0 + row_step);
+        if (kSrc != 2 && !kEarly && row0 + row_step < M) request_rows(row0 + row_step);
+        float4 ge[kVec], be[kVec];
+        if (kEarly) {
+            int lane16 = 16 * lane;
+            asm volatile("" : "+v"(lane16));   // here: as loop invariants they would be converted ahead of the loop, which takes 32 registers more
+#pragma unroll
+            for (int j = 0; j < kVec; ++j) {
+                ge[j] = load_f4_ln<0>(rg, 1024 * j + lane16);
+                be[j] = load_f4_ln<0>(rb, 1024 * j + lane16);
+            }
+        }
         double mean[kRows], rstd[kRows];
 #pragma unroll
         for (int q = 0; q < kRows; ++q) {
             double s = 0.0;
 #pragma unroll
-            for (int j = 0; j < kVec; ++j)  // lanes past the row hold zeros
+            for (int j = 0; j < kVec; ++j) {  // lanes past the row hold zeros
+                if (j * 64 >= nvec) continue;
                 s += ((double)x[q][j].x + (double)x[q][j].y) + ((double)x[q][j].z + (double)x[q][j].w);
+            }
             mean[q] = s;
         }
 #pragma unroll
-        for (int q = 0; q < kRows; ++q) mean[q] = wave_sum_f64(mean[q]) / (double)H;
+        for (int q = 0; q < kRows; ++q) mean[q] = wave_sum_f64(mean[q]) * inv_h;
 #pragma unroll
         for (int q = 0; q < kRows; ++q) {
             double ss = 0.0;
 #pragma unroll
             for (int j = 0; j < kVec; ++j) {
-                if (j * 64 + lane < nvec) {
-                    const double d0 = (double)x[q][j].x - mean[q], d1 = (double)x[q][j].y - mean[q];
-                    const double d2 = (double)x[q][j].z - mean[q], d3 = (double)x[q][j].w - mean[q];
-                    ss += (d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3);
-                }
+                if (j * 64 >= nvec) continue;
+                const double d0 = (double)x[q][j].x - mean[q], d1 = (double)x[q][j].y - mean[q];
+                const double d2 = (double)x[q][j].z - mean[q], d3 = (double)x[q][j].w - mean[q];
+                const double part = __builtin_fma(d0, d0, d1 * d1) + __builtin_fma(d2, d2, d3 * d3);
+                ss += j * 64 + lane < nvec ? part : 0.0;
             }
             rstd[q] = ss;
         }
 #pragma unroll
-        for (int q = 0; q < kRows; ++q) rstd[q] = 1.0 / sqrt(wave_sum_f64(rstd[q]) / (double)H + eps);
+        for (int q = 0; q < kRows; ++q) rstd[q] = rsqrt_f64(wave_sum_f64(rstd[q]) * inv_h + eps);
 #pragma unroll
         for (int q = 0; q < kRows; ++q) {
-            if (!live[q]) continue;
-            const int64_t row = row0 + q;
-            float4* yv = reinterpret_cast<float4*>(y) + row * nvec;
+            const auto ry = row_rsrc(y, row0 + q, M, 4 * H), rq = row_rsrc(q_out, row0 + q, q_out ? M : 0, H);
 #pragma unroll
             for (int j = 0; j < kVec; ++j) {
+                if (j * 64 >= nvec) continue;
                 const int v = j * 64 + lane;
-                if (v < nvec) {
-                    const float4 g = reinterpret_cast<const float4*>(gamma)[v], b = reinterpret_cast<const float4*>(beta)[v];
-                    float4 o;
-                    o.x = (float)(((double)x[q][j].x - mean[q]) * rstd[q] * (double)g.x + (double)b.x);
-                    o.y = (float)(((double)x[q][j].y - mean[q]) * rstd[q] * (double)g.y + (double)b.y);
-                    o.z = (float)(((double)x[q][j].z - mean[q]) * rstd[q] * (double)g.z + (double)b.z);
-                    o.w = (float)(((double)x[q][j].w - mean[q]) * rstd[q] * (double)g.w + (double)b.w);
-                    yv[v] = o;
-                    if (q_out)  // stored-scale quantizer of the next FC (Eq. 1 on the rounded fp32 value), 4 codes per lane
-                        q_out[row * nvec + v] = ((unsigned)quantize_code(o.x, qs) & 0xffu) | (((unsigned)quantize_code(o.y, qs) & 0xffu) << 8) |
-                                                (((unsigned)quantize_code(o.z, qs) & 0xffu) << 16) | ((unsigned)quantize_code(o.w, qs) << 24);
-                    amax = __builtin_fmaxf(amax, __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(o.x), __builtin_fabsf(o.y)),
-                                                                __builtin_fmaxf(__builtin_fabsf(o.z), __builtin_fabsf(o.w))));
-                }
+                const float4 g = kEarly ? ge[j] : load_f4_ln<0>(rg, 16 * v), b = kEarly ? be[j] : load_f4_ln<0>(rb, 16 * v);
+                float4 o;   // zero where gamma and beta end
+                o.x = (float)__builtin_fma(((double)x[q][j].x - mean[q]) * rstd[q], (double)g.x, (double)b.x);
+                o.y = (float)__builtin_fma(((double)x[q][j].y - mean[q]) * rstd[q], (double)g.y, (double)b.y);
+                o.z = (float)__builtin_fma(((double)x[q][j].z - mean[q]) * rstd[q], (double)g.z, (double)b.z);
+                o.w = (float)__builtin_fma(((double)x[q][j].w - mean[q]) * rstd[q], (double)g.w, (double)b.w);
+                const u32x4_ln ob = {__float_as_uint(o.x), __float_as_uint(o.y), __float_as_uint(o.z), __float_as_uint(o.w)};
+                __builtin_amdgcn_raw_buffer_store_b128(ob, ry, 16 * v, 0, 0);
+                if (q_out)  // stored-scale quantizer of the next FC (Eq. 1 on the rounded fp32 value), 4 codes per lane
+                    __builtin_amdgcn_raw_buffer_store_b32(((unsigned)quantize_code(o.x, qs) & 0xffu) | (((unsigned)quantize_code(o.y, qs) & 0xffu) << 8) |
+                                                              (((unsigned)quantize_code(o.z, qs) & 0xffu) << 16) | ((unsigned)quantize_code(o.w, qs) << 24),
+                                                          rq, 4 * v, 0, 0);
+                const float most = __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(o.x), __builtin_fabsf(o.y)), __builtin_fmaxf(__builtin_fabsf(o.z), __builtin_fabsf(o.w)));
+                if (live[q]) amax = __builtin_fmaxf(amax, most);
             }
         }
     }
@@ -218,8 +254,6 @@ __global__ __launch_bounds__(kLnThreads) void layernorm_rows_kernel(const float*
             for (int w = 1; w < kLnThreads / 64; ++w) m = max(m, wave_amax[w]);
             amax_slots[blockIdx.x] = m;
         }
-        if (blockIdx.x == 0)  // slots no workgroup owns
-            for (int i = gridDim.x + threadIdx.x; i < kLnSlots; i += kLnThreads) amax_slots[i] = 0u;
     }
 }
 
@@ -330,17 +364,17 @@ int launch_layernorm(const float* a, const float* r, const float* gamma, const f
     if (fast) {
         if (r)
             if (H <= 1024)
-                hipLaunchKernelGGL((layernorm_rows_kernel<1, 4, 1>), dim3(ln_grid(M, 1)), block, 0, st, a, r, es, gamma, beta, (double)eps, M,
-                               (int)H, y, slots, q_scale, reinterpret_cast<unsigned*>(q_out));
+                hipLaunchKernelGGL((M <= kLnOneTrip ? layernorm_rows_kernel<1, 4, 1, true> : layernorm_rows_kernel<1, 4, 1, false>), dim3(ln_grid(M, 1)), block, 0, st, a, r,
+                                   es, gamma, beta, (double)eps, 1.0 / (double)H, M, (int)H, y, slots, q_scale, reinterpret_cast<unsigned*>(q_out));
             else
-                hipLaunchKernelGGL((layernorm_rows_kernel<1, 8, 1>), grid, block, 0, st, a, r, es, gamma, beta, (double)eps, M,
+                hipLaunchKernelGGL((layernorm_rows_kernel<1, 8, 1, false>), grid, block, 0, st, a, r, es, gamma, beta, (double)eps, 1.0 / (double)H, M,
                                (int)H, y, slots, q_scale, reinterpret_cast<unsigned*>(q_out));
         else
             if (H <= 1024)
-                hipLaunchKernelGGL((layernorm_rows_kernel<0, 4, kLnRowsShort>), dim3(ln_grid(M, kLnRowsShort)), block, 0, st, a, r, es, gamma, beta, (double)eps, M,
+                hipLaunchKernelGGL((layernorm_rows_kernel<0, 4, kLnRowsShort, false>), dim3(ln_grid(M, kLnRowsShort)), block, 0, st, a, r, es, gamma, beta, (double)eps, 1.0 / (double)H, M,
                                (int)H, y, slots, q_scale, reinterpret_cast<unsigned*>(q_out));
             else
-                hipLaunchKernelGGL((layernorm_rows_kernel<0, 8, 1>), grid, block, 0, st, a, r, es, gamma, beta, (double)eps, M,
+                hipLaunchKernelGGL((layernorm_rows_kernel<0, 8, 1, false>), grid, block, 0, st, a, r, es, gamma, beta, (double)eps, 1.0 / (double)H, M,
                                (int)H, y, slots, q_scale, reinterpret_cast<unsigned*>(q_out));
     } else {
         if (r)
@@ -378,11 +412,11 @@ int launch_embedding_sum3_layernorm(const int8_t* word, int64_t Vw, const int8_t
     const dim3 grid(ln_grid(T)), block(kLnThreads);
     if (fast)
         if (H <= 1024)
-                hipLaunchKernelGGL((layernorm_rows_kernel<2, 4, 1>), dim3(ln_grid(T, 1)), block, 0, st, nullptr, nullptr, es, gamma, beta,
-                           (double)eps, T, (int)H, y, slots, q_scale, reinterpret_cast<unsigned*>(q_out));
+                hipLaunchKernelGGL((T <= kLnOneTrip ? layernorm_rows_kernel<2, 4, 1, true> : layernorm_rows_kernel<2, 4, 1, false>), dim3(ln_grid(T, 1)), block, 0, st,
+                                   nullptr, nullptr, es, gamma, beta, (double)eps, 1.0 / (double)H, T, (int)H, y, slots, q_scale, reinterpret_cast<unsigned*>(q_out));
             else
-                hipLaunchKernelGGL((layernorm_rows_kernel<2, 8, 1>), grid, block, 0, st, nullptr, nullptr, es, gamma, beta,
-                           (double)eps, T, (int)H, y, slots, q_scale, reinterpret_cast<unsigned*>(q_out));
+                hipLaunchKernelGGL((layernorm_rows_kernel<2, 8, 1, false>), grid, block, 0, st, nullptr, nullptr, es, gamma, beta,
+                           (double)eps, 1.0 / (double)H, T, (int)H, y, slots, q_scale, reinterpret_cast<unsigned*>(q_out));
     else
         hipLaunchKernelGGL(layernorm_generic_kernel<2>, grid, block, 0, st, nullptr, nullptr, es, word, pos, typ, gamma,
                            beta, (double)eps, T, H, y, slots, q_scale, q_out);

@@ -166,3 +166,27 @@ def test_layernorm_argument_checks(q8):
     assert lib.q8_embedding_sum3_layernorm(p, 4, p, 4, p, 4, p, 4, None, p, p, 2, p, p, 1e-12, p, None, None, None, None, None) == 1
     assert lib.q8_embedding_sum3_layernorm(p, 4, p, 4, p, 4, p, 0, p, p, p, 2, p, p, 1e-12, p, None, None, None, None, None) == 2
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("M,H", [(4096, 260), (4097, 260), (4099, 1024), (8200, 252), (4100, 1028), (1023, 12)])
+@pytest.mark.parametrize("with_residual", [False, True])
+def test_layernorm_of_one_trip_and_of_several(q8, M, H, with_residual):
+    """Both sides of the launches of one trip, rows that end inside a vector of the wave or fill all of them."""
+    test_layernorm_absmax(q8, M, H, with_residual)
+
+
+def test_layernorm_writes_its_rows_only(q8):
+    """Ragged rows between guards: nothing in front of, between or behind the rows is touched, and what lies behind the inputs does
+    not matter."""
+    M, H = 37, 300
+    g = synth.rng(77)
+    a, r = synth.activations(g, M, H), synth.activations(g, M, H)
+    gamma, beta = params(g, H)
+    pad = lambda x: torch.cat([dev(x).reshape(-1), torch.full((256,), float("nan"), device="cuda")])
+    buf = torch.full((M * H + 512,), 7.0, device="cuda")
+    codes = torch.full((M * H + 512,), 5, dtype=torch.int8, device="cuda")
+    q8.q8_layernorm_absmax(pad(a)[:M * H].view(M, H), pad(gamma)[:H], pad(beta)[:H], buf[256:256 + M * H].view(M, H), eps=1e-12, residual=pad(r)[:M * H].view(M, H),
+                           q_scale=torch.tensor([30.0], device="cuda"), q_out=codes[256:256 + M * H].view(M, H))
+    close(host(buf[256:256 + M * H].view(M, H)), O.layernorm(a, gamma, beta, eps=1e-12, residual=r))
+    assert bool((buf[:256] == 7.0).all()) and bool((buf[256 + M * H:] == 7.0).all())
+    assert bool((codes[:256] == 5).all()) and bool((codes[256 + M * H:] == 5).all())
