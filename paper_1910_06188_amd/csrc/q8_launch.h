@@ -58,7 +58,7 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M, int64_t N, int64_
 int launch_gemm_direct(const int8_t* xq, const int8_t* wq, int64_t M, int64_t N, int64_t K, const Epilogue& ep, hipStream_t st);
 
 // The dynamic-quantization FC layer of at most 32 tokens in one launch (q8_fc_small.hip): every workgroup runs the
-// quantizer itself and keeps the codes in LDS.  Eligible: M <= 32, M * K <= 16384, K a multiple of 128 up to 1024,
+// quantizer itself and keeps the codes in LDS.  Eligible: M <= 32, K a multiple of 128 up to 1024,
 // 16-byte aligned x and wq, no abs-max epilogue.  scal_out[0] = max|x|, scal_out[1] = S_x, xq_out = the codes.
 bool fc_small_eligible(const float* x, const int8_t* wq, int64_t M, int64_t N, int64_t K, unsigned flags);
 int launch_fc_small(const float* x, const int8_t* wq, int64_t M, int64_t N, int64_t K, int8_t* xq_out, float* scal_out,

@@ -706,6 +706,12 @@ def test_linear_f32_few_tokens_one_launch(q8, M, K, N, groups):
             np.testing.assert_array_equal(host(y), O.quantize(host(yf), ns_h))     # codes of the GPU's own fp32 outputs
 
 
+@pytest.mark.parametrize("M,K,N,groups", [(32, 1024, 200, 2), (32, 768, 64, 1), (31, 896, 33, 1), (23, 640, 129, 3), (33, 1024, 64, 1), (32, 128, 31, 1)])
+def test_linear_f32_few_tokens_one_launch_to_its_end(q8, M, K, N, groups):
+    """Up to all 32 rows of 1024 columns, and one row more."""
+    test_linear_f32_few_tokens_one_launch(q8, M, K, N, groups)
+
+
 @pytest.mark.parametrize("n", [4096, 16383, 16384, 16385])
 def test_linear_f32_small_tensor_single_launch_boundary(q8, n):
     """Around the size up to which one workgroup does abs-max, scale and quantize in one launch: same bytes on
