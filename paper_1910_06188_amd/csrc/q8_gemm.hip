@@ -13,8 +13,8 @@
 // conflicts; the swizzle costs nothing on the way in because each lane of a
 // direct-to-LDS load picks its own global address while the LDS side stays linear.
 //
-// Short reductions go to the kernel of q8_gemm_ring_kernel.h, the same but for how it overlaps; any other K or alignment, and
-// launches of at most 256 tiles of 32x32, to the kernel of q8_gemm_direct.hip; a handful of products to the one-thread-per-output
+// Short reductions go to the kernel of q8_gemm_ring_kernel.h, the same but for how it overlaps, and so does any K that is a multiple of
+// 4; any other K or alignment, and launches of at most 256 tiles of 32x32, go to the kernel of q8_gemm_direct.hip; a handful of products to the one-thread-per-output
 // kernel below.
 #include "q8_device.h"
 #include "q8_epilogue.h"
@@ -102,6 +102,12 @@ static const Ring kRings[] = {
 constexpr int kNumRings = sizeof(kRings) / sizeof(kRings[0]);
 
 // That kernel has no accumulator dump and no residual, and only the flag combinations that mean something.
+static bool ring_operands_eligible(const int8_t* xq, const int8_t* wq, int64_t M, int64_t N, int64_t K)
+{
+    if (K < 1 || K % 4 != 0 || ((reinterpret_cast<uintptr_t>(xq) | reinterpret_cast<uintptr_t>(wq)) & 3)) return false;
+    const int64_t lim = (int64_t)1 << 31;  // 32-bit offsets span one tile of 192 rows
+    return M > 0 && N > 0 && M < lim && N < lim && K < (lim / 192) - 256 && ((M + 63) / 64) * ((N + 63) / 64) < lim;
+}
 static bool ring_eligible(const Epilogue& ep) { return !ep.acc_out && !ep.residual && ep.flags <= 5u; }
 static int launch_ring(const Ring& r, const int8_t* xq, const int8_t* wq, int M, int N, int K, const Epilogue& ep, hipStream_t st)
 {
@@ -110,7 +116,7 @@ static int launch_ring(const Ring& r, const int8_t* xq, const int8_t* wq, int M,
 static const Ring& choose_ring(int M, int N, int K, unsigned flags)
 {
     const int kind = (flags & 4u) ? 2 : (flags & 3u) ? 1 : 0;
-    const float stages = (float)(K / kBK);
+    const float stages = (float)((K + kBK - 1) / kBK);
     int best = 0;
     float best_us = 0.0f;
     for (int i = 0; i < kNumRings; ++i) {
@@ -154,7 +160,19 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
         hipLaunchKernelGGL(gemm_scalar_kernel, dim3((unsigned)((M64 * N64 + 255) / 256)), dim3(256), 0, st, xq, wq, M64, N64, K64, ep);
         return hipGetLastError() == hipSuccess ? 0 : 1;
     }
-    if (v == kVariantDirect || !gemm_staged_eligible(xq, wq, M64, N64, K64)) return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);
+    if (v == kVariantDirect) return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);
+    if (!gemm_staged_eligible(xq, wq, M64, N64, K64)) {
+        // Rows that are 4-byte aligned whatever their width go to the rings from more than one 32x32 tile per compute unit on: 777 x 1000 x
+        // 520 (425 tiles) 5.9 us against 6.9 with the direct kernel, 700 x 60 x 600 4.3 against 5.9, 2000 x 520 x 2000 8.8 against 18.4,
+        // 16000 x 60 x 300 8.0 against 16.6; with 100 tiles (300 x 1000 x 300) 5.6 against 5.5, with 90 of 4092 columns 12.2 against 7.3.  Long
+        // reductions in one round of 32x32 tiles are the direct kernel's, whose waves share them (600 x 2100 x 500, 304 tiles: 8.0 against 8.3).
+        const int64_t t32 = ((M64 + 31) / 32) * ((N64 + 31) / 32);
+        if (ring_operands_eligible(xq, wq, M64, N64, K64) && ring_eligible(ep) && (v >= kVariantRing || t32 > (K64 < 2048 ? 256 : 512))) {
+            const Ring& r = v >= kVariantRing && v < kVariantRing + kNumRings ? kRings[v - kVariantRing] : choose_ring((int)M64, (int)N64, (int)K64, ep.flags);
+            return launch_ring(r, xq, wq, (int)M64, (int)N64, (int)K64, ep, st);
+        }
+        return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);
+    }
     const int M = (int)M64, N = (int)N64, K = (int)K64;
     if (v >= kVariantRing) {
         if (v < kVariantRing + kNumRings && ring_eligible(ep)) return launch_ring(kRings[v - kVariantRing], xq, wq, M, N, K, ep, st);

@@ -21,7 +21,9 @@ namespace q8 {
 
 // kWgs: workgroups per compute unit the kernel is compiled for (they share the unit's 160 KiB of LDS and its registers).
 // kEpi: the combination of Q8_EPI_GELU (1), Q8_EPI_ABSMAX (2) and Q8_EPI_REQUANT (4); no accumulator dump, no residual.
-template <int BM, int BN, int WGM, int WGN, int kSlots, int kWgs, int kEpi>
+// kTail: K is any multiple of 4 and rows are 4-byte aligned (all that the loads need); the last stage then holds the front of the next
+// rows behind the end of K, and the x operand is cleared there.  Else K is a multiple of 128.
+template <int BM, int BN, int WGM, int WGN, int kSlots, int kWgs, int kEpi, bool kTail>
 __global__ __launch_bounds__(WGM* WGN * 64, kWgs* WGM* WGN / 4) void gemm_ring_kernel(const int8_t* __restrict__ X, const int8_t* __restrict__ W, int M, int N,
                                                                                      int K, int tiles_n, int group_m, int by_xcd, Epilogue ep)
 {
@@ -62,7 +64,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, kWgs* WGM* WGN / 4) void gemm_ring_k
         const int r = (wave * B_LOADS + i) * 8 + (lane >> 3);
         b_off[i] = (unsigned)min(r, rows_b - 1) * (unsigned)K + (unsigned)(((lane & 7) ^ swizzle_of_row(r)) * 16);
     }
-    const int KT = K / kBK;
+    const int KT = kTail ? (K + kBK - 1) / kBK : K / kBK;
     auto load_stage = [&](int kt, int slot) {
         const bool live = kt < KT;  // past the end of K: empty descriptor, nothing is fetched
         const v4i qa = make_rsrc(Xt, live ? bytes_a : 0u), qb = make_rsrc(Wt, live ? bytes_b : 0u);
@@ -130,6 +132,15 @@ __global__ __launch_bounds__(WGM* WGN * 64, kWgs* WGM* WGN / 4) void gemm_ring_k
             for (int f = 0; f < FM; ++f) fa[ks & 1][f] = *reinterpret_cast<const v4i*>(stage + a_row[f] + (((ks * 2 + hi) ^ a_sw[f]) << 4));
 #pragma unroll
             for (int f = 0; f < FN; ++f) fb[ks & 1][f] = *reinterpret_cast<const v4i*>(stage + b_row[f] + (((ks * 2 + hi) ^ b_sw[f]) << 4));
+            if constexpr (kTail) {
+                if (kt == KT - 1) {
+                    const int left = K - kt * kBK - ks * 32 - hi * 16;  // bytes of K this lane's operand still covers
+#pragma unroll
+                    for (int f = 0; f < FM; ++f)
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) fa[ks & 1][f][w] = 4 * w < left ? fa[ks & 1][f][w] : 0;
+                }
+            }
         };
         read_step(0);
 #pragma unroll
@@ -220,8 +231,16 @@ int launch_ring(const int8_t* xq, const int8_t* wq, int M, int N, int K, int gro
 {
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const dim3 grid(tiles_m * tiles_n), block(WGM * WGN * 64);
-#define Q8_LAUNCH_EPI(E) \
-    case E: hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, kSlots, kWgs, E>), grid, block, 0, st, xq, wq, M, N, K, tiles_n, group_m, by_xcd, ep); break
+    const bool tail = K % kBK != 0;
+#define Q8_LAUNCH_EPI(E)                                                                                                                       \
+    case E:                                                                                                                                    \
+        if (tail)                                                                                                                              \
+            hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, kSlots, kWgs, E, true>), grid, block, 0, st, xq, wq, M, N, K, tiles_n, group_m, \
+                               by_xcd, ep);                                                                                                    \
+        else                                                                                                                                   \
+            hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, kSlots, kWgs, E, false>), grid, block, 0, st, xq, wq, M, N, K, tiles_n, group_m, \
+                               by_xcd, ep);                                                                                                    \
+        break
     switch (ep.flags) {
         Q8_LAUNCH_EPI(0);
         Q8_LAUNCH_EPI(1);

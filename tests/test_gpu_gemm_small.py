@@ -90,3 +90,17 @@ def test_ring_gemm_equals_the_staged_kernel(q8, variant, bm, bn, dm, dn, K):
 def test_ring_gemm_choice_equals_the_staged_kernel(q8, M, K, N):
     """What the rule takes for ragged launches of a few to many tiles per compute unit."""
     test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, 0, 0)
+
+
+@pytest.mark.parametrize("variant", [9, 10, 11, 12, 13])
+@pytest.mark.parametrize("M,K,N,off", [(70, 4, 70, 0), (130, 36, 129, 4), (200, 124, 66, 8), (193, 132, 130, 12), (129, 256, 128, 4), (257, 500, 190, 0), (65, 1020, 64, 4)])
+def test_ring_gemm_of_any_multiple_of_four(q8, variant, M, K, N, off):
+    """Widths that end inside a stage, a 32-byte step or a 16-byte operand, rows 4 bytes aligned: what lies behind the end of K -- the
+    next row, or nothing -- does not count."""
+    test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, variant, off)
+
+
+@pytest.mark.parametrize("M,K,N,off", [(777, 1000, 520, 0), (513, 36, 545, 4), (512, 1000, 512, 0), (544, 1000, 512, 0), (600, 2100, 500, 0), (700, 2100, 800, 0), (1024, 768, 520, 4), (1024, 998, 520, 0)])
+def test_ring_gemm_choice_of_ragged_widths(q8, M, K, N, off):
+    """Both sides of the rule: 256 and 272 tiles, short and long reductions, rows that are only 2-byte aligned."""
+    test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, 0, off)
