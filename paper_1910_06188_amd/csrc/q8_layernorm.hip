@@ -205,7 +205,10 @@ __global__ __launch_bounds__(kLnThreads, kEarly ? 4 : 1) void layernorm_rows_ker
             mean[q] = s;
         }
 #pragma unroll
-        for (int q = 0; q < kRows; ++q) mean[q] = wave_sum_f64(mean[q]) * inv_h;
+        for (int q = 0; q < kRows; ++q) {  // the quotient by H, rounded once: a row of equal numbers has that number as its mean
+            const double sum = wave_sum_f64(mean[q]), m0 = sum * inv_h;
+            mean[q] = __builtin_fma(__builtin_fma(-m0, (double)H, sum), inv_h, m0);
+        }
 #pragma unroll
         for (int q = 0; q < kRows; ++q) {
             double ss = 0.0;

@@ -190,3 +190,17 @@ def test_layernorm_writes_its_rows_only(q8):
     close(host(buf[256:256 + M * H].view(M, H)), O.layernorm(a, gamma, beta, eps=1e-12, residual=r))
     assert bool((buf[:256] == 7.0).all()) and bool((buf[256 + M * H:] == 7.0).all())
     assert bool((codes[:256] == 5).all()) and bool((codes[256 + M * H:] == 5).all())
+
+
+@pytest.mark.parametrize("M,H", [(5, 768), (4100, 768), (3, 1000), (2, 1028), (2, 2052)])
+@pytest.mark.parametrize("with_residual", [False, True])
+def test_layernorm_of_rows_of_equal_numbers_is_beta(q8, M, H, with_residual):
+    """The mean of equal numbers is that number (H times it is exact in binary64, and so is the rounded quotient): nothing is left to
+    normalise, whatever the size of the number."""
+    g = synth.rng(91 + H)
+    a = np.repeat((g.standard_normal(M) * 10.0 ** g.integers(-3, 9, M)).astype(np.float32)[:, None], H, 1)
+    gamma, beta = params(g, H)
+    beta[::2] = 0.0
+    y = torch.full((M, H), 9.0, device="cuda")
+    q8.q8_layernorm_absmax(dev(a), dev(gamma), dev(beta), y, eps=1e-12, residual=dev(a) if with_residual else None)
+    np.testing.assert_array_equal(host(y), np.repeat(beta[None], M, 0))
