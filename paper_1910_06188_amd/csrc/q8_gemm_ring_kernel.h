@@ -7,7 +7,8 @@
 // workgroups.  Here a workgroup holds kSlots stage buffers of 128 bytes of K (one: it loads a stage, waits, multiplies) and
 // the overlap is between the two to eight workgroups of a unit, each at another point of its tile; tiles are also small
 // enough to spread a launch evenly over the units.  Operand and LDS layout are those of the other kernel.
-// Against the best of its shapes, outputs rotating through more than the Infinity Cache, us:
+// The other kernel -> the best shape of a sweep of tiles and slots, outputs rotating through more than the Infinity Cache, us (five of the
+// shapes are built; the best of the five is within 3 % of these where another one is named):
 //   4096 x  768 x  768   9.2 ->  6.9 (128x64, three slots)        4096 x  768 x 3072        20.8 -> 16.3 (64x64, two slots)
 //   8192 x  768 x 3072  28.3 -> 22.7 (128x96, two slots)          4096 x 3072 x  768 + GELU 20.0 -> 17.2 (128x64, one slot)
 //   1536 x 3072 x  768 + GELU 12.7 -> 9.2 (64x64, one slot)      12288 x 3072 x 1024        54   -> 48.6 (192x128, one slot)
@@ -22,7 +23,7 @@ namespace q8 {
 // kWgs: workgroups per compute unit the kernel is compiled for (they share the unit's 160 KiB of LDS and its registers).
 // kEpi: the combination of Q8_EPI_GELU (1), Q8_EPI_ABSMAX (2) and Q8_EPI_REQUANT (4); no accumulator dump, no residual.
 // kTail: K is any multiple of 4 and rows are 4-byte aligned (all that the loads need); the last stage then holds the front of the next
-// rows behind the end of K, and the x operand is cleared there.  Else K is a multiple of 128.
+// rows behind the end of K -- or zeros, behind the end of the tile -- and the x operand is cleared there.  Else K is a multiple of 128.
 template <int BM, int BN, int WGM, int WGN, int kSlots, int kWgs, int kEpi, bool kTail>
 __global__ __launch_bounds__(WGM* WGN * 64, kWgs* WGM* WGN / 4) void gemm_ring_kernel(const int8_t* __restrict__ X, const int8_t* __restrict__ W, int M, int N,
                                                                                      int K, int tiles_n, int group_m, int by_xcd, Epilogue ep)
@@ -67,10 +68,18 @@ __global__ __launch_bounds__(WGM* WGN * 64, kWgs* WGM* WGN / 4) void gemm_ring_k
     const int KT = kTail ? (K + kBK - 1) / kBK : K / kBK;
     auto load_stage = [&](int kt, int slot) {
         const bool live = kt < KT;  // past the end of K: empty descriptor, nothing is fetched
-        const v4i qa = make_rsrc(Xt, live ? bytes_a : 0u), qb = make_rsrc(Wt, live ? bytes_b : 0u);
         const unsigned koff = live ? (unsigned)(kt * kBK) : 0u, dst = lds_base + (unsigned)(slot * SLOT);
-        static_for<0, A_LOADS>([&](auto ic) { lds_dma16_run<decltype(ic)::value>(qa, a_off[decltype(ic)::value], koff, dst + wave * A_LOADS * 1024); });
-        static_for<0, B_LOADS>([&](auto ic) { lds_dma16_run<decltype(ic)::value>(qb, b_off[decltype(ic)::value], koff, dst + A_BYTES + wave * B_LOADS * 1024); });
+        if constexpr (kTail) {
+            // The last row's operands may end behind the matrix, so the stage is part of the descriptor: the bounds check is documented for
+            // the vector offset alone.  No immediate offsets either: with rows shorter than 128 bytes the vector offset would fall below them.
+            const v4i qa = make_rsrc(Xt + koff, live ? bytes_a - koff : 0u), qb = make_rsrc(Wt + koff, live ? bytes_b - koff : 0u);
+            static_for<0, A_LOADS>([&](auto ic) { lds_dma16_first(qa, a_off[decltype(ic)::value], 0u, dst + (wave * A_LOADS + decltype(ic)::value) * 1024); });
+            static_for<0, B_LOADS>([&](auto ic) { lds_dma16_first(qb, b_off[decltype(ic)::value], 0u, dst + A_BYTES + (wave * B_LOADS + decltype(ic)::value) * 1024); });
+        } else {
+            const v4i qa = make_rsrc(Xt, live ? bytes_a : 0u), qb = make_rsrc(Wt, live ? bytes_b : 0u);
+            static_for<0, A_LOADS>([&](auto ic) { lds_dma16_run<decltype(ic)::value>(qa, a_off[decltype(ic)::value], koff, dst + wave * A_LOADS * 1024); });
+            static_for<0, B_LOADS>([&](auto ic) { lds_dma16_run<decltype(ic)::value>(qb, b_off[decltype(ic)::value], koff, dst + A_BYTES + wave * B_LOADS * 1024); });
+        }
     };
 
     const int wm = wave / WGN, wn = wave % WGN;
