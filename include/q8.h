@@ -120,9 +120,9 @@ q8_status q8_quantize_amax(const float* x, int64_t n, const float* amax, int n_a
  *   (one atomic max per workgroup lands in it).
  *   Epilogue order: dequantize, GELU, abs-max, requantize.
  * M, N >= 0 (either 0: nothing is written); 0 <= K <= Q8_MAX_K; sizes are otherwise
- * free -- shapes with K % 128 == 0 and 16-byte aligned xq/wq take the MFMA kernels with
- * operands staged straight into LDS, anything else one that loads them through registers,
- * with identical results (large launches: at about a quarter of the rate).
+ * free -- shapes with K % 128 == 0 and 16-byte aligned xq/wq, and launches of some size with K % 4 == 0 and
+ * 4-byte aligned ones, take the MFMA kernels with operands staged straight into LDS, anything else one that
+ * loads them through registers, with identical results (large launches: at about a quarter of the rate).
  * bq + sum must fit int32 (it wraps otherwise; unreachable for BERT-sized biases).
  */
 q8_status q8_linear(const int8_t* xq, const int8_t* wq, const float* bias,
@@ -151,7 +151,7 @@ q8_status q8_linear_residual(const int8_t* xq, const int8_t* wq, const float* bi
  * The dynamic quantizer of Section 4.1 on its own: a = max|x| over the whole tensor, S = 127 / a (Eq. 3; 1.0 when
  * a is 0), q = Quantize(x | S, 127) (Eq. 1) -- two launches (per-workgroup partial maxima, then a quantize pass
  * that folds them); one launch for tensors of at most 16384 elements, and one launch that reads x only once for
- * tensors the chip can hold in registers between the two steps (up to half a million elements, and from 1.05 M
+ * tensors the chip can hold in registers between the two steps (up to 524288 elements, and from 2.62 M
  * to 12.5 M on 256 compute units; multiples of 4; see q8_debug_set_quantize_one_pass).  Same results as q8_absmax followed by q8_quantize in every case.
  *   x fp32[n]; q int8[n]; n >= 0 (n = 0: a = 0, S = 1).
  *   scal_work fp32[Q8_SCAL_WORK], caller-provided scratch: on return scal_work[0] = a, scal_work[1] = S (a device

@@ -633,9 +633,14 @@ constexpr int kRqThreads = 1024;
 constexpr int kRqVec = 12;  // float4 per thread
 constexpr int kRqMaxGroups = 256;
 constexpr int kRqRing = 64;
-constexpr int64_t kRqSmall = 524288;  // elements up to which a grid smaller than the chip pays
+constexpr int kRqSmallVec = 2, kRqSmallGroups = 64;  // the instance for small tensors
+constexpr int64_t kRqSmall = 524288, kRqLarge = 2621440;  // elements up to which, and from which on, one pass pays (see resident_fits)
+static_assert(kRqSmall <= (int64_t)kRqSmallGroups * kRqThreads * kRqSmallVec * 4, "a small tensor fits the small instance");
 static __device__ unsigned long long g_rq_slots[kRqRing][kRqMaxGroups];
 
+// kVec: float4 per thread.  kGroups: the most workgroups, a multiple of 64 (one poll of a wave reads 64 slots).  Two instances: with 12 and
+// 256 small tensors waited for ten bounds checks and three empty polls (98 304 elements 5.1 us, with 2 and 64 4.1; 400 000 6.3 and 5.4).
+template <int kVec, int kGroups>
 __global__ __launch_bounds__(kRqThreads) void quantize_resident_kernel(const float4* __restrict__ x4, int n4,
                                                                         unsigned long long* slots, unsigned ticket,
                                                                         unsigned spin_limit, float* amax_out,
@@ -644,19 +649,19 @@ __global__ __launch_bounds__(kRqThreads) void quantize_resident_kernel(const flo
 {
     __shared__ unsigned wave_part[kRqThreads / 64];
     __shared__ unsigned folded;
-    __shared__ unsigned long long missing[kRqMaxGroups / 64];
+    __shared__ unsigned long long missing[kGroups / 64];
     const int G = (int)gridDim.x, w = (int)blockIdx.x, t = (int)threadIdx.x;
     // Workgroup w holds the 16 KiB blocks w, w + G, w + 2 G, ...: the k-th loads of all workgroups together are one
     // contiguous window of x, which is the order the memory system likes best (see absmax_thread).
-    float4 v[kRqVec];
+    float4 v[kVec];
     unsigned m = 0u;
 #pragma unroll
-    for (int k = 0; k < kRqVec; ++k) {
+    for (int k = 0; k < kVec; ++k) {
         const int idx = (k * G + w) * kRqThreads + t;
         v[k] = idx < n4 ? load_f4_nt(&x4[idx]) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
 #pragma unroll
-    for (int k = 0; k < kRqVec; ++k)
+    for (int k = 0; k < kVec; ++k)
         m = max(m, max(max(abs_bits(v[k].x), abs_bits(v[k].y)), max(abs_bits(v[k].z), abs_bits(v[k].w))));
     m = wave_max_u32(m);
     if ((t & 63) == 0) wave_part[t >> 6] = m;
@@ -670,7 +675,7 @@ __global__ __launch_bounds__(kRqThreads) void quantize_resident_kernel(const flo
             a = 0u;
             bool all_here = true;
 #pragma unroll
-            for (int r = 0; r < kRqMaxGroups / 64; ++r) {
+            for (int r = 0; r < kGroups / 64; ++r) {
                 const int i = r * 64 + t;
                 bool here = true;  // slots past the grid count as arrived
                 if (i < G) {
@@ -694,13 +699,13 @@ __global__ __launch_bounds__(kRqThreads) void quantize_resident_kernel(const flo
     unsigned extra = 0u;
     bool scanned = false;
 #pragma unroll 1
-    for (int r = 0; r < kRqMaxGroups / 64; ++r) {
+    for (int r = 0; r < kGroups / 64; ++r) {
         unsigned long long absent = missing[r];
         while (absent) {
             const int g = r * 64 + __builtin_ctzll(absent);
             absent &= absent - 1ull;
             scanned = true;
-            for (int k = 0; k < kRqVec; ++k) {
+            for (int k = 0; k < kVec; ++k) {
                 const int i = (k * G + g) * kRqThreads + t;
                 if (i < n4) {
                     const float4 u = x4[i];
@@ -726,7 +731,7 @@ __global__ __launch_bounds__(kRqThreads) void quantize_resident_kernel(const flo
         if (zero_slot) zero_slot[0] = 0.0f;
     }
 #pragma unroll
-    for (int k = 0; k < kRqVec; ++k) {
+    for (int k = 0; k < kVec; ++k) {
         const int idx = (k * G + w) * kRqThreads + t;
         if (idx < n4) q4[idx] = pack4(v[k], s);
     }
@@ -828,14 +833,16 @@ void set_quantize_resident(bool enabled, unsigned polls)
     g_rq_spin_limit.store(polls);
 }
 
-// What the registers of the grid hold, and is worth the barrier: a tensor that fills the grid is read from memory once; a
-// small one takes as many workgroups as it fills, one launch and a short barrier (us in one pass / in two: 20 000 elements
-// 4.2 / 6.3, 98 304 5.3 / 6.6, 400 000 6.0 / 6.5, but 777 000 6.6 / 6.5 and 1 000 000 7.0 / 6.3: the barrier grows with the
-// workgroups while the second launch stays the same).
+// What the registers of the grid hold, and is worth the barrier, whose cost grows with the workgroups while a second launch stays the
+// same.  Large tensors, one workgroup on every unit: reading once is ahead from about 2.6 M elements on (us in one pass / in two: 3.1 M
+// 8.8 / 8.9, 4.2 M 9.5 / 9.8, 6.3 M 11.4 / 12.7; below, the second reading comes out of the caches, 2.1 M 8.1 / 7.4, 1.6 M 7.9 / 6.9, 1.05 M
+// 7.2 / 6.7).  Small ones as long as 64 workgroups hold them with two float4 a thread (98 304 4.1 / 6.0, 200 000 4.8 / 5.7, 400 000 5.4 / 6.0; one
+// float4 a thread is no faster below 50 000 and slower from 98 304 on, three and more are slower everywhere).
 static bool resident_fits(int64_t n, int units)
 {
     const int64_t n4 = n >> 2, groups = std::min(units, kRqMaxGroups);
-    return n4 <= groups * kRqThreads * kRqVec && (n <= kRqSmall || n4 >= groups * kRqThreads);
+    if (n <= kRqSmall) return n4 <= groups * kRqThreads * kRqSmallVec;
+    return n >= kRqLarge && n4 <= groups * kRqThreads * kRqVec;
 }
 
 // 0: launched.  1: the runtime refused the launch.  2: not a case for this kernel (the caller takes the two-pass path):
@@ -848,9 +855,11 @@ int launch_quantize_resident(const float* x, int64_t n, float* amax_out, float* 
     if (ring.slots && (unsigned)(ring.seq + 1) == 0u) ring = ring_entry(g_rq_ring, st, resident_fits, n);   // ticket 0: the slots start as zeros
     if (!ring.slots) return 2;
     const int64_t n4 = n >> 2;
-    const int groups = (int)std::min<int64_t>(std::min(ring.units, kRqMaxGroups), (n4 + kRqThreads - 1) / kRqThreads);
-    hipLaunchKernelGGL(quantize_resident_kernel, dim3(groups), dim3(kRqThreads), 0, st, reinterpret_cast<const float4*>(x),
-                       (int)n4, ring.slots, (unsigned)(ring.seq + 1), g_rq_spin_limit.load(), amax_out, scale_out,
+    const bool small = n <= kRqSmall;
+    const int64_t share = (int64_t)kRqThreads * (small ? kRqSmallVec : 1);
+    const int groups = (int)std::min<int64_t>(std::min(ring.units, kRqMaxGroups), (n4 + share - 1) / share);
+    hipLaunchKernelGGL((small ? quantize_resident_kernel<kRqSmallVec, kRqSmallGroups> : quantize_resident_kernel<kRqVec, kRqMaxGroups>), dim3(groups), dim3(kRqThreads),
+                       0, st, reinterpret_cast<const float4*>(x), (int)n4, ring.slots, (unsigned)(ring.seq + 1), g_rq_spin_limit.load(), amax_out, scale_out,
                        reinterpret_cast<unsigned*>(q), zero_slot);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }

@@ -872,6 +872,15 @@ def test_quantize_dynamic_register_resident_sizes(q8, n, where, mode):
     np.testing.assert_array_equal(host(q), q_ref)
 
 
+@pytest.mark.parametrize("mode", ["one_pass", "never_wait", "two_pass"])
+@pytest.mark.parametrize("n,where", [(16_388, -1), (24_572, 0), (24_576, 8191), (24_580, 16_400), (65_536, -1), (516_100, 250_000), (524_288, -1), (524_292, 0),
+                                     (2_621_436, -1), (2_621_440, 1_048_600), (4_200_004, -1)])
+def test_quantize_dynamic_register_resident_edges(q8, n, where, mode):
+    """Edges of the small instance's shares, the largest small tensor and the smallest large one, and their neighbours on the two-pass
+    path."""
+    test_quantize_dynamic_register_resident_sizes(q8, n, where, mode)
+
+
 def test_quantize_dynamic_one_pass_all_zero_and_repeated_calls(q8):
     """An all-zero tensor takes S = 1; and the barrier's slots carry a new ticket on every launch, so a maximum
     left by an earlier, larger tensor is never picked up."""
