@@ -77,7 +77,7 @@ static int g_variant = 0;
 void set_gemm_variant(int v) { g_variant = v; }
 
 // Variants 1 to 6 are the staged tile shapes of full launches, 7 the small one with deep rings, 8 the direct kernel, 9 and up the rings.
-constexpr int kVariant64 = 7, kVariantDirect = 8, kVariantRing = 9;
+constexpr int kVariant192x256 = 5, kVariant64 = 7, kVariantDirect = 8, kVariantRing = 9;
 
 // The shapes of q8_gemm_ring_kernel.h and what a launch of each takes (us): `fixed`, the longer of two times per stage of K -- the
 // chain a workgroup walks (`chain`, per round of workgroups) and the work of a compute unit (`work`, per tile) -- and the
@@ -189,12 +189,17 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
         const int64_t tiles32 = (((int64_t)M + 31) / 32) * (((int64_t)N + 31) / 32);
         const int64_t tiles64 = (((int64_t)M + 63) / 64) * (((int64_t)N + 63) / 64);
         if (tiles32 <= 256) return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);
-        // (A plain launch that is one round of 192x256 tiles stays there: BERT-Large attention-output inside the dynamic FC
-        // step 302.6 us against 305.3.)
+        // A plain launch that is one round of 192x256 tiles, more than two thirds full, stores 33 to 48 MiB for the caches, which the rings'
+        // smaller tiles pay for: 4096 x 2304 x 768 15.1 us against 19.1 with the ring of the rule and 15.6 with the best one, 12288 x 768 x 768
+        // 15.4 / 19.6 / 16.1, 3072 x 3072 x 1536 20.4 / 23.1 / 22.6, 4608 x 2304 x 512 13.7 / 13.5 / 13.3; with 168 to 176 such tiles (2688 x 3072 x
+        // 1024, 4096 x 2048 x 768) 14.5 / 13.2 and 14.6 / 14.2.
         const int64_t tiles192x256 = (((int64_t)M + 191) / 192) * (((int64_t)N + 255) / 256);
-        const bool one_round = ep.flags == 0 && tiles192x256 > 224 && tiles192x256 <= 256;
-        if (K < 2048 && ring_eligible(ep) && !one_round) return launch_ring(choose_ring(M, N, K, ep.flags), xq, wq, M, N, K, ep, st);
-        if (tiles64 <= 512) v = kVariant64;
+        const bool one_round = ep.flags == 0 && tiles192x256 > 176 && tiles192x256 <= 256;
+        if (K < 2048 && ring_eligible(ep)) {
+            if (!one_round) return launch_ring(choose_ring(M, N, K, ep.flags), xq, wq, M, N, K, ep, st);
+            v = kVariant192x256;
+        }
+        if (v == 0 && tiles64 <= 512) v = kVariant64;
     }
     if (v == 0) {
         // Pick the tile shape with the best expected use of the chip: the fraction of the launch's

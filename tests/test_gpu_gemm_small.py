@@ -104,3 +104,9 @@ def test_ring_gemm_of_any_multiple_of_four(q8, variant, M, K, N, off):
 def test_ring_gemm_choice_of_ragged_widths(q8, M, K, N, off):
     """Both sides of the rule: 256 and 272 tiles, short and long reductions, rows that are only 2-byte aligned."""
     test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, 0, off)
+
+
+@pytest.mark.parametrize("M,K,N", [(2112, 128, 4096), (2100, 256, 4100), (3072, 384, 3000), (3073, 128, 4090)])
+def test_gemm_choice_around_one_round_of_large_tiles(q8, M, K, N):
+    """176 and 187 tiles of 192 x 256 rows and columns, 192, and more than 256."""
+    test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, 0, 0)
