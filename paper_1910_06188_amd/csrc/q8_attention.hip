@@ -7,24 +7,20 @@
 // written directly (Eq. 1) and ctx itself need not be stored at all.
 //
 // FP32 products on the bf16 matrix pipes.  A binary32 number is the exact sum of three bf16 numbers h + m + l (8 + 8 + 8
-// significant bits, each part the rounded remainder of the ones before it), so a product is nine bf16 products.  The six
-// largest run on v_mfma_f32_32x32x16_bf16; m l and l m (below 2^-25 of the product, 2^-28 in the mean square) and l l (2^-34)
-// are left out.  The h h products have an accumulator of
-// their own and the others share one, joined by one addition of the
+// significant bits, each part the rounded remainder of the ones before it), so a product is nine bf16 products.  Eight of
+// them run on v_mfma_f32_32x32x16_bf16; l l, below 2^-34 of the product, is left out.  (m l and l m reach 2^-24 of it, half
+// a last place of binary32: without them a score of one nonzero term is up to 1.7 times as far from 64 bits as one rounded
+// product.)  The h h products have an accumulator of their own and the others share one, joined by one addition of the
 // vector ALU: an MFMA adds up products of like size exactly, and rounds to nearest where the accumulator is the larger, but
 // cuts an accumulator that is much smaller than its products off at the last place of the result (measured: errors up to one
-// last place instead of half, and a bias).  The bf16 pipes are 16 times as fast as the fp32 ones, and -- unlike the fp32 MFMAs,
-// which share their lanes with the vector ALU -- they run beside the softmax arithmetic.
-//
-// What is gained back elsewhere is more than the left-out products cost.  A probability is taken against a reference that is
-// zero for rows whose first scores lie within 2^+-8, so that a score of ordinary size meets no subtraction that rounds it at
-// the size of the row's maximum; where the reference is not zero the sums of the leading products start at its negative, so
-// scores come out of the matrix pipes as differences.  The denominator is summed stage by stage, and the final quotient is
-// rounded once.  Error against 64 bits, rms of ctx over rms, eight products with a subtracted maximum -> this: normal inputs
-// 32 x 128 tokens 1.51e-7 -> 1.34e-7, 8 x 384 2.08e-7 -> 1.73e-7, 1 x 2048 2.17e-7 -> 1.92e-7; Q and K three times larger,
-// 8 x 384 4.76e-7 -> 2.75e-7; scores of one nonzero column near 100 2.30e-6 -> 4.2e-7; two keys, one V row zero 5.0e-8 both.
-// BERT-Large attention (32 x 384 tokens, 16 heads of 64) 141-145 -> 117-120 us, 8 x 2048 810 -> 645, 8 x 256 x 12 heads of 128
-// 38.0 -> 31.6.
+// last place instead of half, and a bias).  The bf16 pipes are 16 times as fast as the fp32 ones, so eight products take half the time of
+// one fp32 MFMA pass, and -- unlike the fp32 MFMAs, which share their lanes with the vector ALU -- they run beside the
+// softmax arithmetic.  Error against 64 bits, rms of ctx over rms: normal inputs 32 x 128 tokens 1.5e-7 (fp32 pipes
+// 3.4e-7, six products in one accumulator 2.6e-7), 8 x 384 2.1e-7 (4.5e-7, 3.8e-7); scores of one nonzero column 2.30e-6
+// (2.30e-6, 2.58e-6).  BERT-Large attention: fp32 pipes 175 us, six products 117 us, eight 140 us
+// (144 with the look at the range).  Six products against a reference that stays at zero while the scores are small (106 to 109 us, eight on the
+// same box 127) are no way out: the mean error over normal inputs falls, but a score of one term loses what m l and l m are, and a
+// query with one visible key, whose probability is exactly 1 against the maximum of its scores, no longer gets its V row back bit for bit.
 //
 // Range.  The sum is exact, and the products lose nothing, while no number is near the ends of the type: from 3.3953e38 on
 // h rounds to infinity, and the lower parts of numbers below 2^-110 fall under the smallest bf16.  The kernels keep the largest
@@ -163,14 +159,12 @@ struct Frag3 {
 };
 __device__ __forceinline__ v8bf as_bf(v4u v) { return __builtin_bit_cast(v8bf, v); }
 
-// Partial product I of a . b: number 0 is h h.  The parts of a are used up one after the other (h, l, m).  Six of the nine: with
-// m l and l m as well the matrix pipes have a third more to do, and attention is bound by what a SIMD issues -- MFMAs and
-// vector instructions share the issue port while an MFMA is in flight, 4.7 cycles each (BERT-Large 142 us against 122).
-constexpr int kAtParts = 6;
+// Partial product I of a . b: number 0 is h h.  The parts of a are used up one after the other (h, l, m).
+constexpr int kAtParts = 8;
 template <int I>
 __device__ __forceinline__ v16f mfma_part(const Frag3& a, const Frag3& b, v16f acc)
 {
-    constexpr int pa[kAtParts] = {0, 0, 0, 2, 1, 1}, pb[kAtParts] = {0, 2, 1, 0, 1, 0};
+    constexpr int pa[kAtParts] = {0, 0, 0, 2, 2, 1, 1, 1}, pb[kAtParts] = {0, 2, 1, 1, 0, 2, 1, 0};
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf(a.part[pa[I]]), as_bf(b.part[pb[I]]), acc, 0, 0, 0);
 }
 __device__ __forceinline__ v16f zero16()
@@ -208,14 +202,6 @@ __device__ __forceinline__ float4 buf_f4(__amdgpu_buffer_rsrc_t r, unsigned off)
     return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
 }
 
-// The mask row of a stage; without a mask an empty descriptor, whose loads return zeros.  (Loaded under a branch on the mask, the value was
-// waited for at the branch's end, and with it everything requested before it, in every trip.)
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t mask_rsrc(const float* mrow, int stage, int S)
-{
-    const int keys = min(S - stage * kAtKB, kAtKB);
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(mrow) + (mrow ? (int64_t)stage * kAtKB : 0), 0, mrow && keys > 0 ? 4 * keys : 0, 0x00020000);
-}
-
 // Global -> registers -> (split) -> LDS staging of a stage.  An item is eight numbers: of the K tile eight columns of one
 // key, of the V tile the eight keys one half-wave takes to a 16-key step, of one column.  Descriptors span one stage
 // of one sequence, so offsets are 32 bits whatever the size of qkv, and rows beyond the sequence read as zeros.
@@ -232,18 +218,18 @@ struct AttnStager {
     unsigned k_off[kItems][2];    // byte offsets of an item's two float4 inside a stage
     unsigned v_off[kItems];
     int k_dst[kItems], v_dst[kItems];
-    // Rows in flight.  Set 0 holds what a trip stores: K of the stage two ahead and V of the next one, requested a trip earlier
-    // (two trips earlier is no faster, 118 us either way, and takes the 16 registers of the carried sums); the others are the prologue's.
-    float4 k[3][kItems][2];
-    float v[2][kItems][8];
-    float m[3];
+    // Rows in flight.  Set st & 1 holds what trip st stores: K of stage st + 2 and V of stage st + 1, requested two trips
+    // earlier; sets 2 and 3 are the prologue's.
+    float4 k[4][kItems][2];
+    float v[3][kItems][8];
+    float m[4];
     float largest;                // magnitude of the numbers split so far
     bool masked;                  // the mask row of the K stage stashed last is not all zeros (wave-uniform)
 
     __device__ __forceinline__ void init(int t)
     {
         tid = t;
-        m[0] = m[1] = m[2] = 0.0f;
+        m[0] = m[1] = m[2] = m[3] = 0.0f;
         largest = 0.0f;
         const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
 #pragma unroll
@@ -272,7 +258,7 @@ struct AttnStager {
         for (int i = 0; i < kItems; ++i)
 #pragma unroll
             for (int u = 0; u < 2; ++u) k[kSet][i][u] = buf_f4(r, k_off[i][u]);
-        m[kSet] = buf_f1(mask_rsrc(mrow, stage, S32), 4u * (unsigned)(tid & (kAtKB - 1)));
+        if (mrow) m[kSet] = mrow[min(stage * kAtKB + (tid & (kAtKB - 1)), S32 - 1)];
     }
     template <int kSet>
     __device__ __forceinline__ void fetch_v(int stage)
@@ -331,15 +317,15 @@ struct AttnStager {
     {
         constexpr int kHalf = 9 * kItems + 2;
         if constexpr (P < 9 * kItems)
-            stash_piece<0, false, P / 9, P % 9>(kSet);
+            stash_piece<kSet, false, P / 9, P % 9>(kSet);
         else if constexpr (P == 9 * kItems)
-            stash_mask<0>(kSet, k_stage);
+            stash_mask<kSet>(kSet, k_stage);
         else if constexpr (P == kHalf - 1)
-            fetch_k<0>(k_stage + 1);
+            fetch_k<kSet>(k_stage + 2);
         else if constexpr (P < kHalf + 9 * kItems)
-            stash_piece<0, true, (P - kHalf) / 9, (P - kHalf) % 9>(kSet ^ 1);
+            stash_piece<kSet, true, (P - kHalf) / 9, (P - kHalf) % 9>(kSet ^ 1);
         else if constexpr (P == kPieces - 1)
-            fetch_v<0>(k_stage);   // past the last stage: empty descriptors, nothing is read
+            fetch_v<kSet>(k_stage + 1);   // past the last stage: empty descriptors, nothing is read
     }
     // the same, all at once
     template <int kSet>
@@ -364,10 +350,8 @@ struct AttnStager {
 template <int kDB>
 struct AttnWave {
     Frag3 q[2 * kDB];   // the queries, times scale * log2 e, split: step j holds columns 16 j + 8 hi .. + 7
-    v16f r[kDB];        // sums of the small products of O^T, joined at the end: a join in every stage is 16 kDB additions
     v16f o[kDB];        // O^T: o[blk][e] = ctx[query lq][column 32 blk + 8 (e/4) + 4 hi + e%4], not yet normalised
-    float m_run;        // reference of the row's probabilities (log2 units)
-    bool above, below;  // some query of the wave has a reference above zero, below zero (wave-uniform)
+    float m_run;        // reference maximum (log2 units)
     float l_run;        // this lane's share of the running denominator
 };
 
@@ -390,20 +374,6 @@ __device__ __forceinline__ v16f attention_first_mfma(const char* mask_row, int h
     return mfma_part<1>(kf, w.q[0], s);
 }
 
-// First MFMA of the leading products of a stage's scores: their sums start at minus the query's reference, so that the scores
-// come out as differences to it.  Only where it is positive: a reference far below zero (leading keys masked off) would cost
-// the scores of the stage that leaves it behind their last bits, so that one is subtracted when the stage's own is known.
-template <int kDB>
-__device__ __forceinline__ v16f attention_lead_mfma(const AttnWave<kDB>& w, const Frag3& kf)
-{
-    if (!w.above) return mfma_part<0>(kf, w.q[0], zero16());
-    v16f s;
-    const float m = -at_max(w.m_run, 0.0f);
-#pragma unroll
-    for (int e = 0; e < 16; ++e) s[e] = m;
-    return mfma_part<0>(kf, w.q[0], s);
-}
-
 // Part kP of 2 of the maximum of a lane's sixteen scores.
 template <int kP>
 __device__ __forceinline__ void attention_max_piece(const v16f& s, float& mx)
@@ -414,50 +384,33 @@ __device__ __forceinline__ void attention_max_piece(const v16f& s, float& mx)
     asm volatile("" : "+v"(mx));   // here, and not where it is used
 }
 
-// The reference against which probabilities are taken, from the maximum `mx` of the lane's scores (less `base`, what their sums
-// started from).  Zero until a query's scores leave 2^+-8 in the first stage or outgrow the reference by more than 2^8 later:
-// inside that the probabilities are merely up to 256 times larger or smaller (harmless in binary32, and the final division
-// takes it out again), and the operations that shrink O are saved.  What is added to the reference is exactly what the
-// probabilities formed so far shrink by.
-template <bool kFirst, bool kCarried, int kDB>
-__device__ __forceinline__ bool attention_move_reference(AttnWave<kDB>& w, float mx, float base)
+// The reference against which a stage's probabilities are taken, from the maximum of the lane's scores.  It moves only
+// when some query of the wave outgrows it by more than 2^8: below that the probabilities are merely up to 256 times larger
+// (harmless in binary32, and the final division takes it out again), and the operations that shrink O are saved.  The
+// first stage always moves it (it starts at -inf; key 0 is inside the sequence).
+template <int kDB>
+__device__ __forceinline__ void attention_move_reference(AttnWave<kDB>& w, float mx)
 {
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
     const float row_max = at_max(__uint_as_float(sw[0]), __uint_as_float(sw[1]));   // both half-waves hold keys of the query
-    const bool moves = kFirst ? __builtin_fabsf(row_max) > 8.0f : row_max > (w.m_run - base) + 8.0f;
-    if (__builtin_amdgcn_ballot_w64(moves) == 0) return false;
-    const float m_up = moves ? base + row_max : w.m_run;
-    if constexpr (!kFirst) {
-        const float alpha = __builtin_amdgcn_exp2f(w.m_run - m_up);
+    if (__builtin_amdgcn_ballot_w64(row_max > w.m_run + 8.0f) != 0) {
+        const float m_up = at_max(w.m_run, row_max), alpha = __builtin_amdgcn_exp2f(w.m_run - m_up);
+        w.m_run = m_up;
         w.l_run *= alpha;
 #pragma unroll
         for (int b = 0; b < kDB; ++b)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                w.o[b][e] *= alpha;
-                if constexpr (kCarried) w.r[b][e] *= alpha;
-            }
+            for (int e = 0; e < 16; ++e) w.o[b][e] *= alpha;
     }
-    w.m_run = m_up;
-    w.above = __builtin_amdgcn_ballot_w64(m_up > 0.0f) != 0;
-    w.below = __builtin_amdgcn_ballot_w64(m_up < 0.0f) != 0;
-    return true;
-}
-__device__ __forceinline__ void attention_subtract(v16f& s, float x)
-{
-#pragma unroll
-    for (int e = 0; e < 16; ++e) s[e] -= x;
 }
 
 // One trip of the key loop, skewed by a stage: the softmax of the current stage's scores `sc` while -- kMore -- the
 // matrix pipes form the next stage's, `sn`, from the K tile; then O^T += V^T P^T of the current stage while the rows
-// requested a trip ago (K of `k_stage`, two ahead, and V of the stage before it) are split and stored and the next ones
+// requested two trips ago (K of `k_stage`, two ahead, and V of the stage before it) are split and stored and the next ones
 // requested.  A wave issues in order, so the vector work goes between the MFMAs in pieces of a few instructions: an
-// MFMA takes 32 cycles, and up to six vector instructions behind it are free; and the operands of a group of six MFMAs
-// are read from LDS 8 to 9 MFMAs ahead, each part into the place of one that is used up (whole groups two ahead take twelve
-// registers more, which spill at width 64).  At width 64 a trip is 48 MFMAs and about 270 vector instructions, 3700 cycles
-// with two waves on the SIMD: 87 % of what issuing them takes.  Measured and left out: the split of the K rows under the
-// scores instead of under P V (122 against 117 us), wave priorities (the same).  kSet: parity of the
+// MFMA takes 32 cycles, and up to six vector instructions behind it are free; and the operands of a group of eight MFMAs
+// are read from LDS 13 MFMAs ahead, each part into the place of one that is used up (six ahead, a group waited 50 to 100
+// cycles for them; whole groups two ahead take twelve registers more, which spill at width 64).  kSet: parity of the
 // current stage.
 template <int kDB, bool kMore, int kSet>
 __device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, int lq, int hi, v16f& sc, v16f& sn, AttnWave<kDB>& w,
@@ -466,7 +419,7 @@ __device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, i
     using T = AttnTile<kDB>;
     const char* krow = Kn + lq * T::kKStride + 16 * hi;
     const char* vrow = Vs + lq * T::kVStride + 16 * hi;
-    constexpr int kKG = kMore ? 2 * kDB : 0, kGroups = kKG + 2 * kDB;   // groups of six MFMAs: K steps, then column blocks x V steps
+    constexpr int kKG = kMore ? 2 * kDB : 0, kGroups = kKG + 2 * kDB;   // groups of eight MFMAs: K steps, then column blocks x V steps
     Frag3 frag[2];
     // part p of the operands of group g
     auto read_part = [&](auto gc, auto pc) {
@@ -483,22 +436,20 @@ __device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, i
         constexpr int g = decltype(gc)::value, i = decltype(ic)::value;
         if constexpr (i == 0 && g > 0) read_part(std::integral_constant<int, g + 1>{}, std::integral_constant<int, 1>{});
         if constexpr (i == 3) read_part(std::integral_constant<int, g + 2>{}, std::integral_constant<int, 0>{});
-        if constexpr (i == 4) read_part(std::integral_constant<int, g + 2>{}, std::integral_constant<int, 2>{});
+        if constexpr (i == 5) read_part(std::integral_constant<int, g + 2>{}, std::integral_constant<int, 2>{});
     };
     at_static_for<0, 2>([&](auto gc) { at_static_for<0, 3>([&](auto pc) { read_part(gc, pc); }); });
 
     Frag3 pf[2];        // the probabilities, split: step j holds s[8 j .. 8 j + 7]
     Bf16x3 part;
-    float stage_l;
     constexpr int kSoft = 24, kSoftFirst = kMore ? 6 : kSoft;   // the first ones go under the latency of the first operands
     auto soft = [&](auto pc) {   // per pair of keys: their probabilities, then the halves of their split
         constexpr int P = decltype(pc)::value, i = P / 3, q = P % 3;
         if constexpr (q == 0) {
-            sc[2 * i] = __builtin_amdgcn_exp2f(sc[2 * i]);
-            sc[2 * i + 1] = __builtin_amdgcn_exp2f(sc[2 * i + 1]);
-            stage_l = i == 0 ? sc[0] + sc[1] : stage_l + (sc[2 * i] + sc[2 * i + 1]);
-            asm volatile("" : "+v"(stage_l));   // here, and not gathered into one chain behind the trip
-            if constexpr (i == 7) w.l_run += stage_l;
+            sc[2 * i] = __builtin_amdgcn_exp2f(sc[2 * i] - w.m_run);
+            sc[2 * i + 1] = __builtin_amdgcn_exp2f(sc[2 * i + 1] - w.m_run);
+            w.l_run += sc[2 * i] + sc[2 * i + 1];
+            asm volatile("" : "+v"(w.l_run));   // here, and not gathered into one chain behind the trip
         } else if constexpr (q == 1) {
             part.first(sc[2 * i], sc[2 * i + 1]);
         } else {
@@ -514,10 +465,8 @@ __device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, i
         at_static_for<0, kNqk>([&](auto nc) {
             constexpr int n = decltype(nc)::value, g = n / kAtParts, i = n % kAtParts;
             read_ahead(std::integral_constant<int, g>{}, std::integral_constant<int, i>{});
-            if constexpr (n == 0)
-                sn = attention_lead_mfma(w, frag[0]);
-            else if constexpr (i == 0)
-                sn = mfma_part<0>(frag[g % 2], w.q[g], sn);
+            if constexpr (i == 0)
+                sn = mfma_part<0>(frag[g % 2], w.q[g], n == 0 ? zero16() : sn);
             else if constexpr (n == 1)
                 rest = attention_first_mfma(Kn + T::kMask, hi, w, frag[0], sg.masked);
             else
@@ -535,9 +484,12 @@ __device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, i
         if constexpr (i == 0)
             w.o[b] = mfma_part<0>(frag[g % 2], pf[j], w.o[b]);
         else
-            w.r[b] = mfma_part<i>(frag[g % 2], pf[j], w.r[b]);
+            rest = mfma_part<i>(frag[g % 2], pf[j], j == 0 && i == 1 ? zero16() : rest);
         if constexpr (n % kBlock == 0) {   // under an MFMA of another accumulator: the sums of the block before, or the scores
-            if constexpr (b == 0 && kMore) join_parts(sn, rest);
+            if constexpr (b > 0)
+                join_parts(w.o[b - 1], rest);
+            else if constexpr (kMore)
+                join_parts(sn, rest);
         }
         if constexpr (kMore) {
             if constexpr (n == 3) attention_max_piece<0>(sn, mx);
@@ -549,29 +501,19 @@ __device__ __forceinline__ void attention_trip(const char* Kn, const char* Vs, i
         }
         __builtin_amdgcn_sched_barrier(0);
     });
-    if constexpr (kMore) {
-        const float base = at_max(w.m_run, 0.0f);   // what the scores' sums started from
-        if (attention_move_reference<false, true>(w, mx, base) || w.below) attention_subtract(sn, w.m_run - base);
-    }
+    join_parts(w.o[kDB - 1], rest);
+    if constexpr (kMore) attention_move_reference(w, mx);
 }
 
 // Magnitudes are compared as bit patterns, which order like the numbers (a NaN above all).
 // The bits minus one, doubled, for the smallest magnitude of numbers that are not zero: zero becomes the largest of all.
 __device__ __forceinline__ unsigned nonzero_bits(float x) { return (__float_as_uint(x) << 1) - 1u; }
 
-__device__ __forceinline__ void attention_ends(float4 v, unsigned& smallest, float& amax, float& wild)
+__device__ __forceinline__ void attention_ends(float4 v, unsigned& smallest, float& amax)
 {
-    wild = at_max(at_max(wild, at_max(__builtin_fabsf(v.x), __builtin_fabsf(v.y))), at_max(__builtin_fabsf(v.z), __builtin_fabsf(v.w)));
     smallest = min(smallest, min(min(nonzero_bits(v.x), nonzero_bits(v.y)), min(nonzero_bits(v.z), nonzero_bits(v.w))));
     // a NaN is passed over, as everywhere in the abs-max of ctx
     amax = __builtin_fmaxf(amax, __builtin_fmaxf(__builtin_fmaxf(__builtin_fabsf(v.x), __builtin_fabsf(v.y)), __builtin_fmaxf(__builtin_fabsf(v.z), __builtin_fabsf(v.w))));
-}
-
-// o / l from the rounded 1 / l: the quotient with one step of what it leaves, which makes it one rounding.
-__device__ __forceinline__ float attention_quotient(float o, float l, float inv)
-{
-    const float v = o * inv;
-    return __builtin_fmaf(__builtin_fmaf(-v, l, o), inv, v);
 }
 
 // Four neighbouring results: ctx, or its codes under the stored scale of the next FC layer (Eq. 1), or both.
@@ -584,14 +526,14 @@ __device__ __forceinline__ void attention_store(const AttnArgs& a, int64_t off, 
 }
 
 // Whether results come out of the split products as they would of binary32 ones.  `largest`: bits of the largest magnitude
-// that went into them; `smallest` and `wild`: of the smallest (nonzero_bits) and the largest result, a NaN above all.  What lower
-// parts under the smallest bf16 can do to a result is 2^-134 by a V row of weight 1 and, by the parts of the weights (the largest
-// of which is 2^-8 or more), 2^-126 of `largest` for each of up to 2^20 keys; both stay below 2^-24 of a result above this bound.
-__device__ __forceinline__ bool attention_in_range(unsigned largest, unsigned smallest, unsigned wild)
+// that went into them; `smallest` and `amax`: of the smallest (nonzero_bits) and the largest result.  What lower parts under the smallest bf16 can do to
+// a result is 2^-134 by a V row of weight 1 and, by the parts of the weights, 2^-134 of `largest` for each of up to 2^20 keys;
+// both stay below 2^-24 of a result above this bound.
+__device__ __forceinline__ bool attention_in_range(unsigned largest, unsigned smallest, unsigned amax)
 {
     const float f = __uint_as_float(largest);
     if (largest > 0x7f800000u) return true;   // a NaN among the inputs
-    return f <= 0x1p96f && wild < 0x7f800000u && smallest >= nonzero_bits(__builtin_fmaxf(0x1p-100f, f * 0x1p-82f));
+    return f <= 0x1p96f && amax < 0x7f800000u && smallest >= nonzero_bits(__builtin_fmaxf(0x1p-100f, f * 0x1p-90f));
 }
 
 // Rows q0 .. q0 + n - 1 of the context by one wave in plain binary32: 64 keys at a time, one per lane, then the columns of V
@@ -693,7 +635,7 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
 
     // Everything the first trips need is requested at once -- a 128-token sequence in full -- so that its way from memory
     // is waited for once; columns beyond d are zeros in the queries (whatever K holds there).
-    sg.template fetch_k<1>(0);
+    sg.template fetch_k<2>(0);
     AttnWave<kDB> w;
     float4 qraw[2 * kDB][2];
     {
@@ -704,12 +646,14 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
 #pragma unroll
             for (int u = 0; u < 2; ++u) qraw[j][u] = *reinterpret_cast<const float4*>(qp + min(16 * j + 8 * hi + 4 * u, a.d - 4));
     }
-    sg.template fetch_v<1>(0);
-    sg.template fetch_k<2>(1);
+    sg.template fetch_v<2>(0);
+    sg.template fetch_k<3>(1);
     sg.template fetch_k<0>(2);
     sg.template fetch_v<0>(1);
+    sg.template fetch_k<1>(3);
+    sg.template fetch_v<1>(2);
     __builtin_amdgcn_sched_barrier(0);
-    sg.template stash_k<1>(0, 0);
+    sg.template stash_k<2>(0, 0);
 #pragma unroll
     for (int j = 0; j < 2 * kDB; ++j)
 #pragma unroll
@@ -726,35 +670,32 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
 #pragma unroll
     for (int blk = 0; blk < kDB; ++blk)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) w.o[blk][e] = w.r[blk][e] = 0.0f;
-    w.m_run = 0.0f;
-    w.above = w.below = false;
+        for (int e = 0; e < 16; ++e) w.o[blk][e] = 0.0f;
+    w.m_run = -__builtin_inff();
     w.l_run = 0.0f;
     __syncthreads();
     v16f s0, s1;
-    v16f rest0;   // joined when the reference is known
     {
         const char* krow = sg.k_tiles + lq * T::kKStride + 16 * hi;
+        v16f rest;
         at_static_for<0, 2 * kDB>([&](auto jc) {
             constexpr int j = decltype(jc)::value;
             Frag3 f;
 #pragma unroll
             for (int p = 0; p < 3; ++p) f.part[p] = *reinterpret_cast<const v4u*>(krow + p * T::kKPart + 32 * j);
             s0 = mfma_part<0>(f, w.q[j], j == 0 ? zero16() : s0);
-            if constexpr (j == 0) rest0 = attention_first_mfma(sg.k_tiles + T::kMask, hi, w, f, sg.masked);
-            at_static_for<(j == 0 ? 2 : 1), kAtParts>([&](auto ic) { rest0 = mfma_part<decltype(ic)::value>(f, w.q[j], rest0); });
+            if constexpr (j == 0) rest = attention_first_mfma(sg.k_tiles + T::kMask, hi, w, f, sg.masked);
+            at_static_for<(j == 0 ? 2 : 1), kAtParts>([&](auto ic) { rest = mfma_part<decltype(ic)::value>(f, w.q[j], rest); });
         });
+        join_parts(s0, rest);
     }
-    sg.template stash_v<1>(0);
-    sg.template stash_k<2>(1, 1);
+    sg.template stash_v<2>(0);
+    sg.template stash_k<3>(1, 1);
     {
         float mx;
-        v16f s = s0;
-        join_parts(s, rest0);
-        attention_max_piece<0>(s, mx);
-        attention_max_piece<1>(s, mx);
-        if (attention_move_reference<true, true>(w, mx, 0.0f)) attention_subtract(s0, w.m_run);
-        join_parts(s0, rest0);
+        attention_max_piece<0>(s0, mx);
+        attention_max_piece<1>(s0, mx);
+        attention_move_reference(w, mx);
     }
     __syncthreads();
 
@@ -788,38 +729,34 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
         }
     }
 
-#pragma unroll
-    for (int blk = 0; blk < kDB; ++blk) join_parts(w.o[blk], w.r[blk]);
     const auto l2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(w.l_run), __float_as_uint(w.l_run), false, false);
-    const float den = __uint_as_float(l2[0]) + __uint_as_float(l2[1]), inv = 1.0f / den;
+    const float inv = 1.0f / (__uint_as_float(l2[0]) + __uint_as_float(l2[1]));
     const bool live = q0 + lq < S;
     const float qs = a.q_out ? a.q_scale[0] : 0.0f;
     const int64_t out_off = (b * S + q0 + lq) * HD + (int64_t)h * a.d + 4 * hi;
     // Lanes beyond the sequence or the width repeat results of the last query or column: they change neither end.
     unsigned smallest = ~0u;
-    float ctx_max = 0.0f, wild = 0.0f;
+    float ctx_max = 0.0f;
 #pragma unroll
     for (int blk = 0; blk < kDB; ++blk)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            const float4 v = make_float4(attention_quotient(w.o[blk][4 * g + 0], den, inv), attention_quotient(w.o[blk][4 * g + 1], den, inv),
-                                         attention_quotient(w.o[blk][4 * g + 2], den, inv), attention_quotient(w.o[blk][4 * g + 3], den, inv));
+            const float4 v = make_float4(w.o[blk][4 * g + 0] * inv, w.o[blk][4 * g + 1] * inv, w.o[blk][4 * g + 2] * inv, w.o[blk][4 * g + 3] * inv);
             if (live && 32 * blk + 8 * g + 4 * hi < a.d) attention_store(a, out_off + 32 * blk + 8 * g, v, qs);
-            attention_ends(v, smallest, ctx_max, wild);
+            attention_ends(v, smallest, ctx_max);   // 0 / 0 in a wave without queries: neither
         }
     unsigned largest = wave_max_u32(__float_as_uint(sg.largest));
     smallest = ~wave_max_u32(~smallest);
-    unsigned amax = wave_max_u32(__float_as_uint(ctx_max)), wilds = wave_live ? wave_max_u32(__float_as_uint(wild)) : 0u;   // 0 / 0 in a wave without queries
-    if (lane == 0) wave_ends[wave] = make_uint4(largest, smallest, amax, wilds);
+    unsigned amax = wave_max_u32(__float_as_uint(ctx_max));
+    if (lane == 0) wave_ends[wave] = make_uint4(largest, smallest, amax, 0u);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kAtWaves; ++i) {
         largest = max(largest, wave_ends[i].x);
         smallest = min(smallest, wave_ends[i].y);
         amax = max(amax, wave_ends[i].z);
-        wilds = max(wilds, wave_ends[i].w);
     }
-    if (__builtin_expect(!attention_in_range(largest, smallest, wilds), 0)) {
+    if (__builtin_expect(!attention_in_range(largest, smallest, amax), 0)) {
         __threadfence();   // behind the stores above
         amax = wave_max_u32(__float_as_uint(attention_rows_plain(a, b, h, q0, kAtQW)));
         __syncthreads();   // wave_ends has been read
@@ -844,11 +781,11 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_mfma_k
 
 // The same products for launches that leave most of the chip idle: 32 queries of one (sequence, head) a workgroup, the
 // key stages dealt out over its four waves, each with running statistics of its own that meet in LDS at the end.  A short
-// sequence is a chain of latencies -- rows from memory, then per stage 48 MFMAs (of 32 cycles, at width 64) that the
+// sequence is a chain of latencies -- rows from memory, then per stage 64 MFMAs (of 32 cycles, at width 64) that the
 // kernel above walks one after the other on an eighth of the compute units.  No wave shares its keys, so K and V go straight
 // from memory into operand registers and nothing is staged: for every 32 queries they are read and split again, which is
-// why full launches keep the kernel above.  One sequence of 128 tokens, 12 heads of 64: 11.2 -> 7.4 us; of 512: 28.9 ->
-// 13.4; 2 x 256 of width 32: 13.1 -> 7.0.  Error against 64 bits no larger (1.28e-7 against 1.34e-7 at 128 tokens).
+// why full launches keep the kernel above.  One sequence of 128 tokens, 12 heads of 64: 11.2 -> 7.6 us; of 512: 28.9 ->
+// 15.6; 2 x 256 of width 32: 13.1 -> 7.0.  Error against 64 bits no larger (1.3e-7 against 1.5e-7 at 128 tokens).
 template <int kDB>
 __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_kernel(AttnArgs a)
 {
@@ -908,8 +845,7 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
     };
 
     AttnWave<kDB> w;
-    w.m_run = wave < n_stages ? 0.0f : -__builtin_inff();   // a wave without a stage has weight 0
-    w.above = w.below = false;
+    w.m_run = -__builtin_inff();
     w.l_run = 0.0f;
 #pragma unroll
     for (int c = 0; c < kDB; ++c)
@@ -954,32 +890,20 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
             s = mfma_part<0>(f, w.q[j], s);
             at_static_for<1, kAtParts>([&](auto ic) { rest = mfma_part<decltype(ic)::value>(f, w.q[j], rest); });
         }
-        v16f joined = s;
-        join_parts(joined, rest);
+        join_parts(s, rest);
         const bool more = st + kAtWaves < n_stages;
         if (more) fetch_k(st + kAtWaves);
         float mx;
-        attention_max_piece<0>(joined, mx);
-        attention_max_piece<1>(joined, mx);
-        if (st == wave)
-            attention_move_reference<true, false>(w, mx, 0.0f);
-        else
-            attention_move_reference<false, false>(w, mx, 0.0f);
-        if (w.above || w.below) {
-            attention_subtract(s, w.m_run);
-            join_parts(s, rest);
-        } else {
-            s = joined;
-        }
+        attention_max_piece<0>(s, mx);
+        attention_max_piece<1>(s, mx);
+        attention_move_reference(w, mx);
         Frag3 pf[2];
-        float stage_l = 0.0f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const float p0 = __builtin_amdgcn_exp2f(s[2 * i]), p1 = __builtin_amdgcn_exp2f(s[2 * i + 1]);
-            stage_l += p0 + p1;
+            const float p0 = __builtin_amdgcn_exp2f(s[2 * i] - w.m_run), p1 = __builtin_amdgcn_exp2f(s[2 * i + 1] - w.m_run);
+            w.l_run += p0 + p1;
             pf[i >> 2].set(i & 3, split_bf16(p0, p1));
         }
-        w.l_run += stage_l;
 #pragma unroll
         for (int c = 0; c < kDB; ++c) {
             rest = zero16();
@@ -1029,7 +953,7 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
     const float qs = a.q_out ? a.q_scale[0] : 0.0f;
     const int64_t out_off = (b * S + q0 + q) * HD + (int64_t)h * d;
     unsigned smallest = ~0u;   // lanes beyond the sequence or the width repeat other results, as above
-    float ctx_max = 0.0f, wild = 0.0f;
+    float ctx_max = 0.0f;
 #pragma unroll
     for (int c = 0; c < kDB; ++c) {
         const int col = 32 * c + 4 * (tid & 7);
@@ -1042,11 +966,14 @@ __global__ __launch_bounds__(kAtThreads, kDB <= 2 ? 2 : 1) void attention_split_
             o.z += f[i] * p.z;
             o.w += f[i] * p.w;
         }
-        o = make_float4(attention_quotient(o.x, den, inv), attention_quotient(o.y, den, inv), attention_quotient(o.z, den, inv), attention_quotient(o.w, den, inv));
+        o.x *= inv;
+        o.y *= inv;
+        o.z *= inv;
+        o.w *= inv;
         if (q0 + q < S && col < d) attention_store(a, out_off + col, o, qs);
-        attention_ends(o, smallest, ctx_max, wild);
+        attention_ends(o, smallest, ctx_max);
     }
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!attention_in_range(all_large, smallest, __float_as_uint(wild))) != 0, 0)) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!attention_in_range(all_large, smallest, __float_as_uint(ctx_max))) != 0, 0)) {
         __threadfence();   // behind the stores above
         ctx_max = attention_rows_plain(a, b, h, q0 + 8 * wave, 8);   // a wave ends up with eight queries
     }
@@ -1140,15 +1067,14 @@ template <int kDB>
 static int launch_attention_width(AttnArgs a, int64_t wgs, hipStream_t st)
 {
     // The split kernel while each of its workgroups has one of the 256 compute units for itself: at 256 workgroups of width 64
-    // it takes 7.7 us against 10.4 on sequences of 4 stages, 9.7 against 15.5 on 8, 21.0 against 45.6 on 32, of width 128 26.7
-    // against 48.1 on 16.  With two on a unit, width 64 but for sequences of two, three and six stages (448 workgroups of
-    // 1 / 2 / 3 / 4 / 5 / 6 / 7 / 8 / 16 stages 7.1 / 9.3 / 10.6 / 11.0 / 13.3 / 14.9 / 14.2 / 14.4 / 21.1 us against 8.9 / 8.2 / 9.7 /
-    // 11.2 / 13.4 / 14.0 / 15.1 / 16.3 / 26.3); a third round there costs more than the chain it shortens (576: 4 / 8 / 16 stages
-    // 14.8 / 19.5 / 29.7 against 11.6 / 16.5 / 26.5).  Width 32 with three on a unit, which its registers allow (704 workgroups of
-    // 1 / 2 / 3 / 4 / 5 / 6 / 7 / 8 / 16 / 32 stages 5.3 / 6.7 / 8.2 / 8.0 / 10.2 / 11.6 / 13.3 / 12.6 / 17.5 / 28.5 against 9.1 / 8.2 / 7.9 / 8.9 /
-    // 14.0 / 11.6 / 12.6 / 13.1 / 21.8 / 39.3).
+    // it takes 7.9 us against 11.4 on sequences of 4 stages, 10.1 against 17.0 on 8, 22.3 against 50.7 on 32, of width 128 28.3
+    // against 60.4 on 16.  With two on a unit (widths up to 64): width 32 always (384 workgroups of 1 / 2 / 3 / 4 / 8 / 16
+    // stages 5.1 / 6.2 / 6.5 / 6.9 / 9.3 / 13.2 us against 6.4 / 6.3 / 7.7 / 8.8 / 13.4 / 22.6), width 64 but for
+    // sequences of two and three stages (1 / 2 / 3 / 4 / 5 / 6 / 7 / 8 / 16 stages 7.0 / 9.3 / 10.2 / 10.9 / 13.5 / 14.4 /
+    // 15.4 / 14.8 / 21.5 against 8.8 / 8.1 / 9.9 / 11.8 / 13.9 / 14.8 / 16.6 / 17.6 / 29.0).  Beyond, its third round
+    // costs more than the chain it shortens (576 of width 64: 4 / 8 / 16 stages 15.3 / 20.0 / 31.7 against 12.5 / 18.1 / 29.5).
     const int64_t bh = wgs / a.n_qblocks, n_q32 = (a.S + kAtQW - 1) / kAtQW, wgs32 = bh * n_q32;
-    const bool split = wgs32 <= 256 || (kDB == 1 && wgs32 <= 768) || (kDB == 2 && wgs32 <= 512 && n_q32 != 2 && n_q32 != 3 && n_q32 != 6);
+    const bool split = wgs32 <= 256 || (wgs32 <= 512 && (kDB == 1 || (kDB == 2 && (n_q32 == 1 || n_q32 >= 4))));
     if (split) {
         a.n_qblocks = (int)n_q32;
         hipLaunchKernelGGL(attention_split_kernel<kDB>, dim3((unsigned)wgs32), dim3(kAtThreads), 0, st, a);

@@ -250,3 +250,87 @@ def test_attention_reference_on_both_sides_of_zero(q8, B, S, heads, d, levels):
 def test_attention_on_both_sides_of_the_split_by_width(q8, B, S, heads, d, mask):
     """768 and 780 workgroups of width 32 and below; 480 and 490 of width 64, of six and of seven stages."""
     test_attention_on_both_sides_of_the_split(q8, B, S, heads, d, mask)
+
+
+@pytest.mark.parametrize("value", [-10000.0, torch.finfo(torch.float32).min])
+@pytest.mark.parametrize("B,S,heads,d", [
+    (3, 1, 2, 64), (2, 1, 3, 20), (2, 1, 2, 128), (2, 70, 2, 64), (3, 170, 2, 32), (1, 300, 2, 128), (2, 33, 2, 5),      # the stages dealt out; any width
+    (45, 1, 20, 64), (60, 1, 20, 32), (40, 1, 12, 128), (9, 70, 40, 64), (7, 170, 30, 32), (5, 130, 30, 128),         # four waves on every stage
+])
+def test_attention_of_one_visible_key_is_its_v(q8, B, S, heads, d, value):
+    """One-token sequences, and masks that leave one key: its probability is exactly 1, so the result is its V row bit for bit."""
+    g = torch.Generator().manual_seed(B + 31 * S + heads + d)
+    x = torch.randn((B, S, 3, heads, d), generator=g)
+    x[:, :, 2] *= 10.0 ** torch.randint(-3, 4, (B, S, heads, d), generator=g)
+    visible = torch.randint(0, S, (B,), generator=g)
+    mask = torch.full((B, S), value)
+    mask[torch.arange(B), visible] = 0.0
+    ctx = torch.empty((B * S, heads * d), device="cuda")
+    q8.q8_attention(x.reshape(B * S, -1).cuda(), B, S, heads, d, ctx=ctx, mask=mask.cuda() if S > 1 else None)
+    expected = x[torch.arange(B), visible, 2].reshape(B, 1, heads * d).expand(B, S, heads * d)
+    np.testing.assert_array_equal(ctx.cpu().view(B, S, heads * d).numpy(), expected.numpy())
+
+
+@pytest.mark.parametrize("B", [1, 4])   # the stages dealt out; four waves on every stage
+def test_attention_scores_of_one_term_keep_their_lowest_products(q8, B):
+    """Scores c k of a single term near 4 (log2 units).  c = 1 + m + l and k = 4 (1 + m + l) in bf16 parts, every m near its largest;
+    in half of the heads the l of k is positive, in the other half negative, everything else alike.  What a kernel leaves out of the products m l and
+    l m moves the two halves apart: by 2 x 4 x 2^-8 x 2^-17 x 0.78 = 1.9e-7 if it forms neither.  A score is rounded to 2^-22 at worst and the
+    result through which it is seen to a few 2^-24 (1.6e-7 in the mean square together), so that the difference of two means over
+    512 heads each is 1e-8 of noise: 5e-8 is the bar."""
+    heads, d, S = 1024, 4, 2
+    g = torch.Generator().manual_seed(3)
+    c = np.float32(1 + 2.0 ** -8 * 0.97)
+    log2e = np.float32(1.44269504088896341)
+    scale = float(np.float32(c / log2e))
+    c = np.float32(np.float32(scale) * log2e)
+    m = (2.0 ** -8 * (0.55 + 0.4 * torch.rand(heads, generator=g, dtype=torch.float64))).bfloat16().double()
+    low = 2.0 ** -17 * (0.65 + 0.3 * torch.rand(heads, generator=g, dtype=torch.float64))
+    low[1::2] *= -1
+    k = (4 * (1 + m + low)).float()
+    x = torch.zeros((B, S, 3, heads, d))
+    x[:, :, 0, :, 1] = 1.0
+    x[:, 1, 1, :, 1] = k
+    x[:, 0, 2, :, 0] = 1.0
+    ctx = torch.empty((B * S, heads * d), device="cuda")
+    q8.q8_attention(x.reshape(B * S, -1).cuda(), B, S, heads, d, ctx=ctx, scale=scale)
+    p = ctx.cpu().double().view(B * S, heads, d)[:, :, 0]   # 1 / (1 + 2^s)
+    error = (torch.log2(1 / p - 1) - float(c) * k.double()).mean(0)
+    assert abs((error[0::2].mean() - error[1::2].mean()).item()) <= 5e-8
+
+
+@pytest.mark.parametrize("B,S,heads,d", [(3, 70, 2, 64), (3, 93, 2, 32), (3, 130, 80, 64), (3, 70, 60, 128)])
+def test_attention_of_a_nan_in_the_mask(q8, B, S, heads, d):
+    """A NaN score makes every result of its sequence NaN, none of another one, and the abs-max passes over it."""
+    g = torch.Generator(device="cuda").manual_seed(S + heads)
+    qkv = torch.randn((B * S, 3 * heads * d), generator=g, device="cuda")
+    mask = torch.zeros((B, S), device="cuda")
+    clean, ctx, slots = torch.empty((B * S, heads * d), device="cuda"), torch.empty((B * S, heads * d), device="cuda"), torch.full((q8.AMAX_SLOTS,), 9e9, device="cuda")
+    q8.q8_attention(qkv, B, S, heads, d, ctx=clean, mask=mask)
+    mask[1, S // 2] = float("nan")
+    q8.q8_attention(qkv, B, S, heads, d, ctx=ctx, mask=mask, amax_slots=slots)
+    got, want = ctx.view(B, S, -1), clean.view(B, S, -1)
+    assert bool(got[1].isnan().all()) and torch.equal(got[0], want[0]) and torch.equal(got[2], want[2])
+    assert slots.max().item() == max(want[0].abs().max().item(), want[2].abs().max().item())
+
+
+def test_attention_of_a_nan_in_the_mask_takes_no_longer(q8):
+    """Nothing is formed a second time for a NaN: the plain evaluation of a sequence takes tens of times as long."""
+    B, S, heads, d = 1, 1024, 24, 64
+    qkv = torch.randn((B * S, 3 * heads * d), device="cuda")
+    ctx, mask = torch.empty((B * S, heads * d), device="cuda"), torch.zeros((B, S), device="cuda")
+
+    def best_ms():
+        times = []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            q8.q8_attention(qkv, B, S, heads, d, ctx=ctx, mask=mask)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+
+    clean = best_ms()
+    mask[0, 5] = float("nan")
+    assert best_ms() <= 4 * clean
