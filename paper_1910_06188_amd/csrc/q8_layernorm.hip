@@ -74,7 +74,7 @@ __device__ __forceinline__ double rsqrt_f64(double v)
     const double h = 0.5 * v;
 #pragma unroll
     for (int i = 0; i < 2; ++i) y = __builtin_fma(y, __builtin_fma(-h * y, y, 0.5), y);
-    return y;
+    return h == v ? __builtin_amdgcn_rsq(v) : y;   // the ends, where a step would be 0 times infinity: v = 0 and an infinite eps
 }
 
 struct EmbedSrc {

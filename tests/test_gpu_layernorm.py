@@ -204,3 +204,15 @@ def test_layernorm_of_rows_of_equal_numbers_is_beta(q8, M, H, with_residual):
     y = torch.full((M, H), 9.0, device="cuda")
     q8.q8_layernorm_absmax(dev(a), dev(gamma), dev(beta), y, eps=1e-12, residual=dev(a) if with_residual else None)
     np.testing.assert_array_equal(host(y), np.repeat(beta[None], M, 0))
+
+
+@pytest.mark.parametrize("M,H", [(5, 768), (4100, 768), (3, 1028), (2, 770)])
+@pytest.mark.parametrize("with_residual", [False, True])
+def test_layernorm_with_an_infinite_eps_is_beta(q8, M, H, with_residual):
+    """x / sqrt(var + inf) is zero, in the kernel that keeps rows in registers as in the one that does not."""
+    g = synth.rng(17 + H)
+    a, r = synth.activations(g, M, H), synth.activations(g, M, H)
+    gamma, beta = params(g, H)
+    y = torch.full((M, H), 9.0, device="cuda")
+    q8.q8_layernorm_absmax(dev(a), dev(gamma), dev(beta), y, eps=float("inf"), residual=dev(r) if with_residual else None)
+    np.testing.assert_array_equal(host(y), np.repeat(beta[None], M, 0))
