@@ -172,8 +172,9 @@ q8_status q8_quantize_dynamic(const float* x, int64_t n, int8_t* q, float* scal_
  *   Launches: two (quantizer, GEMM) -- the quantizer is one launch whenever x has at most 16384 elements or
  *   fits the chip's registers (q8_quantize_dynamic) -- and a single one for a handful of tokens (M <= 32,
  *   K a multiple of 128 up to 1024, 16-byte aligned x and wq, 4-byte aligned xq_work, no
- *   Q8_EPI_ABSMAX): there the layer is bound by launch latency, so every workgroup quantizes x itself and keeps
- *   the codes on chip.  Results do not depend on the path taken.
+ *   Q8_EPI_ABSMAX, y and acc_out apart from x, inputs apart from xq_work and scal_work): there the layer is bound by launch
+ *   latency, so every workgroup quantizes x itself and keeps the codes on chip.  Results do not depend on the path taken; y may
+ *   be x itself where it fits.
  */
 q8_status q8_linear_f32(const float* x, const int8_t* wq, const float* bias,
                         const float* sw, int n_groups,

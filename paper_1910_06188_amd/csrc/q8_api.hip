@@ -88,6 +88,26 @@ q8_status linear_launch(const int8_t* xq, const int8_t* wq, const float* bias, c
     return q8::launch_gemm(xq, wq, M, N, K, ep, as_stream(stream)) ? Q8_ERR_LAUNCH : Q8_OK;
 }
 
+// Whether two ranges of device memory share a byte.
+bool overlap(const void* p, int64_t p_bytes, const void* q, int64_t q_bytes)
+{
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+    return p && q && a < b + (uintptr_t)q_bytes && b < a + (uintptr_t)p_bytes;
+}
+
+// Whether the one-launch layer would read what another of its workgroups writes: all of them quantize x for themselves, while the first ones done
+// already store y (in place: y = x) and workgroup 0 the codes and the statistics (the codes as weights of the same call, S_x as its next_scale).  In
+// separate launches these are in order.
+bool few_tokens_overlap(const float* x, const int8_t* wq, const q8::Epilogue& ep, int64_t M, int64_t N, int64_t K, const int8_t* xq_work, const float* scal_work)
+{
+    const int64_t x_bytes = 4 * M * K, y_bytes = M * N * ((ep.flags & Q8_EPI_REQUANT) ? 1 : 4);
+    if (overlap(x, x_bytes, ep.y, y_bytes) || overlap(x, x_bytes, ep.acc_out, 4 * M * N)) return true;
+    const struct { const void* p; int64_t bytes; } read[] = {{x, x_bytes}, {wq, N * K}, {ep.bias, 4 * N}, {ep.sw, 4 * (int64_t)ep.n_groups}, {ep.next_scale, 4}};
+    for (const auto& r : read)
+        if (overlap(r.p, r.bytes, xq_work, M * K) || overlap(r.p, r.bytes, scal_work, 8)) return true;
+    return false;
+}
+
 }  // namespace
 
 extern "C" {
@@ -185,7 +205,8 @@ q8_status q8_linear_f32(const float* x, const int8_t* wq, const float* bias, con
     if (q8::fc_small_eligible(x, wq, M, N, K, flags) && !misaligned(xq_work, 4)) {
         const q8::Epilogue ep =
             make_epilogue(bias, scal_work + 1, sw, n_groups, N, y, acc_out, out_amax, next_scale, nullptr, flags);
-        return q8::launch_fc_small(x, wq, M, N, K, xq_work, scal_work, ep, as_stream(stream)) ? Q8_ERR_LAUNCH : Q8_OK;
+        if (!few_tokens_overlap(x, wq, ep, M, N, K, xq_work, scal_work))
+            return q8::launch_fc_small(x, wq, M, N, K, xq_work, scal_work, ep, as_stream(stream)) ? Q8_ERR_LAUNCH : Q8_OK;
     }
     s = q8_quantize_dynamic(x, M * K, xq_work, scal_work, (flags & Q8_EPI_ABSMAX) ? out_amax : nullptr, stream);
     if (s != Q8_OK) return s;

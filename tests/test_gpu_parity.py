@@ -712,6 +712,44 @@ def test_linear_f32_few_tokens_one_launch_to_its_end(q8, M, K, N, groups):
     test_linear_f32_few_tokens_one_launch(q8, M, K, N, groups)
 
 
+@pytest.mark.parametrize("M,K", [(16, 768), (32, 1024), (5, 128)])
+def test_linear_f32_few_tokens_in_place(q8, M, K):
+    """y is x itself; the next scale is the S_x of the same call; the codes are the weights of the same call: what one workgroup writes,
+    others must have read."""
+    g = synth.rng(M + K)
+    x, b = synth.activations(g, M, K), dev((g.standard_normal(K) * 0.05).astype(np.float32))
+    wq_h, sw_h = O.quantize_tensor(synth.weights(g, K, K))
+    wq, sw, xd = dev(wq_h), scalar(float(sw_h)), dev(x)
+
+    def work():
+        return torch.full((M * K,), 99, dtype=torch.int8, device="cuda"), torch.full((q8.SCAL_WORK,), -3.0, device="cuda")
+
+    xq, scal = work()
+    y = torch.empty((M, K), device="cuda")
+    q8.q8_linear_f32(xd, wq, b, sw, xq, scal, y)
+    sx, codes = scal[1:2].clone(), xq.view(M, K).clone()
+    for _ in range(5):
+        inplace, (xq, scal) = xd.clone(), work()
+        q8.q8_linear_f32(inplace, wq, b, sw, xq, scal, inplace)
+        np.testing.assert_array_equal(host(inplace), host(y))
+        np.testing.assert_array_equal(host(xq).reshape(M, K), host(codes))
+        inplace = xd.clone()
+        q8.q8_linear_f32_static(inplace, wq, b, sw, inplace)
+        np.testing.assert_array_equal(host(inplace), host(y))
+
+    got, want = torch.empty((M, K), dtype=torch.int8, device="cuda"), torch.empty((M, K), dtype=torch.int8, device="cuda")
+    xq, scal = work()
+    q8.q8_linear_f32(xd, wq, b, sw, xq, scal, got, next_scale=scal[1:2], flags=q8.EPI_REQUANT)
+    q8.q8_linear(codes, wq, b, sx, sw, want, next_scale=sx, flags=q8.EPI_REQUANT)
+    np.testing.assert_array_equal(host(got), host(want))
+
+    got, want = torch.empty((M, M), device="cuda"), torch.empty((M, M), device="cuda")
+    xq, scal = work()
+    q8.q8_linear_f32(xd, xq.view(M, K), None, scal[1:2], xq, scal, got)
+    q8.q8_linear(codes, codes, None, sx, sx, want)
+    np.testing.assert_array_equal(host(got), host(want))
+
+
 @pytest.mark.parametrize("n", [4096, 16383, 16384, 16385])
 def test_linear_f32_small_tensor_single_launch_boundary(q8, n):
     """Around the size up to which one workgroup does abs-max, scale and quantize in one launch: same bytes on
