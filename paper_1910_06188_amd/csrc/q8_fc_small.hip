@@ -6,7 +6,8 @@
 // (x is at most 32768 elements: 128 KiB out of L2) and keeps the codes in LDS as the A operand of its MFMAs, so no
 // workgroup waits for another and nothing goes through memory between the two halves of the layer.
 //
-//   workgroup = 16 waves, owns 64 output columns and all (at most 32) rows
+//   workgroup = 16 waves, owns 64 output columns and all (at most 32) rows -- of layers wider than 16384, whose blocks outnumber the compute
+//               units, several such blocks one after the other, so that x is quantized once a unit
 //   the quantizer is dealt out over all of them (at most eight vectors of x a thread)
 //   wave w < 8 = block w % 2 of 32 columns, quarter w / 2 of the reduction; its share of the weights goes
 //               straight from global memory into MFMA operand registers (a weight row is K-contiguous, 16 bytes of it
@@ -15,9 +16,11 @@
 //   the four partial accumulators are summed through LDS (exact: Int32), then the common per-element epilogue.
 //
 // The workgroup is a chain -- x from the L2, its abs-max, the codes, the products, the sums -- and what the threads do one after the
-// other is in it: with four waves and the per-column constants fetched at the end, 16 x 768 -> 768 took 6.9 us a call, now 5.5;
-// 16 x 1024 -> 4096 8.0, now 6.3.  All of 32 rows and 1024 columns of x are worth it: 32 x 768 -> 768 6.5 us against 8.6 in two launches,
-// 32 x 1024 -> 1024 7.4 against 8.6.
+// other is in it: with four waves and the per-column constants fetched at the end, 16 x 768 -> 768 took 6.9 us a call, now 5.4;
+// 16 x 1024 -> 4096 7.8, now 6.2.  All of 32 rows and 1024 columns of x are worth it: 32 x 768 -> 768 6.3 us against 8.0 in two launches,
+// 32 x 1024 -> 1024 7.2 against 7.9.  Wide layers with a workgroup for every block (a second round that quantized x again; four waves and
+// smaller x before that): 16 x 768 -> 24576 9.7 us (8.9), now 7.3; 32 x 1024 -> 30522 14.2 (two launches 11.3), now 10.8; 1 x 256 -> 50000
+// 10.8 (6.7), now 5.8.
 //
 // Same device functions as the two-launch path for every rounding step, hence the same bits.
 #include "q8_device.h"
@@ -31,7 +34,8 @@ typedef int v16i_s __attribute__((ext_vector_type(16)));
 
 constexpr int kFsThreads = 1024;
 constexpr int kFsRows = 32;        // rows of the A operand (tokens, zero-padded)
-constexpr int kFsCols = 64;        // output columns per workgroup
+constexpr int kFsCols = 64;        // output columns of a workgroup at a time
+constexpr int kFsMaxGroups = 256;  // one workgroup a compute unit: more would quantize x once more each, in a second round
 constexpr int kFsMaxK = 1024;
 constexpr int kFsGemmWaves = 8;    // two blocks of columns x four quarters of K
 constexpr int kFsMaxElems = kFsRows * kFsMaxK;  // elements of x a workgroup keeps in registers between abs-max and quantize
@@ -47,25 +51,29 @@ __global__ __launch_bounds__(kFsThreads) void fc_small_kernel(const float* __res
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     // A operand: row r at r * (K + 16) bytes -- the 16 bytes of padding put the 32 rows a fragment read touches on
-    // different banks.  The partial accumulators reuse the space afterwards.
+    // different banks.
     __shared__ __attribute__((aligned(16))) char lds[kFsRows * (kFsMaxK + 16)];
+    __shared__ int part[4 * 2 * 16 * 64];  // partial accumulators: [quarter][b][e][lane]
     __shared__ unsigned wave_part[kFsThreads / 64];
-    static_assert(sizeof(lds) >= 4 * 2 * 16 * 64 * 4, "room for the four waves' partial accumulators");
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int l32 = lane & 31, hi = lane >> 5;
-    const int n0 = blockIdx.x * kFsCols;
     constexpr int K = kSteps * 128, stride = K + 16;
 
     // every thread ends up with outputs of one column; the waves that multiply own the weights of the same block
-    const int b = wave & 1, quarter = wave >> 1, n = n0 + 32 * b + l32;
-    const int nc = min(n, N - 1);  // clamped inside W: such columns are never stored
+    const int b = wave & 1, quarter = wave >> 1;
     v4i_s fb[kSteps];
-    if (wave < kFsGemmWaves) {
-        const int8_t* wr = W + (int64_t)nc * K + quarter * (K / 4) + 16 * hi;
+    float sw, bias;
+    auto request = [&](int n) {
+        const int nc = min(n, N - 1);  // clamped inside W: such columns are never stored
+        if (wave < kFsGemmWaves) {
+            const int8_t* wr = W + (int64_t)nc * K + quarter * (K / 4) + 16 * hi;
 #pragma unroll
-        for (int s = 0; s < kSteps; ++s) fb[s] = *reinterpret_cast<const v4i_s*>(wr + 32 * s);
-    }
-    const float sw = ep.sw[nc / ep.cols_per_group], bias = ep.bias ? ep.bias[nc] : 0.0f;
+            for (int s = 0; s < kSteps; ++s) fb[s] = *reinterpret_cast<const v4i_s*>(wr + 32 * s);
+        }
+        sw = ep.sw[nc / ep.cols_per_group];
+        bias = ep.bias ? ep.bias[nc] : 0.0f;
+    };
+    request(blockIdx.x * kFsCols + 32 * b + l32);
     const float next_scale = (ep.flags & 4u) ? ep.next_scale[0] : 0.0f;
 
     // the quantizer: x into registers, abs-max, S, codes into LDS
@@ -103,37 +111,39 @@ __global__ __launch_bounds__(kFsThreads) void fc_small_kernel(const float* __res
     }
     __syncthreads();
 
-    // Int8 GEMM: acc register e of lane (l32, hi) = row 8 (e/4) + 4 hi + e%4, column n0 + 32 b + l32
-    v16i_s acc;
+    for (int n0 = blockIdx.x * kFsCols; n0 < N; n0 += gridDim.x * kFsCols) {
+        // Int8 GEMM: acc register e of lane (l32, hi) = row 8 (e/4) + 4 hi + e%4, column n0 + 32 b + l32
+        const int n = n0 + 32 * b + l32;
+        const ColConst cc = ColConst{ep.bias ? quantize_bias(bias, sx, sw) : 0, dequant_factor(sx, sw)};
+        if (wave < kFsGemmWaves) {
+            v16i_s acc;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0;
-    if (wave < kFsGemmWaves) {
-        const char* arow = lds + l32 * stride + quarter * (K / 4) + 16 * hi;
-        v4i_s fa[kSteps];
+            for (int e = 0; e < 16; ++e) acc[e] = 0;
+            const char* arow = lds + l32 * stride + quarter * (K / 4) + 16 * hi;
+            v4i_s fa[kSteps];
 #pragma unroll
-        for (int s = 0; s < kSteps; ++s) fa[s] = *reinterpret_cast<const v4i_s*>(arow + 32 * s);
+            for (int s = 0; s < kSteps; ++s) fa[s] = *reinterpret_cast<const v4i_s*>(arow + 32 * s);
 #pragma unroll
-        for (int s = 0; s < kSteps; ++s) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[s], fb[s], acc, 0, 0, 0);
-    }
-    const ColConst cc = ColConst{ep.bias ? quantize_bias(bias, sx, sw) : 0, dequant_factor(sx, sw)};
-    __syncthreads();  // every wave is done reading the A operand
-    int* part = reinterpret_cast<int*>(lds);  // [quarter][b][e][lane]
-    if (wave < kFsGemmWaves) {
+            for (int s = 0; s < kSteps; ++s) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[s], fb[s], acc, 0, 0, 0);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) part[((quarter * 2 + b) * 16 + e) * 64 + lane] = acc[e];
-    }
-    __syncthreads();
-
-    // 2 x 16 x 64 outputs over 1024 threads: thread (wave, lane) takes column 32 b + lane % 32 and the registers e = wave / 2 + 8 i
-    if (n < N) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int e = (wave >> 1) + 8 * i;
-            const int sum = part[((0 * 2 + b) * 16 + e) * 64 + lane] + part[((1 * 2 + b) * 16 + e) * 64 + lane] +
-                            part[((2 * 2 + b) * 16 + e) * 64 + lane] + part[((3 * 2 + b) * 16 + e) * 64 + lane];
-            const int row = 8 * (e >> 2) + 4 * hi + (e & 3);
-            if (row < M) epilogue_store(ep, (int64_t)row * N + n, sum + cc.bq, cc.r, next_scale);
+            for (int e = 0; e < 16; ++e) part[((quarter * 2 + b) * 16 + e) * 64 + lane] = acc[e];
         }
+        const bool more = n0 + (int)gridDim.x * kFsCols < N;
+        if (more) request(n + gridDim.x * kFsCols);
+        __syncthreads();
+
+        // 2 x 16 x 64 outputs over 1024 threads: thread (wave, lane) takes column 32 b + lane % 32 and the registers e = wave / 2 + 8 i
+        if (n < N) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int e = (wave >> 1) + 8 * i;
+                const int sum = part[((0 * 2 + b) * 16 + e) * 64 + lane] + part[((1 * 2 + b) * 16 + e) * 64 + lane] +
+                                part[((2 * 2 + b) * 16 + e) * 64 + lane] + part[((3 * 2 + b) * 16 + e) * 64 + lane];
+                const int row = 8 * (e >> 2) + 4 * hi + (e & 3);
+                if (row < M) epilogue_store(ep, (int64_t)row * N + n, sum + cc.bq, cc.r, next_scale);
+            }
+        }
+        if (more) __syncthreads();  // the sums of this block have been read
     }
 #endif
 }
@@ -148,7 +158,9 @@ bool fc_small_eligible(const float* x, const int8_t* wq, int64_t M, int64_t N, i
 int launch_fc_small(const float* x, const int8_t* wq, int64_t M, int64_t N, int64_t K, int8_t* xq_out, float* scal_out,
                     const Epilogue& ep, hipStream_t st)
 {
-    const dim3 grid((unsigned)((N + kFsCols - 1) / kFsCols)), block(kFsThreads);
+    // as many workgroups as it takes to give each the same number of column blocks
+    const int64_t blocks = (N + kFsCols - 1) / kFsCols, each = (blocks + kFsMaxGroups - 1) / kFsMaxGroups;
+    const dim3 grid((unsigned)((blocks + each - 1) / each)), block(kFsThreads);
 #define Q8_FS_LAUNCH(S) \
     case S: hipLaunchKernelGGL(fc_small_kernel<S>, grid, block, 0, st, x, wq, (int)M, (int)N, xq_out, scal_out, ep); break
     switch ((int)(K / 128)) {

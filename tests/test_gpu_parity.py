@@ -712,6 +712,12 @@ def test_linear_f32_few_tokens_one_launch_to_its_end(q8, M, K, N, groups):
     test_linear_f32_few_tokens_one_launch(q8, M, K, N, groups)
 
 
+@pytest.mark.parametrize("M,K,N,groups", [(16, 128, 16384, 1), (32, 128, 16385, 1), (7, 256, 16449, 3), (32, 1024, 16448, 2), (20, 384, 32768, 1), (3, 128, 32769, 1), (9, 128, 50001, 3)])
+def test_linear_f32_few_tokens_of_wide_layers(q8, M, K, N, groups):
+    """As many blocks of 64 columns as workgroups and one more; two and three blocks a workgroup, the last of them ragged or missing."""
+    test_linear_f32_few_tokens_one_launch(q8, M, K, N, groups)
+
+
 @pytest.mark.parametrize("M,K", [(16, 768), (32, 1024), (5, 128)])
 def test_linear_f32_few_tokens_in_place(q8, M, K):
     """y is x itself; the next scale is the S_x of the same call; the codes are the weights of the same call: what one workgroup writes,
