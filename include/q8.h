@@ -369,15 +369,17 @@ q8_status q8_attention(const float* qkv, int64_t B, int64_t S, int heads, int d,
  *
  * Forces the tile shape of the MFMA GEMM behind q8_linear for every later call of this process:
  * 0 = automatic choice from the shape (the default), 1..7 = one fixed tile variant of the staged
- * kernel (shapes it cannot take go to the direct kernel), 8 = the direct kernel (tests and tile
- * sweeps use it to run every variant on every shape).  Process-global and unsynchronised: set it
+ * kernel (shapes it cannot take go to the direct kernel), 8 = the direct kernel, 9..13 = one fixed tile of the
+ * kernel with few stage buffers (shapes it cannot take go to the direct kernel, launches with a residual, an accumulator dump or
+ * another combination of flags than 0 to 5 to the automatic choice).  Tests and tile
+ * sweeps use it to run every variant on every shape.  Process-global and unsynchronised: set it
  * while no other thread is inside q8_linear.  An unknown variant makes q8_linear return Q8_ERR_LAUNCH.
  */
 void q8_debug_set_gemm_variant(int variant);
 
 /*
  * The dynamic quantizer (q8_quantize_dynamic, q8_linear_f32, q8_linear_f32_static) takes a one-pass kernel for
- * tensors that fit the register files of the chip: 4-element multiples of n up to 524288 floats, or between 4096 and
+ * tensors that fit the register files of the chip: 4-element multiples of n up to 524288 floats, or from 2621440 floats on to
  * 49152 floats per compute unit, x 16-byte aligned, stream not under graph capture.  Its workgroups meet at a barrier; one that has
  * polled `barrier_polls` times (default 64, about 80 us) stops waiting and reads the shares of the absent
  * workgroups itself, so the result never depends on the wait.  enabled = 0 turns the kernel off (two passes over

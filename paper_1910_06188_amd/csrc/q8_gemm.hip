@@ -162,6 +162,7 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
     ep.stream_out = y_mib > 64.0 || y_mib < 32.0;
     const bool cached = !ep.stream_out && !(ep.flags & 4u) && N64 % 32 == 0;
     int v = g_variant;
+    if (v < 0 || v >= kVariantRing + kNumRings) return 1;
     if (v == 0 && K64 <= kScalarMaxK && M64 * N64 <= kScalarMaxProducts / (K64 > 0 ? K64 : 1)) {
         hipLaunchKernelGGL(gemm_scalar_kernel, dim3((unsigned)((M64 * N64 + 255) / 256)), dim3(256), 0, st, xq, wq, M64, N64, K64, ep);
         return hipGetLastError() == hipSuccess ? 0 : 1;
@@ -173,15 +174,15 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
         // 16000 x 60 x 300 8.0 against 16.6; with 100 tiles (300 x 1000 x 300) 5.6 against 5.5, with 90 of 4092 columns 12.2 against 7.3.  Long
         // reductions in one round of 32x32 tiles are the direct kernel's, whose waves share them (600 x 2100 x 500, 304 tiles: 8.0 against 8.3).
         const int64_t t32 = ((M64 + 31) / 32) * ((N64 + 31) / 32);
-        if (ring_operands_eligible(xq, wq, M64, N64, K64) && ring_eligible(ep) && (v >= kVariantRing || t32 > (K64 < 2048 ? 256 : 512))) {
-            const Ring& r = v >= kVariantRing && v < kVariantRing + kNumRings ? kRings[v - kVariantRing] : choose_ring((int)M64, (int)N64, (int)K64, ep.flags, cached);
+        if (ring_operands_eligible(xq, wq, M64, N64, K64) && ring_eligible(ep) && (v >= kVariantRing || (v == 0 && t32 > (K64 < 2048 ? 256 : 512)))) {
+            const Ring& r = v >= kVariantRing ? kRings[v - kVariantRing] : choose_ring((int)M64, (int)N64, (int)K64, ep.flags, cached);
             return launch_ring(r, xq, wq, (int)M64, (int)N64, (int)K64, ep, st);
         }
         return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);
     }
     const int M = (int)M64, N = (int)N64, K = (int)K64;
     if (v >= kVariantRing) {
-        if (v < kVariantRing + kNumRings && ring_eligible(ep)) return launch_ring(kRings[v - kVariantRing], xq, wq, M, N, K, ep, st);
+        if (ring_eligible(ep)) return launch_ring(kRings[v - kVariantRing], xq, wq, M, N, K, ep, st);
         v = 0;
     }
     if (v == 0) {

@@ -110,3 +110,18 @@ def test_ring_gemm_choice_of_ragged_widths(q8, M, K, N, off):
 def test_gemm_choice_around_one_round_of_large_tiles(q8, M, K, N):
     """176 and 187 tiles of 192 x 256 rows and columns, 192, and more than 256."""
     test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, 0, 0)
+
+
+@pytest.mark.parametrize("variant", [-1, 14, 99])
+@pytest.mark.parametrize("M,K,N", [(300, 256, 300), (700, 600, 500), (40, 33, 40)])
+def test_unknown_gemm_variant_is_an_error(q8, variant, M, K, N):
+    """Whatever kernel the shape would get by itself: staged or with few stage buffers, the same for ragged widths, direct."""
+    x, w = torch.zeros((M, K), dtype=torch.int8, device="cuda"), torch.zeros((N, K), dtype=torch.int8, device="cuda")
+    one, y = torch.ones(1, device="cuda"), torch.full((M, N), 7.0, device="cuda")
+    q8.set_gemm_variant(variant)
+    try:
+        with pytest.raises(RuntimeError, match="launch failed"):
+            q8.q8_linear(x, w, None, one, one, y)
+    finally:
+        q8.set_gemm_variant(0)
+    assert bool((y == 7.0).all())
