@@ -115,8 +115,7 @@ static int launch_ring(const Ring& r, const int8_t* xq, const int8_t* wq, int M,
 }
 // `cached`: an fp32 output stored for the caches (32 to 64 MiB), its rows whole 128-byte lines (others write parts of lines whatever the tile:
 // 9000 x 1000 x 1024 + GELU 23.0 us with 128x64, 24.7 with 128x128).  There the small tiles pay 2 to 4 us that the model does not know of, so only the
-// two large shapes are looked at: 8192 x 1536 x 512 18.1 -> 16.1 us, 4096 x 3584 x 512 22.3 -> 19.2, 4096 x 2304 x 768 + GELU 20.1 -> 17.0; the other
-// such launches measured within 2 %.
+// two large shapes are looked at: 4096 x 3584 x 512 22.3 -> 19.2 us, 4096 x 2304 x 768 + GELU 20.1 -> 17.0; the other such launches measured within 2 %.
 static const Ring& choose_ring(int M, int N, int K, unsigned flags, bool cached)
 {
     const int kind = (flags & 4u) ? 2 : (flags & 3u) ? 1 : 0;
@@ -196,12 +195,13 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
         const int64_t tiles32 = (((int64_t)M + 31) / 32) * (((int64_t)N + 31) / 32);
         const int64_t tiles64 = (((int64_t)M + 63) / 64) * (((int64_t)N + 63) / 64);
         if (tiles32 <= 256) return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);
-        // A plain launch that is one round of 192x256 tiles, more than two thirds full, stores 33 to 48 MiB for the caches, which the rings'
-        // smaller tiles pay for: 4096 x 2304 x 768 15.1 us against 19.1 with the ring of the rule and 15.6 with the best one, 12288 x 768 x 768
-        // 15.4 / 19.6 / 16.1, 3072 x 3072 x 1536 20.4 / 23.1 / 22.6, 4608 x 2304 x 512 13.7 / 13.5 / 13.3; with 168 to 176 such tiles (2688 x 3072 x
-        // 1024, 4096 x 2048 x 768) 14.5 / 13.2 and 14.6 / 14.2.
+        // A plain launch of at most one round of 192x256 tiles whose 32 to 48 MiB are stored for the caches (so that two thirds of the round are
+        // outputs), which the rings' smaller tiles pay for: 4096 x 2304 x 768 15.4 us against 16.3 with the ring of the rule, 12288 x 768 x 768 16.3 /
+        // 17.4, 3072 x 3072 x 1536 21.9 / 25.8.  Over 400 such launches this tile takes 0.98 of the ring's time at K = 512, 0.91 at 768 to 1024, 0.87 at
+        // 1152 to 1920, but 1.03 at 128 and 256.  Narrow outputs fill as many tiles without that: 40000 x 64 x 768 13.0 / 6.6, 48000 x 128 x 128
+        // 10.4 / 6.6, 36000 x 2 x 1024 12.0 / 8.5, 12288 x 576 x 768 13.3 / 12.5.
         const int64_t tiles192x256 = (((int64_t)M + 191) / 192) * (((int64_t)N + 255) / 256);
-        const bool one_round = ep.flags == 0 && tiles192x256 > 176 && tiles192x256 <= 256;
+        const bool one_round = ep.flags == 0 && cached && K >= 512 && tiles192x256 <= 256;
         if (K < 2048 && ring_eligible(ep)) {
             if (!one_round) return launch_ring(choose_ring(M, N, K, ep.flags, cached), xq, wq, M, N, K, ep, st);
             v = kVariant192x256;
