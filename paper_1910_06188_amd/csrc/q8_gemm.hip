@@ -113,17 +113,19 @@ static int launch_ring(const Ring& r, const int8_t* xq, const int8_t* wq, int M,
 {
     return r.launch(xq, wq, M, N, K, r.group_m, r.by_xcd, ep, st);
 }
-// `cached`: an fp32 output stored for the caches (32 to 64 MiB), its rows whole 128-byte lines (others write parts of lines whatever the tile:
-// 9000 x 1000 x 1024 + GELU 23.0 us with 128x64, 24.7 with 128x128).  There the small tiles pay 2 to 4 us that the model does not know of, so only the
-// two large shapes are looked at: 4096 x 3584 x 512 22.3 -> 19.2 us, 4096 x 2304 x 768 + GELU 20.1 -> 17.0; the other such launches measured within 2 %.
-static const Ring& choose_ring(int M, int N, int K, unsigned flags, bool cached)
+// `cached`: an fp32 output stored for the caches (32 to 64 MiB), its rows whole 128-byte lines.  There the small tiles pay 2 to 4 us that the model
+// does not know of, so only the two large shapes are looked at: 4096 x 3584 x 512 22.3 -> 19.2 us, 4096 x 2304 x 768 + GELU 20.1 -> 17.0; the other such
+// launches measured within 2 %.  `broken`: an fp32 output of 16 MiB or more with rows of other lengths, the lines of which are written in parts.  The wider
+// the tile the more that costs, so only the three small shapes are looked at: 61749 x 999 x 512 180 us with 192x128, 101 with 64x64; 20746 x 356 x 768
+// 22.0 with 128x128, 18.0 with 128x64; 9000 x 1000 x 1024 + GELU 24.7 with 128x128, 23.0 with 128x64.
+static const Ring& choose_ring(int M, int N, int K, unsigned flags, bool cached, bool broken)
 {
     const int kind = (flags & 4u) ? 2 : (flags & 3u) ? 1 : 0;
     const float stages = (float)((K + kBK - 1) / kBK);
-    const int first = cached ? kFirstLargeRing : 0;
+    const int first = cached ? kFirstLargeRing : 0, last = broken ? kFirstLargeRing : kNumRings;
     int best = first;
     float best_us = 0.0f;
-    for (int i = first; i < kNumRings; ++i) {
+    for (int i = first; i < last; ++i) {
         const Ring& r = kRings[i];
         const float mean = (float)((((int64_t)M + r.bm - 1) / r.bm) * (((int64_t)N + r.bn - 1) / r.bn)) / 256.0f;   // tiles per compute unit
         const float most = ceilf(mean), tiles = r.smooth * most + (1.0f - r.smooth) * mean;
@@ -156,10 +158,12 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
     // to drain under them (whole BERT-Large layer step 5-6 % faster).  Below the 32 MB that the L2s hold they would all be dirty
     // there at the end of the kernel, which waits for them to be written back (4096 x 768 x 768 8.4 -> 6.8 us, 4096 x 768 x 3072
     // 18.2 -> 16.5, BERT-Base layer 32 x 128 127 -> 125.5).  In between the hint costs the reader as much as it gains (stored-scale BERT-Large
-    // layer 359.3 -> 356.5 us without it).
+    // layer 359.3 -> 356.5 us without it).  Rows that are not whole 128-byte lines: their parts meet in the L2s without the hint, which takes 4 %
+    // off outputs below 8 MiB (64x64 tiles, 97 launches); from 8 to 32 MiB the hint is 4 % ahead there too.
     const double y_mib = (double)M64 * (double)N64 * 4.0 / (1 << 20);
-    ep.stream_out = y_mib > 64.0 || y_mib < 32.0;
-    const bool cached = !ep.stream_out && !(ep.flags & 4u) && N64 % 32 == 0;
+    const bool whole_lines = N64 % 32 == 0;
+    ep.stream_out = y_mib > 64.0 || (y_mib < 32.0 && (whole_lines || y_mib >= 8.0));
+    const bool cached = y_mib >= 32.0 && y_mib <= 64.0 && !(ep.flags & 4u) && whole_lines, broken = y_mib >= 16.0 && !(ep.flags & 4u) && !whole_lines;
     int v = g_variant;
     if (v < 0 || v >= kVariantRing + kNumRings) return 1;
     if (v == 0 && K64 <= kScalarMaxK && M64 * N64 <= kScalarMaxProducts / (K64 > 0 ? K64 : 1)) {
@@ -174,7 +178,7 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
         // reductions in one round of 32x32 tiles are the direct kernel's, whose waves share them (600 x 2100 x 500, 304 tiles: 8.0 against 8.3).
         const int64_t t32 = ((M64 + 31) / 32) * ((N64 + 31) / 32);
         if (ring_operands_eligible(xq, wq, M64, N64, K64) && ring_eligible(ep) && (v >= kVariantRing || (v == 0 && t32 > (K64 < 2048 ? 256 : 512)))) {
-            const Ring& r = v >= kVariantRing ? kRings[v - kVariantRing] : choose_ring((int)M64, (int)N64, (int)K64, ep.flags, cached);
+            const Ring& r = v >= kVariantRing ? kRings[v - kVariantRing] : choose_ring((int)M64, (int)N64, (int)K64, ep.flags, cached, broken);
             return launch_ring(r, xq, wq, (int)M64, (int)N64, (int)K64, ep, st);
         }
         return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);
@@ -203,7 +207,7 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
         const int64_t tiles192x256 = (((int64_t)M + 191) / 192) * (((int64_t)N + 255) / 256);
         const bool one_round = ep.flags == 0 && cached && K >= 512 && tiles192x256 <= 256;
         if (K < 2048 && ring_eligible(ep)) {
-            if (!one_round) return launch_ring(choose_ring(M, N, K, ep.flags, cached), xq, wq, M, N, K, ep, st);
+            if (!one_round) return launch_ring(choose_ring(M, N, K, ep.flags, cached, broken), xq, wq, M, N, K, ep, st);
             v = kVariant192x256;
         }
         if (v == 0 && tiles64 <= 512) v = kVariant64;
