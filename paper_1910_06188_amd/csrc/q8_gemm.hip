@@ -114,15 +114,16 @@ static int launch_ring(const Ring& r, const int8_t* xq, const int8_t* wq, int M,
     return r.launch(xq, wq, M, N, K, r.group_m, r.by_xcd, ep, st);
 }
 // `cached`: an fp32 output stored for the caches (32 to 64 MiB), its rows whole 128-byte lines.  There the small tiles pay 2 to 4 us that the model
-// does not know of, so only the two large shapes are looked at: 4096 x 3584 x 512 22.3 -> 19.2 us, 4096 x 2304 x 768 + GELU 20.1 -> 17.0; the other such
-// launches measured within 2 %.  `broken`: an fp32 output of 16 MiB or more with rows of other lengths, the lines of which are written in parts.  The wider
-// the tile the more that costs, so only the three small shapes are looked at: 61749 x 999 x 512 180 us with 192x128, 101 with 64x64; 20746 x 356 x 768
-// 22.0 with 128x128, 18.0 with 128x64; 9000 x 1000 x 1024 + GELU 24.7 with 128x128, 23.0 with 128x64.
+// does not know of, so only the two large shapes are looked at from K = 512 on: 4096 x 3584 x 512 22.3 -> 19.2 us, 4096 x 2304 x 768 + GELU 20.1 -> 17.0, 2 % over
+// 17 launches of 512; shorter reductions lose by that (3839 x 3712 x 256 22.4 us, 16.2 with 128x64; 4 % over 20 launches of 256).
+// `broken`: an fp32 output of 16 MiB or more with rows of other lengths, the lines of which are written in parts.  The wider the tile the more that costs, so only
+// the three small shapes are looked at: 61749 x 999 x 512 180 us with 192x128, 101 with 64x64; 9000 x 1000 x 1024 + GELU 24.7 with 128x128, 23.0 with 128x64; 14 % over
+// 14 launches from 32 MiB on.
 static const Ring& choose_ring(int M, int N, int K, unsigned flags, bool cached, bool broken)
 {
     const int kind = (flags & 4u) ? 2 : (flags & 3u) ? 1 : 0;
     const float stages = (float)((K + kBK - 1) / kBK);
-    const int first = cached ? kFirstLargeRing : 0, last = broken ? kFirstLargeRing : kNumRings;
+    const int first = cached && K >= 512 ? kFirstLargeRing : 0, last = broken ? kFirstLargeRing : kNumRings;
     int best = first;
     float best_us = 0.0f;
     for (int i = first; i < last; ++i) {
@@ -159,11 +160,11 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
     // there at the end of the kernel, which waits for them to be written back (4096 x 768 x 768 8.4 -> 6.8 us, 4096 x 768 x 3072
     // 18.2 -> 16.5, BERT-Base layer 32 x 128 127 -> 125.5).  In between the hint costs the reader as much as it gains (stored-scale BERT-Large
     // layer 359.3 -> 356.5 us without it).  Rows that are not whole 128-byte lines: their parts meet in the L2s without the hint, which takes 4 %
-    // off outputs below 8 MiB (64x64 tiles, 97 launches); from 8 to 32 MiB the hint is 4 % ahead there too.
+    // off outputs below 4 MiB (small ring tiles, 26 launches); from 4 MiB on the hint is 4 to 10 % ahead there too (56 launches).
     const double y_mib = (double)M64 * (double)N64 * 4.0 / (1 << 20);
     const bool whole_lines = N64 % 32 == 0;
-    ep.stream_out = y_mib > 64.0 || (y_mib < 32.0 && (whole_lines || y_mib >= 8.0));
-    const bool cached = y_mib >= 32.0 && y_mib <= 64.0 && !(ep.flags & 4u) && whole_lines, broken = y_mib >= 16.0 && !(ep.flags & 4u) && !whole_lines;
+    ep.stream_out = y_mib > 64.0 || (y_mib < 32.0 && (whole_lines || y_mib >= 4.0));
+    const bool fp32 = !(ep.flags & 4u), cached = fp32 && whole_lines && y_mib >= 32.0 && y_mib <= 64.0, broken = fp32 && !whole_lines && y_mib >= 16.0;
     int v = g_variant;
     if (v < 0 || v >= kVariantRing + kNumRings) return 1;
     if (v == 0 && K64 <= kScalarMaxK && M64 * N64 <= kScalarMaxProducts / (K64 > 0 ? K64 : 1)) {
@@ -201,15 +202,23 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
         if (tiles32 <= 256) return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);
         // A plain launch of at most one round of 192x256 tiles whose 32 to 48 MiB are stored for the caches (so that two thirds of the round are
         // outputs), which the rings' smaller tiles pay for: 4096 x 2304 x 768 15.4 us against 16.3 with the ring of the rule, 12288 x 768 x 768 16.3 /
-        // 17.4, 3072 x 3072 x 1536 21.9 / 25.8.  Over 400 such launches this tile takes 0.98 of the ring's time at K = 512, 0.91 at 768 to 1024, 0.87 at
-        // 1152 to 1920, but 1.03 at 128 and 256.  Narrow outputs fill as many tiles without that: 40000 x 64 x 768 13.0 / 6.6, 48000 x 128 x 128
+        // 17.4, 3072 x 3072 x 1536 21.9 / 25.8.  Over 200 such launches this tile takes 0.97 of the ring's time at K = 640 and 768, 0.93 at 896 and 1024, 0.89
+        // beyond, the same at 512 (2860 x 3008 13.5, 14.3; 3270 x 3584 16.7, 16.2) and 1.01 below.  Narrow outputs fill as many tiles without that: 40000 x 64 x 768 13.0 / 6.6, 48000 x 128 x 128
         // 10.4 / 6.6, 36000 x 2 x 1024 12.0 / 8.5, 12288 x 576 x 768 13.3 / 12.5.
         const int64_t tiles192x256 = (((int64_t)M + 191) / 192) * (((int64_t)N + 255) / 256);
         const bool one_round = ep.flags == 0 && cached && K >= 512 && tiles192x256 <= 256;
+        // At most one 64x64 tile a unit: from 1152 on five stages in flight outweigh the ring's neighbours, where nothing but the dequantization follows (158 x
+        // 2304 x 1920 6.8 -> 6.3 us; 0.97 of the ring's time over 70 launches, 1.08 with abs-max, 1.13 with GELU; two tiles a unit 1.05).
         if (K < 2048 && ring_eligible(ep)) {
-            if (!one_round) return launch_ring(choose_ring(M, N, K, ep.flags, cached, broken), xq, wq, M, N, K, ep, st);
-            v = kVariant192x256;
+            if (one_round)
+                v = kVariant192x256;
+            else if (!(ep.flags & 3u) && K > 1024 && tiles64 <= 256)
+                v = kVariant64;
+            else
+                return launch_ring(choose_ring(M, N, K, ep.flags, cached, broken), xq, wq, M, N, K, ep, st);
         }
+        // of broken lines the hint is the rings': wide outputs of staged tiles take 3 to 7 % longer with it (3903 x 2115 x 3456 45.0 us, 48.3)
+        if (!whole_lines && N > 1024 && y_mib < 32.0) ep.stream_out = 0;
         if (v == 0 && tiles64 <= 512) v = kVariant64;
     }
     if (v == 0) {
