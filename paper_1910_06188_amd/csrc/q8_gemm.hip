@@ -176,9 +176,12 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
         // Rows that are 4-byte aligned whatever their width go to the rings from more than one 32x32 tile per compute unit on: 777 x 1000 x
         // 520 (425 tiles) 5.9 us against 6.9 with the direct kernel, 700 x 60 x 600 4.3 against 5.9, 2000 x 520 x 2000 8.8 against 18.4,
         // 16000 x 60 x 300 8.0 against 16.6; with 100 tiles (300 x 1000 x 300) 5.6 against 5.5, with 90 of 4092 columns 12.2 against 7.3.  Long
-        // reductions in one round of 32x32 tiles are the direct kernel's, whose waves share them (600 x 2100 x 500, 304 tiles: 8.0 against 8.3).
+        // reductions in at most two rounds of 32x32 tiles are the direct kernel's, whose waves share them: plain ones from 1412 on (direct over ring 0.98 up to 2044,
+        // 0.91 beyond; 1.07 around 1000), with GELU or abs-max from 1156 on (0.95; 0.88 from 1668 on; 1.06 around 900), to int8 from 644 on (0.91; 0.87 from 1412 on;
+        // 1.05 below) -- of at most 32 columns, of which a ring tile wastes half, with an epilogue of any kind from half of that on (0.87; 1.09 below).
         const int64_t t32 = ((M64 + 31) / 32) * ((N64 + 31) / 32);
-        if (ring_operands_eligible(xq, wq, M64, N64, K64) && ring_eligible(ep) && (v >= kVariantRing || (v == 0 && t32 > (K64 < 2048 ? 256 : 512)))) {
+        const int64_t shared = ((ep.flags & 4u) ? 640 : (ep.flags & 3u) ? 1152 : 1408) / (ep.flags && N64 <= 32 ? 2 : 1);
+        if (ring_operands_eligible(xq, wq, M64, N64, K64) && ring_eligible(ep) && (v >= kVariantRing || (v == 0 && t32 > (K64 <= shared ? 256 : 512)))) {
             const Ring& r = v >= kVariantRing ? kRings[v - kVariantRing] : choose_ring((int)M64, (int)N64, (int)K64, ep.flags, cached, broken);
             return launch_ring(r, xq, wq, (int)M64, (int)N64, (int)K64, ep, st);
         }

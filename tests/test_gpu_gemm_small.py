@@ -140,6 +140,14 @@ def test_gemm_choice_of_longer_reductions(q8, M, K, N):
     test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, 0, 0)
 
 
+@pytest.mark.parametrize("M,K,N", [(300, 640, 1000), (300, 644, 1000), (290, 1148, 1000), (290, 1156, 1000), (300, 1404, 1000), (300, 1412, 1000), (9000, 316, 20), (9000, 324, 20),
+                                   (9000, 572, 32), (9000, 580, 32), (16400, 1604, 10)])
+def test_gemm_choice_of_long_ragged_reductions(q8, M, K, N):
+    """Both sides of the lines between the direct kernel and the tiles with few stage buffers, per kind of epilogue, in two rounds of 32 x 32 tiles and one
+    tile more."""
+    test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, 0, 0)
+
+
 def time_of(q8, variant, M, K, N):
     """Microseconds of a plain layer, the smallest of several runs of ten, outputs past the caches."""
     x, w = (torch.randint(-127, 128, s, dtype=torch.int8, device="cuda") for s in ((M, K), (N, K)))
