@@ -203,13 +203,13 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
         const int64_t tiles32 = (((int64_t)M + 31) / 32) * (((int64_t)N + 31) / 32);
         const int64_t tiles64 = (((int64_t)M + 63) / 64) * (((int64_t)N + 63) / 64);
         if (tiles32 <= 256) return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);
-        // A plain launch of at most one round of 192x256 tiles whose 32 to 48 MiB are stored for the caches (so that two thirds of the round are
-        // outputs), which the rings' smaller tiles pay for: 4096 x 2304 x 768 15.4 us against 16.3 with the ring of the rule, 12288 x 768 x 768 16.3 /
-        // 17.4, 3072 x 3072 x 1536 21.9 / 25.8.  Over 200 such launches this tile takes 0.97 of the ring's time at K = 640 and 768, 0.93 at 896 and 1024, 0.89
-        // beyond, the same at 512 (2860 x 3008 13.5, 14.3; 3270 x 3584 16.7, 16.2) and 1.01 below.  Narrow outputs fill as many tiles without that: 40000 x 64 x 768 13.0 / 6.6, 48000 x 128 x 128
-        // 10.4 / 6.6, 36000 x 2 x 1024 12.0 / 8.5, 12288 x 576 x 768 13.3 / 12.5.
+        // A plain launch of at most one round of 192x256 tiles, about two thirds of them outputs or more, whose 32 to 48 MiB are stored for the caches, which
+        // the rings' smaller tiles pay for: 4096 x 2304 x 768 15.4 us against 16.3 with the ring of the rule, 12288 x 768 x 768 16.3 / 17.4, 3072 x 3072 x 1536
+        // 21.9 / 25.8.  Over 200 such launches this tile takes 0.97 of the ring's time at K = 640 and 768, 0.93 at 896 and 1024, 0.89 beyond, the same at 512
+        // (2860 x 3008 13.5, 14.3; 3270 x 3584 16.7, 16.2) and 1.01 below; of 28 to 32 MiB it is ahead beyond 1024 only (0.94 over 85 launches).  Narrow outputs
+        // fill as many tiles without that: 40000 x 64 x 768 13.0 / 6.6, 48000 x 128 x 128 10.4 / 6.6, 36000 x 2 x 1024 12.0 / 8.5, 12288 x 576 x 768 13.3 / 12.5.
         const int64_t tiles192x256 = (((int64_t)M + 191) / 192) * (((int64_t)N + 255) / 256);
-        const bool one_round = ep.flags == 0 && cached && K >= 512 && tiles192x256 <= 256;
+        const bool one_round = ep.flags == 0 && whole_lines && (cached ? K >= 512 : (y_mib >= 28.0 && K > 1024)) && tiles192x256 <= 256;
         // At most one 64x64 tile a unit: from 1152 on five stages in flight outweigh the ring's neighbours, where nothing but the dequantization follows (158 x
         // 2304 x 1920 6.8 -> 6.3 us; 0.97 of the ring's time over 70 launches, 1.08 with abs-max, 1.13 with GELU; two tiles a unit 1.05).
         if (K < 2048 && ring_eligible(ep)) {

@@ -133,10 +133,10 @@ def test_gemm_choice_of_narrow_and_full_rounds_of_large_tiles(q8, M, K, N):
     test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, 0, 0)
 
 
-@pytest.mark.parametrize("M,K,N", [(1024, 1152, 1024), (1025, 1152, 1024), (1024, 1024, 1000), (300, 1920, 2300), (3000, 640, 2816), (4097, 384, 2080), (4097, 512, 2080), (2100, 2048, 1500)])
+@pytest.mark.parametrize("M,K,N", [(1024, 1152, 1024), (1025, 1152, 1024), (1024, 1024, 1000), (300, 1920, 2300), (3300, 1152, 2304), (3300, 1024, 2304), (3100, 1152, 2304), (3000, 640, 2816), (4097, 384, 2080), (4097, 512, 2080), (2100, 2048, 1500)])
 def test_gemm_choice_of_longer_reductions(q8, M, K, N):
-    """Both sides of the lines between the staged tiles and those with few buffers: 256 and 272 tiles of 64 x 64 and one stage less, outputs stored for
-    the caches of 384, 512 and 640, wide ones of broken lines."""
+    """Both sides of the lines between the staged tiles and those with few buffers: 256 and 272 tiles of 64 x 64 and one stage less, a round of large tiles of 29 and 27 MiB,
+    outputs stored for the caches of 384, 512 and 640, wide ones of broken lines."""
     test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, 0, 0)
 
 
