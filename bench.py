@@ -33,7 +33,7 @@ sys.path.insert(0, ROOT)
 METRIC = "int8 TOPS + % MFMA peak on BERT FC GEMMs; tokens/s per quantized BERT layer"
 INT8_PEAK_TOPS = 5033.0      # MI355X published dense int8 matrix peak
 BF16_PEAK_TFLOPS = 2516.6    # MI355X published dense bf16 matrix peak
-ATTN_PARTS = 6               # bf16 products behind one fp32 product of the attention kernels
+ATTN_PARTS = 8               # bf16 products behind one fp32 product of the attention kernels
 HBM_PEAK_GBS = 8000.0
 PREWARM_STEPS = 200         # untimed steps in front of --warmup: the clock takes a few dozen launches to settle after idle
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "bench_bert_large_layer_pmc_traffic.txt")
@@ -546,7 +546,7 @@ def main():
     out["fused_layernorm_static_mode"] = {"ms_per_step": round(dtfs * 1e3, 4), "tokens_per_s": round(M / dtfs, 1), "steps": n_static,
                                           "note": "stored scales; the embedding block and both residual+LayerNorm passes also "
                                                   "write the int8 codes of their output, so QKV and FFN1 have no quantize pass"}
-    # the whole encoder layer, FP32 softmax attention included (4 S^2 d flops per head; every fp32 product is formed as six
+    # the whole encoder layer, FP32 softmax attention included (4 S^2 d flops per head; every fp32 product is formed as eight
     # products on the bf16 matrix pipes, which is the work its rate is counted in), every operation in the library -- the layer-level tokens/s; the attention kernel is timed with events inside the step
     for _ in range(n_warm):
         layer.step_layer()

@@ -233,22 +233,23 @@ def test_attention_where_two_workgroups_share_a_compute_unit(q8, B, S, heads, d,
 @pytest.mark.parametrize("B,S,heads,d", [(1, 200, 2, 64), (2, 330, 2, 32), (1, 290, 2, 128), (4, 330, 44, 64), (6, 290, 40, 32), (3, 200, 50, 128)])
 @pytest.mark.parametrize("levels", [(-60, -60, -200, -20, 0), (-7, 20, 0, 75, 90), (0, 5, -30), (-150,), (60,), (-20, 3, 40, -40)])
 def test_attention_reference_on_both_sides_of_zero(q8, B, S, heads, d, levels):
-    """Stages whose scores lie around given levels: a reference that stays at zero, starts below it or above it, jumps from far
-    below to zero or beyond, and climbs.  Both kernels."""
+    """Stages whose scores lie around given levels: a maximum near zero, far below and far above it, one that jumps from far below to
+    zero or beyond, and one that climbs.  Both kernels."""
     g = torch.Generator().manual_seed(S + heads + d + len(levels))
     qkv = torch.randn((B * S, 3 * heads * d), generator=g).cuda()
     m = torch.tensor([float(levels[min(j // 32, len(levels) - 1)]) for j in range(S)]).repeat(B, 1).cuda()
     ctx = torch.empty((B * S, heads * d), device="cuda")
     q8.q8_attention(qkv, B, S, heads, d, ctx=ctx, mask=m)
     ref = reference(qkv, B, S, heads, d, m)
-    # a score of up to 2^7.8 (log2 units) is rounded where its sum starts, in four steps of it, where the mask enters and where the
-    # parts meet: seven times 2^-17.2 at worst, 2.3e-6 in the mean square; 1e-5 of the largest |V| is the bar of such scores
+    # a score of up to 2^7.8 (log2 units) is rounded where the mask enters, in the sums of the small products, where the sums meet and where the
+    # maximum is subtracted: seven times 2^-17.2 at worst, 2.3e-6 in the mean square; 1e-5 of the largest |V| is the bar of such scores
     assert (ctx.cpu().double() - ref).abs().max().item() <= 1e-5 * qkv[:, 2 * heads * d:].abs().max().item()
 
 
 @pytest.mark.parametrize("B,S,heads,d,mask", [(16, 380, 4, 32, "some"), (64, 96, 4, 28, "low"), (13, 480, 4, 32, "some"), (16, 190, 5, 64, "some"), (10, 200, 7, 64, "low")])
 def test_attention_on_both_sides_of_the_split_by_width(q8, B, S, heads, d, mask):
-    """768 and 780 workgroups of width 32 and below; 480 and 490 of width 64, of six and of seven stages."""
+    """Four waves on every stage: 768 and 780 workgroups of width 32 and below.  The stages dealt out: 480 and 490 of width 64, of six and of
+    seven stages."""
     test_attention_on_both_sides_of_the_split(q8, B, S, heads, d, mask)
 
 

@@ -1,6 +1,6 @@
-"""The kernels of small and ragged FC launches: 64x64 tiles with deep rings (variant 7) and the direct kernel (variant 8,
-and variant 0 wherever K is no multiple of 128 or an operand is not 16-byte aligned), and the one-thread-per-output kernel
-of the very shortest reductions.  Every output must carry the bits of
+"""The kernels of small and ragged FC launches: 64x64 tiles with deep rings (variant 7), the direct kernel (variant 8; by itself for few
+tiles, for operands that are not 4-byte aligned and for long reductions in few tiles), the tiles with few stage buffers (variants 9 to 13) and the
+one-thread-per-output kernel of the very shortest reductions; and the choice among all of them (variant 0).  Every output must carry the bits of
 the staged 128x128 kernel on operands zero-padded to a multiple of 128, which the other tests pin to the oracle."""
 import numpy as np
 import pytest
@@ -77,6 +77,12 @@ def test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, variant, of
     _, _, acc = run(variant, x, w, 3, dump=True)
     bq = O.quantize_bias(b.cpu().numpy(), N, 24.0, [900.0])
     np.testing.assert_array_equal(acc.cpu().numpy(), O.gemm_i8(xh, wh, bq, threads=8))
+
+
+@pytest.mark.parametrize("M,K,N,off", [(512, 130, 1024, 0), (513, 130, 1000, 0), (1024, 257, 1024, 0), (1025, 40, 1020, 0), (2048, 100, 1024, 0), (2050, 300, 1030, 1), (1100, 1024, 1000, 4)])
+def test_direct_gemm_of_many_tiles_equals_the_staged_kernel(q8, M, K, N, off):
+    """Eight, four, two and one wave a tile, whatever the automatic choice would take."""
+    test_small_and_ragged_gemm_equals_the_staged_kernel(q8, M, K, N, 8, off)
 
 
 @pytest.mark.parametrize("variant,bm,bn", [(9, 64, 64), (10, 64, 64), (11, 128, 64), (12, 128, 128), (13, 192, 128)])
