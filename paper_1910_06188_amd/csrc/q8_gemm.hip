@@ -14,8 +14,8 @@
 // direct-to-LDS load picks its own global address while the LDS side stays linear.
 //
 // Short reductions go to the kernel of q8_gemm_ring_kernel.h, the same but for how it overlaps, and so does any K that is a multiple of
-// 4; any other K or alignment, and launches of at most 256 tiles of 32x32, go to the kernel of q8_gemm_direct.hip; a handful of products to the one-thread-per-output
-// kernel below.
+// 4; any other K or alignment, launches of at most 256 tiles of 32x32 and long reductions of other widths in few such tiles go to the kernel of
+// q8_gemm_direct.hip; a handful of products to the one-thread-per-output kernel below.
 #include "q8_device.h"
 #include "q8_epilogue.h"
 #include "q8_launch.h"
@@ -83,7 +83,7 @@ constexpr int kVariant192x256 = 5, kVariant64 = 7, kVariantDirect = 8, kVariantR
 // chain a workgroup walks (`chain`, per round of workgroups) and the work of a compute unit (`work`, per tile) -- and the
 // epilogue of every tile (fp32, fp32 with GELU or abs-max, int8).  The constants are a fit to 143 launches of 300 to 16384
 // rows and N x K from 512 x 512 to 4096 x 1024, outputs rotating through more than the Infinity Cache, off by 5 to 10 % (rms).
-// Choosing by it costs 2.6 % (geometric mean; 14 % at worst) against the best of all shapes measured.  `smooth` says how much
+// Choosing by it costs 3.4 % against the best of the five (geometric mean of 860 launches of any size; a tenth lose 11 % or more).  `smooth` says how much
 // of a last, partly filled round counts in full.  Large tiles store better with neighbouring tiles on different XCDs, in panels of four
 // rows (12288 x 3072 x 1024 54.8 -> 48.6 us with 192x128): what is written at the same time then lies together.
 struct Ring {
@@ -174,8 +174,8 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
     if (v == kVariantDirect) return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);
     if (!gemm_staged_eligible(xq, wq, M64, N64, K64)) {
         // Rows that are 4-byte aligned whatever their width go to the rings from more than one 32x32 tile per compute unit on: 777 x 1000 x
-        // 520 (425 tiles) 5.9 us against 6.9 with the direct kernel, 700 x 60 x 600 4.3 against 5.9, 2000 x 520 x 2000 8.8 against 18.4,
-        // 16000 x 60 x 300 8.0 against 16.6; with 100 tiles (300 x 1000 x 300) 5.6 against 5.5, with 90 of 4092 columns 12.2 against 7.3.  Long
+        // 520 (425 tiles) 5.6 us against 6.6 with the direct kernel, 700 x 60 x 600 4.4 against 5.8, 2000 x 520 x 2000 8.4 against 17.8,
+        // 16000 x 60 x 300 8.2 against 19.2; with 100 tiles (300 x 1000 x 300) 5.4 against 5.3.  Long
         // reductions in at most two rounds of 32x32 tiles are the direct kernel's, whose waves share them: plain ones from 1412 on (direct over ring 0.98 up to 2044,
         // 0.91 beyond; 1.07 around 1000), with GELU or abs-max from 1156 on (0.95; 0.88 from 1668 on; 1.06 around 900), to int8 from 644 on (0.91; 0.87 from 1412 on;
         // 1.05 below) -- of at most 32 columns, of which a ring tile wastes half, with an epilogue of any kind from half of that on (0.87; 1.09 below).
@@ -195,11 +195,11 @@ int launch_gemm(const int8_t* xq, const int8_t* wq, int64_t M64, int64_t N64, in
     if (v == 0) {
         // Launches that leave compute units idle are bound by the chain of stages each workgroup walks, so they get the
         // smallest tile that still fits the chip in one round.  One 32x32 tile per unit, the reduction split over eight
-        // waves: 256 x 768 x 3072 6.5 us against 8.4 with 64x64 tiles, 128 x 768 x 768 4.1 against 4.4; at 288 such tiles
+        // waves: 256 x 768 x 3072 5.8 us against 7.9 with 64x64 tiles, 128 x 768 x 768 4.3 against 4.4; at 288 such tiles
         // (384 x 768 x 768) the 64x64 ones are ahead, 4.4 against 4.8.  Long reductions: two 64x64 tiles per unit with five
-        // stages in flight (651 x 768 x 3072 8.2 us against 14.6 with 128x128).  Short ones: many workgroups a unit instead of deep
-        // pipelines (choose_ring); from 16 stages on the large staged tiles come out even or ahead (4096 x 768 x 3072 15.5 us against
-        // 17.0 with the best ring, 12288 x 1024 x 4096 47.5 against 53.8).
+        // stages in flight (651 x 768 x 3072 8.2 us against 12.7 with 128x128).  Short ones: many workgroups a unit instead of deep
+        // pipelines (choose_ring); from 16 stages on the large staged tiles come out even or ahead (4096 x 768 x 3072 15.2 us against
+        // 16.6 with the best ring, 12288 x 1024 x 4096 50.5 against 56.3).
         const int64_t tiles32 = (((int64_t)M + 31) / 32) * (((int64_t)N + 31) / 32);
         const int64_t tiles64 = (((int64_t)M + 63) / 64) * (((int64_t)N + 63) / 64);
         if (tiles32 <= 256) return launch_gemm_direct(xq, wq, M64, N64, K64, ep, st);

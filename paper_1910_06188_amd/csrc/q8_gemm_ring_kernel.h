@@ -5,16 +5,19 @@
 // five stages, every load placed by hand.  Where the reduction is short, or the launch is not many times the chip, what
 // it cannot overlap is a large part of a tile's life: filling the ring, the epilogue with its stores, the last round of
 // workgroups.  Here a workgroup holds kSlots stage buffers of 128 bytes of K (one: it loads a stage, waits, multiplies) and
-// the overlap is between the two to eight workgroups of a unit, each at another point of its tile; tiles are also small
+// the overlap is between the three to five workgroups of a unit, each at another point of its tile; tiles are also small
 // enough to spread a launch evenly over the units.  Operand and LDS layout are those of the other kernel.
-// The other kernel -> the best shape of a sweep of tiles and slots, outputs rotating through more than the Infinity Cache, us (five of the
-// shapes are built; the best of the five is within 3 % of these where another one is named):
-//   4096 x  768 x  768   9.2 ->  6.9 (128x64, three slots)        4096 x  768 x 3072        20.8 -> 16.3 (64x64, two slots)
-//   8192 x  768 x 3072  28.3 -> 22.7 (128x96, two slots)          4096 x 3072 x  768 + GELU 20.0 -> 17.2 (128x64, one slot)
-//   1536 x 3072 x  768 + GELU 12.7 -> 9.2 (64x64, one slot)      12288 x 3072 x 1024        54   -> 48.6 (192x128, one slot)
-//  12288 x 4096 x 1024 + GELU 72 -> 68 (192x128, one slot)        1536 x 1024 x 1024         6.9 ->  6.1 (64x64, three slots)
-// Long reductions of full launches stay with the other kernel (12288 x 1024 x 4096: 48.5 against 51): there the bytes staged
-// per MFMA count, and its tiles are the largest.
+// The best tile of the other kernel -> the one that the launcher takes here, outputs rotating through more than the Infinity Cache, each warmed up by
+// itself, us:
+//   4096 x  768 x  768   6.7 ->  6.5 (128x64, two slots)           8192 x 2304 x  768        26.2 -> 24.6 (128x128, one slot)
+//   1536 x 1024 x 1024   6.3 ->  6.0 (64x64, three slots)         12288 x 3072 x 1024        54.9 -> 51.6 (192x128, one slot)
+//   8192 x 3072 x  768 + GELU + abs-max 37.9 -> 33 (128x128)      12288 x 4096 x 1024 + GELU + abs-max 76.5 -> 70.3 (192x128)
+//   4096 x 3072 x  768 + GELU + abs-max 21.7 -> 20.0 (128x128)     1536 x 3072 x  768 + GELU + abs-max 10.4 -> 10.1 (192x128)
+// Long reductions stay with the other kernel (12288 x 1024 x 4096 50.5 against 56.3, 8192 x 768 x 3072 26.1 against 28.7, 4096 x 768 x 3072 15.2 against
+// 16.6): there the bytes staged per MFMA count, and its tiles are the largest.
+// What bounds the large launches: 12288 x 4096 x K with GELU and abs-max takes 41 us at K = 128, 42 at 256 -- the stores, at 4.8 TB/s -- and from there on
+// 0.040 us a unit of K (2.5 POP/s), 72 at 1024: what does not hide behind the stores adds.  In those 72 us the matrix pipes are busy in 42 % of the cycles,
+// the L1 waits for outstanding requests in 47 % and is held by the L2's request path in 9 % (12288 x 3072 x 1024: 38, 42 and 20 %).
 #pragma once
 #include "q8_gemm_kernel.h"
 
